@@ -7,7 +7,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpconv.so")
-SOURCES = ["pconv_capi.cpp", "pconv_pack.cpp", "pconv_kernels.hip", "pconv_tiled.hip", "pconv_mfma.hip"]
+SOURCES = ["pconv_capi.cpp", "pconv_pack.cpp", "pconv_kernels.hip", "pconv_tiled.hip", "pconv_mfma.hip",
+           "pconv_mfma_flat.hip"]
 
 # packed-FP32 instructions are switched off for every device compile of this project
 HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -60,9 +60,10 @@ struct pconv_handle {
     uint32_t *d_chan_ptr = nullptr;
     uint32_t *d_meta = nullptr;
     float    *d_w4 = nullptr;
-    // device copies (matrix-core kernel, bf16 handles only): the masked weights as nine dense
-    // [filter][channel] matrices, tap-major, in blocks of 16 channels: [9][cb16][fpad][16] bf16, fpad
-    // = c_out rounded up to 32, cb16 = c_in rounded up to 32, in sixteens; and per (block of 32
+    // device copies (matrix-core kernels, bf16 handles only): the masked weights as dense
+    // [filter][channel] matrices per tap, in blocks of 32 filters and 16 channels, the nine taps of a
+    // block next to each other: [fpad / 32][cb16][9][32][16] bf16, fpad = c_out rounded up to 32,
+    // cb16 = c_in rounded up to 32, in sixteens; and per (block of 32
     // channels, block of 32 filters) a word whose bit 2 * tap + half says whether that
     // (tap, 16 channels, 32 filters) block holds any kept weight
     uint16_t *d_wdense = nullptr;
@@ -119,6 +120,9 @@ bool mfma_supported(const pconv_handle *h, int dtype, int n, int hin, int win);
 bool mfma_preferred(const pconv_handle *h);
 int launch_conv_mfma(const pconv_handle *h, const void *x, void *y, const float *bias, int n,
                      int hin, int win, int stride, int layout, int relu, void *stream);
+// The main matrix-core kernel (pconv_mfma_flat.hip); false (nothing launched) if it does not serve the call.
+bool launch_conv_flat(const pconv_handle *h, const void *x, void *y, const float *bias, int n, int hin, int win,
+                      int stride, int layout, int relu, void *stream, int &rc);
 // masked weights of a bf16 handle in the matrix-core kernel's layout (see pconv_handle::d_wdense)
 void build_dense_taps(const Canonical &cn, const uint16_t *table, int c_out, int c_in,
                       std::vector<uint16_t> &wd, std::vector<uint32_t> &nz);

@@ -1,4 +1,9 @@
-// bf16 PCONV on the matrix cores of gfx950: Eq. (1) as nine shifted contractions.
+// bf16 PCONV on the matrix cores of gfx950: Eq. (1) as nine shifted contractions, over tiles of images.
+//
+// This kernel serves what pconv_mfma_flat.hip does not: images of fewer than eight pixels, NHWC with a
+// channel count that is no multiple of eight, and images so wide that the rows around a run of
+// pixels outgrow that kernel's staging (there both take about the same time: 64 channels at 224 x 224,
+// stride 2, NHWC 9.4 us here, 10.9 there).
 //
 // For every tap (r, s) of the 3x3 kernel the layer is a matrix product over the input channels,
 //     Y[f, p] += sum_c  W_rs[f, c] * X[c, p shifted by (r, s)],
@@ -39,7 +44,7 @@ constexpr int kPitch = 40;          // bf16 per staged pixel: 32 channels + 8 of
 
 struct MfmaArgs {
     const uint16_t *x; uint16_t *y; const float *bias;
-    const uint16_t *wd;             // [9][cb16][fpad][16] bf16 bit patterns
+    const uint16_t *wd;             // [fpad / 32][cb16][9][32][16] bf16 bit patterns
     const uint32_t *nz;             // [cb32][fpad / 32]: bit (2 * tap + half) = block holds a kept weight
     int n, c_in, h, w, c_out, ho, wo, stride, relu;
     int cb32, fpad;
@@ -203,7 +208,7 @@ conv_mfma_kernel(const MfmaArgs a)
     auto weight_frag = [&](int cb, int q, uint32_t nzb) -> u32x4 {
         if (!((nzb >> q) & 1u)) return u32x4{0u, 0u, 0u, 0u};
         const int tap = q >> 1, half = q & 1;
-        const size_t e = ((size_t(tap) * cb16n + cb * 2 + half) * a.fpad + fb * 32 + col) * 16 + kg * 8;
+        const size_t e = (((size_t(fb) * cb16n + cb * 2 + half) * 9 + tap) * 32 + col) * 16 + kg * 8;
         return *reinterpret_cast<const u32x4 *>(a.wd + e);
     };
     auto block_map = [&](int cb) -> uint32_t { return fb_ok ? a.nz[cb * (a.fpad / 32) + fb] : 0u; };
@@ -348,6 +353,8 @@ bool mfma_preferred(const pconv_handle *h)
 int launch_conv_mfma(const pconv_handle *h, const void *x, void *y, const float *bias, int n,
                      int hin, int win, int stride, int layout, int relu, void *stream)
 {
+    int rc = PCONV_OK;
+    if (launch_conv_flat(h, x, y, bias, n, hin, win, stride, layout, relu, stream, rc)) return rc;
     MfmaArgs a;
     a.x = static_cast<const uint16_t *>(x); a.y = static_cast<uint16_t *>(y); a.bias = bias;
     a.wd = h->d_wdense; a.nz = h->d_wnz;

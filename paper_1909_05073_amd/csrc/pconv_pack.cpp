@@ -269,7 +269,7 @@ void build_dense_taps(const Canonical &cn, const uint16_t *table, int c_out, int
             uint32_t v = cn.val_ptr[k];
             for (int t = 0; t < 9; ++t)
                 if (mask & (1u << t)) {
-                    wd[((size_t(t) * cb16 + c / 16) * fpad + f) * 16 + c % 16] = uint16_t(cn.vals_bits[v++] >> 16);
+                    wd[(((size_t(f / 32) * cb16 + c / 16) * 9 + t) * 32 + f % 32) * 16 + c % 16] = uint16_t(cn.vals_bits[v++] >> 16);
                     nz[size_t(c / 32) * (fpad / 32) + f / 32] |= 1u << (2 * t + (c / 16) % 2);
                 }
         }

@@ -434,6 +434,27 @@ def test_matrix_core_kernel_shapes(layout):
                    what=f"mfma{j}_{layout}")
 
 
+FLAT_SHAPES = [  # (n, c_in, c_out, h, w, stride)
+    (1, 1, 1, 2, 4, 1), (1, 16, 32, 1, 8, 2), (3, 8, 33, 3, 3, 1),          # eight and nine pixels: items moved back to the plane's end
+    (1, 7, 5, 1, 7, 1), (2, 12, 40, 5, 6, 2),                              # seven pixels; NHWC channels no multiple of eight
+    (40, 24, 65, 7, 7, 1), (33, 17, 31, 3, 5, 2), (70, 16, 16, 3, 3, 2),    # runs over many images, partial blocks of channels
+    (1, 64, 64, 16, 16, 1), (1, 128, 33, 9, 17, 1), (2, 144, 96, 11, 13, 1),  # channel parts, the last one with less to do
+    (8, 64, 128, 57, 55, 1), (12, 32, 64, 64, 64, 2), (16, 48, 64, 30, 30, 1),  # many workgroups: large blocks per wave
+    (1, 24, 40, 6, 224, 1), (1, 32, 64, 9, 224, 2), (1, 16, 24, 4, 900, 2), (1, 8, 8, 5, 2000, 1),  # wide images
+]
+
+
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+@pytest.mark.parametrize("shape", FLAT_SHAPES)
+def test_matrix_core_flat_pixel_runs(shape, layout):
+    """The flat-run matrix-core kernel at the edges of its staging items, runs, channel blocks and
+    channel parts, and the calls next to them that go to the other kernel."""
+    n, ci, co, h, w, stride = shape
+    spec = LayerSpec("flat", n, ci, co, h, w, stride=stride, dtype="bf16", keep_div=2.0)
+    L = make_layer(spec, 7200 + ci); x = make_input(spec, 7200 + ci, layout)
+    check_full(spec, L, x, "bf16", layout, stride, relu=bool(n & 1), use_bias=bool(co & 1), policy=3, what=f"flat{shape}_{layout}")
+
+
 def test_matrix_core_kernel_skips_empty_weight_blocks():
     """Connectivity so sparse that whole (tap, 16 channels, 32 filters) blocks hold no weight: the
     kernel skips them; and a layer with nothing kept at all."""
