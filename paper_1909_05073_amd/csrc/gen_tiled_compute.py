@@ -17,7 +17,8 @@ pins / clobbers the same registers):
     v22 LDS address of the patch, v23 LDS address of the next record's weights
     s84 record index, s85 record word, s86 the word after it, s90 scratch, s91 byte offset of the
     word being loaded, s[92:93] address of body 0, s[94:95] target
-Operands: %[recm] per-lane record words (lane j = record j; only lanes 0 and 1 are read), %[mp]
+Operands: %[recm] per-lane record words (lane j = record j; only lanes 0 and 1 are read; the second
+form of the text takes those two words as scalars %[w0], %[w1]), %[mp]
 address of the record stream in global memory (SGPR pair) and %[koff] byte offset of record 0 in
 it (SGPR; words 2.. are read from there with scalar
 loads, because moving a lane of a vector register to a scalar register costs about a tenth of the
@@ -108,7 +109,7 @@ def in_reg(row, col):
     return INP + 4 * row + col - 1
 
 
-def generate():
+def generate(words_in_scalars=False):
     L = []
     L += [
         "s_getpc_b64 s[92:93]",
@@ -118,9 +119,10 @@ def generate():
         "s_mov_b32 s84, 0",
         "v_mov_b32 v23, %[wa]",
         # the first two record words come from the lanes of a register that was loaded a chunk
-        # ahead; every later word comes through the scalar cache, one body ahead of its use
-        "v_readlane_b32 s85, %[recm], 0",
-        "v_readlane_b32 s86, %[recm], 1",
+        # ahead (or in scalars); every later word comes through the scalar cache, one body ahead
+        # of its use
+        "s_mov_b32 s85, %[w0]" if words_in_scalars else "v_readlane_b32 s85, %[recm], 0",
+        "s_mov_b32 s86, %[w1]" if words_in_scalars else "v_readlane_b32 s86, %[recm], 1",
         "s_add_u32 s91, %[koff], 4",
         # The records run at the lowest issue priority, everything around them (staging the next
         # chunk, the counters that other waves wait for) at the highest: see the end.
@@ -177,6 +179,20 @@ def generate_takeover():
     return L
 
 
+def generate_patch():
+    """Loads the lane's 6x6 neighbourhood of one channel staged as rows: the four centre columns of
+    every row (LDS address %[va]) and the halo columns out of the neighbouring lanes' quads (address
+    %[left] / %[right] of row 0, %[lstep] / %[rstep] from row to row)."""
+    L = ["v_mov_b32 v24, %[left]", "v_mov_b32 v25, %[right]"]
+    for r in range(6):
+        L.append("ds_read_b128 v[%d:%d], %%[va] offset:%d" % (INP + 4 * r, INP + 4 * r + 3, r * QUAD_BYTES))
+        L.append("ds_read_b32 v%d, v24" % in_reg(r, 0))
+        L.append("ds_read_b32 v%d, v25" % in_reg(r, 5))
+        if r < 5:
+            L += ["v_add_u32 v24, v24, %[lstep]", "v_add_u32 v25, v25, %[rstep]"]
+    return L + ["s_waitcnt lgkmcnt(0)"]
+
+
 def write_code_header(path):
     assert all(bin(m).count("1") <= 4 for m in CODE_MASKS)
     with open(path, "w") as f:
@@ -200,6 +216,8 @@ def main():
     import os
     out = sys.argv[1]
     write_inc(out, generate())
+    write_inc(os.path.join(os.path.dirname(out), "pconv_tiled_compute_scalar.inc"), generate(True))
+    write_inc(os.path.join(os.path.dirname(out), "pconv_tiled_patch.inc"), generate_patch())
     write_inc(os.path.join(os.path.dirname(out), "pconv_tiled_takeover.inc"), generate_takeover())
     write_code_header(os.path.join(os.path.dirname(out), "pconv_tiled_code_masks.inc"))
 

@@ -238,6 +238,7 @@ void build_tiled_stream(const Canonical &cn, const uint16_t *table, int np, int 
                 for (const Piece &pc : pieces[cn.pat[k]]) {
                     out.meta.push_back(uint32_t(s * kNumCodes + pc.code) << kMetaCaseShift | uint32_t(c % kTileCH) |
                                        (first ? kMetaFirstOfChannel : 0u));
+                    if (first) ++out.visits;
                     first = false;
                     for (int j = 0; j < 4; ++j) {
                         float v = 0.0f;

@@ -23,6 +23,7 @@
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <cstdlib>
 
 #include "pconv_internal.h"
@@ -46,6 +47,7 @@ constexpr int FB = kTileFB, BATCH = kTileBatch;
 // whole 6x6 neighbourhood with nine 128-bit LDS reads.
 constexpr int QUAD_FLOATS = 64 * 4;
 constexpr int CHAN_FLOATS = 9 * QUAD_FLOATS;  // 2304
+constexpr int ROWS_FLOATS = 6 * QUAD_FLOATS + 64;   // a channel of a wave on its own (PRIV)
 constexpr int INV_FLOATS = 2 * 64;            // per-lane invariants {offset, mask}
 constexpr int SYNC_WORDS = 8;                 // counters that order the waves
 constexpr int HALO_TAB_WORDS = 12 * 64;       // source offsets of the halo loads (VEC)
@@ -79,6 +81,7 @@ __device__ __forceinline__ void st_act(bf16_t *p, size_t i, float v)
 }
 
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 // Byte offset that lies beyond any tensor the VEC kernel accepts (at most 2^31 - 1 bytes): a buffer
 // load at such an offset touches no memory and returns zero.
@@ -97,8 +100,10 @@ struct TiledArgs {
     int n_units;                // n_tiles * n_groups: (tile, filter group) pairs
     int n_chunks;               // chunks of CH input channels
     int split_units;            // 1: a workgroup's share of the work may begin and end inside a unit
+    int priv;                   // 1: the 16 waves are 16 channel ranges of one filter block (VEC kernel)
     int one_set;                // 1 (with split_units): the iterations are dealt over all workgroups as one set
     uint32_t *flags;            // [gridDim.x] hand-over words of this call (split_units only)
+    uint32_t n_records;         // records of the stream (the padding record's index)
     uint32_t epoch;             // value that marks a hand-over word as set by this call (never 0)
     uint32_t x_bytes;           // size of the input tensor (VEC kernel: below 2^31)
     uint32_t y_bytes;           // size of the output tensor (shared units only: below 2^31)
@@ -133,9 +138,20 @@ __device__ __forceinline__ size_t act_at(int n, int c, int y, int x, int C, int 
 // the hardware starts workgroups in order of their ids, so whatever a workgroup waits for
 // belongs to a workgroup that has already started and handed over at its very beginning.
 //
+//
+// PRIV: few units of work.  A workgroup is one filter block, its 16 waves are 16 ranges of channels;
+// each wave stages its channels into a slot of its own, runs their records and goes on, with nothing to
+// wait for but its own loads, and the 16 partial sums are added through LDS at the end.  The halo
+// columns are not staged but read out of the neighbouring lanes' quads: what bounds this form is the
+// number of load instructions per channel (7 instead of 18; 256 channels @56, one image: 41 us with
+// 18, 29 with 7; shared units 99).  Staging the next channel while the records of the present one run
+// changes little (the other waves fill the gap) but costs nothing, the input registers are the buffer.
+// One image, us, against the shared or whole units used before: 64->64@224 30 (56, whole units too),
+// 128@112 39 (91), 128->256@56 20 (59), 256->512@28 28 (94), 512@28 42 (108), 512@14 40 (103).
+//
 // VEC: fp32 NCHW tensors at least 4 wide move the four centre columns of a patch row (and the four
 // outputs of a row) with one 128-bit access; the inputs go from global memory straight to LDS.
-template <typename T, int LAYOUT, bool VEC, int NW, int CH, bool SPLIT>
+template <typename T, int LAYOUT, bool VEC, int NW, int CH, bool SPLIT, bool PRIV = false>
 __global__ void __launch_bounds__(NW * 64, 4)   // 4 waves per SIMD: at most 128 VGPRs
 conv_tiled_kernel(const TiledArgs a)
 {
@@ -185,7 +201,7 @@ conv_tiled_kernel(const TiledArgs a)
     // ---- this workgroup's range of iterations ----
     // (one_set: no XCD sets - the shares of all workgroups are then equal whatever the number of tiles,
     // and the workgroup that a piece waits for is simply the one before it)
-    const bool one_set = SPLIT && a.one_set;
+    const bool one_set = PRIV || (SPLIT && a.one_set);
     const int set = one_set ? 0 : int(blockIdx.x & 7), j_in_set = one_set ? int(blockIdx.x) : int(blockIdx.x >> 3);
     const int set_stride = one_set ? 1 : 8;
     // set s: the contiguous block of tiles [s * tps, (s + 1) * tps): neighbouring tiles (which share
@@ -304,7 +320,36 @@ conv_tiled_kernel(const TiledArgs a)
         // each of which fills 64 consecutive words of the halo blocks: word i of load j belongs to patch
         // 16 * (j % 4) + i / 4 and is its halo value e = 4 * (j / 4) + i % 4.  The element offset of that
         // value in channel 0, in bytes (or kOutOfRange outside the image), is the same for every chunk: tabulated once.
-        if (VEC) {
+        if constexpr (PRIV) {
+            // A staged channel of a wave that works on its own is six rows of quads, 1 KB each, and 64
+            // further words: the twelve halo values that no patch of the tile holds (word 2 r: left of
+            // lane 0's patch in row r, word 2 r + 1: right of lane 63's) and zeros.  Every other halo
+            // value is a centre column of the neighbouring lane's patch.  Tabulated once: the source
+            // offsets of the further words, and per lane {offset, step per row} of the left and of the
+            // right halo column inside the channel.
+            if (threadIdx.x < 64) {
+                const int i = threadIdx.x, r = i >> 1;
+                const int pidx_h = tile * 64 + ((i & 1) ? 63 : 0);
+                const int n_h = pidx_h / per_img, prem_h = pidx_h - n_h * per_img;
+                const int xh = min((prem_h % a.px) * 4, a.w - 4);
+                const int iy = (prem_h / a.px) * 4 - 1 + r, ix = (i & 1) ? xh + 4 : xh - 1;
+                const bool ok = i < 12 && pidx_h < a.n_patches && iy >= 0 && iy < a.h && ix >= 0 && ix < a.w;
+                halo_tab[i] = ok ? ((n_h * a.c_in * a.h + iy) * a.w + ix) * 4 : int(kOutOfRange);
+                // (the last patch of a row is shifted left by `over` columns over its left neighbour)
+                const int over = a.px * 4 - a.w, col = prem % a.px;
+                constexpr int kFurther = 6 * QUAD_FLOATS * 4, kZero = kFurther + 12 * 4;
+                int4 v = make_int4(kZero, 0, kZero, 0);
+                if (pvalid && col > 0) {
+                    if (lane == 0) { v.x = kFurther; v.y = 8; }
+                    else { v.x = (lane - 1) * 16 + (col == a.px - 1 ? 3 - over : 3) * 4; v.y = QUAD_FLOATS * 4; }
+                }
+                if (pvalid && col < a.px - 1) {
+                    if (lane == 63) { v.z = kFurther + 4; v.w = 8; }
+                    else { v.z = (lane + 1) * 16 + (col == a.px - 2 ? over : 0) * 4; v.w = QUAD_FLOATS * 4; }
+                }
+                *reinterpret_cast<int4 *>(halo_tab + 64 + 4 * lane) = v;
+            }
+        } else if (VEC) {
             for (int t = threadIdx.x; t < HALO_TAB_WORDS; t += NW * 64) {
                 const int j = t >> 6, i = t & 63;
                 const int e = 4 * (j >> 2) + (i & 3);
@@ -355,6 +400,24 @@ conv_tiled_kernel(const TiledArgs a)
                 asm volatile("s_mov_b32 m0, %1\n s_nop 0\n buffer_load_dword %0, %2, %3 offen lds"
                              ::"v"(off[k]), "s"(dst_b), "s"(rsrc), "s"(soff));
             }
+        };
+        // a wave on its own: the six rows of a channel and the further words, see above
+        auto stage_rows = [&](int c, float *slot) {
+            const int ln = fresh_lane();
+            const uint32_t soff = __builtin_amdgcn_readfirstlane(uint32_t(c) * uint32_t(hw) * 4u);
+            const int lane_off_now = inv[2 * ln];
+            const uint32_t vmask = uint32_t(inv[2 * ln + 1]);
+            const uint32_t further = uint32_t(halo_tab[ln]);
+#pragma unroll
+            for (int r = 0; r < 6; ++r) {
+                const uint32_t voff = ((vmask >> r) & 1u) ? uint32_t(lane_off_now + r * a.w) * 4u : kOutOfRange;
+                const uint32_t dst_b = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(slot + r * QUAD_FLOATS));
+                asm volatile("s_mov_b32 m0, %1\n s_nop 0\n buffer_load_dwordx4 %0, %2, %3 offen lds"
+                             ::"v"(voff), "s"(dst_b), "s"(rsrc), "s"(soff));
+            }
+            const uint32_t dst_b = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(slot + 6 * QUAD_FLOATS));
+            asm volatile("s_mov_b32 m0, %1\n s_nop 0\n buffer_load_dword %0, %2, %3 offen lds"
+                         ::"v"(further), "s"(dst_b), "s"(rsrc), "s"(soff));
         };
         // generic path (any layout / dtype / width): through registers, with conversion to fp32;
         // every thread owns SEGS (channel, row) segments of its lane's patch
@@ -473,7 +536,77 @@ conv_tiled_kernel(const TiledArgs a)
         uint32_t k0, k_cnt, rec_m;
         const int n_rel = c_end - c_begin;
 
-        if constexpr (VEC) {
+        if constexpr (PRIV) {
+            // ---- every wave on its own: its range of channels, one LDS slot, no counters ----
+            const int per_wave = (a.c_in + NW - 1) / NW;
+            const int c_lo = min(a.c_in, wave * per_wave), c_hi = min(a.c_in, c_lo + per_wave);
+            float *slot = lds + wave * ROWS_FLOATS;
+            const uint32_t slot_at = lds_base + uint32_t(wave) * uint32_t(ROWS_FLOATS * 4);
+            int win = c_lo;                                          // lane j: first record of channel win + j
+            uint32_t first = ptr_row[min(win + lane, ptr_max)];
+            uint32_t kb = 0, kb_end = 0;                             // records whose words and weights are at hand
+            uint32_t words = 0;
+            // the next channel at or after c that one of the four filters is connected to, its records
+            uint32_t nk = 0, nk_end = 0;
+            auto next_channel = [&](int c) {
+                for (; c < c_hi; ++c) {
+                    if (c + 1 - win > 63) { win = c; first = ptr_row[min(win + fresh_lane(), ptr_max)]; }
+                    nk = __builtin_amdgcn_readlane(first, c - win);
+                    nk_end = __builtin_amdgcn_readlane(first, c + 1 - win);
+                    if (nk != nk_end) break;
+                }
+                return c;
+            };
+            int c = next_channel(c_lo);
+            if (c < c_hi) stage_rows(c, slot);
+            while (c < c_hi) {
+                uint32_t k = nk;
+                const uint32_t k_end = nk_end;
+                __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): the channel is in LDS
+                // the lane's neighbourhood moves to the registers of the record loop; the slot is then
+                // free, and the next channel is on its way to it while the records run
+                v16f in0, in1;
+                v4f in2;
+                {
+                    const int ln = fresh_lane();
+                    const int4 ht = *reinterpret_cast<const int4 *>(halo_tab + 64 + 4 * ln);
+                    asm volatile(
+#include "pconv_tiled_patch.inc"
+                        : "=&{v[28:43]}"(in0), "=&{v[44:59]}"(in1), "=&{v[60:63]}"(in2)
+                        : [va] "v"(slot_at + uint32_t(ln) * 16u), [left] "v"(slot_at + uint32_t(ht.x)), [lstep] "v"(ht.y),
+                          [right] "v"(slot_at + uint32_t(ht.z)), [rstep] "v"(ht.w)
+                        : "v24", "v25");
+                }
+                c = next_channel(c + 1);
+                if (c < c_hi) stage_rows(c, slot);
+                while (k < k_end) {
+                    if (k_end > kb_end) {
+                        // (words and weights of the next BATCH records; index at most that of the padding record)
+                        kb = k; kb_end = k + BATCH;
+                        const uint32_t ridx = min(k + uint32_t(fresh_lane() & (BATCH - 1)), a.n_records);
+                        words = a.meta[ridx];
+                        const float4 rec_w = a.w4[ridx];
+                        __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0)
+                        if (fresh_lane() < BATCH) {
+                            volatile float *wv = wlds + fresh_lane() * 4;
+                            wv[0] = rec_w.x; wv[1] = rec_w.y; wv[2] = rec_w.z; wv[3] = rec_w.w;
+                        }
+                    }
+                    const uint32_t nb = min(k_end, kb_end) - k;
+                    const uint32_t w0 = __builtin_amdgcn_readlane(words, k - kb) & ~kMetaFirstOfChannel;
+                    const uint32_t w1 = __builtin_amdgcn_readlane(words, min(k + 1 - kb, uint32_t(BATCH - 1)));
+                    asm volatile(
+#include "pconv_tiled_compute_scalar.inc"
+                        : "+{v[64:79]}"(acc[0]), "+{v[80:95]}"(acc[1]), "+{v[96:111]}"(acc[2]), "+{v[112:127]}"(acc[3]),
+                          "+{v[28:43]}"(in0), "+{v[44:59]}"(in1), "+{v[60:63]}"(in2)
+                        : [w0] "s"(w0), [w1] "s"(w1), [va] "v"(slot_at),
+                          [wa] "s"(wa + (k - kb) * 16u), [mp] "s"(a.meta), [koff] "s"(k * 4u), [nb] "s"(nb), [chmask] "n"(0)
+                        : "v22", "v23", "v24", "v25", "v26", "v27",
+                          "s84", "s85", "s86", "s90", "s91", "s92", "s93", "s94", "s95", "scc");
+                    k += nb;
+                }
+            }
+        } else if constexpr (VEC) {
             // ---- no barrier in this loop: three counters per LDS buffer order the waves ----
             //   tickets  staging work asked for           (a chunk has UNITS units of half a channel)
             //   staged   staging units whose data landed  chunk r is readable when staged == UNITS * (r/2 + 1)
@@ -778,7 +911,7 @@ conv_tiled_kernel(const TiledArgs a)
     }
 }
 
-template <typename T, int LAYOUT, bool VEC, int NW, int CH, bool SPLIT>
+template <typename T, int LAYOUT, bool VEC, int NW, int CH, bool SPLIT, bool PRIV = false>
 hipError_t launch_shape(const TiledArgs &a, int64_t wgs, hipStream_t st, int dev)
 {
     // The kernel needs more dynamic LDS than the default limit: raised once per device (the flag is
@@ -786,18 +919,20 @@ hipError_t launch_shape(const TiledArgs &a, int64_t wgs, hipStream_t st, int dev
     static std::atomic<bool> attr_done[64];
     constexpr size_t lds_bytes = Shape<NW, CH>::LDS_BYTES;
     if (dev < 0 || dev >= 64 || !attr_done[dev].load(std::memory_order_acquire)) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_tiled_kernel<T, LAYOUT, VEC, NW, CH, SPLIT>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_tiled_kernel<T, LAYOUT, VEC, NW, CH, SPLIT, PRIV>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, int(lds_bytes));
         if (e != hipSuccess) return e;
         if (dev >= 0 && dev < 64) attr_done[dev].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((conv_tiled_kernel<T, LAYOUT, VEC, NW, CH, SPLIT>), dim3(unsigned(wgs)), dim3(NW * 64), lds_bytes, st, a);
+    hipLaunchKernelGGL((conv_tiled_kernel<T, LAYOUT, VEC, NW, CH, SPLIT, PRIV>), dim3(unsigned(wgs)), dim3(NW * 64), lds_bytes, st, a);
     return hipGetLastError();
 }
 
 template <int NW, int CH>
 hipError_t launch_any(const TiledArgs &a, int64_t wgs, hipStream_t st, bool vec, int layout, int dtype, int dev)
 {
+    if constexpr (NW == 16)
+        if (a.priv) return launch_shape<float, PCONV_NCHW, true, NW, CH, false, true>(a, wgs, st, dev);
     if (vec)
         return a.split_units ? launch_shape<float, PCONV_NCHW, true, NW, CH, true>(a, wgs, st, dev)
                              : launch_shape<float, PCONV_NCHW, true, NW, CH, false>(a, wgs, st, dev);
@@ -819,7 +954,7 @@ std::atomic<int> g_spin_limit{kDefaultSpinLimit};
 void set_tiled_tuning(int waves, int ks_log2, int split_units)
 {
     g_force_waves.store((waves == 8 || waves == 16) ? waves : 0);
-    g_force_ks.store((ks_log2 >= 0 && ks_log2 <= 2) ? ks_log2 : -1);
+    g_force_ks.store((ks_log2 >= 0 && ks_log2 <= 2) || ks_log2 == 4 ? ks_log2 : -1);
     g_force_split.store((split_units >= 0 && split_units <= 2) ? split_units : -1);
 }
 
@@ -879,18 +1014,102 @@ std::atomic<uint32_t> g_static_calls{0};             // epochs of the calls that
 
 }  // namespace
 
+namespace {
+
+// How a call is spread over the chip.
+struct TiledPlan {
+    int nw;               // waves per workgroup
+    bool vec, split, one_set, priv;
+    int ks_log2;
+};
+
+TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout, int dtype, bool pool, bool sub2)
+{
+    TiledPlan p{};
+    const int64_t x_bytes = int64_t(n) * h->c_in * hin * win * 4, y_bytes = int64_t(n) * h->c_out * hin * win * 4;
+    const int force_waves = g_force_waves.load(), force_ks = g_force_ks.load(), force_split = g_force_split.load();
+    p.vec = dtype == PCONV_F32 && layout == PCONV_NCHW && win >= 4 && x_bytes < (int64_t(1) << 31);
+    // Shape: 16-wave workgroups, one per compute unit.  A layer whose input channels fit one 4-channel
+    // chunk is all staging and output stores: there two 8-wave workgroups per compute unit overlap
+    // one's stores with the other's loads.
+    p.nw = force_waves ? force_waves : (h->c_in <= 4 ? 8 : 16);
+    const int ch = p.nw == 16 ? 8 : 4;
+    const int n_chunks = (h->c_in + ch - 1) / ch, px = (win + 3) / 4;
+    const int n_tiles = int((int64_t(n) * ((hin + 3) / 4) * px + 63) / 64);
+    const int cus = h->cus > 0 ? h->cus : 256;
+    const int slots = cus * (16 / p.nw);                 // workgroups that can run at once
+    const int blocks = h->tiled.num_blocks;
+    // Sharing a unit between workgroups needs fp32 outputs written 128 bits at a time, the full-size
+    // output tensor for the partial sums (no fused max-pool, no stride 2), below 2 GiB (they are read
+    // back with range-checked buffer loads), and tiles whose borders fall between patch rows: where the
+    // image width is no multiple of 4 the last patch of a row overlaps its neighbour, and both
+    // write the columns they share; if the two lay in different tiles, their workgroups would read
+    // and overwrite each other's partial sums.
+    const bool rows_whole = win % 4 == 0 || n_tiles == 1 || 64 % px == 0;
+    const bool can_split = p.vec && !pool && !sub2 && y_bytes < (int64_t(1) << 31) && rows_whole;
+    const int64_t whole_units = int64_t(n_tiles) * ((blocks + p.nw - 1) / p.nw);
+    auto units_of = [&](int ks) { return (blocks + (p.nw >> ks) - 1) / (p.nw >> ks); };   // filter groups per tile
+    if (whole_units > slots / 2) {
+        if (can_split && p.nw == 16) {
+            // Many units, but not a multiple of the number of compute units: whole units leave part of
+            // the chip idle in the last round.  Dealing the chunks of all units evenly (every workgroup
+            // one contiguous share, over all workgroups as one set) was measured to cost each workgroup
+            // the time of about ten chunks (further start-ups, the partial sums through memory with a
+            // device-wide release and acquire); a last round with few units runs faster than a full
+            // one (measured: 0.87 of it at 53 % busy).  So it pays for few, long units only (VGG
+            // conv9: 200 units of 64 chunks, -4 %).
+            constexpr double kShareOverhead = 10.0;
+            const double full = double(whole_units / slots), rest = double(whole_units % slots) / slots;
+            const double t_whole = n_chunks * (full + (rest > 0.0 ? 0.72 + 0.28 * rest : 0.0));
+            const double t_share = double(whole_units) * n_chunks / slots + kShareOverhead;
+            if (t_share < kShareGain * t_whole) p.split = p.one_set = true;
+        }
+    } else {
+        // Few units: the form with the smallest estimate, in microseconds, fitted to the VGG-16 layers
+        // with one and four images.
+        const double records = double(h->tiled.meta.size()) * p.nw / blocks / n_chunks;   // of a whole unit's chunk
+        double best = 0.0;
+        auto consider = [&](double t, bool split, int ks, bool priv) {
+            if (best == 0.0 || t < best) { best = t; p.split = split; p.ks_log2 = ks; p.priv = priv; }
+        };
+        // whole units, the waves of a workgroup splitting the channels of a chunk 1, 2 or 4 ways: a chunk
+        // costs about 2 for its staging and 1.9 for 142 records on the whole workgroup (256 channels
+        // @56: 133, 98, 84 us); the tiles of an eighth of the image share the units of one XCD
+        const double chunk_scale = p.nw == 16 ? 1.0 : 0.5;
+        for (int ks = 0; ks <= 2; ++ks) {
+            if (ks > 0 && int64_t(n_tiles) * units_of(ks - 1) > slots / 2) break;
+            const double rounds = std::ceil(double((n_tiles + 7) / 8) * units_of(ks) / (slots / 8.0));
+            consider(rounds * (6.0 + chunk_scale * n_chunks * (2.0 + 1.9 * records / 142.0 / (1 << ks))), false, ks, false);
+        }
+        // units shared by P workgroups, which pass the sums on one after the other (256 channels @56, one
+        // image: 99 us, four: 83)
+        if (can_split)
+            consider(6.0 + 4.0 * chunk_scale * whole_units * n_chunks / slots + std::min(90.0, 10.0 * slots / double(whole_units)), true, 0, false);
+        // one filter block per workgroup, every wave its own channels: per visited channel 0.055 and per
+        // record 0.03 (256 channels @56, one image: 29 us; 512 @14: 40 us)
+        // (it waits for nothing: a test that limits the waits gets a form that has them)
+        if (p.vec && p.nw == 16 && g_spin_limit.load() == kDefaultSpinLimit) {
+            const double visits = double(h->tiled.visits) / blocks, recs = double(h->tiled.meta.size()) / blocks;
+            consider(std::ceil(double(n_tiles) * blocks / slots) * (9.6 + 0.055 * visits + 0.03 * recs), false, 4, true);
+        }
+    }
+    if (force_split >= 0) { p.split = can_split && force_split != 0; p.one_set = p.split && force_split == 2; if (p.split) { p.ks_log2 = 0; p.priv = false; } }
+    if (force_ks >= 0) {
+        p.priv = force_ks == 4 && p.vec && p.nw == 16;
+        p.ks_log2 = force_ks < 4 || p.priv ? force_ks : 0;
+        if (p.priv) p.split = p.one_set = false;
+    }
+    if (p.split && force_ks < 0) p.ks_log2 = 0;
+    return p;
+}
+
+}  // namespace
+
 bool tiled_shares_units(const pconv_handle *h, int n, int hin, int win)
 {
     // the automatic choice of launch_conv_tiled for an fp32 NCHW call with stride 1 and no fused pool
-    const int py = (hin + 3) / 4, px = (win + 3) / 4;
-    const int64_t n_tiles = (int64_t(n) * py * px + 63) / 64;
-    const int64_t x_bytes = int64_t(n) * h->c_in * hin * win * 4, y_bytes = int64_t(n) * h->c_out * hin * win * 4;
-    const bool vec = win >= 4 && x_bytes < (int64_t(1) << 31);
-    const int nw = h->c_in <= 4 ? 8 : 16;
-    const int slots = (h->cus > 0 ? h->cus : 256) * (16 / nw);
-    const bool rows_whole = win % 4 == 0 || n_tiles == 1 || 64 % px == 0;
-    return vec && y_bytes < (int64_t(1) << 31) && rows_whole &&
-           n_tiles * ((h->tiled.num_blocks + nw - 1) / nw) <= slots / 2;
+    const TiledPlan p = plan_tiled(h, n, hin, win, PCONV_NCHW, PCONV_F32, false, false);
+    return p.split && !p.one_set;
 }
 
 int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float *bias, int n,
@@ -908,55 +1127,16 @@ int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float
     a.n_tiles = (a.n_patches + 63) / 64;
     a.n_blocks = h->tiled.num_blocks;
     a.relu = relu; a.pool = pool;
-    const int64_t x_bytes = int64_t(n) * h->c_in * hin * win * 4;
-    const bool vec = dtype == PCONV_F32 && layout == PCONV_NCHW && win >= 4 && x_bytes < (int64_t(1) << 31);
-    a.x_bytes = uint32_t(std::min<int64_t>(x_bytes, 0x7FFFFFFF));
-    // Shape: 16-wave workgroups, one per compute unit.  A layer whose input channels fit one 4-channel
-    // chunk is all staging and output stores: there two 8-wave workgroups per compute unit overlap
-    // one's stores with the other's loads.
-    const int force_waves = g_force_waves.load(), force_ks = g_force_ks.load(), force_split = g_force_split.load();
+    a.x_bytes = uint32_t(std::min<int64_t>(int64_t(n) * h->c_in * hin * win * 4, 0x7FFFFFFF));
+    a.y_bytes = uint32_t(std::min<int64_t>(int64_t(n) * h->c_out * hin * win * 4, 0x7FFFFFFF));
     a.err = h->h_err; a.spin_limit = g_spin_limit.load();
-    const int nw = force_waves ? force_waves : (h->c_in <= 4 ? 8 : 16);
-    const int ch = nw == 16 ? 8 : 4;
+    const TiledPlan plan = plan_tiled(h, n, hin, win, layout, dtype, pool != 0, stride == 2);
+    const int nw = plan.nw, ch = nw == 16 ? 8 : 4;
+    const bool vec = plan.vec;
+    const int slots = (h->cus > 0 ? h->cus : 256) * (16 / nw);
     a.n_chunks = (h->c_in + ch - 1) / ch;
-    // Few units: share them between workgroups (needs fp32 outputs written 128 bits at a time, the
-    // VEC kernel), else split the channels inside the workgroups.
-    const int cus = h->cus > 0 ? h->cus : 256;
-    const int slots = cus * (16 / nw);                   // workgroups that can run at once
-    // Sharing units costs every workgroup a second start-up and a pass of the partial sums through
-    // memory: it pays where whole units would leave half of the compute units or more without work.
-    // (Not with a fused max-pool: the partial sums need the full-size output tensor.)
-    // (and needs an output below 2 GiB: the partial sums are read back with range-checked buffer loads)
-    const int64_t y_bytes = int64_t(n) * h->c_out * hin * win * 4;
-    // (and tiles whose borders fall between patch rows: where the image width is no multiple of 4
-    // the last patch of a row overlaps its neighbour, and both write the columns they share; if the
-    // two lay in different tiles, their workgroups would read and overwrite each other's partial sums)
-    const bool rows_whole = win % 4 == 0 || a.n_tiles == 1 || 64 % a.px == 0;
-    const bool can_split = vec && !pool && !a.sub2 && y_bytes < (int64_t(1) << 31) && rows_whole;
-    a.y_bytes = uint32_t(std::min<int64_t>(y_bytes, 0x7FFFFFFF));
-    const int64_t whole_units = int64_t(a.n_tiles) * ((a.n_blocks + nw - 1) / nw);
-    a.split_units = can_split && whole_units <= slots / 2;
-    a.one_set = 0;
-    if (can_split && !a.split_units && nw == 16) {
-        // Many units, but not a multiple of the number of compute units: whole units leave part of
-        // the chip idle in the last round.  Dealing the chunks of all units evenly (every workgroup
-        // one contiguous share, over all workgroups as one set) was measured to cost each workgroup
-        // the time of about ten chunks (further start-ups, the partial sums through memory with a
-        // device-wide release and acquire); a last round with few units runs faster than a full
-        // one (measured: 0.87 of it at 53 % busy).  So it pays for few, long units only (VGG
-        // conv9: 200 units of 64 chunks, -4 %).
-        constexpr double kShareOverhead = 10.0;
-        const double full = double(whole_units / slots), rest = double(whole_units % slots) / slots;
-        const double t_whole = a.n_chunks * (full + (rest > 0.0 ? 0.72 + 0.28 * rest : 0.0));
-        const double t_share = double(whole_units) * a.n_chunks / slots + kShareOverhead;
-        if (t_share < kShareGain * t_whole) { a.split_units = 1; a.one_set = 1; }
-    }
-    if (force_split >= 0) { a.split_units = can_split ? (force_split != 0) : 0; a.one_set = a.split_units && force_split == 2; }
-    a.ks_log2 = 0;
-    if (!a.split_units)
-        while (a.ks_log2 < 2 && int64_t(a.n_tiles) * ((a.n_blocks + (nw >> a.ks_log2) - 1) / (nw >> a.ks_log2)) <= slots / 2)
-            ++a.ks_log2;
-    if (force_ks >= 0) a.ks_log2 = force_ks;
+    a.split_units = plan.split; a.one_set = plan.one_set; a.priv = plan.priv; a.ks_log2 = plan.ks_log2;
+    a.n_records = uint32_t(h->tiled.meta.size()) - 3u;
     const int fw = nw >> a.ks_log2;
     a.n_groups = (a.n_blocks + fw - 1) / fw;
     const int64_t units = int64_t(a.n_tiles) * a.n_groups;
@@ -986,7 +1166,7 @@ int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float
             a.epoch = call + 1u ? call + 1u : 1u;
         }
     } else {
-        wgs = int64_t((a.n_tiles + 7) / 8) * 8 * a.n_groups;   // one per unit of the largest set, in every set
+        wgs = a.priv ? units : int64_t((a.n_tiles + 7) / 8) * 8 * a.n_groups;   // one per unit of the largest set, in every set
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
     const hipError_t e = nw == 16 ? launch_any<16, 8>(a, wgs, st, vec, layout, dtype, h->device)

@@ -291,6 +291,25 @@ def test_shared_units_on_several_tiles(shape, split_units):
     check_full(spec, L, x, "f32", "nchw", 1, relu=True, policy=2, what=f"multitile{shape}_split{split_units}")
 
 
+LONE_SHAPES = [  # (n, c_in, c_out, h, w, stride): widths 0-3 past a multiple of 4, one patch column, tiles that end inside a row
+    (1, 5, 9, 4, 4, 1), (2, 16, 8, 9, 5, 1), (1, 33, 6, 14, 14, 1), (3, 40, 30, 13, 15, 1), (1, 70, 12, 33, 21, 1),
+    (5, 17, 20, 10, 10, 1), (1, 48, 8, 20, 264, 1), (1, 20, 10, 17, 30, 2), (2, 130, 5, 7, 7, 2), (1, 1100, 4, 6, 8, 1),
+]
+
+
+@pytest.mark.parametrize("shape", LONE_SHAPES)
+def test_waves_on_their_own(shape):
+    """The form of the tiled kernel for few units of work: every wave its own channels, halo columns out
+    of the neighbouring lanes' patches."""
+    n, ci, co, h, w, stride = shape
+    P.pconv_debug_set_tiling(16, 4, -1)
+    for dense in (False, True):                          # (a dense kernel is three records)
+        spec = LayerSpec("lone", n, ci, co, h, w, stride=stride, num_patterns=1 if dense else 12,
+                         pattern_dist="dense" if dense else "uniform", keep_div=2.0, count_dist="bernoulli")
+        L = make_layer(spec, 5100 + ci); x = make_input(spec, 5100 + ci)
+        check_full(spec, L, x, "f32", "nchw", stride, relu=bool(n & 1), use_bias=bool(co & 1), policy=2, what=f"lone{shape}")
+
+
 def test_four_scp_table():
     """A table of the paper's four Sparse Convolution Patterns alone (the 4-pattern row of the
     pattern-count experiment)."""
