@@ -48,6 +48,7 @@ constexpr int FB = kTileFB, BATCH = kTileBatch;
 constexpr int QUAD_FLOATS = 64 * 4;
 constexpr int CHAN_FLOATS = 9 * QUAD_FLOATS;  // 2304
 constexpr int ROWS_FLOATS = 6 * QUAD_FLOATS + 64;   // a channel of a wave on its own (PRIV)
+constexpr int PLANE_FLOATS = ROWS_FLOATS + 4;       // the same with channels last: four planes on are 16 banks on
 constexpr int INV_FLOATS = 2 * 64;            // per-lane invariants {offset, mask}
 constexpr int SYNC_WORDS = 8;                 // counters that order the waves
 constexpr int HALO_TAB_WORDS = 12 * 64;       // source offsets of the halo loads (VEC)
@@ -146,6 +147,9 @@ __device__ __forceinline__ size_t act_at(int n, int c, int y, int x, int C, int 
 // number of load instructions per channel (7 instead of 18; 256 channels @56, one image: 41 us with
 // 18, 29 with 7; shared units 99).  Staging the next channel while the records of the present one run
 // changes little (the other waves fill the gap) but costs nothing, the input registers are the buffer.
+// Channels last, a wave cannot load one channel well: there the waves stage 16 channels together, four
+// lanes to a pixel, and then run one each (128 channels @28, eight images: 40 us; with a lane per pixel
+// 111, in whole units with one channel per load 155).
 // One image, us, against the shared or whole units used before: 64->64@224 30 (56, whole units too),
 // 128@112 39 (91), 128->256@56 20 (59), 256->512@28 28 (94), 512@28 42 (108), 512@14 40 (103).
 //
@@ -331,12 +335,12 @@ conv_tiled_kernel(const TiledArgs a)
                 const int i = threadIdx.x, r = i >> 1;
                 const int pidx_h = tile * 64 + ((i & 1) ? 63 : 0);
                 const int n_h = pidx_h / per_img, prem_h = pidx_h - n_h * per_img;
-                const int xh = min((prem_h % a.px) * 4, a.w - 4);
+                const int xh = VEC ? min((prem_h % a.px) * 4, a.w - 4) : 0;
                 const int iy = (prem_h / a.px) * 4 - 1 + r, ix = (i & 1) ? xh + 4 : xh - 1;
-                const bool ok = i < 12 && pidx_h < a.n_patches && iy >= 0 && iy < a.h && ix >= 0 && ix < a.w;
+                const bool ok = VEC && i < 12 && pidx_h < a.n_patches && iy >= 0 && iy < a.h && ix >= 0 && ix < a.w;
                 halo_tab[i] = ok ? ((n_h * a.c_in * a.h + iy) * a.w + ix) * 4 : int(kOutOfRange);
                 // (the last patch of a row is shifted left by `over` columns over its left neighbour)
-                const int over = a.px * 4 - a.w, col = prem % a.px;
+                const int over = VEC ? a.px * 4 - a.w : 0, col = prem % a.px;
                 constexpr int kFurther = 6 * QUAD_FLOATS * 4, kZero = kFurther + 12 * 4;
                 int4 v = make_int4(kZero, 0, kZero, 0);
                 if (pvalid && col > 0) {
@@ -458,15 +462,75 @@ conv_tiled_kernel(const TiledArgs a)
                 cbuf[(6 + (6 + r) / 4) * QUAD_FLOATS + ln * 4 + (6 + r) % 4] = v[5];        // halo value e = 6 + r
             }
         };
+        // four consecutive channels of a pixel (channels last), element offset e, zero unless ok
+        auto four = [&](bool ok, int e) {
+            v4f v;
+            if constexpr (sizeof(T) == 4) {
+                __builtin_memcpy(&v, x + (ok ? e : 0), 16);
+            } else {
+                uint2 u;
+                __builtin_memcpy(&u, x + (ok ? e : 0), 8);
+                v = v4f{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u),
+                        __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xFFFF0000u)};
+            }
+            return ok ? v : v4f{0.f, 0.f, 0.f, 0.f};
+        };
+        // Channels last, c_in a multiple of 4: CH / 4 neighbouring lanes load the chunk's channels of a
+        // pixel, an instruction 256 / CH pixels of one input row (one channel per wave and pixel column
+        // per load, as below, touches a cache line per lane: 12 us a chunk instead of 4).  A pixel is
+        // loaded once and also written to the halo words of the patch beside it; halo words outside
+        // the image are never written and stay zero.
+        auto stage_quads = [&](int c0, float *buf) {
+            constexpr int QUADS = CH / 4, PIX = 64 / QUADS, GROUPS = 256 / PIX;
+            static_assert(6 * GROUPS == SEGS * NW, "items per wave");
+            const int ln = fresh_lane();
+            const int quad = ln & (QUADS - 1), c4 = c0 + quad * 4;
+            float *cbuf = buf + quad * 4 * CHAN_FLOATS;
+            v4f v[SEGS], beside = v4f{0.f, 0.f, 0.f, 0.f};
+            const int eb = ln / QUADS, rb = eb >> 1, pb = (eb & 1) ? 63 : 0;       // wave 0: beside the tile's first and last patch
+#pragma unroll
+            for (int i = 0; i < SEGS; ++i) {
+                const int item = wave * SEGS + i, r = item / GROUPS, pix = (item % GROUPS) * PIX + ln / QUADS, patch = pix >> 2, q = pix & 3;
+                const uint32_t vmask = uint32_t(inv[2 * patch + 1]);
+                const bool ok = ((vmask >> r) & (vmask >> (9 + q)) & 1u) && c4 < a.c_in;
+                v[i] = four(ok, inv[2 * patch] + (r * a.w + q) * a.c_in + c4);
+            }
+            if (wave == 0 && eb < 12) {
+                const uint32_t vmask = uint32_t(inv[2 * pb + 1]);
+                const bool ok = ((vmask >> rb) & (vmask >> (pb ? 13 : 8)) & 1u) && c4 < a.c_in;
+                beside = four(ok, inv[2 * pb] + (rb * a.w + (pb ? 4 : -1)) * a.c_in + c4);
+            }
+#pragma unroll
+            for (int i = 0; i < SEGS; ++i) {
+                const int item = wave * SEGS + i, r = item / GROUPS, pix = (item % GROUPS) * PIX + ln / QUADS, patch = pix >> 2, q = pix & 3;
+                const uint32_t vmask = uint32_t(inv[2 * patch + 1]);
+                // halo value e of a patch lies at word 4 * patch + e % 4 of block 6 + e / 4
+                int halo = -1;
+                if (q == 3 && ((vmask >> 13) & 1u) && patch < 63) halo = (6 + r / 4) * QUAD_FLOATS + (patch + 1) * 4 + r % 4;
+                if (q == 0 && ((vmask >> 8) & 1u) && patch > 0) halo = (6 + (6 + r) / 4) * QUAD_FLOATS + (patch - 1) * 4 + (6 + r) % 4;
+#pragma unroll
+                for (int k4 = 0; k4 < 4; ++k4) {
+                    cbuf[k4 * CHAN_FLOATS + r * QUAD_FLOATS + pix] = v[i][k4];
+                    if (halo >= 0) cbuf[k4 * CHAN_FLOATS + halo] = v[i][k4];
+                }
+            }
+            if (wave == 0 && eb < 12) {
+                const int e = pb ? 6 + rb : rb;
+#pragma unroll
+                for (int k4 = 0; k4 < 4; ++k4) cbuf[k4 * CHAN_FLOATS + (6 + e / 4) * QUAD_FLOATS + pb * 4 + e % 4] = beside[k4];
+            }
+        };
         // (rel = chunk index relative to the piece; it selects the LDS buffer)
         auto stage = [&](int rel) {
+            if constexpr (LAYOUT == PCONV_NHWC)
+                if (a.c_in % 4 == 0) { stage_quads((c_begin + rel) * CH, lds + (rel & 1) * BUF_FLOATS); return; }
             float t[SEGS][6];
             stage_load((c_begin + rel) * CH, t);
             stage_store((c_begin + rel) * CH, lds + (rel & 1) * BUF_FLOATS, t);
         };
 
-        if (VEC) {
-            // zero both staged buffers (see stage_direct)
+        if (VEC || LAYOUT == PCONV_NHWC) {
+            // zero both staged buffers (see stage_direct, stage_quads)
 #pragma unroll
             for (int j = 0; j < 2 * BUF_FLOATS / (NW * 64 * 4); ++j)
                 *reinterpret_cast<float4 *>(lds + (j * NW * 64 + threadIdx.x) * 4) = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -537,60 +601,41 @@ conv_tiled_kernel(const TiledArgs a)
         const int n_rel = c_end - c_begin;
 
         if constexpr (PRIV) {
-            // ---- every wave on its own: its range of channels, one LDS slot, no counters ----
-            const int per_wave = (a.c_in + NW - 1) / NW;
-            const int c_lo = min(a.c_in, wave * per_wave), c_hi = min(a.c_in, c_lo + per_wave);
-            float *slot = lds + wave * ROWS_FLOATS;
-            const uint32_t slot_at = lds_base + uint32_t(wave) * uint32_t(ROWS_FLOATS * 4);
-            int win = c_lo;                                          // lane j: first record of channel win + j
-            uint32_t first = ptr_row[min(win + lane, ptr_max)];
             uint32_t kb = 0, kb_end = 0;                             // records whose words and weights are at hand
             uint32_t words = 0;
-            // the next channel at or after c that one of the four filters is connected to, its records
-            uint32_t nk = 0, nk_end = 0;
-            auto next_channel = [&](int c) {
-                for (; c < c_hi; ++c) {
-                    if (c + 1 - win > 63) { win = c; first = ptr_row[min(win + fresh_lane(), ptr_max)]; }
-                    nk = __builtin_amdgcn_readlane(first, c - win);
-                    nk_end = __builtin_amdgcn_readlane(first, c + 1 - win);
-                    if (nk != nk_end) break;
-                }
-                return c;
-            };
-            int c = next_channel(c_lo);
-            if (c < c_hi) stage_rows(c, slot);
-            while (c < c_hi) {
-                uint32_t k = nk;
-                const uint32_t k_end = nk_end;
-                __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): the channel is in LDS
-                // the lane's neighbourhood moves to the registers of the record loop; the slot is then
-                // free, and the next channel is on its way to it while the records run
-                v16f in0, in1;
-                v4f in2;
-                {
-                    const int ln = fresh_lane();
-                    const int4 ht = *reinterpret_cast<const int4 *>(halo_tab + 64 + 4 * ln);
-                    asm volatile(
+            // the lane's neighbourhood of the channel in slot `at` (bytes) to the registers of the record loop
+            v16f in0, in1;
+            v4f in2;
+            auto load_patch = [&](uint32_t at) {
+                const int ln = fresh_lane();
+                const int4 ht = *reinterpret_cast<const int4 *>(halo_tab + 64 + 4 * ln);
+                asm volatile(
 #include "pconv_tiled_patch.inc"
-                        : "=&{v[28:43]}"(in0), "=&{v[44:59]}"(in1), "=&{v[60:63]}"(in2)
-                        : [va] "v"(slot_at + uint32_t(ln) * 16u), [left] "v"(slot_at + uint32_t(ht.x)), [lstep] "v"(ht.y),
-                          [right] "v"(slot_at + uint32_t(ht.z)), [rstep] "v"(ht.w)
-                        : "v24", "v25");
+                    : "=&{v[28:43]}"(in0), "=&{v[44:59]}"(in1), "=&{v[60:63]}"(in2)
+                    : [va] "v"(at + uint32_t(ln) * 16u), [left] "v"(at + uint32_t(ht.x)), [lstep] "v"(ht.y),
+                      [right] "v"(at + uint32_t(ht.z)), [rstep] "v"(ht.w)
+                    : "v24", "v25");
+            };
+            // words and weights of the next BATCH records (index at most that of the padding record)
+            auto fetch_batch = [&](uint32_t k, float4 &rec_w) {
+                kb = k; kb_end = k + BATCH;
+                const uint32_t ridx = min(k + uint32_t(fresh_lane() & (BATCH - 1)), a.n_records);
+                words = a.meta[ridx];
+                rec_w = a.w4[ridx];
+            };
+            auto store_batch = [&](const float4 &rec_w) {
+                if (fresh_lane() < BATCH) {
+                    volatile float *wv = wlds + fresh_lane() * 4;
+                    wv[0] = rec_w.x; wv[1] = rec_w.y; wv[2] = rec_w.z; wv[3] = rec_w.w;
                 }
-                c = next_channel(c + 1);
-                if (c < c_hi) stage_rows(c, slot);
+            };
+            auto run_records = [&](uint32_t k, uint32_t k_end) {
                 while (k < k_end) {
                     if (k_end > kb_end) {
-                        // (words and weights of the next BATCH records; index at most that of the padding record)
-                        kb = k; kb_end = k + BATCH;
-                        const uint32_t ridx = min(k + uint32_t(fresh_lane() & (BATCH - 1)), a.n_records);
-                        words = a.meta[ridx];
-                        const float4 rec_w = a.w4[ridx];
+                        float4 rec_w;
+                        fetch_batch(k, rec_w);
                         __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0)
-                        if (fresh_lane() < BATCH) {
-                            volatile float *wv = wlds + fresh_lane() * 4;
-                            wv[0] = rec_w.x; wv[1] = rec_w.y; wv[2] = rec_w.z; wv[3] = rec_w.w;
-                        }
+                        store_batch(rec_w);
                     }
                     const uint32_t nb = min(k_end, kb_end) - k;
                     const uint32_t w0 = __builtin_amdgcn_readlane(words, k - kb) & ~kMetaFirstOfChannel;
@@ -599,11 +644,97 @@ conv_tiled_kernel(const TiledArgs a)
 #include "pconv_tiled_compute_scalar.inc"
                         : "+{v[64:79]}"(acc[0]), "+{v[80:95]}"(acc[1]), "+{v[96:111]}"(acc[2]), "+{v[112:127]}"(acc[3]),
                           "+{v[28:43]}"(in0), "+{v[44:59]}"(in1), "+{v[60:63]}"(in2)
-                        : [w0] "s"(w0), [w1] "s"(w1), [va] "v"(slot_at),
+                        : [w0] "s"(w0), [w1] "s"(w1), [va] "v"(0u),
                           [wa] "s"(wa + (k - kb) * 16u), [mp] "s"(a.meta), [koff] "s"(k * 4u), [nb] "s"(nb), [chmask] "n"(0)
                         : "v22", "v23", "v24", "v25", "v26", "v27",
                           "s84", "s85", "s86", "s90", "s91", "s92", "s93", "s94", "s95", "scc");
                     k += nb;
+                }
+            };
+            const uint32_t slot_at = lds_base + uint32_t(wave) * uint32_t((VEC ? ROWS_FLOATS : PLANE_FLOATS) * 4);
+            if constexpr (VEC) {
+                // ---- every wave on its own: its range of channels, one LDS slot, no counters ----
+                const int per_wave = (a.c_in + NW - 1) / NW;
+                const int c_lo = min(a.c_in, wave * per_wave), c_hi = min(a.c_in, c_lo + per_wave);
+                float *slot = lds + wave * ROWS_FLOATS;
+                int win = c_lo;                                      // lane j: first record of channel win + j
+                uint32_t first = ptr_row[min(win + lane, ptr_max)];
+                // the next channel at or after c that one of the four filters is connected to, its records
+                uint32_t nk = 0, nk_end = 0;
+                auto next_channel = [&](int c) {
+                    for (; c < c_hi; ++c) {
+                        if (c + 1 - win > 63) { win = c; first = ptr_row[min(win + fresh_lane(), ptr_max)]; }
+                        nk = __builtin_amdgcn_readlane(first, c - win);
+                        nk_end = __builtin_amdgcn_readlane(first, c + 1 - win);
+                        if (nk != nk_end) break;
+                    }
+                    return c;
+                };
+                int c = next_channel(c_lo);
+                if (c < c_hi) stage_rows(c, slot);
+                while (c < c_hi) {
+                    const uint32_t k = nk, k_end = nk_end;
+                    __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): the channel is in LDS
+                    // with the neighbourhood in registers the slot is free, and the next channel is on its
+                    // way to it while the records run
+                    load_patch(slot_at);
+                    c = next_channel(c + 1);
+                    if (c < c_hi) stage_rows(c, slot);
+                    run_records(k, k_end);
+                }
+            } else {
+                // ---- channels last: the waves stage 16 channels together, then every wave runs one ----
+                // (four channels of a pixel are one load, so a wave cannot stage one channel well)
+                uint32_t first = 0, count = 0;                       // lane j: records of this wave's channel in step win + j
+                const int steps = (a.c_in + NW - 1) / NW;
+                for (int step = 0; step < steps; ++step) {
+                    if ((step & 63) == 0) {
+                        const int at = (step + fresh_lane()) * NW + wave;
+                        first = ptr_row[min(at, ptr_max)];
+                        count = ptr_row[min(at + 1, ptr_max)] - first;
+                    }
+                    const uint32_t k = __builtin_amdgcn_readlane(first, step & 63);
+                    const uint32_t k_end = k + __builtin_amdgcn_readlane(count, step & 63);
+                    float4 rec_w;
+                    fetch_batch(k, rec_w);
+                    // Four lanes load the 16 channels of a pixel (64 bytes in a row), an instruction 16
+                    // pixels of one input row: four patches.  96 such items (six rows of 64 patches) are
+                    // six per wave; wave 0 also loads the pixels beside the tile's first and last patch.
+                    // A lane's four channels go to four planes.
+                    const int ln = fresh_lane();
+                    const int c4 = step * NW + (ln & 3) * 4;         // (c_in is a multiple of 4)
+                    v4f px[6], beside = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int i = 0; i < 6; ++i) {
+                        const int pix = wave * 16 + (ln >> 2), patch = pix >> 2, q = pix & 3;   // row i
+                        const int off = inv[2 * patch];
+                        const uint32_t vmask = uint32_t(inv[2 * patch + 1]);
+                        const bool ok = ((vmask >> i) & (vmask >> (9 + q)) & 1u) && c4 < a.c_in;
+                        px[i] = four(ok, off + (i * a.w + q) * a.c_in + c4);
+                    }
+                    if (wave == 0 && ln < 48) {
+                        const int e = ln >> 2, r = e >> 1, patch = (e & 1) ? 63 : 0;
+                        const int off = inv[2 * patch];
+                        const uint32_t vmask = uint32_t(inv[2 * patch + 1]);
+                        const bool ok = ((vmask >> r) & (vmask >> ((e & 1) ? 13 : 8)) & 1u) && c4 < a.c_in;
+                        beside = four(ok, off + (r * a.w + ((e & 1) ? 4 : -1)) * a.c_in + c4);
+                    }
+                    if (step > 0) __syncthreads();                   // every wave has read its channel of the step before
+#pragma unroll
+                    for (int i = 0; i < 6; ++i)
+#pragma unroll
+                        for (int k4 = 0; k4 < 4; ++k4)
+                            lds[((ln & 3) * 4 + k4) * PLANE_FLOATS + i * QUAD_FLOATS + wave * 16 + (ln >> 2)] = px[i][k4];
+                    if (wave == 0 && ln < 48) {
+#pragma unroll
+                        for (int k4 = 0; k4 < 4; ++k4) lds[((ln & 3) * 4 + k4) * PLANE_FLOATS + 6 * QUAD_FLOATS + (ln >> 2)] = beside[k4];
+                    }
+                    store_batch(rec_w);
+                    __syncthreads();
+                    if (k != k_end) {
+                        load_patch(slot_at);
+                        run_records(k, k_end);
+                    }
                 }
             }
         } else if constexpr (VEC) {
@@ -932,7 +1063,11 @@ template <int NW, int CH>
 hipError_t launch_any(const TiledArgs &a, int64_t wgs, hipStream_t st, bool vec, int layout, int dtype, int dev)
 {
     if constexpr (NW == 16)
-        if (a.priv) return launch_shape<float, PCONV_NCHW, true, NW, CH, false, true>(a, wgs, st, dev);
+        if (a.priv) {
+            if (vec) return launch_shape<float, PCONV_NCHW, true, NW, CH, false, true>(a, wgs, st, dev);
+            return dtype == PCONV_F32 ? launch_shape<float, PCONV_NHWC, false, NW, CH, false, true>(a, wgs, st, dev)
+                                      : launch_shape<bf16_t, PCONV_NHWC, false, NW, CH, false, true>(a, wgs, st, dev);
+        }
     if (vec)
         return a.split_units ? launch_shape<float, PCONV_NCHW, true, NW, CH, true>(a, wgs, st, dev)
                              : launch_shape<float, PCONV_NCHW, true, NW, CH, false>(a, wgs, st, dev);
@@ -1047,6 +1182,8 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
     // and overwrite each other's partial sums.
     const bool rows_whole = win % 4 == 0 || n_tiles == 1 || 64 % px == 0;
     const bool can_split = p.vec && !pool && !sub2 && y_bytes < (int64_t(1) << 31) && rows_whole;
+    // waves on their own: rows of patches by 128-bit loads, or channels last in whole quads
+    const bool can_priv = p.nw == 16 && (p.vec || (layout == PCONV_NHWC && h->c_in % 4 == 0));
     const int64_t whole_units = int64_t(n_tiles) * ((blocks + p.nw - 1) / p.nw);
     auto units_of = [&](int ks) { return (blocks + (p.nw >> ks) - 1) / (p.nw >> ks); };   // filter groups per tile
     if (whole_units > slots / 2) {
@@ -1074,28 +1211,32 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
         };
         // whole units, the waves of a workgroup splitting the channels of a chunk 1, 2 or 4 ways: a chunk
         // costs about 2 for its staging and 1.9 for 142 records on the whole workgroup (256 channels
-        // @56: 133, 98, 84 us); the tiles of an eighth of the image share the units of one XCD
+        // @56: 133, 98, 84 us; register staging, which nothing overlaps, 2.4 and 4.8 in quads of
+        // channels, 8 and 4 otherwise); an eighth of the tiles shares the compute units of one XCD
+        const bool quads = layout == PCONV_NHWC && h->c_in % 4 == 0;
+        const double t_stage = p.vec ? 2.0 : quads ? 2.4 : 8.0, t_records = p.vec ? 1.9 : quads ? 4.8 : 4.0;
         const double chunk_scale = p.nw == 16 ? 1.0 : 0.5;
         for (int ks = 0; ks <= 2; ++ks) {
             if (ks > 0 && int64_t(n_tiles) * units_of(ks - 1) > slots / 2) break;
             const double rounds = std::ceil(double((n_tiles + 7) / 8) * units_of(ks) / (slots / 8.0));
-            consider(rounds * (6.0 + chunk_scale * n_chunks * (2.0 + 1.9 * records / 142.0 / (1 << ks))), false, ks, false);
+            consider(rounds * (6.0 + chunk_scale * n_chunks * (t_stage + t_records * records / 142.0 / (1 << ks))), false, ks, false);
         }
         // units shared by P workgroups, which pass the sums on one after the other (256 channels @56, one
         // image: 99 us, four: 83)
         if (can_split)
             consider(6.0 + 4.0 * chunk_scale * whole_units * n_chunks / slots + std::min(90.0, 10.0 * slots / double(whole_units)), true, 0, false);
         // one filter block per workgroup, every wave its own channels: per visited channel 0.055 and per
-        // record 0.03 (256 channels @56, one image: 29 us; 512 @14: 40 us)
+        // record 0.03 (256 channels @56, one image: 29 us; 512 @14: 40 us); channels last 3.3 for 16
+        // channels (128 @28, eight images: 40 us, whole units 120, 81, 62)
         // (it waits for nothing: a test that limits the waits gets a form that has them)
-        if (p.vec && p.nw == 16 && g_spin_limit.load() == kDefaultSpinLimit) {
+        if (can_priv && !(p.vec && g_spin_limit.load() != kDefaultSpinLimit)) {
             const double visits = double(h->tiled.visits) / blocks, recs = double(h->tiled.meta.size()) / blocks;
-            consider(std::ceil(double(n_tiles) * blocks / slots) * (9.6 + 0.055 * visits + 0.03 * recs), false, 4, true);
+            consider(std::ceil(double(n_tiles) * blocks / slots) * (p.vec ? 9.6 + 0.055 * visits + 0.03 * recs : 10.0 + 3.3 * ((h->c_in + 15) / 16)), false, 4, true);
         }
     }
     if (force_split >= 0) { p.split = can_split && force_split != 0; p.one_set = p.split && force_split == 2; if (p.split) { p.ks_log2 = 0; p.priv = false; } }
     if (force_ks >= 0) {
-        p.priv = force_ks == 4 && p.vec && p.nw == 16;
+        p.priv = force_ks == 4 && can_priv;
         p.ks_log2 = force_ks < 4 || p.priv ? force_ks : 0;
         if (p.priv) p.split = p.one_set = false;
     }

@@ -310,6 +310,21 @@ def test_waves_on_their_own(shape):
         check_full(spec, L, x, "f32", "nchw", stride, relu=bool(n & 1), use_bias=bool(co & 1), policy=2, what=f"lone{shape}")
 
 
+@pytest.mark.parametrize("ks_log2", [4, 0, 2])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_channels_last_in_quads(ks_log2, dtype):
+    """Channels-last staging four channels at a time (c_in a multiple of 4), by waves on their own and by
+    chunk, at ragged widths, tiles that end inside a row of patches and partial steps of channels;
+    the last shape's channel count takes the scalar staging."""
+    P.pconv_debug_set_tiling(16, ks_log2, -1)
+    for j, (n, ci, co, h, w, stride) in enumerate([(1, 4, 5, 3, 2, 1), (2, 20, 9, 9, 5, 1), (1, 36, 70, 14, 15, 1), (3, 44, 8, 33, 22, 1),
+                                                   (1, 24, 6, 5, 300, 1), (2, 68, 10, 17, 30, 2), (1, 1040, 4, 6, 7, 1), (1, 18, 5, 9, 11, 1)]):
+        spec = LayerSpec("quads", n, ci, co, h, w, stride=stride, dtype=dtype, num_patterns=12,
+                         pattern_dist="uniform", keep_div=2.0, count_dist="bernoulli")
+        L = make_layer(spec, 5200 + j); x = make_input(spec, 5200 + j, "nhwc")
+        check_full(spec, L, x, dtype, "nhwc", stride, relu=bool(j & 1), use_bias=bool(j & 2), policy=2, what=f"quads{j}_ks{ks_log2}")
+
+
 def test_four_scp_table():
     """A table of the paper's four Sparse Convolution Patterns alone (the 4-pattern row of the
     pattern-count experiment)."""
