@@ -193,6 +193,24 @@ def generate_patch():
     return L + ["s_waitcnt lgkmcnt(0)"]
 
 
+def generate_patch_shifted():
+    """The same where every patch starts four columns after its left neighbour: the halo columns are
+    the neighbouring lanes' registers, by wave shifts, masked to zero at the image's edge (%[maskl],
+    %[maskr]).  Half the LDS cycles of the form above.  What lane 0 and lane 63 have no neighbour for
+    is twelve further words (LDS address %[further] + 4 * lane), put in place lane by lane."""
+    L = ["ds_read_b128 v[%d:%d], %%[va] offset:%d" % (INP + 4 * r, INP + 4 * r + 3, r * QUAD_BYTES) for r in range(6)]
+    L += ["ds_read_b32 v24, %[further]", "s_waitcnt lgkmcnt(0)"]
+    L += ["v_readlane_b32 s%d, v24, %d" % (68 + i, i) for i in range(12)]
+    for r in range(6):
+        for col, source, mask, way in ((0, 4, "maskl", "wave_shr"), (5, 1, "maskr", "wave_shl")):
+            L.append("v_and_b32_dpp v%d, v%d, %%[%s] %s:1 row_mask:0xf bank_mask:0xf bound_ctrl:0" % (in_reg(r, col), in_reg(r, source), mask, way))
+    L.append("s_nop 4")
+    for r in range(6):
+        L.append("v_writelane_b32 v%d, s%d, 0" % (in_reg(r, 0), 68 + 2 * r))
+        L.append("v_writelane_b32 v%d, s%d, 63" % (in_reg(r, 5), 68 + 2 * r + 1))
+    return L
+
+
 def write_code_header(path):
     assert all(bin(m).count("1") <= 4 for m in CODE_MASKS)
     with open(path, "w") as f:
@@ -218,6 +236,7 @@ def main():
     write_inc(out, generate())
     write_inc(os.path.join(os.path.dirname(out), "pconv_tiled_compute_scalar.inc"), generate(True))
     write_inc(os.path.join(os.path.dirname(out), "pconv_tiled_patch.inc"), generate_patch())
+    write_inc(os.path.join(os.path.dirname(out), "pconv_tiled_patch_shifted.inc"), generate_patch_shifted())
     write_inc(os.path.join(os.path.dirname(out), "pconv_tiled_takeover.inc"), generate_takeover())
     write_code_header(os.path.join(os.path.dirname(out), "pconv_tiled_code_masks.inc"))
 

@@ -206,7 +206,10 @@ conv_tiled_kernel(const TiledArgs a)
     // (one_set: no XCD sets - the shares of all workgroups are then equal whatever the number of tiles,
     // and the workgroup that a piece waits for is simply the one before it)
     const bool one_set = PRIV || (SPLIT && a.one_set);
-    const int set = one_set ? 0 : int(blockIdx.x & 7), j_in_set = one_set ? int(blockIdx.x) : int(blockIdx.x >> 3);
+    // (PRIV: XCD s gets the s-th eighth of the units, so that its L2 serves few tiles)
+    const int per_xcd = PRIV ? (a.n_units + 7) >> 3 : 0;
+    const int set = one_set ? 0 : int(blockIdx.x & 7);
+    const int j_in_set = PRIV ? int(blockIdx.x & 7) * per_xcd + int(blockIdx.x >> 3) : one_set ? int(blockIdx.x) : int(blockIdx.x >> 3);
     const int set_stride = one_set ? 1 : 8;
     // set s: the contiguous block of tiles [s * tps, (s + 1) * tps): neighbouring tiles (which share
     // input rows and columns) then run next to each other in time on one XCD and find them in its L2
@@ -238,7 +241,7 @@ conv_tiled_kernel(const TiledArgs a)
         head_c0 = int(it0 - int64_t(ua) * n_chunks);                         // > 0: unit ua begins elsewhere
         tail_c1 = int(it1 - int64_t(ub) * n_chunks);                         // < n_chunks: unit ub ends elsewhere
     } else {
-        if (j_in_set >= set_units) return;
+        if (j_in_set >= set_units || (PRIV && int(blockIdx.x >> 3) >= per_xcd)) return;
     }
     const bool has_head = head_c0 > 0, has_tail = tail_c1 < n_chunks;
     const bool one_piece = ua == ub;
@@ -606,8 +609,21 @@ conv_tiled_kernel(const TiledArgs a)
             // the lane's neighbourhood of the channel in slot `at` (bytes) to the registers of the record loop
             v16f in0, in1;
             v4f in2;
+            const bool even = !VEC || a.px * 4 == a.w;               // every patch starts four columns after its neighbour
             auto load_patch = [&](uint32_t at) {
                 const int ln = fresh_lane();
+                if (even) {
+                    // all ones where the column beside the patch lies in the image
+                    const uint32_t vmask = uint32_t(inv[2 * ln + 1]);
+                    const int maskl = int(vmask << 23) >> 31, maskr = int(vmask << 18) >> 31;
+                    asm volatile(
+#include "pconv_tiled_patch_shifted.inc"
+                        : "=&{v[28:43]}"(in0), "=&{v[44:59]}"(in1), "=&{v[60:63]}"(in2)
+                        : [va] "v"(at + uint32_t(ln) * 16u), [further] "v"(at + uint32_t(6 * QUAD_FLOATS * 4) + uint32_t(ln) * 4u),
+                          [maskl] "v"(maskl), [maskr] "v"(maskr)
+                        : "v24", "s68", "s69", "s70", "s71", "s72", "s73", "s74", "s75", "s76", "s77", "s78", "s79");
+                    return;
+                }
                 const int4 ht = *reinterpret_cast<const int4 *>(halo_tab + 64 + 4 * ln);
                 asm volatile(
 #include "pconv_tiled_patch.inc"
@@ -631,7 +647,7 @@ conv_tiled_kernel(const TiledArgs a)
             };
             auto run_records = [&](uint32_t k, uint32_t k_end) {
                 while (k < k_end) {
-                    if (k_end > kb_end) {
+                    if (k_end > kb_end || k < kb) {
                         float4 rec_w;
                         fetch_batch(k, rec_w);
                         __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0)
@@ -657,29 +673,40 @@ conv_tiled_kernel(const TiledArgs a)
                 const int per_wave = (a.c_in + NW - 1) / NW;
                 const int c_lo = min(a.c_in, wave * per_wave), c_hi = min(a.c_in, c_lo + per_wave);
                 float *slot = lds + wave * ROWS_FLOATS;
-                int win = c_lo;                                      // lane j: first record of channel win + j
-                uint32_t first = ptr_row[min(win + lane, ptr_max)];
+                // The workgroups of an XCD walk the same channels: each starts one further on, so that what it
+                // asks for was fetched into the L2 by its neighbour a step before.
+                const int c_start = c_hi > c_lo ? c_lo + int(blockIdx.x >> 3) % (c_hi - c_lo) : c_lo;
+                const int c_stop = c_start + (c_hi - c_lo);          // (channels from c_hi on stand for those from c_lo on)
+                auto channel = [&](int c) { return c < c_hi ? c : c - (c_hi - c_lo); };
+                int win = c_start;                                   // lane j: first record of channel win + j and their number
+                uint32_t first = 0, count = 0;
+                auto load_window = [&]() {
+                    const int at = channel(min(win + fresh_lane(), c_stop));
+                    first = ptr_row[min(at, ptr_max)];
+                    count = ptr_row[min(at + 1, ptr_max)] - first;
+                };
+                load_window();
                 // the next channel at or after c that one of the four filters is connected to, its records
                 uint32_t nk = 0, nk_end = 0;
                 auto next_channel = [&](int c) {
-                    for (; c < c_hi; ++c) {
-                        if (c + 1 - win > 63) { win = c; first = ptr_row[min(win + fresh_lane(), ptr_max)]; }
+                    for (; c < c_stop; ++c) {
+                        if (c - win > 63) { win = c; load_window(); }
                         nk = __builtin_amdgcn_readlane(first, c - win);
-                        nk_end = __builtin_amdgcn_readlane(first, c + 1 - win);
+                        nk_end = nk + __builtin_amdgcn_readlane(count, c - win);
                         if (nk != nk_end) break;
                     }
                     return c;
                 };
-                int c = next_channel(c_lo);
-                if (c < c_hi) stage_rows(c, slot);
-                while (c < c_hi) {
+                int c = next_channel(c_start);
+                if (c < c_stop) stage_rows(channel(c), slot);
+                while (c < c_stop) {
                     const uint32_t k = nk, k_end = nk_end;
                     __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): the channel is in LDS
                     // with the neighbourhood in registers the slot is free, and the next channel is on its
                     // way to it while the records run
                     load_patch(slot_at);
                     c = next_channel(c + 1);
-                    if (c < c_hi) stage_rows(c, slot);
+                    if (c < c_stop) stage_rows(channel(c), slot);
                     run_records(k, k_end);
                 }
             } else {
@@ -1307,7 +1334,7 @@ int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float
             a.epoch = call + 1u ? call + 1u : 1u;
         }
     } else {
-        wgs = a.priv ? units : int64_t((a.n_tiles + 7) / 8) * 8 * a.n_groups;   // one per unit of the largest set, in every set
+        wgs = a.priv ? (units + 7) / 8 * 8 : int64_t((a.n_tiles + 7) / 8) * 8 * a.n_groups;   // one per unit of the largest set, in every set
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
     const hipError_t e = nw == 16 ? launch_any<16, 8>(a, wgs, st, vec, layout, dtype, h->device)
