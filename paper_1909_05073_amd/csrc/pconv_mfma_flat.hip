@@ -451,12 +451,13 @@ bool launch_conv_flat(const pconv_handle *h, const void *x, void *y, const float
     a.rhw = (a.hw + 7) & ~7;
     a.div_howo = make_fast_div(uint32_t(a.howo)); a.div_wo = make_fast_div(uint32_t(a.wo));
     a.div_rhw = make_fast_div(uint32_t(a.rhw));
-    // The shape with the smallest estimate of the layer's time, in microseconds, fitted to all shapes on
-    // the ResNet-50 layers with 1, 8 and 32 images.  Few workgroups: the time of one workgroup, which
-    // is start and end (4) and per block of channels the latency of its loads and LDS traffic (1.1 to
-    // 1.75).  Many: the time a compute unit is busy with a workgroup, per wave 0.34 for start and end
-    // of every block of outputs and per block of channels 0.03 for each block of weights, 0.035 for each
-    // block of matrix instructions and 0.43 for 64 staging items, times workgroups per unit.
+    // The shape with the smallest estimate of the layer's time, in microseconds.  Few workgroups: the
+    // time of one, a start and end and per block of channels the latency of its loads and LDS traffic.
+    // Many: what a compute unit spends on a workgroup, per wave and block of outputs, and per wave and
+    // block of channels for every block of weights, of matrix instructions and for 64 staging items.
+    // The constants are a fit to all shapes on thirteen layers (24 to 512 channels, 7 to 224 pixels
+    // square, both strides) with 1 to 32 images: the shape chosen takes 1 % longer than the fastest
+    // one on average, 20 % at most.
     static constexpr int kShapes[][4] = {{2, 2, 4, 1}, {2, 2, 2, 1}, {2, 2, 2, 2}, {2, 2, 1, 4}, {2, 1, 4, 1}, {2, 1, 2, 2},
                                          {1, 2, 4, 1}, {1, 2, 2, 2}, {1, 2, 1, 4}, {1, 1, 4, 1}, {1, 1, 2, 2}, {1, 1, 2, 4}, {1, 1, 1, 8}};
     FlatShape best{};
@@ -474,14 +475,13 @@ bool launch_conv_flat(const pconv_handle *h, const void *x, void *y, const float
         if (items > 64 * s.wp * s.r || (s.r == 2 && (s.mb == 2 || layout == PCONV_NHWC)) || s.lds > kLdsOfUnit) continue;
         const int iters = (a.cb16 + s.wk - 1) / s.wk;
         const double groups = double((a.total + np - 1) / np) * ((a.fblocks + s.mb - 1) / s.mb) / cus;
-        // (planes of an odd number of pixels make half of the loads unaligned)
-        const double share = double(items) / (64 * s.wp) * (layout == PCONV_NCHW && a.hw % 2 ? 1.6 : 1.0);
-        const double chain = 4.0 + iters * ((s.mb == 1 ? 0.9 : s.nb == 1 ? 1.85 : 1.6) + 0.5 * share);
-        const double busy = waves * (0.34 * s.mb * s.nb + iters * (0.03 * s.mb + 0.035 * s.mb * s.nb + 0.43 * share));
+        const double share = double(items) / (64 * s.wp);
+        const double chain = 2.4 + iters * ((s.mb == 1 ? 1.33 : s.nb == 1 ? 1.44 : 1.99) + 0.1 * share);
+        const double busy = waves * (0.064 * s.mb * s.nb + iters * (0.04 * s.mb + 0.1 * s.mb * s.nb + 0.04 * share));
         const int resident = int(std::min<int64_t>(kLdsOfUnit / s.lds, 8 / waves));
         const double rounds = std::ceil(groups / resident);
         const double lo = std::min(groups * busy, rounds * chain), hi = std::max(groups * busy, rounds * chain);
-        const double time = hi + 0.2 * lo;
+        const double time = hi + 0.25 * lo;
         if (best.mb == 0 || time < best_time) { best = s; best_time = time; }
     }
     if (best.mb == 0) return false;
