@@ -37,7 +37,9 @@ struct TiledStream {
     int row_len = 0;                    // entries per chan_ptr row: round_up(C, kTileCH) + 1
     std::vector<int32_t>  slot_filter;  // [num_blocks * kTileFB] original filter index or -1
     std::vector<uint32_t> chan_ptr;     // [num_blocks][row_len]
+    std::vector<uint32_t> chan_mid;     // [num_blocks][row_len] first record of slots 2 and 3 of the channel
     int64_t visits = 0;                 // (block, channel) pairs with a record
+    int64_t half_visits = 0;            // (block, half of its slots, channel) triples with a record
     std::vector<uint32_t> meta;         // [R+1] record words (see pconv_tiled_codes.h), one pad
     std::vector<float>    w4;           // [R+1][4]
 };
@@ -59,6 +61,7 @@ struct pconv_handle {
     // device copies (register-tiled kernel)
     int32_t  *d_slot_filter = nullptr;
     uint32_t *d_chan_ptr = nullptr;
+    uint32_t *d_chan_mid = nullptr;
     uint32_t *d_meta = nullptr;
     float    *d_w4 = nullptr;
     // device copies (matrix-core kernels, bf16 handles only): the masked weights as dense
@@ -111,7 +114,7 @@ int measure_fma_peak(double *tflops);
 // whether the automatic policy should take the tiled kernel for a call it supports
 bool tiled_preferred(int hin, int win, int stride);
 // Test override of the tiled kernel's launch choices: waves per workgroup (8 or 16, anything else =
-// automatic), log2 of the channel split inside a workgroup (0..2 or 4, anything else = automatic), and
+// automatic), log2 of the channel split inside a workgroup (0..2, 4 or 5, anything else = automatic), and
 // whether workgroups may share a unit of work (0 / 1, anything else = automatic).
 void set_tiled_tuning(int waves, int ks_log2, int split_units);
 // Test override of the iteration limit of the kernels' bounded waits (<= 0 restores the default).

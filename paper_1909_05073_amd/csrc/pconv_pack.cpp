@@ -218,6 +218,7 @@ void build_tiled_stream(const Canonical &cn, const uint16_t *table, int np, int 
     }
 
     out.chan_ptr.assign(size_t(nb) * out.row_len, 0);
+    out.chan_mid.assign(size_t(nb) * out.row_len, 0);
     out.meta.clear();
     out.w4.clear();
     std::vector<std::vector<int32_t>> by_slot(FB, std::vector<int32_t>(size_t(c_in), -1));
@@ -233,6 +234,7 @@ void build_tiled_stream(const Canonical &cn, const uint16_t *table, int np, int 
             row[c] = uint32_t(out.meta.size());
             bool first = true;
             for (int s = 0; s < FB; ++s) {
+                if (s == FB / 2) out.chan_mid[size_t(b) * out.row_len + c] = uint32_t(out.meta.size());
                 const int32_t k = by_slot[s][c];
                 if (k < 0) continue;
                 for (const Piece &pc : pieces[cn.pat[k]]) {
@@ -248,7 +250,11 @@ void build_tiled_stream(const Canonical &cn, const uint16_t *table, int np, int 
                 }
             }
         }
-        for (int c = c_in; c <= cpad; ++c) row[c] = uint32_t(out.meta.size());
+        for (int c = c_in; c <= cpad; ++c) row[c] = out.chan_mid[size_t(b) * out.row_len + c] = uint32_t(out.meta.size());
+        for (int c = 0; c < c_in; ++c) {
+            const uint32_t mid = out.chan_mid[size_t(b) * out.row_len + c];
+            out.half_visits += (mid > row[c]) + (row[c + 1] > mid);
+        }
     }
     // padding: the kernel asks for the words of records k+1 and k+2 while it executes record k
     for (int j = 0; j < 3; ++j) out.meta.push_back(0u);

@@ -101,6 +101,8 @@ struct TiledArgs {
     int n_units;                // n_tiles * n_groups: (tile, filter group) pairs
     int n_chunks;               // chunks of CH input channels
     int split_units;            // 1: a workgroup's share of the work may begin and end inside a unit
+    int halves;                 // 1 (with priv): a workgroup works on two of its block's four slots
+    const uint32_t *chan_mid;   // first record of slots 2 and 3 per (block, channel), rows as chan_ptr
     int priv;                   // 1: the 16 waves are 16 channel ranges of one filter block (VEC kernel)
     int one_set;                // 1 (with split_units): the iterations are dealt over all workgroups as one set
     uint32_t *flags;            // [gridDim.x] hand-over words of this call (split_units only)
@@ -145,13 +147,17 @@ __device__ __forceinline__ size_t act_at(int n, int c, int y, int x, int C, int 
 // wait for but its own loads, and the 16 partial sums are added through LDS at the end.  The halo
 // columns are not staged but read out of the neighbouring lanes' quads: what bounds this form is the
 // number of load instructions per channel (7 instead of 18; 256 channels @56, one image: 41 us with
-// 18, 29 with 7; shared units 99).  Staging the next channel while the records of the present one run
+// 18, 28 with 7; shared units 99).  Staging the next channel while the records of the present one run
 // changes little (the other waves fill the gap) but costs nothing, the input registers are the buffer.
 // Channels last, a wave cannot load one channel well: there the waves stage 16 channels together, four
-// lanes to a pixel, and then run one each (128 channels @28, eight images: 40 us; with a lane per pixel
+// lanes to a pixel, and then run one each (128 channels @28, eight images: 38 us; with a lane per pixel
 // 111, in whole units with one channel per load 155).
+// Where there are fewer blocks than half of the compute units, a workgroup takes two of its block's four
+// slots (halves): 512@14 31 us instead of 40, 512@28 33 (42), 256->512@28 21 (26); with enough blocks
+// it loses (256@56 39 for 28), since either half visits more than half of the channels.
 // One image, us, against the shared or whole units used before: 64->64@224 30 (56, whole units too),
-// 128@112 39 (91), 128->256@56 20 (59), 256->512@28 28 (94), 512@28 42 (108), 512@14 40 (103).
+// 128@112 35 (91), 128->256@56 19 (59), 256@56 28 (99), 256->512@28 21 (94), 512@28 33 (108),
+// 512@14 31 (103).
 //
 // VEC: fp32 NCHW tensors at least 4 wide move the four centre columns of a patch row (and the four
 // outputs of a row) with one 128-bit access; the inputs go from global memory straight to LDS.
@@ -257,7 +263,8 @@ conv_tiled_kernel(const TiledArgs a)
         else { unit = ua; c_begin = head_c0; }
         const bool takes_over = SPLIT && c_begin > 0, hands_on = SPLIT && c_end < n_chunks;
         const int tile = one_set ? unit / a.n_groups : set_tile0 + unit / a.n_groups, group = unit % a.n_groups;
-        const int fblk = group * fw + (wave - ksplit * fw);
+        const int half = PRIV && a.halves ? group & 1 : -1;              // slots 0 and 1, or 2 and 3; -1: all
+        const int fblk = PRIV ? (a.halves ? group >> 1 : group) : group * fw + (wave - ksplit * fw);
         const bool active = fblk < a.n_blocks;
 
         if (SPLIT) __syncthreads();                      // every wave has left the previous piece: LDS is free
@@ -268,6 +275,13 @@ conv_tiled_kernel(const TiledArgs a)
         // (Loaded first: they are on the way while the tables below are set up.)
         const int ptr_max = a.row_len - 1;               // last entry of a row: end of the block's records
         const uint32_t *__restrict__ ptr_row = a.chan_ptr + size_t(active ? fblk : 0) * a.row_len;
+        // (PRIV: the records of the workgroup's slots of a channel)
+        const uint32_t *__restrict__ mid_row = a.chan_mid + size_t(active ? fblk : 0) * a.row_len;
+        auto channel_records = [&](int at, uint32_t &first, uint32_t &count) {
+            const int c0 = min(at, ptr_max);
+            first = half == 1 ? mid_row[c0] : ptr_row[c0];
+            count = (half == 0 ? mid_row[c0] : ptr_row[min(at + 1, ptr_max)]) - first;
+        };
         int win_base = c_begin;
         // one register holds both bounds: first record (24 bits) and number of records (8 bits)
         auto load_bounds = [&]() {
@@ -681,9 +695,7 @@ conv_tiled_kernel(const TiledArgs a)
                 int win = c_start;                                   // lane j: first record of channel win + j and their number
                 uint32_t first = 0, count = 0;
                 auto load_window = [&]() {
-                    const int at = channel(min(win + fresh_lane(), c_stop));
-                    first = ptr_row[min(at, ptr_max)];
-                    count = ptr_row[min(at + 1, ptr_max)] - first;
+                    channel_records(channel(min(win + fresh_lane(), c_stop)), first, count);
                 };
                 load_window();
                 // the next channel at or after c that one of the four filters is connected to, its records
@@ -716,9 +728,7 @@ conv_tiled_kernel(const TiledArgs a)
                 const int steps = (a.c_in + NW - 1) / NW;
                 for (int step = 0; step < steps; ++step) {
                     if ((step & 63) == 0) {
-                        const int at = (step + fresh_lane()) * NW + wave;
-                        first = ptr_row[min(at, ptr_max)];
-                        count = ptr_row[min(at + 1, ptr_max)] - first;
+                        channel_records((step + fresh_lane()) * NW + wave, first, count);
                     }
                     const uint32_t k = __builtin_amdgcn_readlane(first, step & 63);
                     const uint32_t k_end = k + __builtin_amdgcn_readlane(count, step & 63);
@@ -878,6 +888,7 @@ conv_tiled_kernel(const TiledArgs a)
             v4f *red = reinterpret_cast<v4f *>(lds);
 #pragma unroll
             for (int pass = 0; pass < FB / 2; ++pass) {
+                if (half >= 0 && pass != half) continue;
                 __syncthreads();                         // the staging slots, or the pass before, are done with
                 if (wave < parts) {
 #pragma unroll
@@ -941,7 +952,7 @@ conv_tiled_kernel(const TiledArgs a)
         // the patch coordinates are recomputed here instead of being kept in registers across the loop
         int pidx_e = tile * 64 + lane;
         asm volatile("" : "+v"(pidx_e));
-        const bool writer = active && (PRIV ? wave < FB : ksplit == 0) && pidx_e < a.n_patches;
+        const bool writer = active && (PRIV ? wave < FB && (half < 0 || wave >> 1 == half) : ksplit == 0) && pidx_e < a.n_patches;
         if constexpr (VEC && SPLIT) {
             if (takes_over) {
                 // The predecessor (id - 8: same set, previous range) started before this workgroup
@@ -1151,7 +1162,7 @@ std::atomic<int> g_spin_limit{kDefaultSpinLimit};
 void set_tiled_tuning(int waves, int ks_log2, int split_units)
 {
     g_force_waves.store((waves == 8 || waves == 16) ? waves : 0);
-    g_force_ks.store((ks_log2 >= 0 && ks_log2 <= 2) || ks_log2 == 4 ? ks_log2 : -1);
+    g_force_ks.store((ks_log2 >= 0 && ks_log2 <= 2) || ks_log2 == 4 || ks_log2 == 5 ? ks_log2 : -1);
     g_force_split.store((split_units >= 0 && split_units <= 2) ? split_units : -1);
 }
 
@@ -1216,7 +1227,7 @@ namespace {
 // How a call is spread over the chip.
 struct TiledPlan {
     int nw;               // waves per workgroup
-    bool vec, split, one_set, priv;
+    bool vec, split, one_set, priv, halves;
     int ks_log2;
 };
 
@@ -1268,8 +1279,8 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
         // with one and four images.
         const double records = double(h->tiled.meta.size()) * p.nw / blocks / n_chunks;   // of a whole unit's chunk
         double best = 0.0;
-        auto consider = [&](double t, bool split, int ks, bool priv) {
-            if (best == 0.0 || t < best) { best = t; p.split = split; p.ks_log2 = ks; p.priv = priv; }
+        auto consider = [&](double t, bool split, int ks, bool priv, bool halves = false) {
+            if (best == 0.0 || t < best) { best = t; p.split = split; p.ks_log2 = ks; p.priv = priv; p.halves = halves; }
         };
         // whole units, the waves of a workgroup splitting the channels of a chunk 1, 2 or 4 ways: a chunk
         // costs about 2 for its staging and 1.9 for 142 records on the whole workgroup (256 channels
@@ -1288,18 +1299,23 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
         if (can_split)
             consider(6.0 + 4.0 * chunk_scale * whole_units * n_chunks / slots + std::min(90.0, 10.0 * slots / double(whole_units)), true, 0, false);
         // one filter block per workgroup, every wave its own channels: per visited channel 0.055 and per
-        // record 0.03 (256 channels @56, one image: 29 us; 512 @14: 40 us); channels last 3.3 for 16
-        // channels (128 @28, eight images: 40 us, whole units 120, 81, 62)
+        // record 0.03 (256 channels @56, one image: 28 us; 512 @14: 40 us); channels last 3.3 for 16
+        // channels (128 @28, eight images: 38 us, whole units 120, 81, 62)
         // (it waits for nothing: a test that limits the waits gets a form that has them)
         if (can_priv && !(p.vec && g_spin_limit.load() != kDefaultSpinLimit)) {
             const double visits = double(h->tiled.visits) / blocks, recs = double(h->tiled.meta.size()) / blocks;
-            consider(std::ceil(double(n_tiles) * blocks / slots) * (p.vec ? 9.6 + 0.055 * visits + 0.03 * recs : 10.0 + 3.3 * ((h->c_in + 15) / 16)), false, 4, true);
+            auto lone = [&](double v, double r) { return p.vec ? 8.5 + 0.055 * v + 0.03 * r : 10.0 + 3.3 * ((h->c_in + 15) / 16); };
+            consider(std::ceil(double(n_tiles) * blocks / slots) * lone(visits, recs), false, 4, true);
+            // two of the block's four filters per workgroup, where there are not enough blocks for the chip
+            if (p.vec)
+                consider(std::ceil(2.0 * n_tiles * blocks / slots) * lone(double(h->tiled.half_visits) / (2 * blocks), recs / 2), false, 4, true, true);
         }
     }
     if (force_split >= 0) { p.split = can_split && force_split != 0; p.one_set = p.split && force_split == 2; if (p.split) { p.ks_log2 = 0; p.priv = false; } }
     if (force_ks >= 0) {
-        p.priv = force_ks == 4 && can_priv;
-        p.ks_log2 = force_ks < 4 || p.priv ? force_ks : 0;
+        p.priv = force_ks >= 4 && can_priv;
+        p.halves = force_ks == 5 && p.priv;
+        p.ks_log2 = p.priv ? 4 : force_ks < 4 ? force_ks : 0;
         if (p.priv) p.split = p.one_set = false;
     }
     if (p.split && force_ks < 0) p.ks_log2 = 0;
@@ -1341,7 +1357,8 @@ int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float
     a.split_units = plan.split; a.one_set = plan.one_set; a.priv = plan.priv; a.ks_log2 = plan.ks_log2;
     a.n_records = uint32_t(h->tiled.meta.size()) - 3u;
     const int fw = nw >> a.ks_log2;
-    a.n_groups = (a.n_blocks + fw - 1) / fw;
+    a.halves = plan.priv && plan.halves; a.chan_mid = h->d_chan_mid;
+    a.n_groups = ((a.n_blocks + fw - 1) / fw) << a.halves;
     const int64_t units = int64_t(a.n_tiles) * a.n_groups;
     if (units > 0x3FFFFFFF) { set_error("pconv_conv2d: too many workgroups"); return PCONV_UNSUPPORTED; }
     a.n_units = int(units);

@@ -297,12 +297,13 @@ LONE_SHAPES = [  # (n, c_in, c_out, h, w, stride): widths 0-3 past a multiple of
 ]
 
 
+@pytest.mark.parametrize("ks_log2", [4, 5])              # 5: two of a block's four filters per workgroup
 @pytest.mark.parametrize("shape", LONE_SHAPES)
-def test_waves_on_their_own(shape):
+def test_waves_on_their_own(shape, ks_log2):
     """The form of the tiled kernel for few units of work: every wave its own channels, halo columns out
     of the neighbouring lanes' patches."""
     n, ci, co, h, w, stride = shape
-    P.pconv_debug_set_tiling(16, 4, -1)
+    P.pconv_debug_set_tiling(16, ks_log2, -1)
     for dense in (False, True):                          # (a dense kernel is three records)
         spec = LayerSpec("lone", n, ci, co, h, w, stride=stride, num_patterns=1 if dense else 12,
                          pattern_dist="dense" if dense else "uniform", keep_div=2.0, count_dist="bernoulli")
