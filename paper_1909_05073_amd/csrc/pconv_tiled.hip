@@ -94,6 +94,7 @@ struct TiledArgs {
     int n_img, c_in, row_len, h, w, c_out;
     int py, px;                 // patches per image column / row
     int n_patches, n_tiles, n_groups, n_blocks;
+    int tile_base;              // first tile of this launch
     int relu;
     int pool;                   // 1: y is the 2x2 / stride-2 max-pooled output (VEC kernel, whole units only)
     int sub2;                   // 1: stride 2: y holds the outputs at even rows and columns only
@@ -262,7 +263,7 @@ conv_tiled_kernel(const TiledArgs a)
         else if (piece - (has_tail ? 1 : 0) < n_whole) unit = first_whole + piece - (has_tail ? 1 : 0);
         else { unit = ua; c_begin = head_c0; }
         const bool takes_over = SPLIT && c_begin > 0, hands_on = SPLIT && c_end < n_chunks;
-        const int tile = one_set ? unit / a.n_groups : set_tile0 + unit / a.n_groups, group = unit % a.n_groups;
+        const int tile = a.tile_base + (one_set ? 0 : set_tile0) + unit / a.n_groups, group = unit % a.n_groups;
         const int half = PRIV && a.halves ? group & 1 : -1;              // slots 0 and 1, or 2 and 3; -1: all
         const int fblk = PRIV ? (a.halves ? group >> 1 : group) : group * fw + (wave - ksplit * fw);
         const bool active = fblk < a.n_blocks;
@@ -1229,6 +1230,7 @@ struct TiledPlan {
     int nw;               // waves per workgroup
     bool vec, split, one_set, priv, halves;
     int ks_log2;
+    int tail_tiles;       // tiles at the end that a second launch computes, by waves on their own
 };
 
 TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout, int dtype, bool pool, bool sub2)
@@ -1259,6 +1261,10 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
     const bool can_priv = p.nw == 16 && (p.vec || (layout == PCONV_NHWC && h->c_in % 4 == 0));
     const int64_t whole_units = int64_t(n_tiles) * ((blocks + p.nw - 1) / p.nw);
     auto units_of = [&](int ks) { return (blocks + (p.nw >> ks) - 1) / (p.nw >> ks); };   // filter groups per tile
+    const double records = double(h->tiled.meta.size()) * p.nw / blocks / n_chunks;       // of a whole unit's chunk
+    const double visits = double(h->tiled.visits) / blocks, recs = double(h->tiled.meta.size()) / blocks;
+    auto lone = [&](double v, double r) { return p.vec ? 8.5 + 0.055 * v + 0.03 * r : 10.0 + 3.3 * ((h->c_in + 15) / 16); };
+    const bool lone_ok = can_priv && !(p.vec && g_spin_limit.load() != kDefaultSpinLimit);
     if (whole_units > slots / 2) {
         if (can_split && p.nw == 16) {
             // Many units, but not a multiple of the number of compute units: whole units leave part of
@@ -1274,10 +1280,19 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
             const double t_share = double(whole_units) * n_chunks / slots + kShareOverhead;
             if (t_share < kShareGain * t_whole) p.split = p.one_set = true;
         }
+        // A last round with few units: their tiles go to a second launch, in which the waves work on their
+        // own and which takes a fraction of a round (128 channels @112, 32 images: 784 units are 3.06
+        // rounds, 323 us; 280 with the tiles of the last 16 units apart).
+        if (p.vec && lone_ok && !p.split && whole_units > slots && force_split < 0 && force_ks < 0) {
+            const int64_t full = whole_units / slots;
+            const int main_tiles = int(full * (slots / 8) / units_of(0)) * 8, tail = n_tiles - main_tiles;
+            const double rest = double(whole_units % slots) / slots;
+            const double t_last = (0.72 + 0.28 * rest) * (6.0 + n_chunks * (2.0 + 1.9 * records / 142.0));
+            if (main_tiles > 0 && rest > 0.0 && 3.0 + std::ceil(double(tail) * blocks / slots) * lone(visits, recs) < 0.8 * t_last) p.tail_tiles = tail;
+        }
     } else {
         // Few units: the form with the smallest estimate, in microseconds, fitted to the VGG-16 layers
         // with one and four images.
-        const double records = double(h->tiled.meta.size()) * p.nw / blocks / n_chunks;   // of a whole unit's chunk
         double best = 0.0;
         auto consider = [&](double t, bool split, int ks, bool priv, bool halves = false) {
             if (best == 0.0 || t < best) { best = t; p.split = split; p.ks_log2 = ks; p.priv = priv; p.halves = halves; }
@@ -1302,9 +1317,7 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
         // record 0.03 (256 channels @56, one image: 28 us; 512 @14: 40 us); channels last 3.3 for 16
         // channels (128 @28, eight images: 38 us, whole units 120, 81, 62)
         // (it waits for nothing: a test that limits the waits gets a form that has them)
-        if (can_priv && !(p.vec && g_spin_limit.load() != kDefaultSpinLimit)) {
-            const double visits = double(h->tiled.visits) / blocks, recs = double(h->tiled.meta.size()) / blocks;
-            auto lone = [&](double v, double r) { return p.vec ? 8.5 + 0.055 * v + 0.03 * r : 10.0 + 3.3 * ((h->c_in + 15) / 16); };
+        if (lone_ok) {
             consider(std::ceil(double(n_tiles) * blocks / slots) * lone(visits, recs), false, 4, true);
             // two of the block's four filters per workgroup, where there are not enough blocks for the chip
             if (p.vec)
@@ -1344,6 +1357,7 @@ int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float
     a.py = (hin + 3) / 4; a.px = (win + 3) / 4;
     a.n_patches = n * a.py * a.px;
     a.n_tiles = (a.n_patches + 63) / 64;
+    a.tile_base = 0;
     a.n_blocks = h->tiled.num_blocks;
     a.relu = relu; a.pool = pool;
     a.x_bytes = uint32_t(std::min<int64_t>(int64_t(n) * h->c_in * hin * win * 4, 0x7FFFFFFF));
@@ -1356,6 +1370,7 @@ int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float
     a.n_chunks = (h->c_in + ch - 1) / ch;
     a.split_units = plan.split; a.one_set = plan.one_set; a.priv = plan.priv; a.ks_log2 = plan.ks_log2;
     a.n_records = uint32_t(h->tiled.meta.size()) - 3u;
+    a.n_tiles -= plan.tail_tiles;
     const int fw = nw >> a.ks_log2;
     a.halves = plan.priv && plan.halves; a.chan_mid = h->d_chan_mid;
     a.n_groups = ((a.n_blocks + fw - 1) / fw) << a.halves;
@@ -1389,8 +1404,14 @@ int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float
         wgs = a.priv ? (units + 7) / 8 * 8 : int64_t((a.n_tiles + 7) / 8) * 8 * a.n_groups;   // one per unit of the largest set, in every set
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const hipError_t e = nw == 16 ? launch_any<16, 8>(a, wgs, st, vec, layout, dtype, h->device)
-                                  : launch_any<8, 4>(a, wgs, st, vec, layout, dtype, h->device);
+    hipError_t e = nw == 16 ? launch_any<16, 8>(a, wgs, st, vec, layout, dtype, h->device)
+                            : launch_any<8, 4>(a, wgs, st, vec, layout, dtype, h->device);
+    if (e == hipSuccess && plan.tail_tiles > 0) {
+        a.tile_base = a.n_tiles; a.n_tiles = plan.tail_tiles;
+        a.priv = 1; a.halves = 0; a.ks_log2 = 4;
+        a.n_groups = a.n_blocks; a.n_units = a.n_tiles * a.n_groups;
+        e = launch_any<16, 8>(a, (int64_t(a.n_units) + 7) / 8 * 8, st, vec, layout, dtype, h->device);
+    }
     if (e != hipSuccess) {
         set_error(std::string("pconv_conv2d (tiled kernel): ") + hipGetErrorName(e));
         return PCONV_HIP_ERROR;

@@ -311,6 +311,16 @@ def test_waves_on_their_own(shape, ks_log2):
         check_full(spec, L, x, "f32", "nchw", stride, relu=bool(n & 1), use_bias=bool(co & 1), policy=2, what=f"lone{shape}")
 
 
+@pytest.mark.parametrize("shape", [(17, 64, 16, 126, 126, 1), (17, 64, 16, 128, 124, 1), (17, 64, 16, 127, 126, 2)])
+def test_last_round_in_a_second_launch(shape):
+    """Some units more than whole rounds over the compute units: the tiles of the last ones are computed
+    by a second launch, also where patches of the two launches overlap (widths 2 past a multiple of 4)."""
+    n, ci, co, h, w, stride = shape
+    spec = LayerSpec("tail", n, ci, co, h, w, stride=stride)
+    L = make_layer(spec, 5300 + w); x = make_input(spec, 5300 + w)
+    check_full(spec, L, x, "f32", "nchw", stride, relu=True, policy=0, what=f"tail{shape}")
+
+
 @pytest.mark.parametrize("ks_log2", [4, 0, 2])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_channels_last_in_quads(ks_log2, dtype):
