@@ -245,7 +245,7 @@ def main():
         other["c4_resnet50_3x3_16layers_batch32_bf16"] = dict(
             ms=round(c4_ms, 4), eff_tflops=round(c4_flop / c4_ms / 1e9, 2), bytes=c4_bytes,
             roof_frac=round(c4_roof / c4_ms, 4),            # against the fp32 vector / HBM roof, effective FLOPs
-            kernel="conv_mfma_kernel (bf16 matrix cores, dense over masked weights)",
+            kernel="conv_flat_kernel (bf16 matrix cores, dense over masked weights)",
             mfma_frac_effective=round(c4_flop / c4_ms / 1e9 / PEAK_MFMA_BF16_TFLOPS, 4),
             mfma_frac_dense_equivalent=round(c4_dense / c4_ms / 1e9 / PEAK_MFMA_BF16_TFLOPS, 4),
             layer_ms=c4_layers)
