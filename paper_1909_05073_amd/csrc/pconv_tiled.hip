@@ -307,9 +307,11 @@ conv_tiled_kernel(const TiledArgs a)
         const bool pvalid = pidx < a.n_patches;
         const int n = pvalid ? pidx / per_img : 0;
         const int prem = pvalid ? pidx - n * per_img : 0;
-        // VEC: the last patch of a row is shifted left so that it ends at the image edge (it then
-        // overlaps its neighbour and both compute identical values for the shared columns): the four
-        // centre columns of a patch row are then always inside the image.
+        // VEC: the last patch of a row is shifted left so that it ends at the image edge: the four
+        // centre columns of a patch row are then always inside the image.  It overlaps its neighbour, and
+        // both store the shared columns, also from two workgroups where a tile ends between them: the
+        // order of the additions must not depend on the tile (in every form of a launch it follows
+        // from the filter; a second launch for the last tiles comes after the first one's stores).
         const int y0 = (prem / a.px) * 4;
         const int x0 = VEC ? min((prem % a.px) * 4, a.w - 4) : (prem % a.px) * 4;
 
@@ -688,9 +690,11 @@ conv_tiled_kernel(const TiledArgs a)
                 const int per_wave = (a.c_in + NW - 1) / NW;
                 const int c_lo = min(a.c_in, wave * per_wave), c_hi = min(a.c_in, c_lo + per_wave);
                 float *slot = lds + wave * ROWS_FLOATS;
-                // The workgroups of an XCD walk the same channels: each starts one further on, so that what it
-                // asks for was fetched into the L2 by its neighbour a step before.
-                const int c_start = c_hi > c_lo ? c_lo + int(blockIdx.x >> 3) % (c_hi - c_lo) : c_lo;
+                // The workgroups of a tile walk the same channels: each starts one further on, so that what it
+                // asks for was fetched into the L2 by its neighbour a step before.  Where a channel range
+                // starts follows from the filters alone, never from the tile: two tiles that both store
+                // the columns an overlapping last patch shares must have added them in one order.
+                const int c_start = c_hi > c_lo ? c_lo + group % (c_hi - c_lo) : c_lo;
                 const int c_stop = c_start + (c_hi - c_lo);          // (channels from c_hi on stand for those from c_lo on)
                 auto channel = [&](int c) { return c < c_hi ? c : c - (c_hi - c_lo); };
                 int win = c_start;                                   // lane j: first record of channel win + j and their number

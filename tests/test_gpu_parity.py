@@ -311,6 +311,33 @@ def test_waves_on_their_own(shape, ks_log2):
         check_full(spec, L, x, "f32", "nchw", stride, relu=bool(n & 1), use_bias=bool(co & 1), policy=2, what=f"lone{shape}")
 
 
+@pytest.mark.parametrize("ks_log2", [-1, 4, 5])
+@pytest.mark.parametrize("shape,form", [((8, 96, 92, 35, 35), "plain"), ((8, 256, 256, 27, 27), "plain"),
+                                        ((6, 80, 22, 50, 50), "pool"), ((6, 80, 22, 50, 50), "stride2")])
+def test_waves_on_their_own_add_in_one_order(shape, form, ks_log2):
+    """Widths no multiple of 4, tiles that end between the last two patches of a row (64 * k % px == px - 1):
+    the columns the two patches share are stored by two workgroups, so every tile has to add the
+    channels in the same order.  Equal images in one batch lie differently in their tiles: their
+    outputs, and those of repeated calls, agree bit for bit."""
+    import torch
+    n, ci, co, h, w = shape
+    px, patches = (w + 3) // 4, n * ((h + 3) // 4) * ((w + 3) // 4)
+    assert any(64 * k % px == px - 1 for k in range(1, (patches + 63) // 64))
+    spec = LayerSpec("order", 1, ci, co, h, w)
+    L = make_layer(spec, 5400 + w); x = make_input(spec, 5400 + w)
+    hd = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "f32")
+    xd = to_device(x, "f32").repeat(n, 1, 1, 1); b = torch.from_numpy(L["bias"]).cuda()
+    P.pconv_debug_set_tiling(0 if ks_log2 < 0 else 16, ks_log2, -1)
+    say(f"[case] order {shape} {form} ks={ks_log2}")
+    call = {"plain": lambda: P.conv2d(hd, xd, b), "pool": lambda: P.conv2d_pool2x2(hd, xd, b),
+            "stride2": lambda: P.conv2d(hd, xd, b, stride=2)}[form]
+    ys = [call() for _ in range(6)]
+    torch.cuda.synchronize()
+    assert all(torch.equal(y, ys[0]) for y in ys), "repeated calls differ"
+    assert torch.equal(ys[0], ys[0][:1].expand_as(ys[0])), "equal images of a batch differ"
+    hd.free()
+
+
 @pytest.mark.parametrize("shape", [(17, 64, 16, 126, 126, 1), (17, 64, 16, 128, 124, 1), (17, 64, 16, 127, 126, 2)])
 def test_last_round_in_a_second_launch(shape):
     """Some units more than whole rounds over the compute units: the tiles of the last ones are computed
