@@ -253,6 +253,23 @@ int pconv_set_kernel_policy(int policy);
  * Process-wide; results are the same for every choice up to the order of the fp32 additions. */
 int pconv_debug_set_tiling(int waves, int ks_log2, int split_units);
 
+/* pconv_debug_plan - how the automatic choices (and what the functions above pin) would run a call, without
+ * launching anything, so that a test of one form of a kernel can make sure that it gets it.  Works on
+ * handles from pconv_debug_pack_host as well (for a device of 256 compute units).  fuse_pool != 0: the
+ * plan of pconv_conv2d_pool2x2, else of pconv_conv2d.  Errors: PCONV_INVALID_ARG, and
+ * PCONV_UNSUPPORTED where the call itself would give it. */
+typedef struct {
+    int32_t kernel;        /* numbered as in pconv_set_kernel_policy: 1, 2 or 3                       */
+    int32_t waves;         /* register-tiled kernel, as in pconv_debug_set_tiling                     */
+    int32_t ks_log2;
+    int32_t split_units;
+    int32_t tail_tiles;    /* register-tiled kernel: tiles of the last round that a second launch computes */
+    int32_t reserved[3];
+} pconv_plan;
+
+int pconv_debug_plan(const pconv_handle *h, int n, int h_in, int w_in, int stride, pconv_layout layout,
+                     int fuse_pool, pconv_plan *out);
+
 /* pconv_debug_set_spin_limit - for tests of the error path: the number of polls after which a
  * wait inside the register-tiled kernel gives up (limit <= 0 restores the default, about half a
  * second).  With limit = 1 every such wait gives up at once: the kernels still run to their end,

@@ -134,9 +134,7 @@ static int pack_impl(const float *w_dense, const uint8_t *pattern_id, const uint
         if (rc == PCONV_OK) rc = upload(h->d_slot_filter, h->tiled.slot_filter.data(), h->tiled.slot_filter.size(), h->device_bytes);
         if (rc == PCONV_OK) rc = upload(h->d_chan_mid, h->tiled.chan_mid.data(), h->tiled.chan_mid.size(), h->device_bytes);
         if (rc == PCONV_OK) rc = upload(h->d_chan_ptr, h->tiled.chan_ptr.data(), h->tiled.chan_ptr.size(), h->device_bytes);
-        // (the tiled kernel keeps a record index in 24 bits: a longer stream stays off the device,
-        //  and the layer runs on the general kernels)
-        if (rc == PCONV_OK && h->tiled.meta.size() < (size_t(1) << 24))
+        if (rc == PCONV_OK && h->tiled.meta.size() < kTiledMaxRecords)
             rc = upload(h->d_meta, h->tiled.meta.data(), h->tiled.meta.size(), h->device_bytes);
         if (rc == PCONV_OK) rc = upload(h->d_w4, h->tiled.w4.data(), h->tiled.w4.size(), h->device_bytes);
         if (rc == PCONV_OK && weight_dtype == PCONV_BF16) {
@@ -219,6 +217,19 @@ int pconv_get_info(const pconv_handle *h, pconv_info *info)
     return PCONV_OK;
 }
 
+// Which kernel a call takes, numbered as in pconv_set_kernel_policy (1 gather, 2 register-tiled, 3 matrix
+// cores), or PCONV_UNSUPPORTED where the policy requires one that cannot serve it.
+static int choose_kernel(const pconv_handle *h, int n, int h_in, int w_in, int stride, int layout, int dtype)
+{
+    const int policy = g_policy.load();
+    const bool can_mfma = mfma_supported(h, dtype, n, h_in, w_in);
+    if (policy == 3 && !can_mfma) { set_error("pconv_conv2d: the matrix-core kernel serves bf16 handles with inputs below 2 GiB only"); return PCONV_UNSUPPORTED; }
+    if (can_mfma && (policy == 3 || (policy == 0 && mfma_preferred(h)))) return 3;
+    const bool can_tile = tiled_supported(h, n, h_in, w_in, stride, layout, dtype);
+    if (policy == 2 && !can_tile) { set_error("pconv_conv2d: register-tiled kernel not available for this call"); return PCONV_UNSUPPORTED; }
+    return can_tile && (policy == 2 || (policy == 0 && tiled_preferred(h_in, w_in, stride))) ? 2 : 1;
+}
+
 static int conv2d_impl(const pconv_handle *h, const void *x_dev, void *y_dev, const float *bias_dev,
                        int n, int h_in, int w_in, int stride, int pad, pconv_layout layout,
                        pconv_dtype act_dtype, int fuse_relu, void *hip_stream, bool static_scratch)
@@ -239,14 +250,11 @@ static int conv2d_impl(const pconv_handle *h, const void *x_dev, void *y_dev, co
         return PCONV_INVALID_ARG;
     }
     if (const int rc = take_async_error(h, "pconv_conv2d")) return rc;
-    const int policy = g_policy.load();
-    const bool can_mfma = mfma_supported(h, int(act_dtype), n, h_in, w_in);
-    if (policy == 3 && !can_mfma) { set_error("pconv_conv2d: the matrix-core kernel serves bf16 handles with inputs below 2 GiB only"); return PCONV_UNSUPPORTED; }
-    if (can_mfma && (policy == 3 || (policy == 0 && mfma_preferred(h))))
+    const int kernel = choose_kernel(h, n, h_in, w_in, stride, int(layout), int(act_dtype));
+    if (kernel < 0) return kernel;
+    if (kernel == 3)
         return launch_conv_mfma(h, x_dev, y_dev, bias_dev, n, h_in, w_in, stride, int(layout), fuse_relu ? 1 : 0, hip_stream);
-    const bool can_tile = tiled_supported(h, n, h_in, w_in, stride, int(layout), int(act_dtype));
-    if (policy == 2 && !can_tile) { set_error("pconv_conv2d: register-tiled kernel not available for this call"); return PCONV_UNSUPPORTED; }
-    if (can_tile && (policy == 2 || (policy == 0 && tiled_preferred(h_in, w_in, stride))))
+    if (kernel == 2)
         return launch_conv_tiled(h, x_dev, y_dev, bias_dev, n, h_in, w_in, stride, int(layout),
                                  int(act_dtype), fuse_relu ? 1 : 0, 0, hip_stream, static_scratch);
     return launch_conv_generic(h, x_dev, y_dev, bias_dev, n, h_in, w_in, stride, int(layout),
@@ -303,6 +311,26 @@ int pconv_pool2x2_fusion(const pconv_handle *h, int n, int h_in, int w_in, pconv
         !tiled_pool_supported(h, n, h_in, w_in, int(layout), int(act_dtype)))
         return 0;
     return tiled_shares_units(h, n, h_in, w_in) ? 1 : 2;
+}
+
+int pconv_debug_plan(const pconv_handle *h, int n, int h_in, int w_in, int stride, pconv_layout layout, int fuse_pool, pconv_plan *out)
+{
+    if (!h || !out) { set_error("pconv_debug_plan: null pointer argument"); return PCONV_INVALID_ARG; }
+    if (n <= 0 || h_in <= 0 || w_in <= 0 || (stride != 1 && stride != 2) || (fuse_pool && stride != 1) ||
+        (layout != PCONV_NCHW && layout != PCONV_NHWC)) {
+        set_error("pconv_debug_plan: sizes, stride or layout out of range");
+        return PCONV_INVALID_ARG;
+    }
+    std::memset(out, 0, sizeof *out);
+    if (fuse_pool && (g_policy.load() == 1 || !tiled_pool_supported(h, n, h_in, w_in, int(layout), h->wdtype))) {
+        set_error("pconv_debug_plan: this call cannot be fused with a max-pool");
+        return PCONV_UNSUPPORTED;
+    }
+    const int kernel = fuse_pool ? 2 : choose_kernel(h, n, h_in, w_in, stride, int(layout), h->wdtype);
+    if (kernel < 0) return kernel;
+    out->kernel = kernel;
+    if (kernel == 2) describe_tiled_plan(h, n, h_in, w_in, stride, int(layout), fuse_pool != 0, *out);
+    return PCONV_OK;
 }
 
 int pconv_debug_measure_fma_peak(double *tflops)

@@ -11,6 +11,9 @@
 namespace pconv {
 
 constexpr int kFlagSlots = 64, kFlagWords = 1024;
+// The register-tiled kernel keeps a record index in 24 bits: a longer stream stays off the device,
+// and the layer runs on the other kernels.
+constexpr size_t kTiledMaxRecords = size_t(1) << 24;
 
 // Thread-local message for pconv_last_error().
 void set_error(const std::string &msg);
@@ -109,6 +112,8 @@ bool tiled_supported(const pconv_handle *h, int n, int hin, int win, int stride,
 // whether pconv_conv2d (fp32 NCHW, stride 1) would let workgroups share tiles of this call, which a
 // fused max-pool rules out
 bool tiled_shares_units(const pconv_handle *h, int n, int hin, int win);
+// the launch choices of launch_conv_tiled for a call (fills all but `kernel`)
+void describe_tiled_plan(const pconv_handle *h, int n, int hin, int win, int stride, int layout, bool pool, pconv_plan &out);
 // plain vector-FMA rate of the device (see pconv_debug_measure_fma_peak)
 int measure_fma_peak(double *tflops);
 // whether the automatic policy should take the tiled kernel for a call it supports

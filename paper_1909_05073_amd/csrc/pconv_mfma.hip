@@ -338,7 +338,7 @@ constexpr int kLdsLimit = 64 * 1024;    // two workgroups per compute unit
 bool mfma_supported(const pconv_handle *h, int dtype, int n, int hin, int win)
 {
     // (the kernel addresses its input through a buffer resource with 32-bit byte offsets)
-    return dtype == PCONV_BF16 && h->wdtype == PCONV_BF16 && h->d_wdense != nullptr &&
+    return dtype == PCONV_BF16 && h->wdtype == PCONV_BF16 &&
            int64_t(n) * h->c_in * hin * win * 2 < (int64_t(1) << 31);
 }
 

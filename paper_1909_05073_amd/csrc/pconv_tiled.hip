@@ -1177,7 +1177,7 @@ bool tiled_supported(const pconv_handle *h, int n, int hin, int win, int stride,
 {
     (void)layout; (void)dtype;
     // (stride 2 runs at full resolution and stores every other output)
-    if (!h->d_meta || (stride != 1 && stride != 2)) return false;
+    if (h->tiled.meta.size() >= kTiledMaxRecords || (stride != 1 && stride != 2)) return false;
     const int64_t patches = int64_t(n) * ((hin + 3) / 4) * ((win + 3) / 4);
     return patches < (int64_t(1) << 30);
 }
@@ -1268,7 +1268,6 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
     const double records = double(h->tiled.meta.size()) * p.nw / blocks / n_chunks;       // of a whole unit's chunk
     const double visits = double(h->tiled.visits) / blocks, recs = double(h->tiled.meta.size()) / blocks;
     auto lone = [&](double v, double r) { return p.vec ? 8.5 + 0.055 * v + 0.03 * r : 10.0 + 3.3 * ((h->c_in + 15) / 16); };
-    const bool lone_ok = can_priv && !(p.vec && g_spin_limit.load() != kDefaultSpinLimit);
     if (whole_units > slots / 2) {
         if (can_split && p.nw == 16) {
             // Many units, but not a multiple of the number of compute units: whole units leave part of
@@ -1287,7 +1286,7 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
         // A last round with few units: their tiles go to a second launch, in which the waves work on their
         // own and which takes a fraction of a round (128 channels @112, 32 images: 784 units are 3.06
         // rounds, 323 us; 280 with the tiles of the last 16 units apart).
-        if (p.vec && lone_ok && !p.split && whole_units > slots && force_split < 0 && force_ks < 0) {
+        if (p.vec && can_priv && !p.split && whole_units > slots && force_split < 0 && force_ks < 0) {
             const int64_t full = whole_units / slots;
             const int main_tiles = int(full * (slots / 8) / units_of(0)) * 8, tail = n_tiles - main_tiles;
             const double rest = double(whole_units % slots) / slots;
@@ -1320,8 +1319,7 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
         // one filter block per workgroup, every wave its own channels: per visited channel 0.055 and per
         // record 0.03 (256 channels @56, one image: 28 us; 512 @14: 40 us); channels last 3.3 for 16
         // channels (128 @28, eight images: 38 us, whole units 120, 81, 62)
-        // (it waits for nothing: a test that limits the waits gets a form that has them)
-        if (lone_ok) {
+        if (can_priv) {
             consider(std::ceil(double(n_tiles) * blocks / slots) * lone(visits, recs), false, 4, true);
             // two of the block's four filters per workgroup, where there are not enough blocks for the chip
             if (p.vec)
@@ -1340,6 +1338,14 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
 }
 
 }  // namespace
+
+void describe_tiled_plan(const pconv_handle *h, int n, int hin, int win, int stride, int layout, bool pool, pconv_plan &out)
+{
+    const TiledPlan p = plan_tiled(h, n, hin, win, layout, h->wdtype, pool, stride == 2);
+    out.waves = p.nw; out.ks_log2 = p.priv && p.halves ? 5 : p.ks_log2;
+    out.split_units = p.split ? (p.one_set ? 2 : 1) : 0;
+    out.tail_tiles = p.tail_tiles;
+}
 
 bool tiled_shares_units(const pconv_handle *h, int n, int hin, int win)
 {

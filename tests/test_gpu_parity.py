@@ -409,9 +409,11 @@ def test_expired_wait_is_reported_by_the_next_call():
     kernel gives up at once.  The kernels still run to their end; the handle reports the failure
     on the next call (which launches nothing) and works again afterwards."""
     import torch
-    spec = config_layers(2)[0]                       # shared units: both kinds of wait are used
+    spec = config_layers(2)[0]
     L = make_layer(spec, base_seed(2)); x = make_input(spec, base_seed(2))
     h = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "f32")
+    P.pconv_debug_set_tiling(0, -1, 1)               # shared units: both kinds of wait are used
+    assert P.pconv_debug_plan(h, 1, spec.h, spec.w).split_units == 1
     xd = to_device(x, "f32"); b = torch.from_numpy(L["bias"]).cuda()
     good = P.conv2d(h, xd, b, relu=True).clone()
     torch.cuda.synchronize()

@@ -159,3 +159,43 @@ def test_blocks_are_a_balanced_deal_of_all_filters():
                     trial[ba - g0] += cb - ca
                     trial[bb - g0] += ca - cb
                     assert cost(trial) >= base, (seed, ba, sa, bb, sb)
+
+
+PLAN_CALLS = [  # (n, c_in, c_out, h, w): waves on their own, whole units, a second launch for the last round
+    (1, 256, 256, 56, 56), (1, 512, 512, 14, 14), (32, 256, 256, 56, 56), (32, 128, 128, 112, 112),
+]
+
+
+@pytest.mark.parametrize("call", PLAN_CALLS)
+def test_spin_limit_leaves_the_plan_alone(call):
+    """The test hook that shortens the kernels' waits must not change which form of a kernel runs."""
+    n, ci, co, hh, ww = call
+    L = make_layer(LayerSpec("plan", n, ci, co, hh, ww), 4100)
+    h = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "f32", host_only=True)
+    usual = bytes(P.pconv_debug_plan(h, n, hh, ww))
+    try:
+        P.pconv_debug_set_spin_limit(1)
+        assert bytes(P.pconv_debug_plan(h, n, hh, ww)) == usual
+    finally:
+        P.pconv_debug_set_spin_limit(0)
+    h.free()
+
+
+def test_plan_reports_the_pinned_form_and_rejects_bad_calls():
+    L = make_layer(LayerSpec("plan", 1, 256, 64, 28, 28), 4200)
+    h = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "f32", host_only=True)
+    try:
+        for waves, ks, split, want in [(16, 4, -1, (16, 4, 0)), (16, 5, -1, (16, 5, 0)), (16, 0, 1, (16, 0, 1)),
+                                       (0, -1, 2, (16, 0, 2)), (8, 1, 0, (8, 1, 0)), (8, 4, 0, (8, 0, 0))]:
+            P.pconv_debug_set_tiling(waves, ks, split)
+            p = P.pconv_debug_plan(h, 1, 28, 28)
+            assert p.kernel == 2 and (p.waves, p.ks_log2, p.split_units) == want and p.tail_tiles == 0
+            assert P.pconv_debug_plan(h, 1, 28, 28, fuse_pool=True).split_units == 0       # a fused pool cannot share
+    finally:
+        P.pconv_debug_set_tiling(0, -1, -1)
+    for kw, status in [(dict(stride=3), P.INVALID_ARG), (dict(stride=2, fuse_pool=True), P.INVALID_ARG),
+                       (dict(layout="nhwc", fuse_pool=True), P.UNSUPPORTED)]:
+        with pytest.raises(P.PconvError) as e:
+            P.pconv_debug_plan(h, 1, 28, 28, **kw)
+        assert e.value.status == status
+    h.free()
