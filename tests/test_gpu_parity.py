@@ -633,14 +633,17 @@ def test_run_to_run_bit_identical_and_stream():
     h.free()
 
 
-def test_concurrent_calls_on_one_handle_with_shared_units():
+@pytest.mark.parametrize("split_units", [1, 2])
+def test_concurrent_calls_on_one_handle_with_shared_units(split_units):
     """Two streams run the same handle at the same time on a layer whose workgroups share units
     (they signal each other through per-call words of the handle): every result must equal, bit
     for bit, what the same call gives alone."""
     import torch
-    spec = config_layers(2)[0]                       # 256 -> 256 at 56x56, batch 1: 16 units, shared
+    spec = config_layers(2)[0]                       # 256 -> 256 at 56x56, batch 1: 52 units
     L = make_layer(spec, base_seed(2))
     h = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "f32")
+    P.pconv_debug_set_tiling(0, -1, split_units)
+    assert P.pconv_debug_plan(h, 1, spec.h, spec.w).split_units == split_units
     b = torch.from_numpy(L["bias"]).cuda()
     xs = [to_device(make_input(spec, base_seed(2) + 7 * k), "f32") for k in range(2)]
     refs = [P.conv2d(h, x, b, relu=True).clone() for x in xs]
@@ -659,6 +662,7 @@ def test_concurrent_calls_on_one_handle_with_shared_units():
     for k in range(2):
         for it, y in enumerate(outs[k]):
             assert torch.equal(y, refs[k]), f"stream {k}, call {it}: differs from the call run alone"
+    P.pconv_get_async_error(h)                       # no wait ran out
     h.free()
 
 

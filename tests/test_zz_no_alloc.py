@@ -14,9 +14,17 @@ from gpu_util import assert_close, say, to_device
 pytestmark = pytest.mark.gpu
 
 
-def test_static_scratch_entry_point_two_calls_second_smaller():
+@pytest.fixture(autouse=True)
+def _reset_tiling():
+    yield
+    P.pconv_debug_set_tiling(0, -1, -1)
+
+
+@pytest.mark.parametrize("split_units", [1, 2])
+def test_static_scratch_entry_point_two_calls_second_smaller(split_units):
     import torch
-    spec = config_layers(2)[0]                       # 256 -> 256 at 56x56, batch 1: workgroups share units
+    spec = config_layers(2)[0]                       # 256 -> 256 at 56x56, batch 1
+    P.pconv_debug_set_tiling(0, -1, split_units)     # workgroups share units: the hand-over words are used
     L = make_layer(spec, base_seed(2))
     h = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "f32")
     b = torch.from_numpy(L["bias"]).cuda()
@@ -25,7 +33,8 @@ def test_static_scratch_entry_point_two_calls_second_smaller():
     for k, (hh, ww) in enumerate([(56, 56), (28, 20)]):
         x = make_input(LayerSpec("s", 1, 256, 256, hh, ww), base_seed(2) + k)
         xd = to_device(x, "f32")
-        say(f"[case] pconv_conv2d_static call {k}: x={x.shape}")
+        say(f"[case] pconv_conv2d_static call {k}: x={x.shape} split={split_units}")
+        assert P.pconv_debug_plan(h, 1, hh, ww).split_units == split_units
         ref = P.conv2d(h, xd, b, relu=True)
         y = torch.full_like(ref, float("nan"))
         P.pconv_conv2d_static(h, xd.data_ptr(), y.data_ptr(), b.data_ptr(), 1, hh, ww, 1, 1, P.NCHW, P.F32,
