@@ -328,7 +328,9 @@ def test_waves_on_their_own_add_in_one_order(shape, form, ks_log2):
     hd = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "f32")
     xd = to_device(x, "f32").repeat(n, 1, 1, 1); b = torch.from_numpy(L["bias"]).cuda()
     P.pconv_debug_set_tiling(0 if ks_log2 < 0 else 16, ks_log2, -1)
-    say(f"[case] order {shape} {form} ks={ks_log2}")
+    plan = P.pconv_debug_plan(hd, n, h, w, 2 if form == "stride2" else 1, fuse_pool=form == "pool")
+    assert plan.ks_log2 >= 4 if ks_log2 < 0 else plan.ks_log2 == ks_log2
+    say(f"[case] order {shape} {form} ks={plan.ks_log2}")
     call = {"plain": lambda: P.conv2d(hd, xd, b), "pool": lambda: P.conv2d_pool2x2(hd, xd, b),
             "stride2": lambda: P.conv2d(hd, xd, b, stride=2)}[form]
     ys = [call() for _ in range(6)]
@@ -338,13 +340,22 @@ def test_waves_on_their_own_add_in_one_order(shape, form, ks_log2):
     hd.free()
 
 
-@pytest.mark.parametrize("shape", [(17, 64, 16, 126, 126, 1), (17, 64, 16, 128, 124, 1), (17, 64, 16, 127, 126, 2)])
-def test_last_round_in_a_second_launch(shape):
+@pytest.mark.parametrize("shape,parted", [((17, 64, 16, 126, 126, 1), False), ((17, 64, 16, 128, 124, 1), False),
+                                          ((17, 64, 16, 127, 126, 2), False), ((21, 64, 16, 112, 114, 1), True),
+                                          ((21, 64, 16, 112, 113, 2), True), ((21, 40, 16, 111, 115, 1), True)])
+def test_last_round_in_a_second_launch(shape, parted):
     """Some units more than whole rounds over the compute units: the tiles of the last ones are computed
-    by a second launch, also where patches of the two launches overlap (widths 2 past a multiple of 4)."""
+    by a second launch, also where it begins with the last patch of a row, which overlaps one of the
+    first launch (parted)."""
     n, ci, co, h, w, stride = shape
     spec = LayerSpec("tail", n, ci, co, h, w, stride=stride)
     L = make_layer(spec, 5300 + w); x = make_input(spec, 5300 + w)
+    hd = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "f32")
+    plan = P.pconv_debug_plan(hd, n, h, w, stride)
+    hd.free()
+    px = (w + 3) // 4
+    first = 64 * ((n * ((h + 3) // 4) * px + 63) // 64 - plan.tail_tiles)
+    assert plan.tail_tiles > 0 and parted == (w % 4 != 0 and first % px == px - 1)
     check_full(spec, L, x, "f32", "nchw", stride, relu=True, policy=0, what=f"tail{shape}")
 
 
@@ -458,7 +469,7 @@ POOL_SHAPES = [  # (n, c_in, c_out, h, w): even widths; odd and tiny heights; se
 ]
 
 
-@pytest.mark.parametrize("waves,ks_log2", [(0, -1), (8, 0), (16, 1), (16, 2)])
+@pytest.mark.parametrize("waves,ks_log2", [(0, -1), (8, 0), (16, 1), (16, 2), (16, 4), (16, 5)])
 def test_fused_maxpool_equals_conv_then_pool(waves, ks_log2):
     """pconv_conv2d_pool2x2 against the oracle's convolution followed by its max-pool; a pooled
     value may be off by what the largest of its four inputs may be off."""
