@@ -253,6 +253,12 @@ int pconv_set_kernel_policy(int policy);
  * Process-wide; results are the same for every choice up to the order of the fp32 additions. */
 int pconv_debug_set_tiling(int waves, int ks_log2, int split_units);
 
+/* pconv_debug_set_flat_shape - for tests: pins the launch shape of the matrix-core kernel over flat runs of
+ * pixels, 0 to 12 (filter blocks and pixel blocks of a wave, pixel parts and channel parts of a
+ * workgroup; a call that the shape cannot serve takes the kernel over tiles of images).  Values out of
+ * range mean automatic.  Process-wide. */
+int pconv_debug_set_flat_shape(int index);
+
 /* pconv_debug_plan - how the automatic choices (and what the functions above pin) would run a call, without
  * launching anything, so that a test of one form of a kernel can make sure that it gets it.  Works on
  * handles from pconv_debug_pack_host as well (for a device of 256 compute units).  fuse_pool != 0: the
@@ -264,7 +270,9 @@ typedef struct {
     int32_t ks_log2;
     int32_t split_units;
     int32_t tail_tiles;    /* register-tiled kernel: tiles of the last round that a second launch computes */
-    int32_t reserved[3];
+    int32_t flat_shape;    /* matrix cores: launch shape of the kernel over flat runs of pixels, as in
+                            * pconv_debug_set_flat_shape; -1: tiles of images (or another kernel)     */
+    int32_t reserved[2];
 } pconv_plan;
 
 int pconv_debug_plan(const pconv_handle *h, int n, int h_in, int w_in, int stride, pconv_layout layout,

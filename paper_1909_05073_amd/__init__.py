@@ -37,7 +37,7 @@ class pconv_info(C.Structure):
 
 class pconv_plan(C.Structure):
     _fields_ = [("kernel", C.c_int32), ("waves", C.c_int32), ("ks_log2", C.c_int32), ("split_units", C.c_int32),
-                ("tail_tiles", C.c_int32), ("reserved", C.c_int32 * 3)]
+                ("tail_tiles", C.c_int32), ("flat_shape", C.c_int32), ("reserved", C.c_int32 * 2)]
 
 
 _lib = None
@@ -85,6 +85,8 @@ def lib():
     L.pconv_set_kernel_policy.argtypes = [ip]
     L.pconv_debug_set_tiling.restype = ip
     L.pconv_debug_set_tiling.argtypes = [ip, ip, ip]
+    L.pconv_debug_set_flat_shape.restype = ip
+    L.pconv_debug_set_flat_shape.argtypes = [ip]
     L.pconv_debug_plan.restype = ip
     L.pconv_debug_plan.argtypes = [vp, ip, ip, ip, ip, ip, ip, C.POINTER(pconv_plan)]
     L.pconv_debug_set_spin_limit.restype = ip
@@ -104,7 +106,7 @@ def lib():
 EXPORTED_SYMBOLS = ["pconv_project", "pconv_pack", "pconv_conv2d", "pconv_conv2d_static", "pconv_conv2d_pool2x2", "pconv_free", "pconv_maxpool2x2",
                     "pconv_get_info", "pconv_debug_export", "pconv_debug_export_blocks", "pconv_debug_pack_host",
                     "pconv_debug_unpack",
-                    "pconv_set_kernel_policy", "pconv_debug_set_tiling", "pconv_debug_plan", "pconv_debug_set_spin_limit",
+                    "pconv_set_kernel_policy", "pconv_debug_set_tiling", "pconv_debug_set_flat_shape", "pconv_debug_plan", "pconv_debug_set_spin_limit",
                     "pconv_get_async_error", "pconv_pool2x2_fusion", "pconv_debug_measure_fma_peak",
                     "pconv_last_error"]
 
@@ -215,6 +217,10 @@ def pconv_set_kernel_policy(policy: int):
 
 def pconv_debug_set_tiling(waves: int = 0, ks_log2: int = -1, split_units: int = -1):
     _check(lib().pconv_debug_set_tiling(int(waves), int(ks_log2), int(split_units)))
+
+
+def pconv_debug_set_flat_shape(index: int = -1):
+    _check(lib().pconv_debug_set_flat_shape(int(index)))
 
 
 def pconv_debug_plan(handle: Handle, n: int, h_in: int, w_in: int, stride: int = 1, layout=NCHW,

@@ -83,6 +83,12 @@ int pconv_debug_set_tiling(int waves, int ks_log2, int split_units)
     return PCONV_OK;
 }
 
+int pconv_debug_set_flat_shape(int index)
+{
+    set_flat_shape(index);
+    return PCONV_OK;
+}
+
 int pconv_debug_set_spin_limit(int limit)
 {
     set_tiled_spin_limit(limit);
@@ -329,6 +335,7 @@ int pconv_debug_plan(const pconv_handle *h, int n, int h_in, int w_in, int strid
     const int kernel = fuse_pool ? 2 : choose_kernel(h, n, h_in, w_in, stride, int(layout), h->wdtype);
     if (kernel < 0) return kernel;
     out->kernel = kernel;
+    out->flat_shape = kernel == 3 ? flat_shape_of(h, n, h_in, w_in, stride, int(layout)) : -1;
     if (kernel == 2) describe_tiled_plan(h, n, h_in, w_in, stride, int(layout), fuse_pool != 0, *out);
     return PCONV_OK;
 }

@@ -132,6 +132,10 @@ int launch_conv_mfma(const pconv_handle *h, const void *x, void *y, const float 
 // The main matrix-core kernel (pconv_mfma_flat.hip); false (nothing launched) if it does not serve the call.
 bool launch_conv_flat(const pconv_handle *h, const void *x, void *y, const float *bias, int n, int hin, int win,
                       int stride, int layout, int relu, void *stream, int &rc);
+// index of the launch shape that kernel would take, -1 if it does not serve the call
+int flat_shape_of(const pconv_handle *h, int n, int hin, int win, int stride, int layout);
+// Test override of that choice (an index out of range restores the automatic one).
+void set_flat_shape(int index);
 // masked weights of a bf16 handle in the matrix-core kernel's layout (see pconv_handle::d_wdense)
 void build_dense_taps(const Canonical &cn, const uint16_t *table, int c_out, int c_in,
                       std::vector<uint16_t> &wd, std::vector<uint32_t> &nz);

@@ -50,7 +50,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// n / d for n < 2^31 by one multiplication
+// n / d for n < 2^31 by one multiplication: Granlund and Montgomery's division by an invariant, with the
+// multiplier floor(2^32 (2^s - d) / d) + 1 and s = ceil(log2 d)
 struct FastDiv { uint32_t mul, shift; };
 FastDiv make_fast_div(uint32_t d)
 {
@@ -429,52 +430,45 @@ hipError_t launch_flat(const FlatArgs &a, dim3 grid, dim3 block, int64_t lds, hi
 }
 
 // Launch shape: MB x NB blocks of 32 filters x 32 pixels per wave, WP pixel parts x WK channel parts.
-struct FlatShape { int mb, nb, wp, wk, r; int64_t plane, lds; };
+struct FlatShape { int index, mb, nb, wp, wk, r; int64_t plane, lds; };
 
-}  // namespace
+constexpr int kShapes[][4] = {{2, 2, 4, 1}, {2, 2, 2, 1}, {2, 2, 2, 2}, {2, 2, 1, 4}, {2, 1, 4, 1}, {2, 1, 2, 2},
+                              {1, 2, 4, 1}, {1, 2, 2, 2}, {1, 2, 1, 4}, {1, 1, 4, 1}, {1, 1, 2, 2}, {1, 1, 2, 4}, {1, 1, 1, 8}};
+constexpr int kNumShapes = int(sizeof kShapes / sizeof kShapes[0]);
+std::atomic<int> g_force_shape{-1};      // test override, see set_flat_shape
 
-bool launch_conv_flat(const pconv_handle *h, const void *x, void *y, const float *bias, int n, int hin, int win,
-                      int stride, int layout, int relu, void *stream, int &rc)
+// The shape with the smallest estimate of the layer's time, in microseconds; false if the kernel does
+// not serve the call.  Few workgroups: the time of one, a start and end and per block of channels the
+// latency of its loads and LDS traffic.  Many: what a compute unit spends on a workgroup, per wave and
+// block of outputs, and per wave and block of channels for every block of weights, of matrix
+// instructions and for 64 staging items.  The constants are a fit to all shapes on thirteen layers (24
+// to 512 channels, 7 to 224 pixels square, both strides) with 1 to 32 images: the shape chosen takes
+// 1 % longer than the fastest one on average, 20 % at most.
+bool choose_flat(const pconv_handle *h, int n, int hin, int win, int stride, int layout, FlatShape &best)
 {
-    FlatArgs a;
-    a.x = static_cast<const uint16_t *>(x); a.y = static_cast<uint16_t *>(y); a.bias = bias;
-    a.wd = h->d_wdense; a.nz = h->d_wnz;
-    a.c_in = h->c_in; a.h = hin; a.w = win; a.c_out = h->c_out;
-    const int ho = (hin - 1) / stride + 1;
-    a.wo = (win - 1) / stride + 1; a.hw = hin * win; a.howo = ho * a.wo;
-    a.stride = stride; a.relu = relu;
+    const int hw = hin * win, wo = (win - 1) / stride + 1, howo = ((hin - 1) / stride + 1) * wo, total = n * howo;
+    const int cb16 = (h->c_in + 15) / 16, wd_cb16 = (h->c_in + 31) / 32 * 2, fblocks = (h->c_out + 31) / 32;
     // (a staging item is eight pixels of a plane; NHWC pixels are read in whole octets of channels)
-    if (a.hw < 8 || (layout == PCONV_NHWC && h->c_in % 8 != 0)) return false;
-    a.cb16 = (h->c_in + 15) / 16; a.wd_cb16 = (h->c_in + 31) / 32 * 2; a.fblocks = (h->c_out + 31) / 32;
-    if (int64_t(a.fblocks) * a.wd_cb16 * 9 * 512 >= (int64_t(1) << 31)) return false;   // (32-bit weight offsets)
-    a.total = n * a.howo;
-    a.rhw = (a.hw + 7) & ~7;
-    a.div_howo = make_fast_div(uint32_t(a.howo)); a.div_wo = make_fast_div(uint32_t(a.wo));
-    a.div_rhw = make_fast_div(uint32_t(a.rhw));
-    // The shape with the smallest estimate of the layer's time, in microseconds.  Few workgroups: the
-    // time of one, a start and end and per block of channels the latency of its loads and LDS traffic.
-    // Many: what a compute unit spends on a workgroup, per wave and block of outputs, and per wave and
-    // block of channels for every block of weights, of matrix instructions and for 64 staging items.
-    // The constants are a fit to all shapes on thirteen layers (24 to 512 channels, 7 to 224 pixels
-    // square, both strides) with 1 to 32 images: the shape chosen takes 1 % longer than the fastest
-    // one on average, 20 % at most.
-    static constexpr int kShapes[][4] = {{2, 2, 4, 1}, {2, 2, 2, 1}, {2, 2, 2, 2}, {2, 2, 1, 4}, {2, 1, 4, 1}, {2, 1, 2, 2},
-                                         {1, 2, 4, 1}, {1, 2, 2, 2}, {1, 2, 1, 4}, {1, 1, 4, 1}, {1, 1, 2, 2}, {1, 1, 2, 4}, {1, 1, 1, 8}};
-    FlatShape best{};
+    if (hw < 8 || (layout == PCONV_NHWC && h->c_in % 8 != 0)) return false;
+    if (int64_t(fblocks) * wd_cb16 * 9 * 512 >= (int64_t(1) << 31)) return false;   // (32-bit weight offsets)
+    best = FlatShape{};
     double best_time = 0.0;
-    const int cus = h->cus > 0 ? h->cus : 256;
-    for (const auto &c : kShapes) {
-        FlatShape s{c[0], c[1], c[2], c[3], 1, 0, 0};
-        if (s.mb > a.fblocks || s.wk > a.cb16) continue;
+    const int cus = h->cus > 0 ? h->cus : 256, forced = g_force_shape.load();
+    for (int k = 0; k < kNumShapes; ++k) {
+        const auto &c = kShapes[k];
+        FlatShape s{k, c[0], c[1], c[2], c[3], 1, 0, 0};
+        if (forced >= 0 && k != forced) continue;
+        if (s.mb > fblocks || s.wk > cb16) continue;
         const int np = 32 * s.nb * s.wp, waves = s.wp * s.wk;
-        const int64_t bound = staged_bound(np, a.hw, a.howo, a.w, a.wo, stride);
+        const int64_t bound = staged_bound(np, hw, howo, win, wo, stride);
         s.plane = bound + bound / 8;
         s.lds = std::max<int64_t>(2 * (s.wk * 2 * s.plane + 1) * 16, int64_t(waves) * s.mb * s.nb * 4 * 65 * 16) + 256;
         const int64_t items = bound / 4;
         s.r = items <= 64 * s.wp ? 1 : 2;
         if (items > 64 * s.wp * s.r || (s.r == 2 && (s.mb == 2 || layout == PCONV_NHWC)) || s.lds > kLdsOfUnit) continue;
-        const int iters = (a.cb16 + s.wk - 1) / s.wk;
-        const double groups = double((a.total + np - 1) / np) * ((a.fblocks + s.mb - 1) / s.mb) / cus;
+        const int iters = (cb16 + s.wk - 1) / s.wk;
+        const int64_t tiles = (total + np - 1) / np, fgroups = (fblocks + s.mb - 1) / s.mb;
+        const double groups = double(tiles) * fgroups / cus;
         const double share = double(items) / (64 * s.wp);
         const double chain = 2.4 + iters * ((s.mb == 1 ? 1.33 : s.nb == 1 ? 1.44 : 1.99) + 0.1 * share);
         const double busy = waves * (0.064 * s.mb * s.nb + iters * (0.04 * s.mb + 0.1 * s.mb * s.nb + 0.04 * share));
@@ -485,15 +479,45 @@ bool launch_conv_flat(const pconv_handle *h, const void *x, void *y, const float
         if (best.mb == 0 || time < best_time) { best = s; best_time = time; }
     }
     if (best.mb == 0) return false;
+    const int np = 32 * best.nb * best.wp;
+    return int64_t((total + np - 1) / np) * ((fblocks + best.mb - 1) / best.mb) <= 0x3FFFFFFF;
+}
+
+}  // namespace
+
+void set_flat_shape(int index) { g_force_shape.store(index >= 0 && index < kNumShapes ? index : -1); }
+
+int flat_shape_of(const pconv_handle *h, int n, int hin, int win, int stride, int layout)
+{
+    FlatShape s;
+    return choose_flat(h, n, hin, win, stride, layout, s) ? s.index : -1;
+}
+
+bool launch_conv_flat(const pconv_handle *h, const void *x, void *y, const float *bias, int n, int hin, int win,
+                      int stride, int layout, int relu, void *stream, int &rc)
+{
+    FlatShape best;
+    if (!choose_flat(h, n, hin, win, stride, layout, best)) return false;
+    FlatArgs a;
+    a.x = static_cast<const uint16_t *>(x); a.y = static_cast<uint16_t *>(y); a.bias = bias;
+    a.wd = h->d_wdense; a.nz = h->d_wnz;
+    a.c_in = h->c_in; a.h = hin; a.w = win; a.c_out = h->c_out;
+    const int ho = (hin - 1) / stride + 1;
+    a.wo = (win - 1) / stride + 1; a.hw = hin * win; a.howo = ho * a.wo;
+    a.stride = stride; a.relu = relu;
+    a.cb16 = (h->c_in + 15) / 16; a.wd_cb16 = (h->c_in + 31) / 32 * 2; a.fblocks = (h->c_out + 31) / 32;
+    a.total = n * a.howo;
+    a.rhw = (a.hw + 7) & ~7;
+    a.div_howo = make_fast_div(uint32_t(a.howo)); a.div_wo = make_fast_div(uint32_t(a.wo));
+    a.div_rhw = make_fast_div(uint32_t(a.rhw));
     const int mb = best.mb, nb = best.nb, wp = best.wp, wk = best.wk, r = best.r;
     const int np = 32 * nb * wp;
     const int64_t lds = best.lds, plane = best.plane;
     a.bias_at = int((lds - 256) / 4);
-    a.wp_log2 = wp == 8 ? 3 : wp == 4 ? 2 : wp == 2 ? 1 : 0; a.wk = wk; a.plane = int(plane);
+    a.wp_log2 = wp == 4 ? 2 : wp == 2 ? 1 : 0; a.wk = wk; a.plane = int(plane);
     a.tiles = (a.total + np - 1) / np; a.fgroups = (a.fblocks + mb - 1) / mb;
     a.filter_major = int64_t(h->c_out) * 9 > int64_t(n) * a.hw;
     const int64_t pairs = int64_t(a.tiles) * a.fgroups;
-    if (pairs > 0x3FFFFFFF) return false;
     const dim3 grid{unsigned((pairs + 7) / 8 * 8)}, block{unsigned(64 * wp * wk)};
     hipStream_t st = static_cast<hipStream_t>(stream);
     auto pick = [&](auto lay, auto rr) {

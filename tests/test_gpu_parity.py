@@ -24,6 +24,7 @@ def _reset_policy():
     yield
     P.pconv_set_kernel_policy(0)
     P.pconv_debug_set_tiling(0, -1, -1)
+    P.pconv_debug_set_flat_shape(-1)
     P.pconv_debug_set_spin_limit(0)
 
 
@@ -524,7 +525,7 @@ FLAT_SHAPES = [  # (n, c_in, c_out, h, w, stride)
     (1, 7, 5, 1, 7, 1), (2, 12, 40, 5, 6, 2),                              # seven pixels; NHWC channels no multiple of eight
     (40, 24, 65, 7, 7, 1), (33, 17, 31, 3, 5, 2), (70, 16, 16, 3, 3, 2),    # runs over many images, partial blocks of channels
     (1, 64, 64, 16, 16, 1), (1, 128, 33, 9, 17, 1), (2, 144, 96, 11, 13, 1),  # channel parts, the last one with less to do
-    (8, 64, 128, 57, 55, 1), (12, 32, 64, 64, 64, 2), (16, 48, 64, 30, 30, 1),  # many workgroups: large blocks per wave
+    (8, 64, 128, 57, 55, 1), (12, 32, 64, 64, 64, 2), (16, 48, 64, 30, 30, 1),  # many workgroups
     (1, 24, 40, 6, 224, 1), (1, 32, 64, 9, 224, 2), (1, 16, 24, 4, 900, 2), (1, 8, 8, 5, 2000, 1),  # wide images
 ]
 
@@ -538,6 +539,33 @@ def test_matrix_core_flat_pixel_runs(shape, layout):
     spec = LayerSpec("flat", n, ci, co, h, w, stride=stride, dtype="bf16", keep_div=2.0)
     L = make_layer(spec, 7200 + ci); x = make_input(spec, 7200 + ci, layout)
     check_full(spec, L, x, "bf16", layout, stride, relu=bool(n & 1), use_bias=bool(co & 1), policy=3, what=f"flat{shape}_{layout}")
+
+
+FLAT_PINNED = [  # ragged in filters (the last pair of filter blocks has one), channels, pixels; many images in a run
+    (5, 24, 65, 7, 7, 1), (3, 72, 97, 13, 11, 1), (2, 72, 65, 13, 11, 2), (9, 72, 33, 7, 7, 2), (2, 136, 65, 7, 7, 1),
+    (1, 72, 40, 6, 100, 1), (1, 24, 65, 6, 224, 1),      # (two staging rounds for the smaller runs)
+]
+
+
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+@pytest.mark.parametrize("index", range(13))
+def test_matrix_core_flat_every_launch_shape(index, layout):
+    """Every launch shape of the flat-run kernel, pinned, on every layer that it can serve."""
+    P.pconv_debug_set_flat_shape(index)
+    served = 0
+    for j, (n, ci, co, h, w, stride) in enumerate(FLAT_PINNED):
+        spec = LayerSpec("flatshape", n, ci, co, h, w, stride=stride, dtype="bf16", keep_div=2.0)
+        L = make_layer(spec, 7300 + j)
+        hd = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "bf16")
+        got = P.pconv_debug_plan(hd, n, h, w, stride, layout).flat_shape
+        hd.free()
+        assert got in (index, -1)
+        if got < 0:
+            continue
+        served += 1
+        check_full(spec, L, make_input(spec, 7300 + j, layout), "bf16", layout, stride, relu=bool(j & 1), use_bias=not j & 2,
+                   policy=3, what=f"flatshape{index}_{j}_{layout}")
+    assert served >= 1
 
 
 def test_matrix_core_kernel_skips_empty_weight_blocks():
