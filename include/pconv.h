@@ -97,7 +97,9 @@ int pconv_project(const float *w_dense, const uint16_t *table, int num_patterns,
  * takes a ticket from a call counter, and, when the layer has so few tiles that workgroups share
  * them, its workgroups signal each other through one of 64 rows of hand-over words in device
  * memory (row = ticket mod 64).  Calls on one handle may therefore run concurrently on different
- * streams, as long as no more than 64 such calls are in flight at once.
+ * streams, as long as no more than 64 such calls are in flight at once.  Under HIP graph capture
+ * workgroups do not share tiles (a replay would find the words of the one before); where that is
+ * the faster form, pconv_conv2d_static keeps it.
  *
  * Every wait inside the kernels is bounded.  If one ever runs out, the affected outputs are set
  * to NaN and the handle remembers it: the next pconv_conv2d / pconv_conv2d_pool2x2 on the handle,
@@ -261,7 +263,8 @@ int pconv_debug_set_flat_shape(int index);
 
 /* pconv_debug_plan - how the automatic choices (and what the functions above pin) would run a call, without
  * launching anything, so that a test of one form of a kernel can make sure that it gets it.  Works on
- * handles from pconv_debug_pack_host as well (for a device of 256 compute units).  fuse_pool != 0: the
+ * handles from pconv_debug_pack_host as well (for a device of 256 compute units); the plan is that of a
+ * call outside graph capture.  fuse_pool != 0: the
  * plan of pconv_conv2d_pool2x2, else of pconv_conv2d.  Errors: PCONV_INVALID_ARG, and
  * PCONV_UNSUPPORTED where the call itself would give it. */
 typedef struct {

@@ -1225,6 +1225,13 @@ uint32_t *static_flags(int dev)
 
 std::atomic<uint32_t> g_static_calls{0};             // epochs of the calls that use `scratch`
 
+bool is_capturing(hipStream_t st)
+{
+    if (!st) return false;                               // (the default stream cannot be captured)
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(st, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
+}
+
 }  // namespace
 
 namespace {
@@ -1237,7 +1244,8 @@ struct TiledPlan {
     int tail_tiles;       // tiles at the end that a second launch computes, by waves on their own
 };
 
-TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout, int dtype, bool pool, bool sub2)
+TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout, int dtype, bool pool, bool sub2,
+                     bool may_share = true)
 {
     TiledPlan p{};
     const int64_t x_bytes = int64_t(n) * h->c_in * hin * win * 4, y_bytes = int64_t(n) * h->c_out * hin * win * 4;
@@ -1260,7 +1268,7 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
     // write the columns they share; if the two lay in different tiles, their workgroups would read
     // and overwrite each other's partial sums.
     const bool rows_whole = win % 4 == 0 || n_tiles == 1 || 64 % px == 0;
-    const bool can_split = p.vec && !pool && !sub2 && y_bytes < (int64_t(1) << 31) && rows_whole;
+    const bool can_split = may_share && p.vec && !pool && !sub2 && y_bytes < (int64_t(1) << 31) && rows_whole;
     // waves on their own: rows of patches by 128-bit loads, or channels last in whole quads
     const bool can_priv = p.nw == 16 && (p.vec || (layout == PCONV_NHWC && h->c_in % 4 == 0));
     const int64_t whole_units = int64_t(n_tiles) * ((blocks + p.nw - 1) / p.nw);
@@ -1373,7 +1381,12 @@ int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float
     a.x_bytes = uint32_t(std::min<int64_t>(int64_t(n) * h->c_in * hin * win * 4, 0x7FFFFFFF));
     a.y_bytes = uint32_t(std::min<int64_t>(int64_t(n) * h->c_out * hin * win * 4, 0x7FFFFFFF));
     a.err = h->h_err; a.spin_limit = g_spin_limit.load();
-    const TiledPlan plan = plan_tiled(h, n, hin, win, layout, dtype, pool != 0, stride == 2);
+    TiledPlan plan = plan_tiled(h, n, hin, win, layout, dtype, pool != 0, stride == 2);
+    // A captured launch keeps its arguments: a replay would find the hand-over words as the one before
+    // left them, with the value that means "handed over".  (With the static words a kernel clears them,
+    // in every replay.)
+    if (plan.split && !static_scratch && is_capturing(static_cast<hipStream_t>(stream)))
+        plan = plan_tiled(h, n, hin, win, layout, dtype, pool != 0, stride == 2, false);
     const int nw = plan.nw, ch = nw == 16 ? 8 : 4;
     const bool vec = plan.vec;
     const int slots = (h->cus > 0 ? h->cus : 256) * (16 / nw);
