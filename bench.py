@@ -22,10 +22,10 @@ sys.path.insert(0, ROOT)
 PEAK_VEC_TFLOPS = 157.3      # MI355X fp32 vector peak (256 CU x 2.4 GHz x 256 flop/clk/CU)
 PEAK_MFMA_BF16_TFLOPS = 2500.0
 PEAK_HBM_GBS = 8000.0
-# HBM bytes of the 13 conv launches of one step, from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE scaled
+# HBM bytes of the 13 conv calls of one step, from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE scaled
 # by a 256 MiB device copy (x2.000 / x1.000); see profiles/pconv_conv2d_vgg16_stack_n32_fp32.md.
 # Valid for the default workload (batch 32) only.
-MEASURED_TRAFFIC_BYTES_BATCH32 = 2.914e9
+MEASURED_TRAFFIC_BYTES_BATCH32 = 2.913e9
 
 
 def main():
@@ -177,7 +177,7 @@ def main():
                      "unit": "TFLOP/s", "frac": round(achieved / PEAK_VEC_TFLOPS, 4),
                      "traffic": MEASURED_TRAFFIC_BYTES_BATCH32 if default_workload else None,
                      "algorithmic_flop": total_flop, "algorithmic_bytes": sum(ly["bytes"] for ly in layers),
-                     "kernel": "pconv_conv2d / pconv_conv2d_pool2x2 (13 launches per step, summed)",
+                     "kernel": "pconv_conv2d / pconv_conv2d_pool2x2 (13 calls per step, summed)",
                      "conv_ms_per_step": round(conv_ms_total, 4),
                      "stack_roof_frac": round(sum(t_roof_s(ly["flop"], ly["bytes"]) for ly in layers)
                                               * 1e3 / conv_ms_total, 4)},

@@ -25,12 +25,14 @@
 // What bounds it: at full occupancy the vector-memory pipe (18 KB of weight fragments per wave, two
 // blocks of filters and 16 channels, for 36 matrix instructions) and the fixed start and end of a
 // workgroup (some 7000 cycles before the first matrix instruction, 2500 to 5000 after the last); with
-// few workgroups the latency of one workgroup's chain of channel blocks.  Measured on one MI355X, the
-// seven ResNet-50 3x3 shapes, NCHW, in us, against the tiled-image kernel of pconv_mfma.hip:
-//   one image    64@56 5.5 (9.3)   128@56/2 9.2 (13.3)  128@28 5.5 (12.7)  256@28/2 11.0 (20.6)
-//                256@14 7.4 (20.3)  512@14/2 10.5 (35.2)  512@7 13.3 (37.6)
-//   32 images    64@56 18.6 (37.9)  128@56/2 29.5 (37.8)  128@28 18.9 (31.1)  256@28/2 28.5 (30.1)
-//                256@14 18.4 (27.5)  512@14/2 36.7 (47.3)  512@7 22 (38.3)
+// few workgroups the latency of one workgroup's chain of channel blocks.  Counters, 32 images 256@14: the
+// matrix units are busy 17 % of the time, a wave waits for data 40 % of it and to issue 27 %.  Measured
+// on one MI355X, the seven ResNet-50 3x3 shapes, NCHW, in us, calls back to back in a graph, against the
+// tiled-image kernel of pconv_mfma.hip:
+//   one image    64@56 5.2 (9.3)   128@56/2 9.0 (13.3)  128@28 5.4 (12.7)  256@28/2 10.8 (20.6)
+//                256@14 7.2 (20.3)  512@14/2 10.3 (35.2)  512@7 13.1 (37.6)
+//   32 images    64@56 18.7 (37.9)  128@56/2 29.3 (37.8)  128@28 16.6 (31.1)  256@28/2 28.9 (30.1)
+//                256@14 16.0 (27.5)  512@14/2 30.7 (47.3)  512@7 25.0 (38.3)
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -443,7 +445,8 @@ std::atomic<int> g_force_shape{-1};      // test override, see set_flat_shape
 // block of outputs, and per wave and block of channels for every block of weights, of matrix
 // instructions and for 64 staging items.  The constants are a fit to all shapes on thirteen layers (24
 // to 512 channels, 7 to 224 pixels square, both strides) with 1 to 32 images: the shape chosen takes
-// 1 % longer than the fastest one on average, 20 % at most.
+// 1 % longer than the fastest one on average, 20 % at most (512@7, 32 images: {1, 2, 1, 4} takes 25.0 us,
+// {2, 2, 1, 4} 21.9).
 bool choose_flat(const pconv_handle *h, int n, int hin, int win, int stride, int layout, FlatShape &best)
 {
     const int hw = hin * win, wo = (win - 1) / stride + 1, howo = ((hin - 1) / stride + 1) * wo, total = n * howo;

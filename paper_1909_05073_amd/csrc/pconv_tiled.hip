@@ -148,17 +148,17 @@ __device__ __forceinline__ size_t act_at(int n, int c, int y, int x, int C, int 
 // wait for but its own loads, and the 16 partial sums are added through LDS at the end.  The halo
 // columns are not staged but read out of the neighbouring lanes' quads: what bounds this form is the
 // number of load instructions per channel (7 instead of 18; 256 channels @56, one image: 41 us with
-// 18, 28 with 7; shared units 99).  Staging the next channel while the records of the present one run
+// 18, 28 with 7, 26 as it stands; shared units 97).  Staging the next channel while the records of the present one run
 // changes little (the other waves fill the gap) but costs nothing, the input registers are the buffer.
 // Channels last, a wave cannot load one channel well: there the waves stage 16 channels together, four
-// lanes to a pixel, and then run one each (128 channels @28, eight images: 38 us; with a lane per pixel
-// 111, in whole units with one channel per load 155).
+// lanes to a pixel, and then run one each (128 channels @28, eight images: 33 us; with a lane per pixel
+// 111, in whole units 118, with their channels split four ways 61).
 // Where there are fewer blocks than half of the compute units, a workgroup takes two of its block's four
-// slots (halves): 512@14 31 us instead of 40, 512@28 33 (42), 256->512@28 21 (26); with enough blocks
-// it loses (256@56 39 for 28), since either half visits more than half of the channels.
-// One image, us, against the shared or whole units used before: 64->64@224 30 (56, whole units too),
-// 128@112 35 (91), 128->256@56 19 (59), 256@56 28 (99), 256->512@28 21 (94), 512@28 33 (108),
-// 512@14 31 (103).
+// slots (halves): 512@14 31 us instead of 39, 512@28 32 (41), 256->512@28 21 (26); with enough blocks
+// it loses (256@56 37 for 27), since either half visits more than half of the channels.
+// One image, us, against the shared or whole units used before: 128@112 33 (91), 128->256@56 19 (59),
+// 256@56 27 (99), 256->512@28 21 (94), 512@28 32 (108), 512@14 31 (103); 64->64@224, where whole units
+// with split channels take 29 and stay, 50.
 //
 // VEC: fp32 NCHW tensors at least 4 wide move the four centre columns of a patch row (and the four
 // outputs of a row) with one 128-bit access; the inputs go from global memory straight to LDS.
@@ -497,7 +497,8 @@ conv_tiled_kernel(const TiledArgs a)
         };
         // Channels last, c_in a multiple of 4: CH / 4 neighbouring lanes load the chunk's channels of a
         // pixel, an instruction 256 / CH pixels of one input row (one channel per wave and pixel column
-        // per load, as below, touches a cache line per lane: 12 us a chunk instead of 4).  A pixel is
+        // per load, as in stage_load, touches a cache line per lane: 16 images @56 to 256 filters in whole
+        // units, records included, 21.0 us a chunk with 254 channels, 10.1 with 256).  A pixel is
         // loaded once and also written to the halo words of the patch beside it; halo words outside
         // the image are never written and stay zero.
         auto stage_quads = [&](int c0, float *buf) {
@@ -883,11 +884,12 @@ conv_tiled_kernel(const TiledArgs a)
             }
         }
 
-        // ---- channel splits: add the partial sums through LDS, split 2s+1 into 2s, then 2 into 0 ----
+        // ---- the partial sums of waves that had different channels are added through LDS ----
         if constexpr (PRIV) {
             // Waves on their own: two slots at a time go to LDS from every wave that had channels, and
             // wave s adds up slot s, in order of the waves, and writes its outputs.  (As a tree over the
-            // waves, with one of them writing everything, this took 12 000 cycles instead of 7 000.)
+            // waves, with one of them writing everything: 16 channels @16 10.3 us instead of 9.6, 256 @56
+            // 26.8 instead of 25.8.)
             const int used = min(NW, (a.c_in + ((a.c_in + NW - 1) / NW) - 1) / ((a.c_in + NW - 1) / NW));
             const int parts = VEC ? used : min(NW, a.c_in);
             v4f *red = reinterpret_cast<v4f *>(lds);
@@ -920,6 +922,7 @@ conv_tiled_kernel(const TiledArgs a)
                     }
             }
         } else if (ks_log2 > 0) {
+            // channel splits of a chunk: split 2s+1 into 2s, then 2 into 0
             __syncthreads();                             // the staging buffers are free now
             float4 *red = reinterpret_cast<float4 *>(lds);
             for (int step = (1 << ks_log2) >> 1; step >= 1; step >>= 1) {
@@ -1311,7 +1314,8 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
         // whole units, the waves of a workgroup splitting the channels of a chunk 1, 2 or 4 ways: a chunk
         // costs about 2 for its staging and 1.9 for 142 records on the whole workgroup (256 channels
         // @56: 133, 98, 84 us; register staging, which nothing overlaps, 2.4 and 4.8 in quads of
-        // channels, 8 and 4 otherwise); an eighth of the tiles shares the compute units of one XCD
+        // channels, 8 and 4 otherwise, all with few units: a full chip stages slower, see
+        // stage_quads); an eighth of the tiles shares the compute units of one XCD
         const bool quads = layout == PCONV_NHWC && h->c_in % 4 == 0;
         const double t_stage = p.vec ? 2.0 : quads ? 2.4 : 8.0, t_records = p.vec ? 1.9 : quads ? 4.8 : 4.0;
         const double chunk_scale = p.nw == 16 ? 1.0 : 0.5;
