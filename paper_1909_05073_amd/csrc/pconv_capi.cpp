@@ -101,6 +101,17 @@ int pconv_get_async_error(const pconv_handle *h)
     return take_async_error(h, "pconv_get_async_error");
 }
 
+// whether no (tap, 16 channels, 32 filters) block of the masked weights is empty (words as in pconv_handle::d_wnz)
+static int all_blocks_full(const std::vector<uint32_t> &nz, int c_out, int c_in)
+{
+    const size_t fblocks = size_t(c_out + 31) / 32, cb16 = size_t(c_in + 15) / 16;
+    for (size_t i = 0; i < nz.size(); ++i) {
+        const uint32_t want = 2 * (i / fblocks) + 1 < cb16 ? 0x3FFFFu : 0x15555u;   // (the last word may hold one half)
+        if ((nz[i] & want) != want) return 0;
+    }
+    return 1;
+}
+
 static int pack_impl(const float *w_dense, const uint8_t *pattern_id, const uint8_t *conn,
                      const uint16_t *table, int num_patterns, int c_out, int c_in,
                      pconv_dtype weight_dtype, pconv_handle **out, bool to_device)
@@ -146,6 +157,7 @@ static int pack_impl(const float *w_dense, const uint8_t *pattern_id, const uint
         if (rc == PCONV_OK && weight_dtype == PCONV_BF16) {
             std::vector<uint16_t> wd; std::vector<uint32_t> nz;
             build_dense_taps(h->canon, table, c_out, c_in, wd, nz);
+            h->wd_full = all_blocks_full(nz, c_out, c_in);
             rc = upload(h->d_wdense, wd.data(), wd.size(), h->device_bytes);
             if (rc == PCONV_OK) rc = upload(h->d_wnz, nz.data(), nz.size(), h->device_bytes);
         }

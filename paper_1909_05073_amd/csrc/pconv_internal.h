@@ -69,12 +69,13 @@ struct pconv_handle {
     float    *d_w4 = nullptr;
     // device copies (matrix-core kernels, bf16 handles only): the masked weights as dense
     // [filter][channel] matrices per tap, in blocks of 32 filters and 16 channels, the nine taps of a
-    // block next to each other: [fpad / 32][cb16][9][32][16] bf16, fpad = c_out rounded up to 32,
-    // cb16 = c_in rounded up to 32, in sixteens; and per (block of 32
+    // block next to each other: [fpad / 32][cb16 + 1][9][32][16] bf16, fpad = c_out rounded up to 32,
+    // cb16 = c_in rounded up to 32, in sixteens (the last block of a row is zeros); and per (block of 32
     // channels, block of 32 filters) a word whose bit 2 * tap + half says whether that
     // (tap, 16 channels, 32 filters) block holds any kept weight
     uint16_t *d_wdense = nullptr;
     uint32_t *d_wnz = nullptr;
+    int wd_full = 0;                 // 1: every such block that lies inside the layer holds a kept weight
     // Hand-over words of the tiled kernel: workgroups that share a unit of work signal each other
     // through kFlagWords words; every call takes the next of kFlagSlots such rows and a fresh
     // value, so calls that overlap on different streams do not see each other's signals.

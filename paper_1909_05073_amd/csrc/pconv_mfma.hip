@@ -44,7 +44,7 @@ constexpr int kPitch = 40;          // bf16 per staged pixel: 32 channels + 8 of
 
 struct MfmaArgs {
     const uint16_t *x; uint16_t *y; const float *bias;
-    const uint16_t *wd;             // [fpad / 32][cb16][9][32][16] bf16 bit patterns
+    const uint16_t *wd;             // [fpad / 32][2 * cb32 + 1][9][32][16] bf16 bit patterns
     const uint32_t *nz;             // [cb32][fpad / 32]: bit (2 * tap + half) = block holds a kept weight
     int n, c_in, h, w, c_out, ho, wo, stride, relu;
     int cb32, fpad;
@@ -204,7 +204,7 @@ conv_mfma_kernel(const MfmaArgs a)
                 for (int k = 0; k < 4; ++k) lp[k] = u32x4{xr[i][4 * k], xr[i][4 * k + 1], xr[i][4 * k + 2], xr[i][4 * k + 3]};
             }
     };
-    const int cb16n = a.cb32 * 2;
+    const int cb16n = a.cb32 * 2 + 1;                            // (a row ends with a block of zeros)
     auto weight_frag = [&](int cb, int q, uint32_t nzb) -> u32x4 {
         if (!((nzb >> q) & 1u)) return u32x4{0u, 0u, 0u, 0u};
         const int tap = q >> 1, half = q & 1;

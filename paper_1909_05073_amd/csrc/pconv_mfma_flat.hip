@@ -5,34 +5,40 @@
 // without a kept weight is skipped.
 //
 // Work decomposition.  The output pixels of the whole batch are one flat list; a workgroup owns a run
-// of it and MB blocks of 32 filters.  Its waves are WP pixel parts x WK channel parts: a wave holds
-// MB x NB blocks of 32 filters x 32 pixels and walks every WK-th block of 16 input channels (the WK
-// partial sums are added through LDS at the end, in a fixed order).  A flat run has no ragged tile
-// edges: 49-pixel images fill the instruction as well as large ones.
+// of it and a group of filters.  Its waves are WP pixel parts x WF filter parts x WK channel parts: a wave
+// holds MB x NB blocks of 32 filters x 32 pixels and walks every WK-th step of KB blocks of 16 input
+// channels (the WK partial sums are added through LDS at the end, in a fixed order).  A flat run has no
+// ragged tile edges: 49-pixel images fill the instruction as well as large ones.
 //
 // Staging.  The taps of a run of pixels read, in every image it touches, one contiguous range of each
 // channel plane (from the first tap of the first pixel to the last tap of the last).  That range is
-// staged for 16 channels at a time as two planes of [pixel][8 channels], so that a lane's operand is
-// one 128-bit read.  One staging item is 8 pixels x 8 channels: eight 16-byte loads, for NCHW an 8x8
-// transpose in registers (32 v_perm), eight 16-byte LDS writes.  The loads of the next block are in
-// flight during the matrix instructions of the present one, and two LDS buffers are used in turn (one
-// barrier per block; none at all with WP = 1, where every wave reads only what it staged itself).
+// staged for a step at a time as planes of [pixel][8 channels], so that a lane's operand is one 128-bit
+// read.  One staging item is 8 pixels x 8 channels: eight 16-byte loads, for NCHW an 8x8 transpose in
+// registers (32 v_perm), eight 16-byte LDS writes; the filter and pixel parts share them.  Two LDS buffers
+// are used in turn (one barrier per step; none at all where a wave reads only what it staged itself).
 // After every eight pixels one 16-byte slot is left free: the LDS writes of neighbouring lanes, which
 // are eight pixels apart, would otherwise all fall on the same banks.  A lane's nine tap addresses do
-// not change from block to block and are kept in registers; a tap outside the image reads a slot of
+// not change from step to step and are kept in registers; a tap outside the image reads a slot of
 // zeros, so the inner loop has no bounds arithmetic.
 //
-// What bounds it: at full occupancy the vector-memory pipe (18 KB of weight fragments per wave, two
-// blocks of filters and 16 channels, for 36 matrix instructions) and the fixed start and end of a
-// workgroup (some 7000 cycles before the first matrix instruction, 2500 to 5000 after the last); with
-// few workgroups the latency of one workgroup's chain of channel blocks.  Counters, 32 images 256@14: the
-// matrix units are busy 17 % of the time, a wave waits for data 40 % of it and to issue 27 %.  Measured
-// on one MI355X, the seven ResNet-50 3x3 shapes, NCHW, in us, calls back to back in a graph, against the
-// tiled-image kernel of pconv_mfma.hip:
-//   one image    64@56 5.2 (9.3)   128@56/2 9.0 (13.3)  128@28 5.4 (12.7)  256@28/2 10.8 (20.6)
-//                256@14 7.2 (20.3)  512@14/2 10.3 (35.2)  512@7 13.1 (37.6)
-//   32 images    64@56 18.7 (37.9)  128@56/2 29.3 (37.8)  128@28 16.6 (31.1)  256@28/2 28.9 (30.1)
-//                256@14 16.0 (27.5)  512@14/2 30.7 (47.3)  512@7 25.0 (38.3)
+// Pipeline.  The loop has no branches and its waits count loads: every weight fragment is replaced, once
+// used, by that of the next step, and the pixels of a step are loaded two steps ahead and go to LDS one
+// step ahead.  (With a branch for partial or empty blocks in it the compiler kept two copies of these
+// registers and waited for all loads at the end of every step; channels and blocks beyond the last are
+// read as zeros instead, and layers with empty blocks have an instance of their own, FULL = false.)
+//
+// What bounds it: the vector-memory pipe, 64 bytes a cycle and compute unit.  2 x 2 blocks take 18 weight
+// loads of 1 KB and 8 or more of pixels per wave for 36 matrix instructions of 32 cycles: with two such
+// workgroups per compute unit a step takes 3000 cycles, of which the matrix units are busy 2300.  Around
+// the loop a workgroup spends some 7000 cycles until its first operands are there and 4000 on the
+// reduction and the stores, which is 40 to 60 % of the layers below.  With few workgroups that is all.
+// Stride 2 stages four input pixels per output pixel, so there the filter parts matter most.
+// Measured on one MI355X, the seven ResNet-50 3x3 shapes, NCHW, in us, calls back to back in a graph
+// (in brackets: with three taps of weights and one step of pixels ahead, and without filter parts):
+//   one image    64@56 5.3 (5.2)   128@56/2 6.9 (9.0)  128@28 5.7 (5.4)  256@28/2 9.3 (10.8)
+//                256@14 6.6 (7.2)  512@14/2 9.1 (10.3)  512@7 10.1 (13.1)
+//   32 images    64@56 16.4 (18.7)  128@56/2 15.4 (29.3)  128@28 14.5 (16.6)  256@28/2 16.2 (28.9)
+//                256@14 14.7 (16.0)  512@14/2 18.9 (30.7)  512@7 17.6 (25.0)
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -68,37 +74,39 @@ __device__ __forceinline__ int fast_div(int n, FastDiv d)
 
 struct FlatArgs {
     const uint16_t *x; uint16_t *y; const float *bias;
-    const uint16_t *wd;             // [fblocks][cb16][9][32][16] bf16 bit patterns
+    const uint16_t *wd;             // [fblocks][wd_row][9][32][16] bf16 bit patterns
     const uint32_t *nz;             // [cb16 / 2][fblocks]: bit (2 * tap + half)
     int c_in, w, c_out, hw, wo, howo, h;
     int stride, relu;
     int cb16, fblocks;              // blocks of 16 channels that hold any, blocks of 32 filters
-    int wd_cb16;                    // blocks of 16 channels in a row of wd (even)
+    uint32_t x_bytes, wd_bytes;     // sizes of x (below 2^31) and wd
+    int iters;                      // steps of a channel part
+    int wd_row;                     // blocks of 16 channels in a row of wd: an even number and one of zeros
     int total;                      // output pixels of the batch
     int rhw;                        // h * w rounded up to 8
     FastDiv div_howo, div_wo, div_rhw;
-    int wp_log2, wk;
+    int wp_log2, wf_log2, wk;
     int bias_at;                    // where the bias lies in LDS, in floats
     int plane;                      // 16-byte slots of a staged plane
     int tiles, fgroups, filter_major;
+    int inner; FastDiv div_inner;   // tiles if filter_major, fgroups otherwise
 };
 
-// 16 bytes from an address that need not be aligned to more than an element
-__device__ __forceinline__ u32x4 load16(const char *p)
+// 16 bytes at byte offset `lane` + `uniform` of a buffer; no more than an element's alignment is needed
+__device__ __forceinline__ u32x4 load16(__amdgpu_buffer_rsrc_t buf, uint32_t lane, uint32_t uniform)
 {
-    u32x4 v;
-    __builtin_memcpy(&v, p, 16);
-    return v;
+    return __builtin_amdgcn_raw_buffer_load_b128(buf, int(lane), int(uniform), 0);
 }
 
-template <int LAYOUT, int MB, int NB, int R>
-__global__ void __launch_bounds__(512)
+template <int LAYOUT, int MB, int NB, int R, int KB, int THREADS, bool FULL, bool ODD>
+__global__ void __launch_bounds__(THREADS, MB * NB == 8 ? 1 : 2)
 conv_flat_kernel(const FlatArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) u32x4 slots[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wp = 1 << a.wp_log2, wpi = wave & (wp - 1), wki = wave >> a.wp_log2;
+    const int part_log2 = a.wp_log2 + a.wf_log2;                               // waves of a channel part
+    const int wpi = wave & ((1 << a.wp_log2) - 1), wfi = (wave >> a.wp_log2) & ((1 << a.wf_log2) - 1), wki = wave >> part_log2;
     const int col = lane & 31, kg = lane >> 5;
 
     // Workgroups whose ids are equal mod 8 run on one XCD (one L2): each gets a contiguous eighth of
@@ -106,8 +114,28 @@ conv_flat_kernel(const FlatArgs a)
     const int pairs = a.tiles * a.fgroups;
     const int u = int(blockIdx.x & 7) * ((pairs + 7) >> 3) + int(blockIdx.x >> 3);
     if (u >= pairs || int(blockIdx.x >> 3) >= ((pairs + 7) >> 3)) return;
-    const int tile = a.filter_major ? u % a.tiles : u / a.fgroups;
-    const int fg = a.filter_major ? u / a.tiles : u % a.fgroups;
+    const int outer = fast_div(u, a.div_inner), inner = u - outer * a.inner;
+    const int tile = a.filter_major ? inner : outer, fg = a.filter_major ? outer : inner;
+
+    // ---- weights: a wave's fragments of a block of channels are 9 KB in a row per block of filters ----
+    // The fragments of a whole step (KB blocks of 16 channels) stay in registers; one that has been used
+    // is replaced at once by that of the next step, so a load has a step's matrix instructions to arrive in.
+    constexpr int Q = 9 * KB;                        // (block of channels, tap) pairs of a step
+    int fb[MB];                      // (a block beyond the last one repeats it; its sums are not stored)
+#pragma unroll
+    for (int m = 0; m < MB; ++m) fb[m] = min(((fg << a.wf_log2) + wfi) * MB + m, a.fblocks - 1);
+    u32x4 wf[Q][MB];
+    const __amdgpu_buffer_rsrc_t wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.wd), 0, a.wd_bytes, 0x00020000);
+    // (ODD: the buffer begins and ends at whole dwords)
+    const uint32_t x_lead = ODD ? uint32_t(reinterpret_cast<uintptr_t>(a.x)) & 2u : 0u;
+    const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.x) - x_lead / 2, 0,
+                                                                           ODD ? (x_lead + a.x_bytes + 3u) & ~3u : a.x_bytes, 0x00020000);
+    const uint32_t wlane = uint32_t(lane & 31) * 32u + uint32_t(kg) * 16u;
+    auto load_weight = [&](int g, int q, int m) {
+        // (beyond the last block: the block of zeros at the end of the row)
+        const int block = fb[m] * a.wd_row + min(g * KB + q / 9, a.wd_row - 1);
+        wf[q][m] = load16(wbuf, wlane + uint32_t(q % 9 % 4) * 1024u, (uint32_t(block) * 9u + uint32_t(q % 9 / 4 * 4)) * 1024u);
+    };
 
     // ---- the run of output pixels and the input ranges it reads ----
     const int p0 = tile * (NB * 32 << a.wp_log2);
@@ -119,15 +147,21 @@ conv_flat_kernel(const FlatArgs a)
     const int base1 = ((img_last == img0 ? hi_last : a.hw) - lo0 + 7) & ~7;      // staged position of the second image
     const int staged = img_last == img0 ? base1 : base1 + (img_last - img0 - 1) * a.rhw + ((hi_last + 7) & ~7);
 
-    // ---- what this thread stages, the same for every block of channels ----
-    const int tid_g = int(threadIdx.x) & ((64 << a.wp_log2) - 1);               // thread within the channel part
-    const int g_item = tid_g & 1;                                              // which plane of 8 channels
+    // ---- what this thread stages, the same for every step ----
+    constexpr int PLANES = 2 * KB;                                             // planes of 8 channels
+    const int block_slots = 2 * a.plane + 1;                                   // two planes and a slot of zeros
+    const int buf_slots = a.wk * KB * block_slots;
+    const int tid_g = int(threadIdx.x) & ((64 << part_log2) - 1);               // thread within the channel part
+    const int g_item = tid_g & (PLANES - 1);                                   // which plane
+    const uint32_t plane_step = uint32_t(a.hw) * 2u, item_step = (LAYOUT == PCONV_NCHW ? plane_step : 2u) * 8u * uint32_t(g_item);
     uint32_t src[R];                                                           // byte offset of the item's first element
-    int dst[R], dst_step[R];                                                   // slot of its first pixel (-1: no item); pixel at which a free slot is stepped over
+    int dst[R], dst_step[R];                                                   // slot of its first pixel; pixel at which a free slot is stepped over
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-        const int pos = ((tid_g >> 1) + i * (32 << a.wp_log2)) * 8;
-        const bool ok = pos < staged;
+        // A thread without an item of its own does one of the first 2^k once more: the same bytes to the
+        // same place, and the loop needs no branches.
+        const int own = tid_g / PLANES + i * ((64 / PLANES) << part_log2);
+        const int pos = (own * 8 < staged ? own : own & ((1 << (31 - __builtin_clz(uint32_t(staged) >> 3))) - 1)) * 8;
         int img = img0, q = lo0 + pos;
         if (pos >= base1) {
             const int t = pos - base1, s = fast_div(t, a.div_rhw);
@@ -137,105 +171,109 @@ conv_flat_kernel(const FlatArgs a)
         const int q8 = min(q, a.hw - 8), wpos = pos - (q - q8);
         const uint32_t e = LAYOUT == PCONV_NCHW ? uint32_t(img * a.c_in * a.hw + q8)
                                                 : uint32_t((img * a.hw + q8) * a.c_in);
-        src[i] = ok ? e * 2u : 0u;
-        dst[i] = ok ? g_item * a.plane + wpos + (wpos >> 3) : -1;
+        src[i] = e * 2u + item_step + x_lead;
+        dst[i] = (wki * KB + (g_item >> 1)) * block_slots + (g_item & 1) * a.plane + wpos + (wpos >> 3);
         dst_step[i] = 8 - (wpos & 7);
     }
-    const char *xb = reinterpret_cast<const char *>(a.x);
-    const uint32_t plane_step = uint32_t(a.hw) * 2u, item_step = (LAYOUT == PCONV_NCHW ? plane_step : 2u) * 8u * uint32_t(g_item);
-    auto load_block = [&](int cb, u32x4 (&raw)[R][8]) {
-        const int c0 = cb * 16;
-        if (c0 + 16 <= a.c_in) {                                               // (uniform)
-            const char *base = xb + (LAYOUT == PCONV_NCHW ? uint32_t(c0) * plane_step : uint32_t(c0) * 2u);
+    // Pixels on their way to LDS.  ODD: where the planes of channels have an odd number of pixels, half of the
+    // items are not aligned to dwords, and such a load costs four times an aligned one: the five dwords
+    // around an item are loaded instead, the fifth into `fifth` (512@7: 11.4 -> 10.1 us with one image,
+    // 18.6 -> 17.6 with 32).
+    u32x4 raw[R][8];
+    uint32_t fifth[R][8];
+    // A channel beyond c_in has an offset beyond the tensor (bit 31 set: tensors are smaller): zeros.
+    auto load_rows = [&](int g, u32x4 (&raw)[R][8], uint32_t (&fifth)[R][8], int j0, int j1) {          // channels (NHWC: pixels) j0 ... j1 - 1 of the items
+        const int c0 = g * (16 * KB), left = a.c_in - 1 - (c0 + g_item * 8);    // (its sign: the item's first channel is beyond)
 #pragma unroll
-            for (int i = 0; i < R; ++i)
+        for (int j = j0; j < j1; ++j) {
+            const uint32_t beyond = uint32_t(LAYOUT == PCONV_NCHW ? left - j : left) & 0x80000000u;   // (NHWC: c_in is a multiple of 8)
+            const uint32_t uniform = LAYOUT == PCONV_NCHW ? uint32_t(c0 + j) * plane_step : uint32_t(c0 + j * a.c_in) * 2u;
 #pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    raw[i][j] = load16(base + (LAYOUT == PCONV_NCHW ? uint32_t(j) * plane_step : uint32_t(j * a.c_in) * 2u) + (src[i] + item_step));
-        } else {
-            // the last, partial block: a channel beyond c_in reads the last one and is zeroed below
-#pragma unroll
-            for (int i = 0; i < R; ++i)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int c = LAYOUT == PCONV_NCHW ? min(c0 + g_item * 8 + j, a.c_in - 1) : min(c0 + g_item * 8, a.c_in - 8);
-                    raw[i][j] = load16(xb + (LAYOUT == PCONV_NCHW ? uint32_t(c) * plane_step : uint32_t(c + j * a.c_in) * 2u) + src[i]);
-                }
-        }
-    };
-    const int buf_slots = a.wk * 2 * a.plane + 1;                              // the last slot of a buffer holds zeros
-    auto store_block = [&](int cb, int buf, u32x4 (&raw)[R][8]) {
-        if (cb * 16 + 16 > a.c_in) {                                           // (uniform)
-            const int left = a.c_in - cb * 16 - g_item * 8;                    // channels of the item that exist
-#pragma unroll
-            for (int i = 0; i < R; ++i)
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    if ((LAYOUT == PCONV_NCHW ? j : 0) >= left) raw[i][j] = u32x4{0u, 0u, 0u, 0u};   // (NHWC: c_in is a multiple of 8)
-        }
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-            if (dst[i] < 0) continue;
-            u32x4 *lp = slots + buf * buf_slots + wki * 2 * a.plane + dst[i];
-            u32x4 *lp1 = lp + 1;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                u32x4 v;
-                if (LAYOUT == PCONV_NCHW) {
-                    // pixel j: 16-bit half j % 2 of dword j / 2 of the eight channel rows
-                    const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u;
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) v[k] = __builtin_amdgcn_perm(raw[i][2 * k + 1][j >> 1], raw[i][2 * k][j >> 1], sel);
+            for (int i = 0; i < R; ++i) {
+                if (ODD) {
+                    // (uniform + 2 * (j & 1) is a multiple of four: the blocks of channels begin at even ones)
+                    const uint32_t lane_at = ((src[i] + 2u * (j & 1)) & ~3u) | beyond, at = uniform - 2u * (j & 1);
+                    raw[i][j] = load16(xbuf, lane_at, at);
+                    fifth[i][j] = __builtin_amdgcn_raw_buffer_load_b32(xbuf, int(lane_at), int(at + 16u), 0);
                 } else {
-                    v = raw[i][j];
+                    raw[i][j] = load16(xbuf, src[i] | beyond, uniform);
                 }
-                (j >= dst_step[i] ? lp1 : lp)[j] = v;
             }
         }
     };
-
-    // ---- weights: a wave's fragments of a block of channels are 9 KB in a row per block of filters ----
-    int fb[MB];                      // (a block beyond the last one repeats it; its sums are not stored)
+    // ODD: eight pixels out of the five dwords around them
+    auto align_rows = [&](u32x4 (&raw)[R][8], const uint32_t (&fifth)[R][8]) {
+        if (!ODD) return;
 #pragma unroll
-    for (int m = 0; m < MB; ++m) fb[m] = min(fg * MB + m, a.fblocks - 1);
-    // a window of kWin taps ahead of the one in use: a fragment that has been used is replaced at once
-    // by the one kWin places later, which may belong to the next block of channels
-    constexpr int kWin = MB * NB == 4 && MB == 2 ? 3 : 9;
-    u32x4 wf[kWin][MB];
-    auto load_weight = [&](int cb, int q, int m) {
-        const uint32_t e = (uint32_t(fb[m] * a.wd_cb16 + cb) * 9u + uint32_t(q)) * 512u;
-        wf[q % kWin][m] = *reinterpret_cast<const u32x4 *>(a.wd + e + uint32_t(lane & 31) * 16u + uint32_t(kg) * 8u);
+        for (int i = 0; i < R; ++i)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const uint32_t shift = ((src[i] + 2u * (j & 1)) & 2u) * 8u;
+                const u32x4 d = raw[i][j];
+                raw[i][j] = u32x4{__builtin_amdgcn_alignbit(d[1], d[0], shift), __builtin_amdgcn_alignbit(d[2], d[1], shift),
+                                  __builtin_amdgcn_alignbit(d[3], d[2], shift), __builtin_amdgcn_alignbit(fifth[i][j], d[3], shift)};
+            }
     };
-
-    u32x4 raw[R][8];
-    const int iters = (a.cb16 + a.wk - 1) / a.wk;
-    {
-        const int cb = min(wki, a.cb16 - 1);
-        load_block(cb, raw);
+    // pixel j of this thread's items to LDS
+    auto store_pixel = [&](int buf, int j, const u32x4 (&raw)[R][8]) {
 #pragma unroll
-        for (int q = 0; q < kWin; ++q)
+        for (int i = 0; i < R; ++i) {
+            u32x4 *lp = slots + buf * buf_slots + dst[i];
+            u32x4 *lp1 = lp + 1;
+            u32x4 v;
+            if (LAYOUT == PCONV_NCHW) {
+                // 16-bit half j % 2 of dword j / 2 of the eight channel rows
+                const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u;
 #pragma unroll
-            for (int m = 0; m < MB; ++m) load_weight(cb, q, m);
-    }
+                for (int k = 0; k < 4; ++k) v[k] = __builtin_amdgcn_perm(raw[i][2 * k + 1][j >> 1], raw[i][2 * k][j >> 1], sel);
+            } else {
+                v = raw[i][j];
+            }
+            (j >= dst_step[i] ? lp1 : lp)[j] = v;
+        }
+    };
+    // The prologue asks for everything that the first step needs, and the pixels of the second, in the
+    // order of the loop below (the waits in the loop count what was asked for since); the tap addresses
+    // are worked out in between, while the memory pipe is busy.
+    constexpr int TURN = Q / 3;                      // the tap of a step at which the next step's pixels go to LDS
+    u32x4 raw0[R][8];
+    uint32_t fifth0[R][8];
+    load_rows(wki, raw0, fifth0, 0, 8);
+    __builtin_amdgcn_sched_barrier(0);
 
     // ---- this lane's tap addresses (bytes, in buffer 0) ----
     int addr[9][NB];
+    const int part_at = wki * KB * block_slots * 16, zeros_at = part_at + 2 * a.plane * 16;
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-        const int p = p0 + (wpi * NB + j) * 32 + col;
-        const int img = fast_div(min(p, a.total - 1), a.div_howo), r = min(p, a.total - 1) - img * a.howo;
+        const int p = p0 + (wpi * NB + j) * 32 + col, pc = min(p, a.total - 1);
+        const int img = fast_div(pc, a.div_howo), r = pc - img * a.howo;
         const int oy = fast_div(r, a.div_wo), ox = r - oy * a.wo;
         const int iy = oy * a.stride, ix = ox * a.stride;
         const int pos = (img == img0 ? -lo0 : base1 + (img - img0 - 1) * a.rhw) + iy * a.w + ix;
+        const int lane_at = part_at + kg * a.plane * 16;
+        // (no short-circuits: selects, not branches)
+        const int col_ok[3] = {ix > 0, 1, ix + 1 < a.w};
+        const int row_ok[3] = {(p < p_end) & (iy > 0), p < p_end, (p < p_end) & (iy + 1 < a.h)};
 #pragma unroll
         for (int q = 0; q < 9; ++q) {
-            const int dy = q / 3 - 1, dx = q % 3 - 1;
-            // (a negative coordinate is a large unsigned one; no short-circuits: selects, not branches)
-            const bool ok = (p < p_end) & (uint32_t(iy + dy) < uint32_t(a.h)) & (uint32_t(ix + dx) < uint32_t(a.w));
-            const int t = pos + dy * a.w + dx;
-            addr[q][j] = (ok ? (wki * 2 + kg) * a.plane + t + (t >> 3) : buf_slots - 1) * 16;
+            const int t = pos + (q / 3 - 1) * a.w + (q % 3 - 1);
+            addr[q][j] = row_ok[q / 3] & col_ok[q % 3] ? lane_at + ((t + (t >> 3)) << 4) : zeros_at;
         }
+        // (half of the weights after the first pixel block's addresses, half after the last one's)
+        if (j == 0) {
+#pragma unroll
+            for (int q = 0; q < TURN; ++q)
+#pragma unroll
+                for (int m = 0; m < MB; ++m) load_weight(wki, q, m);
+        }
+        __builtin_amdgcn_sched_barrier(0);
     }
+    load_rows(a.wk + wki, raw, fifth, 0, 8);     // (also where there is no second step: it reads nothing)
+#pragma unroll
+    for (int q = TURN; q < Q; ++q)
+#pragma unroll
+        for (int m = 0; m < MB; ++m) load_weight(wki, q, m);
 
     f32x16 acc[MB][NB];
 #pragma unroll
@@ -245,12 +283,15 @@ conv_flat_kernel(const FlatArgs a)
 
     // bias of the workgroup's filters, behind everything else in LDS (-0 where there is none: x + -0 = x)
     float *bias_lds = reinterpret_cast<float *>(slots) + a.bias_at;
-    if (int(threadIdx.x) < MB * 32) {
-        const int f = fg * MB * 32 + int(threadIdx.x);
+    if (int(threadIdx.x) < MB * 32 << a.wf_log2) {
+        const int f = (fg << a.wf_log2) * MB * 32 + int(threadIdx.x);
         bias_lds[threadIdx.x] = a.bias && f < a.c_out ? a.bias[f] : -0.0f;
     }
-    if (threadIdx.x < 2) slots[threadIdx.x * buf_slots + buf_slots - 1] = u32x4{0u, 0u, 0u, 0u};
-    store_block(min(wki, a.cb16 - 1), 0, raw);
+    if (int(threadIdx.x) < 2 * a.wk * KB) slots[threadIdx.x * block_slots + 2 * a.plane] = u32x4{0u, 0u, 0u, 0u};
+    align_rows(raw0, fifth0);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) store_pixel(0, j, raw0);
+    const int iters = a.iters;
     __syncthreads();
 
     // NCHW: pixels are the rows of the instruction's result and filters its columns, so that a lane
@@ -264,73 +305,73 @@ conv_flat_kernel(const FlatArgs a)
     // (constant address space: scalar loads, which the waits for vector loads do not involve)
     typedef const uint32_t __attribute__((address_space(4))) *ConstWords;
     const ConstWords nz = reinterpret_cast<ConstWords>(reinterpret_cast<uintptr_t>(a.nz));
-    auto block_bits = [&](int cb, int m) -> uint32_t { return nz[(cb >> 1) * a.fblocks + fb[m]] >> (cb & 1); };
-    uint32_t bits[MB];
-#pragma unroll
-    for (int m = 0; m < MB; ++m) bits[m] = block_bits(min(wki, a.cb16 - 1), m);
 
-    auto step = [&](int it, auto more_c) {
-        constexpr bool MORE = decltype(more_c)::value;
-        const int cb = it * a.wk + wki;
-        const int next = min(cb + a.wk, a.cb16 - 1);
-        const int buf = it & 1;
-        uint32_t next_bits[MB];
-        if (MORE) {
-            load_block(next, raw);
-#pragma unroll
-            for (int m = 0; m < MB; ++m) next_bits[m] = block_bits(next, m);
-        }
-        auto replace_weight = [&](int q, int m) {
-            if (q + kWin < 9) load_weight(min(cb, a.cb16 - 1), q + kWin, m);
-            else if (MORE) load_weight(next, q + kWin - 9, m);
-        };
+    // One step: KB blocks of channels.  Half way the pixels of the next step, whose loads have had a
+    // step to arrive, go to the other LDS buffer, and the loads of the step after that are issued (which
+    // read nothing beyond the last channel).  AFTER: another step follows.
+    auto step = [&](int it, auto after_c) {
+        constexpr bool AFTER = decltype(after_c)::value;
+        const int g = it * a.wk + wki, buf = it & 1;
         const char *bp = lds_bytes + buf * buf_slots * 16;
-        bool full = cb < a.cb16;
+        auto fragment = [&](int q, int j) { return *reinterpret_cast<const bf16x8 *>(bp + (q / 9) * block_slots * 16 + addr[q % 9][j]); };
+        uint32_t bits[KB][MB];
+        if (!FULL) {
 #pragma unroll
-        for (int m = 0; m < MB; ++m) full = full && (bits[m] & 0x15555u) == 0x15555u;
-        if (full) {
-            constexpr int AHEAD = MB * NB <= 2 ? 2 : 1;  // taps by which the pixel fragments are read ahead (registers permitting)
-            bf16x8 xv[AHEAD + 1][NB];
-#pragma unroll
-            for (int q = 0; q < AHEAD; ++q)
-#pragma unroll
-                for (int j = 0; j < NB; ++j) xv[q][j] = *reinterpret_cast<const bf16x8 *>(bp + addr[q][j]);
-#pragma unroll
-            for (int q = 0; q < 9; ++q) {
-                if (q + AHEAD < 9) {
-#pragma unroll
-                    for (int j = 0; j < NB; ++j) xv[(q + AHEAD) % (AHEAD + 1)][j] = *reinterpret_cast<const bf16x8 *>(bp + addr[q + AHEAD][j]);
-                }
-#pragma unroll
-                for (int m = 0; m < MB; ++m)
-#pragma unroll
-                    for (int j = 0; j < NB; ++j) acc[m][j] = mfma(wf[q % kWin][m], xv[q % (AHEAD + 1)][j], acc[m][j]);
-#pragma unroll
-                for (int m = 0; m < MB; ++m) replace_weight(q, m);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < 9; ++q) {
+            for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
-                    if (cb < a.cb16 && ((bits[m] >> (2 * q)) & 1u)) {
-#pragma unroll
-                        for (int j = 0; j < NB; ++j)
-                            acc[m][j] = mfma(wf[q % kWin][m], *reinterpret_cast<const bf16x8 *>(bp + addr[q][j]), acc[m][j]);
-                    }
-                    replace_weight(q, m);
+                    const int cb = g * KB + kb;
+                    bits[kb][m] = cb < a.cb16 ? nz[(cb >> 1) * a.fblocks + fb[m]] >> (cb & 1) : 0u;
                 }
-            }
         }
-        if (MORE) {
-            store_block(next, buf ^ 1, raw);
+        // taps by which the pixel fragments are read ahead (the latency of LDS; registers permitting)
+        constexpr int AHEAD = MB * NB == 1 ? 4 : MB * NB == 2 ? 3 : MB * NB == 4 ? 2 : 1;
+        bf16x8 xv[AHEAD + 1][NB];
 #pragma unroll
-            for (int m = 0; m < MB; ++m) bits[m] = next_bits[m];
-            if (a.wp_log2) __syncthreads();
+        for (int q = 0; q < AHEAD; ++q)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) xv[q][j] = fragment(q, j);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            if (q + AHEAD < Q) {
+#pragma unroll
+                for (int j = 0; j < NB; ++j) xv[(q + AHEAD) % (AHEAD + 1)][j] = fragment(q + AHEAD, j);
+            }
+            if (AFTER && q == TURN) align_rows(raw, fifth);
+#pragma unroll
+            for (int m = 0; m < MB; ++m)
+                if (FULL || ((bits[q / 9][m] >> (2 * (q % 9))) & 1u)) {
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) {
+                        acc[m][j] = mfma(wf[q][m], xv[q % (AHEAD + 1)][j], acc[m][j]);
+                        if (FULL && AFTER && q == TURN) {
+                            // (a few pixels after each matrix instruction, which keeps its unit busy meanwhile)
+#pragma unroll
+                            for (int k = 0; k < 8; ++k)
+                                if (k * MB * NB / 8 == m * NB + j) store_pixel(buf ^ 1, k, raw);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
+                }
+            if (!FULL && AFTER && q == TURN) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) store_pixel(buf ^ 1, k, raw);
+            }
+            if (AFTER) {
+                // (spread over the rest of the step: a load waits for the memory pipe, and the next matrix
+                // instruction behind it)
+                if (q >= TURN) load_rows(g + 2 * a.wk, raw, fifth, (q - TURN) * 8 / (Q - TURN), (q - TURN + 1) * 8 / (Q - TURN));
+#pragma unroll
+                for (int m = 0; m < MB; ++m) load_weight(g + a.wk, q, m);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (AFTER) {
+            if (part_log2) __syncthreads();
             else __builtin_amdgcn_wave_barrier();
         }
     };
+#pragma unroll 1
     for (int it = 0; it + 1 < iters; ++it) step(it, std::true_type{});
     step(iters - 1, std::false_type{});
 
@@ -353,48 +394,92 @@ conv_flat_kernel(const FlatArgs a)
                 red[(wave * G + (m * NB + j) * 4 + g) * kGroupPitch + lane] =
                     f32x4{acc[m][j][4 * g], acc[m][j][4 * g + 1], acc[m][j][4 * g + 2], acc[m][j][4 * g + 3]};
     __syncthreads();
-#pragma unroll 2
-    for (int id = wki * 64 + lane; id < MB * NB * 128; id += a.wk * 64) {
-        const int o = id & (OCT - 1), c = (id / OCT) & 31, outer = id / (OCT * 32);
-        const int m = LAYOUT == PCONV_NCHW ? outer : o >> 2, j = LAYOUT == PCONV_NCHW ? o >> 2 : outer;
-        const f32x4 *rp = red + (wpi * G + (m * NB + j) * 4 + (o & 3)) * kGroupPitch + c;
-        f32x4 v0 = rp[0], v1 = rp[32];
-        for (int k = 1; k < a.wk; ++k) {
-            rp += (G * kGroupPitch) << a.wp_log2;
-            v0 += rp[0]; v1 += rp[32];
-        }
-        union { __bf16 e[8]; uint16_t u[8]; u32x4 d; } out;
-        const int f = (fg * MB + m) * 32 + (LAYOUT == PCONV_NCHW ? c : 8 * (o & 3));
-        const int p = p0 + (wpi * NB + j) * 32 + (LAYOUT == PCONV_NCHW ? 8 * (o & 3) : c);
-        const float *bp = bias_lds + m * 32 + (LAYOUT == PCONV_NCHW ? c : 8 * (o & 3));
+    auto finish = [&](auto wk_c) {
+        constexpr int WK = decltype(wk_c)::value, ROUNDS = (MB * NB * 2 + WK - 1) / WK, STEP = 64 / OCT;
+        if (wki >= MB * NB * 2) return;
+        const int o = lane & (OCT - 1);                                        // this lane's octet in the row, in every round
+        const f32x4 *rp0 = red + (((wfi << a.wp_log2) + wpi) * G + (o & 3)) * kGroupPitch;
+        auto sums = [&](int m, int j, int c, f32x4 &v0, f32x4 &v1) {
+            const f32x4 *rp = rp0 + ((m * NB + j) * 4) * kGroupPitch + c;
+            v0 = rp[0]; v1 = rp[32];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const float t = (k < 4 ? v0[k & 3] : v1[k & 3]) + bp[LAYOUT == PCONV_NCHW ? 0 : k];
-            out.e[k] = __bf16(a.relu ? fmaxf(t, 0.0f) : t);
-        }
-        if ((f >= a.c_out) | (p >= p_end)) continue;
+            for (int k = 1; k < WK; ++k) {
+                rp += (G * kGroupPitch) << part_log2;
+                v0 += rp[0]; v1 += rp[32];
+            }
+        };
+        union Octet { __bf16 e[8]; uint16_t u[8]; u32x4 d; };
+        auto round8 = [&](const f32x4 &v0, const f32x4 &v1, auto &&bias_of) {
+            Octet out;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const float t = (k < 4 ? v0[k & 3] : v1[k & 3]) + bias_of(k);
+                out.e[k] = __bf16(a.relu ? fmaxf(t, 0.0f) : t);
+            }
+            return out;
+        };
         if (LAYOUT == PCONV_NCHW) {
+            // a lane's eight pixels are the same in every round, the filters go on
+            const int p = p0 + wpi * NB * 32 + 8 * o;
             const int img = fast_div(p, a.div_howo), r = p - img * a.howo;
-            if ((r + 8 <= a.howo) & (p + 8 <= p_end)) {
-                __builtin_memcpy(a.y + (uint32_t(img * a.c_out + f) * uint32_t(a.howo) + uint32_t(r)), &out.d, 16);
-            } else {
+            const bool whole = (r + 8 <= a.howo) & (p + 8 <= p_end);
+            uint32_t at[8];                                                    // of each pixel in filter 0 (where they are not in a row)
+            at[0] = uint32_t(img * a.c_out) * uint32_t(a.howo) + uint32_t(r);
+            if (!whole) {
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
+                for (int k = 1; k < 8; ++k) {
                     const int im = fast_div(p + k, a.div_howo);
-                    if (p + k < p_end) a.y[uint32_t(im * a.c_out + f) * uint32_t(a.howo) + uint32_t(p + k - im * a.howo)] = out.u[k];
+                    at[k] = uint32_t(im * a.c_out) * uint32_t(a.howo) + uint32_t(p + k - im * a.howo);
+                }
+            }
+            const int pixels = min(8, p_end - p);
+#pragma unroll 4
+            for (int i = 0; i < ROUNDS; ++i) {
+                const int fl = lane / OCT + (wki + i * WK) * STEP, m = fl >> 5, c = fl & 31;
+                f32x4 v0, v1;
+                sums(m, o >> 2, c, v0, v1);
+                const float b = bias_lds[wfi * MB * 32 + fl];
+                const Octet out = round8(v0, v1, [&](int) { return b; });
+                const int f = ((fg << a.wf_log2) + wfi) * MB * 32 + fl;
+                if (f >= a.c_out) continue;
+                uint16_t *yp = a.y + uint32_t(f) * uint32_t(a.howo);
+                if (whole) {
+                    __builtin_memcpy(yp + at[0], &out.d, 16);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 8; ++k)
+                        if (k < pixels) yp[at[k]] = out.u[k];
                 }
             }
         } else {
-            uint16_t *yp = a.y + (uint32_t(p) * uint32_t(a.c_out) + uint32_t(f));
-            if (f + 8 <= a.c_out) {
-                __builtin_memcpy(yp, &out.d, 16);
-            } else {
+            // a lane's eight filters are the same in every round, the pixels go on
+            const int fl = 8 * o, f = ((fg << a.wf_log2) + wfi) * MB * 32 + fl;
+            float b[8];
 #pragma unroll
-                for (int k = 0; k < 8; ++k)
-                    if (f + k < a.c_out) yp[k] = out.u[k];
+            for (int k = 0; k < 8; ++k) b[k] = bias_lds[wfi * MB * 32 + fl + k];
+#pragma unroll 4
+            for (int i = 0; i < ROUNDS; ++i) {
+                const int pl = lane / OCT + (wki + i * WK) * STEP, j = pl >> 5, c = pl & 31;
+                f32x4 v0, v1;
+                sums(o >> 2, j, c, v0, v1);
+                const Octet out = round8(v0, v1, [&](int k) { return b[k]; });
+                const int p = p0 + wpi * NB * 32 + pl;
+                if ((p >= p_end) | (f >= a.c_out)) continue;
+                uint16_t *yp = a.y + (uint32_t(p) * uint32_t(a.c_out) + uint32_t(f));
+                if (f + 8 <= a.c_out) {
+                    __builtin_memcpy(yp, &out.d, 16);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 8; ++k)
+                        if (f + k < a.c_out) yp[k] = out.u[k];
+                }
             }
         }
-    }
+    };
+    if (a.wk == 1) finish(std::integral_constant<int, 1>{});
+    else if (a.wk == 2) finish(std::integral_constant<int, 2>{});
+    else if (a.wk == 4) finish(std::integral_constant<int, 4>{});
+    else finish(std::integral_constant<int, 8>{});
 }
 
 // Upper bound of the staged pixels of any run of np output pixels (see the kernel's `staged`).
@@ -415,75 +500,93 @@ int64_t staged_bound(int np, int64_t hw, int64_t howo, int64_t w, int64_t wo, in
 
 constexpr int64_t kLdsOfUnit = 160 * 1024;
 
-template <int LAYOUT, int MB, int NB, int R>
+template <int LAYOUT, int MB, int NB, int R, int KB, int THREADS, bool FULL, bool ODD>
 hipError_t launch_flat(const FlatArgs &a, dim3 grid, dim3 block, int64_t lds, hipStream_t st, int dev)
 {
     // More dynamic LDS than the default limit: raised once per device (the flag is set to the same
     // value by every thread that gets here first).
     static std::atomic<bool> attr_done[64];
     if (dev < 0 || dev >= 64 || !attr_done[dev].load(std::memory_order_acquire)) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_flat_kernel<LAYOUT, MB, NB, R>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_flat_kernel<LAYOUT, MB, NB, R, KB, THREADS, FULL, ODD>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, int(kLdsOfUnit));
         if (e != hipSuccess) return e;
         if (dev >= 0 && dev < 64) attr_done[dev].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((conv_flat_kernel<LAYOUT, MB, NB, R>), grid, block, size_t(lds), st, a);
+    hipLaunchKernelGGL((conv_flat_kernel<LAYOUT, MB, NB, R, KB, THREADS, FULL, ODD>), grid, block, size_t(lds), st, a);
     return hipGetLastError();
 }
 
-// Launch shape: MB x NB blocks of 32 filters x 32 pixels per wave, WP pixel parts x WK channel parts.
-struct FlatShape { int index, mb, nb, wp, wk, r; int64_t plane, lds; };
+// Launch shape: MB x NB blocks of 32 filters x 32 pixels per wave, WP pixel parts x WK channel parts x WF
+// filter parts, KB blocks of 16 channels per step; R staging items per thread.
+struct FlatShape { int index, mb, nb, wp, wk, kb, wf, r; int64_t plane, lds; };
 
-constexpr int kShapes[][4] = {{2, 2, 4, 1}, {2, 2, 2, 1}, {2, 2, 2, 2}, {2, 2, 1, 4}, {2, 1, 4, 1}, {2, 1, 2, 2},
-                              {1, 2, 4, 1}, {1, 2, 2, 2}, {1, 2, 1, 4}, {1, 1, 4, 1}, {1, 1, 2, 2}, {1, 1, 2, 4}, {1, 1, 1, 8}};
+// The 24 of 53 shapes measured (the four parts and both block counts in all combinations that looked
+// useful) whose best is within 1 % of the best of all, on average over 192 layers: see choose_flat.
+constexpr int kShapes[][6] = {
+    {2, 2, 1, 4, 1, 1}, {1, 2, 4, 1, 1, 1}, {1, 2, 2, 2, 1, 1}, {1, 2, 1, 4, 1, 1}, {1, 2, 1, 4, 2, 1}, {1, 1, 2, 2, 2, 1},
+    {1, 2, 4, 1, 2, 1}, {1, 1, 2, 2, 1, 1}, {1, 1, 1, 8, 1, 1}, {1, 4, 4, 1, 1, 1}, {1, 4, 2, 2, 1, 1}, {1, 2, 2, 1, 1, 2},
+    {1, 2, 1, 2, 1, 2}, {1, 1, 1, 8, 2, 1}, {2, 2, 4, 1, 1, 2}, {1, 1, 1, 4, 1, 2}, {1, 1, 4, 1, 1, 2}, {2, 4, 2, 1, 1, 2},
+    {1, 1, 1, 1, 2, 4}, {2, 2, 2, 2, 1, 2}, {2, 2, 1, 2, 1, 2}, {1, 2, 1, 4, 1, 2}, {2, 2, 2, 1, 1, 2}, {1, 2, 4, 1, 1, 2},
+    {1, 1, 4, 1, 1, 1}};            // (the last for layers of one block each way)
 constexpr int kNumShapes = int(sizeof kShapes / sizeof kShapes[0]);
 std::atomic<int> g_force_shape{-1};      // test override, see set_flat_shape
 
+// Combinations whose working set outgrows the registers of a wave are not built.
+constexpr bool fits_registers(int mb, int nb, int kb, int r, bool odd)
+{
+    if (r == 1) return true;
+    return mb * nb == 8 ? !odd : nb < 4 && mb == 1 && !(odd && kb == 2);
+}
+
 // The shape with the smallest estimate of the layer's time, in microseconds; false if the kernel does
-// not serve the call.  Few workgroups: the time of one, a start and end and per block of channels the
-// latency of its loads and LDS traffic.  Many: what a compute unit spends on a workgroup, per wave and
-// block of outputs, and per wave and block of channels for every block of weights, of matrix
-// instructions and for 64 staging items.  The constants are a fit to all shapes on thirteen layers (24
-// to 512 channels, 7 to 224 pixels square, both strides) with 1 to 32 images: the shape chosen takes
-// 1 % longer than the fastest one on average, 20 % at most (512@7, 32 images: {1, 2, 1, 4} takes 25.0 us,
-// {2, 2, 1, 4} 21.9).
+// not serve the call.  Few workgroups: the time of one, that is its start, in which all its waves send for
+// their weights and pixels through one memory pipe, and its steps.  Many: what a compute unit spends on a
+// workgroup, per wave and block of outputs, per wave and step for every load and every LDS access.  The
+// constants are a fit to these shapes on 150 layers drawn at random (16 to 512 channels, 7 to 224 pixels
+// square and not, both strides and layouts, 1 to 64 images) and the seven 3x3 shapes of ResNet-50 with 1,
+// 8 and 32 images: the shape chosen takes 2.6 % longer than the fastest one on average, 30 % at most
+// (352->448@40/2, 22 images).
 bool choose_flat(const pconv_handle *h, int n, int hin, int win, int stride, int layout, FlatShape &best)
 {
     const int hw = hin * win, wo = (win - 1) / stride + 1, howo = ((hin - 1) / stride + 1) * wo, total = n * howo;
-    const int cb16 = (h->c_in + 15) / 16, wd_cb16 = (h->c_in + 31) / 32 * 2, fblocks = (h->c_out + 31) / 32;
+    const int cb16 = (h->c_in + 15) / 16, wd_row = (h->c_in + 31) / 32 * 2 + 1, fblocks = (h->c_out + 31) / 32;
     // (a staging item is eight pixels of a plane; NHWC pixels are read in whole octets of channels)
     if (hw < 8 || (layout == PCONV_NHWC && h->c_in % 8 != 0)) return false;
-    if (int64_t(fblocks) * wd_cb16 * 9 * 512 >= (int64_t(1) << 31)) return false;   // (32-bit weight offsets)
+    if (int64_t(fblocks) * wd_row * 9 * 1024 >= (int64_t(1) << 32)) return false;   // (32-bit weight offsets)
     best = FlatShape{};
     double best_time = 0.0;
     const int cus = h->cus > 0 ? h->cus : 256, forced = g_force_shape.load();
+    int64_t bounds[5] = {0, 0, 0, 0, 0};                                        // of runs of 32, 64, 128, 256 and 512 pixels, once asked for
     for (int k = 0; k < kNumShapes; ++k) {
         const auto &c = kShapes[k];
-        FlatShape s{k, c[0], c[1], c[2], c[3], 1, 0, 0};
+        FlatShape s{k, c[0], c[1], c[2], c[3], c[4], c[5], 1, 0, 0};
         if (forced >= 0 && k != forced) continue;
-        if (s.mb > fblocks || s.wk > cb16) continue;
-        const int np = 32 * s.nb * s.wp, waves = s.wp * s.wk;
-        const int64_t bound = staged_bound(np, hw, howo, win, wo, stride);
+        if (s.mb * s.wf > fblocks + s.mb - 1 || s.mb > fblocks || s.wk > (cb16 + s.kb - 1) / s.kb || s.kb > cb16) continue;
+        const int np = 32 * s.nb * s.wp, part = s.wp * s.wf, waves = part * s.wk;
+        int64_t &bound = bounds[31 - __builtin_clz(unsigned(np)) - 5];
+        if (bound == 0) bound = staged_bound(np, hw, howo, win, wo, stride);
         s.plane = bound + bound / 8;
-        s.lds = std::max<int64_t>(2 * (s.wk * 2 * s.plane + 1) * 16, int64_t(waves) * s.mb * s.nb * 4 * 65 * 16) + 256;
-        const int64_t items = bound / 4;
-        s.r = items <= 64 * s.wp ? 1 : 2;
-        if (items > 64 * s.wp * s.r || (s.r == 2 && (s.mb == 2 || layout == PCONV_NHWC)) || s.lds > kLdsOfUnit) continue;
-        const int iters = (cb16 + s.wk - 1) / s.wk;
-        const int64_t tiles = (total + np - 1) / np, fgroups = (fblocks + s.mb - 1) / s.mb;
+        s.lds = std::max<int64_t>(2 * s.wk * s.kb * (2 * s.plane + 1) * 16, int64_t(waves) * s.mb * s.nb * 4 * 65 * 16) + 128 * int64_t(s.mb * s.wf);
+        const int64_t items = bound / 4 * s.kb;
+        s.r = items <= 64 * part ? 1 : 2;
+        if (!fits_registers(s.mb, s.nb, s.kb, s.r, layout == PCONV_NCHW && hw % 2 != 0)) continue;
+        if (items > 64 * part * s.r || s.lds > kLdsOfUnit) continue;
+        const int iters = ((cb16 + s.kb - 1) / s.kb + s.wk - 1) / s.wk;
+        const int64_t tiles = (total + np - 1) / np, fgroups = (fblocks + s.mb * s.wf - 1) / (s.mb * s.wf);
         const double groups = double(tiles) * fgroups / cus;
-        const double share = double(items) / (64 * s.wp);
-        const double chain = 2.4 + iters * ((s.mb == 1 ? 1.33 : s.nb == 1 ? 1.44 : 1.99) + 0.1 * share);
-        const double busy = waves * (0.064 * s.mb * s.nb + iters * (0.04 * s.mb + 0.1 * s.mb * s.nb + 0.04 * share));
-        const int resident = int(std::min<int64_t>(kLdsOfUnit / s.lds, 8 / waves));
+        const int resident = int(std::max<int64_t>(1, std::min<int64_t>(kLdsOfUnit / s.lds, (s.mb * s.nb < 8 ? 8 : 4) / waves)));
+        const bool odd = layout == PCONV_NCHW && hw % 2 != 0;
+        const int staging = 8 * s.r, loads = 9 * s.kb * s.mb + staging * (odd ? 2 : 1), lds_ops = 9 * s.kb * s.nb + staging;
+        const double chain = 2.4 + 0.0052 * waves * loads + iters * (0.054 + 0.0178 * 9 * s.kb * s.mb * s.nb + 0.0051 * waves * loads);
+        const double busy = waves * (0.025 * s.mb * s.nb + 0.0062 * (iters + 1) * loads + 0.0057 * iters * lds_ops);
         const double rounds = std::ceil(groups / resident);
         const double lo = std::min(groups * busy, rounds * chain), hi = std::max(groups * busy, rounds * chain);
-        const double time = hi + 0.25 * lo;
+        const double time = hi + 0.3 * lo;
         if (best.mb == 0 || time < best_time) { best = s; best_time = time; }
     }
     if (best.mb == 0) return false;
     const int np = 32 * best.nb * best.wp;
-    return int64_t((total + np - 1) / np) * ((fblocks + best.mb - 1) / best.mb) <= 0x3FFFFFFF;
+    return int64_t((total + np - 1) / np) * fblocks <= 0x3FFFFFFF;
 }
 
 }  // namespace
@@ -505,38 +608,67 @@ bool launch_conv_flat(const pconv_handle *h, const void *x, void *y, const float
     a.x = static_cast<const uint16_t *>(x); a.y = static_cast<uint16_t *>(y); a.bias = bias;
     a.wd = h->d_wdense; a.nz = h->d_wnz;
     a.c_in = h->c_in; a.h = hin; a.w = win; a.c_out = h->c_out;
+    a.x_bytes = uint32_t(int64_t(n) * h->c_in * hin * win * 2);
+    a.wd_bytes = uint32_t(int64_t((h->c_out + 31) / 32) * ((h->c_in + 31) / 32 * 2 + 1) * 9 * 1024);
     const int ho = (hin - 1) / stride + 1;
     a.wo = (win - 1) / stride + 1; a.hw = hin * win; a.howo = ho * a.wo;
     a.stride = stride; a.relu = relu;
-    a.cb16 = (h->c_in + 15) / 16; a.wd_cb16 = (h->c_in + 31) / 32 * 2; a.fblocks = (h->c_out + 31) / 32;
+    a.cb16 = (h->c_in + 15) / 16; a.wd_row = (h->c_in + 31) / 32 * 2 + 1; a.fblocks = (h->c_out + 31) / 32;
     a.total = n * a.howo;
     a.rhw = (a.hw + 7) & ~7;
     a.div_howo = make_fast_div(uint32_t(a.howo)); a.div_wo = make_fast_div(uint32_t(a.wo));
     a.div_rhw = make_fast_div(uint32_t(a.rhw));
-    const int mb = best.mb, nb = best.nb, wp = best.wp, wk = best.wk, r = best.r;
+    const int mb = best.mb, nb = best.nb, wp = best.wp, wk = best.wk, wf = best.wf;
+    a.iters = ((a.cb16 + best.kb - 1) / best.kb + wk - 1) / wk;
     const int np = 32 * nb * wp;
     const int64_t lds = best.lds, plane = best.plane;
-    a.bias_at = int((lds - 256) / 4);
-    a.wp_log2 = wp == 4 ? 2 : wp == 2 ? 1 : 0; a.wk = wk; a.plane = int(plane);
-    a.tiles = (a.total + np - 1) / np; a.fgroups = (a.fblocks + mb - 1) / mb;
+    a.bias_at = int(lds / 4) - 32 * mb * wf;
+    a.wp_log2 = wp == 4 ? 2 : wp == 2 ? 1 : 0; a.wf_log2 = wf == 8 ? 3 : wf == 4 ? 2 : wf == 2 ? 1 : 0; a.wk = wk; a.plane = int(plane);
+    a.tiles = (a.total + np - 1) / np; a.fgroups = (a.fblocks + mb * wf - 1) / (mb * wf);
     a.filter_major = int64_t(h->c_out) * 9 > int64_t(n) * a.hw;
+    a.inner = a.filter_major ? a.tiles : a.fgroups; a.div_inner = make_fast_div(uint32_t(a.inner));
     const int64_t pairs = int64_t(a.tiles) * a.fgroups;
-    const dim3 grid{unsigned((pairs + 7) / 8 * 8)}, block{unsigned(64 * wp * wk)};
+    const dim3 grid{unsigned((pairs + 7) / 8 * 8)}, block{unsigned(64 * wp * wf * wk)};
     hipStream_t st = static_cast<hipStream_t>(stream);
-    auto pick = [&](auto lay, auto rr) {
-        constexpr int L = decltype(lay)::value, RR = decltype(rr)::value;
-        if constexpr (RR == 1) {
-            if (mb == 2 && nb == 2) return launch_flat<L, 2, 2, RR>(a, grid, block, lds, st, h->device);
-            if (mb == 2 && nb == 1) return launch_flat<L, 2, 1, RR>(a, grid, block, lds, st, h->device);
+    hipError_t e = hipErrorInvalidValue;
+    auto pick = [&](auto lay, auto rr, auto mm, auto nn, auto kk) {
+        constexpr int L = decltype(lay)::value, RR = decltype(rr)::value, M = decltype(mm)::value, N = decltype(nn)::value,
+                      K = decltype(kk)::value;
+        if (mb != M || nb != N || best.kb != K) return;
+        constexpr int most = M * N < 8 ? 512 : 256;
+        if (int(block.x) > most) return;
+        constexpr bool nchw = L == PCONV_NCHW;
+        if constexpr (nchw && fits_registers(M, N, K, RR, true)) {
+            if (a.hw % 2 != 0) {
+                if (h->wd_full) e = launch_flat<L, M, N, RR, K, most, true, true>(a, grid, block, lds, st, h->device);
+                else e = launch_flat<L, M, N, RR, K, most, false, true>(a, grid, block, lds, st, h->device);
+                return;
+            }
         }
-        if (mb == 1 && nb == 2) return launch_flat<L, 1, 2, RR>(a, grid, block, lds, st, h->device);
-        return launch_flat<L, 1, 1, RR>(a, grid, block, lds, st, h->device);
+        if constexpr (fits_registers(M, N, K, RR, false)) {
+            if (h->wd_full) e = launch_flat<L, M, N, RR, K, most, true, false>(a, grid, block, lds, st, h->device);
+            else e = launch_flat<L, M, N, RR, K, most, false, false>(a, grid, block, lds, st, h->device);
+        }
     };
     using std::integral_constant;
-    hipError_t e;
-    if (layout == PCONV_NHWC) e = pick(integral_constant<int, PCONV_NHWC>{}, integral_constant<int, 1>{});
-    else if (r == 1) e = pick(integral_constant<int, PCONV_NCHW>{}, integral_constant<int, 1>{});
-    else e = pick(integral_constant<int, PCONV_NCHW>{}, integral_constant<int, 2>{});
+    auto pick_shape = [&](auto lay, auto rr) {
+        const integral_constant<int, 1> one; const integral_constant<int, 2> two; const integral_constant<int, 4> four;
+        pick(lay, rr, two, two, one);
+        pick(lay, rr, two, four, one);
+        pick(lay, rr, one, four, one);
+        pick(lay, rr, one, two, one);
+        pick(lay, rr, one, two, two);
+        pick(lay, rr, one, one, one);
+        pick(lay, rr, one, one, two);
+    };
+    const integral_constant<int, PCONV_NCHW> nchw; const integral_constant<int, PCONV_NHWC> nhwc;
+    if (layout == PCONV_NHWC) {
+        if (best.r == 1) pick_shape(nhwc, integral_constant<int, 1>{});
+        else pick_shape(nhwc, integral_constant<int, 2>{});
+    } else {
+        if (best.r == 1) pick_shape(nchw, integral_constant<int, 1>{});
+        else pick_shape(nchw, integral_constant<int, 2>{});
+    }
     rc = PCONV_OK;
     if (e != hipSuccess) {
         set_error(std::string("pconv_conv2d (matrix-core kernel): ") + hipGetErrorName(e));

@@ -266,7 +266,7 @@ void build_dense_taps(const Canonical &cn, const uint16_t *table, int c_out, int
                       std::vector<uint16_t> &wd, std::vector<uint32_t> &nz)
 {
     const int fpad = (c_out + 31) / 32 * 32, cb32 = (c_in + 31) / 32, cb16 = cb32 * 2;
-    wd.assign(size_t(9) * cb16 * fpad * 16, 0);
+    wd.assign(size_t(9) * (cb16 + 1) * fpad * 16, 0);            // (a row ends with a block of zeros)
     nz.assign(size_t(cb32) * (fpad / 32), 0u);
     for (int i = 0; i < c_out; ++i) {
         const int f = cn.perm[i];
@@ -276,7 +276,7 @@ void build_dense_taps(const Canonical &cn, const uint16_t *table, int c_out, int
             uint32_t v = cn.val_ptr[k];
             for (int t = 0; t < 9; ++t)
                 if (mask & (1u << t)) {
-                    wd[(((size_t(f / 32) * cb16 + c / 16) * 9 + t) * 32 + f % 32) * 16 + c % 16] = uint16_t(cn.vals_bits[v++] >> 16);
+                    wd[(((size_t(f / 32) * (cb16 + 1) + c / 16) * 9 + t) * 32 + f % 32) * 16 + c % 16] = uint16_t(cn.vals_bits[v++] >> 16);
                     nz[size_t(c / 32) * (fpad / 32) + f / 32] |= 1u << (2 * t + (c / 16) % 2);
                 }
         }

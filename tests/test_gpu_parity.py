@@ -568,6 +568,33 @@ def test_matrix_core_flat_every_launch_shape(index, layout):
     assert served >= 1
 
 
+FLAT_PINNED_WIDE = [  # enough blocks of channels and filters for the launch shapes that split both
+    (2, 272, 97, 9, 11, 1), (3, 264, 260, 14, 14, 2), (1, 40, 264, 13, 30, 1), (40, 16, 30, 5, 7, 1),
+]
+
+
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+@pytest.mark.parametrize("index", range(13, 25))
+def test_matrix_core_flat_wide_launch_shapes(index, layout):
+    """The launch shapes with filter parts, eight channel parts of two blocks and 2 x 4 blocks per wave,
+    pinned: ragged last steps, parts with nothing to do, planes with odd numbers of pixels."""
+    P.pconv_debug_set_flat_shape(index)
+    served = 0
+    for j, (n, ci, co, h, w, stride) in enumerate(FLAT_PINNED + FLAT_PINNED_WIDE):
+        spec = LayerSpec("flatwide", n, ci, co, h, w, stride=stride, dtype="bf16", keep_div=2.0)
+        L = make_layer(spec, 7400 + j)
+        hd = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "bf16")
+        got = P.pconv_debug_plan(hd, n, h, w, stride, layout).flat_shape
+        hd.free()
+        assert got in (index, -1)
+        if got < 0:
+            continue
+        served += 1
+        check_full(spec, L, make_input(spec, 7400 + j, layout), "bf16", layout, stride, relu=bool(j & 1), use_bias=not j & 2,
+                   policy=3, what=f"flatwide{index}_{j}_{layout}")
+    assert served >= 1
+
+
 def test_matrix_core_kernel_skips_empty_weight_blocks():
     """Connectivity so sparse that whole (tap, 16 channels, 32 filters) blocks hold no weight: the
     kernel skips them; and a layer with nothing kept at all."""
