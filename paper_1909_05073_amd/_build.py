@@ -7,8 +7,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpconv.so")
-SOURCES = ["pconv_capi.cpp", "pconv_pack.cpp", "pconv_kernels.hip", "pconv_tiled.hip", "pconv_mfma.hip",
-           "pconv_mfma_flat.hip"]
+SOURCES = ["pconv_capi.cpp", "pconv_pack.cpp", "pconv_kernels.hip", "pconv_tiled.hip", "pconv_lone.hip",
+           "pconv_mfma.hip", "pconv_mfma_flat.hip"]
 
 # packed-FP32 instructions are switched off for every device compile of this project
 HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -20,7 +20,7 @@ HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # a wave stages at all).  By default the AMDGPU backend structurizes uniform control flow as well,
 # with guarded blocks and register copies at every join; this option leaves uniform regions as the
 # plain branches they are.
-EXTRA_FLAGS = {"pconv_tiled.hip": ["-mllvm", "-structurizecfg-skip-uniform-regions"]}
+EXTRA_FLAGS = {src: ["-mllvm", "-structurizecfg-skip-uniform-regions"] for src in ("pconv_tiled.hip", "pconv_lone.hip")}
 
 
 def sources():

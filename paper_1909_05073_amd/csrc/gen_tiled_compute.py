@@ -179,25 +179,12 @@ def generate_takeover():
     return L
 
 
-def generate_patch():
-    """Loads the lane's 6x6 neighbourhood of one channel staged as rows: the four centre columns of
-    every row (LDS address %[va]) and the halo columns out of the neighbouring lanes' quads (address
-    %[left] / %[right] of row 0, %[lstep] / %[rstep] from row to row)."""
-    L = ["v_mov_b32 v24, %[left]", "v_mov_b32 v25, %[right]"]
-    for r in range(6):
-        L.append("ds_read_b128 v[%d:%d], %%[va] offset:%d" % (INP + 4 * r, INP + 4 * r + 3, r * QUAD_BYTES))
-        L.append("ds_read_b32 v%d, v24" % in_reg(r, 0))
-        L.append("ds_read_b32 v%d, v25" % in_reg(r, 5))
-        if r < 5:
-            L += ["v_add_u32 v24, v24, %[lstep]", "v_add_u32 v25, v25, %[rstep]"]
-    return L + ["s_waitcnt lgkmcnt(0)"]
-
-
 def generate_patch_shifted():
-    """The same where every patch starts four columns after its left neighbour: the halo columns are
-    the neighbouring lanes' registers, by wave shifts, masked to zero at the image's edge (%[maskl],
-    %[maskr]).  Half the LDS cycles of the form above.  What lane 0 and lane 63 have no neighbour for
-    is twelve further words (LDS address %[further] + 4 * lane), put in place lane by lane."""
+    """Loads the lane's 6x6 neighbourhood of one channel staged as rows, where every patch starts four
+    columns after its left neighbour: the four centre columns of every row (LDS address %[va]); the halo
+    columns are the neighbouring lanes' registers, by wave shifts, masked to zero at the image's edge
+    (%[maskl], %[maskr]).  What lane 0 and lane 63 have no neighbour for is twelve further words (LDS
+    address %[further] + 4 * lane), put in place lane by lane."""
     L = ["ds_read_b128 v[%d:%d], %%[va] offset:%d" % (INP + 4 * r, INP + 4 * r + 3, r * QUAD_BYTES) for r in range(6)]
     L += ["ds_read_b32 v24, %[further]", "s_waitcnt lgkmcnt(0)"]
     L += ["v_readlane_b32 s%d, v24, %d" % (68 + i, i) for i in range(12)]
@@ -235,7 +222,6 @@ def main():
     out = sys.argv[1]
     write_inc(out, generate())
     write_inc(os.path.join(os.path.dirname(out), "pconv_tiled_compute_scalar.inc"), generate(True))
-    write_inc(os.path.join(os.path.dirname(out), "pconv_tiled_patch.inc"), generate_patch())
     write_inc(os.path.join(os.path.dirname(out), "pconv_tiled_patch_shifted.inc"), generate_patch_shifted())
     write_inc(os.path.join(os.path.dirname(out), "pconv_tiled_takeover.inc"), generate_takeover())
     write_code_header(os.path.join(os.path.dirname(out), "pconv_tiled_code_masks.inc"))

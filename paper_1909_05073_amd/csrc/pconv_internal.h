@@ -6,6 +6,8 @@
 #include <string>
 #include <vector>
 
+#include <hip/hip_runtime.h>
+
 #include "pconv.h"
 
 namespace pconv {
@@ -13,6 +15,7 @@ namespace pconv {
 constexpr int kFlagSlots = 64, kFlagWords = 1024;
 // The register-tiled kernel keeps a record index in 24 bits: a longer stream stays off the device,
 // and the layer runs on the other kernels.
+constexpr int kLoneWaves = 16;         // waves of a workgroup of pconv_lone.hip
 constexpr size_t kTiledMaxRecords = size_t(1) << 24;
 
 // Thread-local message for pconv_last_error().
@@ -41,6 +44,9 @@ struct TiledStream {
     std::vector<int32_t>  slot_filter;  // [num_blocks * kTileFB] original filter index or -1
     std::vector<uint32_t> chan_ptr;     // [num_blocks][row_len]
     std::vector<uint32_t> chan_mid;     // [num_blocks][row_len] first record of slots 2 and 3 of the channel
+    // pconv_lone.hip: {first record, channel | records << 16} of every visited channel, and the first visit of
+    // each wave, [num_blocks][all slots, slots 0 and 1, slots 2 and 3][kLoneWaves + 1]
+    std::vector<uint32_t> lone_visits, lone_bounds;
     int64_t visits = 0;                 // (block, channel) pairs with a record
     int64_t half_visits = 0;            // (block, half of its slots, channel) triples with a record
     std::vector<uint32_t> meta;         // [R+1] record words (see pconv_tiled_codes.h), one pad
@@ -64,7 +70,7 @@ struct pconv_handle {
     // device copies (register-tiled kernel)
     int32_t  *d_slot_filter = nullptr;
     uint32_t *d_chan_ptr = nullptr;
-    uint32_t *d_chan_mid = nullptr;
+    uint32_t *d_lone_visits = nullptr, *d_lone_bounds = nullptr;
     uint32_t *d_meta = nullptr;
     float    *d_w4 = nullptr;
     // device copies (matrix-core kernels, bf16 handles only): the masked weights as dense
@@ -107,6 +113,14 @@ int launch_conv_generic(const pconv_handle *h, const void *x, void *y, const flo
 int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float *bias, int n,
                       int hin, int win, int stride, int layout, int dtype, int relu, int pool, void *stream,
                       bool static_scratch = false);
+// fp32 NCHW with few units of work: every wave on its own (pconv_lone.hip), from patch `patch_base` on.
+struct LoneTiles { int lanes; bool cut; int64_t tiles; };        // patches of a tile, tiles that cut rows, their number
+LoneTiles lone_tiles(int64_t patches, int px, int64_t patch_base, int64_t groups, int slots);
+// Where a launch for the patches from `first` on begins: at a row of patches, if a tile can hold one (up to px - 1
+// patches are computed twice).
+inline int64_t lone_base(int64_t first, int px) { return px <= 64 ? first - first % px : first; }
+hipError_t launch_conv_lone(const pconv_handle *h, const float *x, float *y, const float *bias, int n, int hin, int win,
+                            int stride, int relu, int pool, bool halves, int64_t patch_base, void *stream);
 // whether the tiled kernel can write the 2x2 max-pooled output directly (pool = 1)
 bool tiled_pool_supported(const pconv_handle *h, int n, int hin, int win, int layout, int dtype);
 bool tiled_supported(const pconv_handle *h, int n, int hin, int win, int stride, int layout, int dtype);

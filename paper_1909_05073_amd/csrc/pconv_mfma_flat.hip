@@ -47,6 +47,7 @@
 #include <string>
 #include <type_traits>
 
+#include "pconv_fast_div.h"
 #include "pconv_internal.h"
 
 namespace pconv {
@@ -57,20 +58,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-// n / d for n < 2^31 by one multiplication: Granlund and Montgomery's division by an invariant, with the
-// multiplier floor(2^32 (2^s - d) / d) + 1 and s = ceil(log2 d)
-struct FastDiv { uint32_t mul, shift; };
-FastDiv make_fast_div(uint32_t d)
-{
-    uint32_t s = 0;
-    while ((uint64_t(1) << s) < d) ++s;
-    return {uint32_t(((uint64_t(1) << 32) * ((uint64_t(1) << s) - d)) / d + 1), s};
-}
-__device__ __forceinline__ int fast_div(int n, FastDiv d)
-{
-    return int((__umulhi(uint32_t(n), d.mul) + uint32_t(n)) >> d.shift);
-}
 
 struct FlatArgs {
     const uint16_t *x; uint16_t *y; const float *bias;

@@ -94,7 +94,6 @@ struct TiledArgs {
     int n_img, c_in, row_len, h, w, c_out;
     int py, px;                 // patches per image column / row
     int n_patches, n_tiles, n_groups, n_blocks;
-    int tile_base;              // first tile of this launch
     int relu;
     int pool;                   // 1: y is the 2x2 / stride-2 max-pooled output (VEC kernel, whole units only)
     int sub2;                   // 1: stride 2: y holds the outputs at even rows and columns only
@@ -102,9 +101,7 @@ struct TiledArgs {
     int n_units;                // n_tiles * n_groups: (tile, filter group) pairs
     int n_chunks;               // chunks of CH input channels
     int split_units;            // 1: a workgroup's share of the work may begin and end inside a unit
-    int halves;                 // 1 (with priv): a workgroup works on two of its block's four slots
-    const uint32_t *chan_mid;   // first record of slots 2 and 3 per (block, channel), rows as chan_ptr
-    int priv;                   // 1: the 16 waves are 16 channel ranges of one filter block (VEC kernel)
+    int priv;                   // 1: the 16 waves are 16 channel ranges of one filter block (channels last)
     int one_set;                // 1 (with split_units): the iterations are dealt over all workgroups as one set
     uint32_t *flags;            // [gridDim.x] hand-over words of this call (split_units only)
     uint32_t n_records;         // records of the stream (the padding record's index)
@@ -143,22 +140,12 @@ __device__ __forceinline__ size_t act_at(int n, int c, int y, int x, int C, int 
 // belongs to a workgroup that has already started and handed over at its very beginning.
 //
 //
-// PRIV: few units of work.  A workgroup is one filter block, its 16 waves are 16 ranges of channels;
-// each wave stages its channels into a slot of its own, runs their records and goes on, with nothing to
-// wait for but its own loads, and the 16 partial sums are added through LDS at the end.  The halo
-// columns are not staged but read out of the neighbouring lanes' quads: what bounds this form is the
-// number of load instructions per channel (7 instead of 18; 256 channels @56, one image: 41 us with
-// 18, 28 with 7, 26 as it stands; shared units 97).  Staging the next channel while the records of the present one run
-// changes little (the other waves fill the gap) but costs nothing, the input registers are the buffer.
-// Channels last, a wave cannot load one channel well: there the waves stage 16 channels together, four
-// lanes to a pixel, and then run one each (128 channels @28, eight images: 33 us; with a lane per pixel
-// 111, in whole units 118, with their channels split four ways 61).
-// Where there are fewer blocks than half of the compute units, a workgroup takes two of its block's four
-// slots (halves): 512@14 31 us instead of 39, 512@28 32 (41), 256->512@28 21 (26); with enough blocks
-// it loses (256@56 37 for 27), since either half visits more than half of the channels.
-// One image, us, against the shared or whole units used before: 128@112 33 (91), 128->256@56 19 (59),
-// 256@56 27 (99), 256->512@28 21 (94), 512@28 32 (108), 512@14 31 (103); 64->64@224, where whole units
-// with split channels take 29 and stay, 50.
+// PRIV: few units of work, channels last (pconv_lone.hip does the same for NCHW, where a wave loads its
+// channels by itself).  A workgroup is one filter block, its 16 waves are 16 ranges of channels, and the 16
+// partial sums are added through LDS at the end.  The waves stage 16 channels together, four lanes to a
+// pixel, and then run one each (128 channels @28, eight images: 33 us; with a lane per pixel 111, in whole
+// units 118, with their channels split four ways 61).  The halo columns are not staged but read out of
+// the neighbouring lanes' registers.
 //
 // VEC: fp32 NCHW tensors at least 4 wide move the four centre columns of a patch row (and the four
 // outputs of a row) with one 128-bit access; the inputs go from global memory straight to LDS.
@@ -263,9 +250,8 @@ conv_tiled_kernel(const TiledArgs a)
         else if (piece - (has_tail ? 1 : 0) < n_whole) unit = first_whole + piece - (has_tail ? 1 : 0);
         else { unit = ua; c_begin = head_c0; }
         const bool takes_over = SPLIT && c_begin > 0, hands_on = SPLIT && c_end < n_chunks;
-        const int tile = a.tile_base + (one_set ? 0 : set_tile0) + unit / a.n_groups, group = unit % a.n_groups;
-        const int half = PRIV && a.halves ? group & 1 : -1;              // slots 0 and 1, or 2 and 3; -1: all
-        const int fblk = PRIV ? (a.halves ? group >> 1 : group) : group * fw + (wave - ksplit * fw);
+        const int tile = (one_set ? 0 : set_tile0) + unit / a.n_groups, group = unit % a.n_groups;
+        const int fblk = PRIV ? group : group * fw + (wave - ksplit * fw);
         const bool active = fblk < a.n_blocks;
 
         if (SPLIT) __syncthreads();                      // every wave has left the previous piece: LDS is free
@@ -276,13 +262,6 @@ conv_tiled_kernel(const TiledArgs a)
         // (Loaded first: they are on the way while the tables below are set up.)
         const int ptr_max = a.row_len - 1;               // last entry of a row: end of the block's records
         const uint32_t *__restrict__ ptr_row = a.chan_ptr + size_t(active ? fblk : 0) * a.row_len;
-        // (PRIV: the records of the workgroup's slots of a channel)
-        const uint32_t *__restrict__ mid_row = a.chan_mid + size_t(active ? fblk : 0) * a.row_len;
-        auto channel_records = [&](int at, uint32_t &first, uint32_t &count) {
-            const int c0 = min(at, ptr_max);
-            first = half == 1 ? mid_row[c0] : ptr_row[c0];
-            count = (half == 0 ? mid_row[c0] : ptr_row[min(at + 1, ptr_max)]) - first;
-        };
         int win_base = c_begin;
         // one register holds both bounds: first record (24 bits) and number of records (8 bits)
         auto load_bounds = [&]() {
@@ -344,36 +323,7 @@ conv_tiled_kernel(const TiledArgs a)
         // each of which fills 64 consecutive words of the halo blocks: word i of load j belongs to patch
         // 16 * (j % 4) + i / 4 and is its halo value e = 4 * (j / 4) + i % 4.  The element offset of that
         // value in channel 0, in bytes (or kOutOfRange outside the image), is the same for every chunk: tabulated once.
-        if constexpr (PRIV) {
-            // A staged channel of a wave that works on its own is six rows of quads, 1 KB each, and 64
-            // further words: the twelve halo values that no patch of the tile holds (word 2 r: left of
-            // lane 0's patch in row r, word 2 r + 1: right of lane 63's) and zeros.  Every other halo
-            // value is a centre column of the neighbouring lane's patch.  Tabulated once: the source
-            // offsets of the further words, and per lane {offset, step per row} of the left and of the
-            // right halo column inside the channel.
-            if (threadIdx.x < 64) {
-                const int i = threadIdx.x, r = i >> 1;
-                const int pidx_h = tile * 64 + ((i & 1) ? 63 : 0);
-                const int n_h = pidx_h / per_img, prem_h = pidx_h - n_h * per_img;
-                const int xh = VEC ? min((prem_h % a.px) * 4, a.w - 4) : 0;
-                const int iy = (prem_h / a.px) * 4 - 1 + r, ix = (i & 1) ? xh + 4 : xh - 1;
-                const bool ok = VEC && i < 12 && pidx_h < a.n_patches && iy >= 0 && iy < a.h && ix >= 0 && ix < a.w;
-                halo_tab[i] = ok ? ((n_h * a.c_in * a.h + iy) * a.w + ix) * 4 : int(kOutOfRange);
-                // (the last patch of a row is shifted left by `over` columns over its left neighbour)
-                const int over = VEC ? a.px * 4 - a.w : 0, col = prem % a.px;
-                constexpr int kFurther = 6 * QUAD_FLOATS * 4, kZero = kFurther + 12 * 4;
-                int4 v = make_int4(kZero, 0, kZero, 0);
-                if (pvalid && col > 0) {
-                    if (lane == 0) { v.x = kFurther; v.y = 8; }
-                    else { v.x = (lane - 1) * 16 + (col == a.px - 1 ? 3 - over : 3) * 4; v.y = QUAD_FLOATS * 4; }
-                }
-                if (pvalid && col < a.px - 1) {
-                    if (lane == 63) { v.z = kFurther + 4; v.w = 8; }
-                    else { v.z = (lane + 1) * 16 + (col == a.px - 2 ? over : 0) * 4; v.w = QUAD_FLOATS * 4; }
-                }
-                *reinterpret_cast<int4 *>(halo_tab + 64 + 4 * lane) = v;
-            }
-        } else if (VEC) {
+        if (VEC) {
             for (int t = threadIdx.x; t < HALO_TAB_WORDS; t += NW * 64) {
                 const int j = t >> 6, i = t & 63;
                 const int e = 4 * (j >> 2) + (i & 3);
@@ -424,24 +374,6 @@ conv_tiled_kernel(const TiledArgs a)
                 asm volatile("s_mov_b32 m0, %1\n s_nop 0\n buffer_load_dword %0, %2, %3 offen lds"
                              ::"v"(off[k]), "s"(dst_b), "s"(rsrc), "s"(soff));
             }
-        };
-        // a wave on its own: the six rows of a channel and the further words, see above
-        auto stage_rows = [&](int c, float *slot) {
-            const int ln = fresh_lane();
-            const uint32_t soff = __builtin_amdgcn_readfirstlane(uint32_t(c) * uint32_t(hw) * 4u);
-            const int lane_off_now = inv[2 * ln];
-            const uint32_t vmask = uint32_t(inv[2 * ln + 1]);
-            const uint32_t further = uint32_t(halo_tab[ln]);
-#pragma unroll
-            for (int r = 0; r < 6; ++r) {
-                const uint32_t voff = ((vmask >> r) & 1u) ? uint32_t(lane_off_now + r * a.w) * 4u : kOutOfRange;
-                const uint32_t dst_b = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(slot + r * QUAD_FLOATS));
-                asm volatile("s_mov_b32 m0, %1\n s_nop 0\n buffer_load_dwordx4 %0, %2, %3 offen lds"
-                             ::"v"(voff), "s"(dst_b), "s"(rsrc), "s"(soff));
-            }
-            const uint32_t dst_b = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(slot + 6 * QUAD_FLOATS));
-            asm volatile("s_mov_b32 m0, %1\n s_nop 0\n buffer_load_dword %0, %2, %3 offen lds"
-                         ::"v"(further), "s"(dst_b), "s"(rsrc), "s"(soff));
         };
         // generic path (any layout / dtype / width): through registers, with conversion to fp32;
         // every thread owns SEGS (channel, row) segments of its lane's patch
@@ -627,28 +559,17 @@ conv_tiled_kernel(const TiledArgs a)
             // the lane's neighbourhood of the channel in slot `at` (bytes) to the registers of the record loop
             v16f in0, in1;
             v4f in2;
-            const bool even = !VEC || a.px * 4 == a.w;               // every patch starts four columns after its neighbour
             auto load_patch = [&](uint32_t at) {
                 const int ln = fresh_lane();
-                if (even) {
-                    // all ones where the column beside the patch lies in the image
-                    const uint32_t vmask = uint32_t(inv[2 * ln + 1]);
-                    const int maskl = int(vmask << 23) >> 31, maskr = int(vmask << 18) >> 31;
-                    asm volatile(
-#include "pconv_tiled_patch_shifted.inc"
-                        : "=&{v[28:43]}"(in0), "=&{v[44:59]}"(in1), "=&{v[60:63]}"(in2)
-                        : [va] "v"(at + uint32_t(ln) * 16u), [further] "v"(at + uint32_t(6 * QUAD_FLOATS * 4) + uint32_t(ln) * 4u),
-                          [maskl] "v"(maskl), [maskr] "v"(maskr)
-                        : "v24", "s68", "s69", "s70", "s71", "s72", "s73", "s74", "s75", "s76", "s77", "s78", "s79");
-                    return;
-                }
-                const int4 ht = *reinterpret_cast<const int4 *>(halo_tab + 64 + 4 * ln);
+                // all ones where the column beside the patch lies in the image
+                const uint32_t vmask = uint32_t(inv[2 * ln + 1]);
+                const int maskl = int(vmask << 23) >> 31, maskr = int(vmask << 18) >> 31;
                 asm volatile(
-#include "pconv_tiled_patch.inc"
+#include "pconv_tiled_patch_shifted.inc"
                     : "=&{v[28:43]}"(in0), "=&{v[44:59]}"(in1), "=&{v[60:63]}"(in2)
-                    : [va] "v"(at + uint32_t(ln) * 16u), [left] "v"(at + uint32_t(ht.x)), [lstep] "v"(ht.y),
-                      [right] "v"(at + uint32_t(ht.z)), [rstep] "v"(ht.w)
-                    : "v24", "v25");
+                    : [va] "v"(at + uint32_t(ln) * 16u), [further] "v"(at + uint32_t(6 * QUAD_FLOATS * 4) + uint32_t(ln) * 4u),
+                      [maskl] "v"(maskl), [maskr] "v"(maskr)
+                    : "v24", "s68", "s69", "s70", "s71", "s72", "s73", "s74", "s75", "s76", "s77", "s78", "s79");
             };
             // words and weights of the next BATCH records (index at most that of the padding record)
             auto fetch_batch = [&](uint32_t k, float4 &rec_w) {
@@ -685,99 +606,58 @@ conv_tiled_kernel(const TiledArgs a)
                     k += nb;
                 }
             };
-            const uint32_t slot_at = lds_base + uint32_t(wave) * uint32_t((VEC ? ROWS_FLOATS : PLANE_FLOATS) * 4);
-            if constexpr (VEC) {
-                // ---- every wave on its own: its range of channels, one LDS slot, no counters ----
-                const int per_wave = (a.c_in + NW - 1) / NW;
-                const int c_lo = min(a.c_in, wave * per_wave), c_hi = min(a.c_in, c_lo + per_wave);
-                float *slot = lds + wave * ROWS_FLOATS;
-                // The workgroups of a tile walk the same channels: each starts one further on, so that what it
-                // asks for was fetched into the L2 by its neighbour a step before.  Where a channel range
-                // starts follows from the filters alone, never from the tile: two tiles that both store
-                // the columns an overlapping last patch shares must have added them in one order.
-                const int c_start = c_hi > c_lo ? c_lo + group % (c_hi - c_lo) : c_lo;
-                const int c_stop = c_start + (c_hi - c_lo);          // (channels from c_hi on stand for those from c_lo on)
-                auto channel = [&](int c) { return c < c_hi ? c : c - (c_hi - c_lo); };
-                int win = c_start;                                   // lane j: first record of channel win + j and their number
-                uint32_t first = 0, count = 0;
-                auto load_window = [&]() {
-                    channel_records(channel(min(win + fresh_lane(), c_stop)), first, count);
-                };
-                load_window();
-                // the next channel at or after c that one of the four filters is connected to, its records
-                uint32_t nk = 0, nk_end = 0;
-                auto next_channel = [&](int c) {
-                    for (; c < c_stop; ++c) {
-                        if (c - win > 63) { win = c; load_window(); }
-                        nk = __builtin_amdgcn_readlane(first, c - win);
-                        nk_end = nk + __builtin_amdgcn_readlane(count, c - win);
-                        if (nk != nk_end) break;
-                    }
-                    return c;
-                };
-                int c = next_channel(c_start);
-                if (c < c_stop) stage_rows(channel(c), slot);
-                while (c < c_stop) {
-                    const uint32_t k = nk, k_end = nk_end;
-                    __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): the channel is in LDS
-                    // with the neighbourhood in registers the slot is free, and the next channel is on its
-                    // way to it while the records run
-                    load_patch(slot_at);
-                    c = next_channel(c + 1);
-                    if (c < c_stop) stage_rows(channel(c), slot);
-                    run_records(k, k_end);
+            const uint32_t slot_at = lds_base + uint32_t(wave) * uint32_t(PLANE_FLOATS * 4);
+            // ---- channels last: the waves stage 16 channels together, then every wave runs one ----
+            // (four channels of a pixel are one load, so a wave cannot stage one channel well)
+            uint32_t first = 0, count = 0;                       // lane j: records of this wave's channel in step win + j
+            const int steps = (a.c_in + NW - 1) / NW;
+            for (int step = 0; step < steps; ++step) {
+                if ((step & 63) == 0) {
+                    const int c0 = min((step + fresh_lane()) * NW + wave, ptr_max);
+                    first = ptr_row[c0];
+                    count = ptr_row[min(c0 + 1, ptr_max)] - first;
                 }
-            } else {
-                // ---- channels last: the waves stage 16 channels together, then every wave runs one ----
-                // (four channels of a pixel are one load, so a wave cannot stage one channel well)
-                uint32_t first = 0, count = 0;                       // lane j: records of this wave's channel in step win + j
-                const int steps = (a.c_in + NW - 1) / NW;
-                for (int step = 0; step < steps; ++step) {
-                    if ((step & 63) == 0) {
-                        channel_records((step + fresh_lane()) * NW + wave, first, count);
-                    }
-                    const uint32_t k = __builtin_amdgcn_readlane(first, step & 63);
-                    const uint32_t k_end = k + __builtin_amdgcn_readlane(count, step & 63);
-                    float4 rec_w;
-                    fetch_batch(k, rec_w);
-                    // Four lanes load the 16 channels of a pixel (64 bytes in a row), an instruction 16
-                    // pixels of one input row: four patches.  96 such items (six rows of 64 patches) are
-                    // six per wave; wave 0 also loads the pixels beside the tile's first and last patch.
-                    // A lane's four channels go to four planes.
-                    const int ln = fresh_lane();
-                    const int c4 = step * NW + (ln & 3) * 4;         // (c_in is a multiple of 4)
-                    v4f px[6], beside = v4f{0.f, 0.f, 0.f, 0.f};
+                const uint32_t k = __builtin_amdgcn_readlane(first, step & 63);
+                const uint32_t k_end = k + __builtin_amdgcn_readlane(count, step & 63);
+                float4 rec_w;
+                fetch_batch(k, rec_w);
+                // Four lanes load the 16 channels of a pixel (64 bytes in a row), an instruction 16
+                // pixels of one input row: four patches.  96 such items (six rows of 64 patches) are
+                // six per wave; wave 0 also loads the pixels beside the tile's first and last patch.
+                // A lane's four channels go to four planes.
+                const int ln = fresh_lane();
+                const int c4 = step * NW + (ln & 3) * 4;         // (c_in is a multiple of 4)
+                v4f px[6], beside = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int i = 0; i < 6; ++i) {
-                        const int pix = wave * 16 + (ln >> 2), patch = pix >> 2, q = pix & 3;   // row i
-                        const int off = inv[2 * patch];
-                        const uint32_t vmask = uint32_t(inv[2 * patch + 1]);
-                        const bool ok = ((vmask >> i) & (vmask >> (9 + q)) & 1u) && c4 < a.c_in;
-                        px[i] = four(ok, off + (i * a.w + q) * a.c_in + c4);
-                    }
-                    if (wave == 0 && ln < 48) {
-                        const int e = ln >> 2, r = e >> 1, patch = (e & 1) ? 63 : 0;
-                        const int off = inv[2 * patch];
-                        const uint32_t vmask = uint32_t(inv[2 * patch + 1]);
-                        const bool ok = ((vmask >> r) & (vmask >> ((e & 1) ? 13 : 8)) & 1u) && c4 < a.c_in;
-                        beside = four(ok, off + (r * a.w + ((e & 1) ? 4 : -1)) * a.c_in + c4);
-                    }
-                    if (step > 0) __syncthreads();                   // every wave has read its channel of the step before
+                for (int i = 0; i < 6; ++i) {
+                    const int pix = wave * 16 + (ln >> 2), patch = pix >> 2, q = pix & 3;   // row i
+                    const int off = inv[2 * patch];
+                    const uint32_t vmask = uint32_t(inv[2 * patch + 1]);
+                    const bool ok = ((vmask >> i) & (vmask >> (9 + q)) & 1u) && c4 < a.c_in;
+                    px[i] = four(ok, off + (i * a.w + q) * a.c_in + c4);
+                }
+                if (wave == 0 && ln < 48) {
+                    const int e = ln >> 2, r = e >> 1, patch = (e & 1) ? 63 : 0;
+                    const int off = inv[2 * patch];
+                    const uint32_t vmask = uint32_t(inv[2 * patch + 1]);
+                    const bool ok = ((vmask >> r) & (vmask >> ((e & 1) ? 13 : 8)) & 1u) && c4 < a.c_in;
+                    beside = four(ok, off + (r * a.w + ((e & 1) ? 4 : -1)) * a.c_in + c4);
+                }
+                if (step > 0) __syncthreads();                   // every wave has read its channel of the step before
 #pragma unroll
-                    for (int i = 0; i < 6; ++i)
+                for (int i = 0; i < 6; ++i)
 #pragma unroll
-                        for (int k4 = 0; k4 < 4; ++k4)
-                            lds[((ln & 3) * 4 + k4) * PLANE_FLOATS + i * QUAD_FLOATS + wave * 16 + (ln >> 2)] = px[i][k4];
-                    if (wave == 0 && ln < 48) {
+                    for (int k4 = 0; k4 < 4; ++k4)
+                        lds[((ln & 3) * 4 + k4) * PLANE_FLOATS + i * QUAD_FLOATS + wave * 16 + (ln >> 2)] = px[i][k4];
+                if (wave == 0 && ln < 48) {
 #pragma unroll
-                        for (int k4 = 0; k4 < 4; ++k4) lds[((ln & 3) * 4 + k4) * PLANE_FLOATS + 6 * QUAD_FLOATS + (ln >> 2)] = beside[k4];
-                    }
-                    store_batch(rec_w);
-                    __syncthreads();
-                    if (k != k_end) {
-                        load_patch(slot_at);
-                        run_records(k, k_end);
-                    }
+                    for (int k4 = 0; k4 < 4; ++k4) lds[((ln & 3) * 4 + k4) * PLANE_FLOATS + 6 * QUAD_FLOATS + (ln >> 2)] = beside[k4];
+                }
+                store_batch(rec_w);
+                __syncthreads();
+                if (k != k_end) {
+                    load_patch(slot_at);
+                    run_records(k, k_end);
                 }
             }
         } else if constexpr (VEC) {
@@ -888,14 +768,11 @@ conv_tiled_kernel(const TiledArgs a)
         if constexpr (PRIV) {
             // Waves on their own: two slots at a time go to LDS from every wave that had channels, and
             // wave s adds up slot s, in order of the waves, and writes its outputs.  (As a tree over the
-            // waves, with one of them writing everything: 16 channels @16 10.3 us instead of 9.6, 256 @56
-            // 26.8 instead of 25.8.)
-            const int used = min(NW, (a.c_in + ((a.c_in + NW - 1) / NW) - 1) / ((a.c_in + NW - 1) / NW));
-            const int parts = VEC ? used : min(NW, a.c_in);
+            // waves, with one of them writing everything, it was slower.)
+            const int parts = min(NW, a.c_in);
             v4f *red = reinterpret_cast<v4f *>(lds);
 #pragma unroll
             for (int pass = 0; pass < FB / 2; ++pass) {
-                if (half >= 0 && pass != half) continue;
                 __syncthreads();                         // the staging slots, or the pass before, are done with
                 if (wave < parts) {
 #pragma unroll
@@ -960,7 +837,7 @@ conv_tiled_kernel(const TiledArgs a)
         // the patch coordinates are recomputed here instead of being kept in registers across the loop
         int pidx_e = tile * 64 + lane;
         asm volatile("" : "+v"(pidx_e));
-        const bool writer = active && (PRIV ? wave < FB && (half < 0 || wave >> 1 == half) : ksplit == 0) && pidx_e < a.n_patches;
+        const bool writer = active && (PRIV ? wave < FB : ksplit == 0) && pidx_e < a.n_patches;
         if constexpr (VEC && SPLIT) {
             if (takes_over) {
                 // The predecessor (id - 8: same set, previous range) started before this workgroup
@@ -1145,7 +1022,6 @@ hipError_t launch_any(const TiledArgs &a, int64_t wgs, hipStream_t st, bool vec,
 {
     if constexpr (NW == 16)
         if (a.priv) {
-            if (vec) return launch_shape<float, PCONV_NCHW, true, NW, CH, false, true>(a, wgs, st, dev);
             return dtype == PCONV_F32 ? launch_shape<float, PCONV_NHWC, false, NW, CH, false, true>(a, wgs, st, dev)
                                       : launch_shape<bf16_t, PCONV_NHWC, false, NW, CH, false, true>(a, wgs, st, dev);
         }
@@ -1260,7 +1136,8 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
     p.nw = force_waves ? force_waves : (h->c_in <= 4 ? 8 : 16);
     const int ch = p.nw == 16 ? 8 : 4;
     const int n_chunks = (h->c_in + ch - 1) / ch, px = (win + 3) / 4;
-    const int n_tiles = int((int64_t(n) * ((hin + 3) / 4) * px + 63) / 64);
+    const int64_t patches = int64_t(n) * ((hin + 3) / 4) * px;
+    const int n_tiles = int((patches + 63) / 64);
     const int cus = h->cus > 0 ? h->cus : 256;
     const int slots = cus * (16 / p.nw);                 // workgroups that can run at once
     const int blocks = h->tiled.num_blocks;
@@ -1278,7 +1155,13 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
     auto units_of = [&](int ks) { return (blocks + (p.nw >> ks) - 1) / (p.nw >> ks); };   // filter groups per tile
     const double records = double(h->tiled.meta.size()) * p.nw / blocks / n_chunks;       // of a whole unit's chunk
     const double visits = double(h->tiled.visits) / blocks, recs = double(h->tiled.meta.size()) / blocks;
-    auto lone = [&](double v, double r) { return p.vec ? 8.5 + 0.055 * v + 0.03 * r : 10.0 + 3.3 * ((h->c_in + 15) / 16); };
+    // a round of waves on their own: fp32 NCHW (pconv_lone.hip) per visited channel 0.035 us and per record 0.023,
+    // fitted to 15 layers with 1 to 8 images (8 % off on average; 256 channels @56, one image: 17.3 us, 512
+    // @28 and two slots 22; a sixth more where tiles cut rows of patches);
+    // channels last 3.3 for 16 channels (128 @28, eight images: 38 us, whole units 120, 81, 62)
+    auto lone = [&](double v, double r, bool cut) {
+        return p.vec ? (3.6 + 0.035 * v + 0.023 * r) * (cut ? 1.17 : 1.0) : 10.0 + 3.3 * ((h->c_in + 15) / 16);
+    };
     if (whole_units > slots / 2) {
         if (can_split && p.nw == 16) {
             // Many units, but not a multiple of the number of compute units: whole units leave part of
@@ -1294,15 +1177,27 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
             const double t_share = double(whole_units) * n_chunks / slots + kShareOverhead;
             if (t_share < kShareGain * t_whole) p.split = p.one_set = true;
         }
-        // A last round with few units: their tiles go to a second launch, in which the waves work on their
-        // own and which takes a fraction of a round (128 channels @112, 32 images: 784 units are 3.06
-        // rounds, 323 us; 280 with the tiles of the last 16 units apart).
-        if (p.vec && can_priv && !p.split && whole_units > slots && force_split < 0 && force_ks < 0) {
-            const int64_t full = whole_units / slots;
-            const int main_tiles = int(full * (slots / 8) / units_of(0)) * 8, tail = n_tiles - main_tiles;
-            const double rest = double(whole_units % slots) / slots;
-            const double t_last = (0.72 + 0.28 * rest) * (6.0 + n_chunks * (2.0 + 1.9 * records / 142.0));
-            if (main_tiles > 0 && rest > 0.0 && 3.0 + std::ceil(double(tail) * blocks / slots) * lone(visits, recs) < 0.8 * t_last) p.tail_tiles = tail;
+        if (p.vec && can_priv && !p.split && force_split < 0 && force_ks < 0) {
+            const double full = double(whole_units / slots), rest = double(whole_units % slots) / slots;
+            const double round = 6.0 + n_chunks * (2.0 + 1.9 * records / 142.0), last = rest > 0.0 ? (0.72 + 0.28 * rest) * round : 0.0;
+            double t_best = full * round + last;
+            // A last round with few units: their tiles go to a second launch, in which the waves work on their
+            // own and which takes a fraction of a round (128 channels @112, 32 images: 784 units are 3.06
+            // rounds, 323 us; 280 with the tiles of the last 16 units apart).
+            const int main_tiles = int(int64_t(full) * (slots / 8) / units_of(0)) * 8, tail = n_tiles - main_tiles;
+            if (full > 0.0 && rest > 0.0 && main_tiles > 0) {
+                const LoneTiles t = lone_tiles(patches, px, lone_base(int64_t(main_tiles) * 64, px), blocks, slots);
+                const double t_tail = 3.0 + std::ceil(double(t.tiles) * blocks / slots) * lone(visits, recs, t.cut);
+                if (t_tail < 0.8 * last) { p.tail_tiles = tail; t_best = full * round + t_tail; }
+            }
+            // Up to three blocks of filters leave most of a whole unit's waves idle: waves on their own may still be
+            // faster (160 to 8 channels @95x102, 44 images: 81 us for 117).
+            if (blocks < p.nw / 4) {
+                const LoneTiles t = lone_tiles(patches, px, 0, blocks, slots);
+                if (2.5 + std::ceil(double(t.tiles) * blocks / slots) * lone(visits, recs, t.cut) < 0.9 * t_best) {
+                    p.priv = true; p.ks_log2 = 4; p.tail_tiles = 0;
+                }
+            }
         }
     } else {
         // Few units: the form with the smallest estimate, in microseconds, fitted to the VGG-16 layers
@@ -1327,15 +1222,16 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
         // units shared by P workgroups, which pass the sums on one after the other (256 channels @56, one
         // image: 99 us, four: 83)
         if (can_split)
-            consider(6.0 + 4.0 * chunk_scale * whole_units * n_chunks / slots + std::min(90.0, 10.0 * slots / double(whole_units)), true, 0, false);
-        // one filter block per workgroup, every wave its own channels: per visited channel 0.055 and per
-        // record 0.03 (256 channels @56, one image: 28 us; 512 @14: 40 us); channels last 3.3 for 16
-        // channels (128 @28, eight images: 38 us, whole units 120, 81, 62)
+            consider(6.0 + 4.6 * chunk_scale * whole_units * n_chunks / slots + std::min(90.0, 10.0 * slots / double(whole_units)), true, 0, false);
+        // one filter block per workgroup, every wave its own channels
         if (can_priv) {
-            consider(std::ceil(double(n_tiles) * blocks / slots) * lone(visits, recs), false, 4, true);
+            const LoneTiles t = lone_tiles(patches, px, 0, blocks, slots);
+            const double tiles = p.vec ? double(t.tiles) : double(n_tiles), start = p.vec ? 2.5 : 0.0;
+            const LoneTiles t2 = lone_tiles(patches, px, 0, 2 * blocks, slots);
+            consider(start + std::ceil(tiles * blocks / slots) * lone(visits, recs, t.cut), false, 4, true);
             // two of the block's four filters per workgroup, where there are not enough blocks for the chip
             if (p.vec)
-                consider(std::ceil(2.0 * n_tiles * blocks / slots) * lone(double(h->tiled.half_visits) / (2 * blocks), recs / 2), false, 4, true, true);
+                consider(start + std::ceil(2.0 * t2.tiles * blocks / slots) * lone(double(h->tiled.half_visits) / (2 * blocks), recs / 2, t2.cut), false, 4, true, true);
         }
     }
     if (force_split >= 0) { p.split = can_split && force_split != 0; p.one_set = p.split && force_split == 2; if (p.split) { p.ks_log2 = 0; p.priv = false; } }
@@ -1379,7 +1275,6 @@ int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float
     a.py = (hin + 3) / 4; a.px = (win + 3) / 4;
     a.n_patches = n * a.py * a.px;
     a.n_tiles = (a.n_patches + 63) / 64;
-    a.tile_base = 0;
     a.n_blocks = h->tiled.num_blocks;
     a.relu = relu; a.pool = pool;
     a.x_bytes = uint32_t(std::min<int64_t>(int64_t(n) * h->c_in * hin * win * 4, 0x7FFFFFFF));
@@ -1399,8 +1294,7 @@ int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float
     a.n_records = uint32_t(h->tiled.meta.size()) - 3u;
     a.n_tiles -= plan.tail_tiles;
     const int fw = nw >> a.ks_log2;
-    a.halves = plan.priv && plan.halves; a.chan_mid = h->d_chan_mid;
-    a.n_groups = ((a.n_blocks + fw - 1) / fw) << a.halves;
+    a.n_groups = (a.n_blocks + fw - 1) / fw;
     const int64_t units = int64_t(a.n_tiles) * a.n_groups;
     if (units > 0x3FFFFFFF) { set_error("pconv_conv2d: too many workgroups"); return PCONV_UNSUPPORTED; }
     a.n_units = int(units);
@@ -1431,14 +1325,14 @@ int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float
         wgs = a.priv ? (units + 7) / 8 * 8 : int64_t((a.n_tiles + 7) / 8) * 8 * a.n_groups;   // one per unit of the largest set, in every set
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipError_t e = nw == 16 ? launch_any<16, 8>(a, wgs, st, vec, layout, dtype, h->device)
-                            : launch_any<8, 4>(a, wgs, st, vec, layout, dtype, h->device);
-    if (e == hipSuccess && plan.tail_tiles > 0) {
-        a.tile_base = a.n_tiles; a.n_tiles = plan.tail_tiles;
-        a.priv = 1; a.halves = 0; a.ks_log2 = 4;
-        a.n_groups = a.n_blocks; a.n_units = a.n_tiles * a.n_groups;
-        e = launch_any<16, 8>(a, (int64_t(a.n_units) + 7) / 8 * 8, st, vec, layout, dtype, h->device);
-    }
+    auto lone = [&](bool halves, int64_t patch_base) {
+        return launch_conv_lone(h, static_cast<const float *>(x), static_cast<float *>(y), bias, n, hin, win, stride, relu,
+                                pool, halves, patch_base, stream);
+    };
+    hipError_t e = vec && plan.priv ? lone(plan.halves, 0)
+                   : nw == 16       ? launch_any<16, 8>(a, wgs, st, vec, layout, dtype, h->device)
+                                    : launch_any<8, 4>(a, wgs, st, vec, layout, dtype, h->device);
+    if (e == hipSuccess && plan.tail_tiles > 0) e = lone(false, lone_base(int64_t(a.n_tiles) * 64, a.px));
     if (e != hipSuccess) {
         set_error(std::string("pconv_conv2d (tiled kernel): ") + hipGetErrorName(e));
         return PCONV_HIP_ERROR;

@@ -568,6 +568,37 @@ def test_matrix_core_flat_every_launch_shape(index, layout):
     assert served >= 1
 
 
+LONE_SHAPES = [  # (n, c_in, c_out, h, w): the last patch of a row shifted by 0, 1, 2, 3 columns; part tiles; several images a tile
+    (1, 1, 4, 4, 4), (3, 17, 9, 5, 7), (2, 40, 6, 9, 60), (1, 33, 5, 14, 14), (5, 20, 8, 7, 9), (2, 15, 7, 6, 59),
+    (1, 70, 4, 13, 256), (1, 12, 6, 10, 130), (1, 9, 5, 6, 262), (2, 24, 4, 11, 101),      # (the last three: tiles that cut rows)
+]
+
+
+@pytest.mark.parametrize("ks", [4, 5])
+@pytest.mark.parametrize("shape", LONE_SHAPES)
+def test_waves_on_their_own_tiles(shape, ks):
+    """fp32 NCHW, every wave its own channels, all four or two slots per workgroup: whole rows of patches in
+    a tile and not, every shift of the last patch, waves without a channel, dense kernels (three records
+    each), stride 2 and the fused max-pool."""
+    import torch
+    n, ci, co, h, w = shape
+    for dense in (False, True):
+        spec = LayerSpec("lone", n, ci, co, h, w, keep_div=1.0 if dense else 2.0, num_patterns=1 if dense else 8,
+                         pattern_dist="dense" if dense else "zipf", count_dist="all" if dense else "pm30")
+        L = make_layer(spec, 7700 + ci); x = make_input(spec, 7700 + ci)
+        P.pconv_debug_set_tiling(16, ks, 0)
+        for stride in (1, 2):
+            y, hd = gpu_conv(L, x, "f32", stride=stride, relu=bool(n & 1))
+            assert P.pconv_debug_plan(hd, n, h, w, 1).ks_log2 == ks
+            yr, sr = oracle_full(L, x, "f32", "nchw", stride, bool(n & 1))
+            assert_close(y, yr, sr, "f32", f"lone{shape}_{ks}_{stride}")
+        if w % 2 == 0:
+            xd = to_device(x, "f32")
+            y = P.conv2d_pool2x2(hd, xd, relu=True)
+            assert torch.equal(y, P.maxpool2x2(P.conv2d(hd, xd, relu=True)))
+        hd.free()
+
+
 FLAT_PINNED_WIDE = [  # enough blocks of channels and filters for the launch shapes that split both
     (2, 272, 97, 9, 11, 1), (3, 264, 260, 14, 14, 2), (1, 40, 264, 13, 30, 1), (40, 16, 30, 5, 7, 1),
 ]
