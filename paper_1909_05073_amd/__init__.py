@@ -281,9 +281,18 @@ def pconv_debug_unpack(handle: Handle) -> np.ndarray:
 
 # ---- torch conveniences (device memory + streams only) ---------------------------------
 
-def _torch_dtype(dtype):
-    import torch
-    return torch.float32 if _DTYPE[dtype] == F32 else torch.bfloat16
+_raw_stream = None
+
+
+def _stream(index: int):
+    """torch's current stream on device `index`, as the C entry points take it."""
+    # (a stream object costs 1.9 us, more than everything else around a call but the launch)
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _raw_stream = raw or (lambda i: torch.cuda.current_stream(i).cuda_stream)
+    return _raw_stream(index) or None
 
 
 def conv2d(handle: Handle, x, bias=None, stride: int = 1, relu: bool = False, layout="nchw",
@@ -299,17 +308,20 @@ def conv2d(handle: Handle, x, bias=None, stride: int = 1, relu: bool = False, la
         n, h, w, c = x.shape
     if c != handle.c_in:
         raise ValueError("channel count does not match the handle")
-    if x.dtype != _torch_dtype(handle.dtype):
+    dtype = handle.dtype
+    if x.dtype != (torch.float32 if dtype == F32 else torch.bfloat16):
         raise ValueError("activation dtype does not match the handle")
-    ho, wo = (h - 1) // stride + 1, (w - 1) // stride + 1
-    shape = (n, handle.c_out, ho, wo) if lay == NCHW else (n, ho, wo, handle.c_out)
-    y = out if out is not None else torch.empty(shape, dtype=x.dtype, device=x.device)
+    if out is None:
+        ho, wo = (h - 1) // stride + 1, (w - 1) // stride + 1
+        shape = (n, handle.c_out, ho, wo) if lay == NCHW else (n, ho, wo, handle.c_out)
+        out = torch.empty(shape, dtype=x.dtype, device=x.device)
     if bias is not None and (bias.dtype != torch.float32 or not bias.is_cuda):
         raise ValueError("bias must be a float32 CUDA tensor")
-    stream = torch.cuda.current_stream(x.device).cuda_stream
-    pconv_conv2d(handle, x.data_ptr(), y.data_ptr(), bias.data_ptr() if bias is not None else 0,
-                 n, h, w, stride, 1, lay, handle.dtype, relu, stream)
-    return y
+    rc = (_lib or lib()).pconv_conv2d(handle.ptr, x.data_ptr(), out.data_ptr(), (bias.data_ptr() or None) if bias is not None else None,
+                                      n, h, w, stride, 1, lay, dtype, 1 if relu else 0, _stream(x.get_device()))
+    if rc != OK:
+        _check(rc)
+    return out
 
 
 def conv2d_pool2x2(handle: Handle, x, bias=None, relu: bool = False, out=None):
@@ -320,14 +332,13 @@ def conv2d_pool2x2(handle: Handle, x, bias=None, relu: bool = False, out=None):
     n, c, h, w = x.shape
     if c != handle.c_in:
         raise ValueError("channel count does not match the handle")
-    if x.dtype != _torch_dtype(handle.dtype):
+    if x.dtype != (torch.float32 if handle.dtype == F32 else torch.bfloat16):
         raise ValueError("activation dtype does not match the handle")
     y = out if out is not None else torch.empty((n, handle.c_out, h // 2, w // 2), dtype=x.dtype, device=x.device)
     if bias is not None and (bias.dtype != torch.float32 or not bias.is_cuda):
         raise ValueError("bias must be a float32 CUDA tensor")
-    stream = torch.cuda.current_stream(x.device).cuda_stream
     pconv_conv2d_pool2x2(handle, x.data_ptr(), y.data_ptr(), bias.data_ptr() if bias is not None else 0,
-                         n, h, w, NCHW, handle.dtype, relu, stream)
+                         n, h, w, NCHW, handle.dtype, relu, _stream(x.get_device()))
     return y
 
 
@@ -343,5 +354,5 @@ def maxpool2x2(x, layout="nchw"):
     y = torch.empty(shape, dtype=x.dtype, device=x.device)
     dt = F32 if x.dtype == torch.float32 else BF16
     pconv_maxpool2x2(x.data_ptr(), y.data_ptr(), n, c, h, w, lay, dt,
-                     torch.cuda.current_stream(x.device).cuda_stream)
+                     _stream(x.get_device()))
     return y

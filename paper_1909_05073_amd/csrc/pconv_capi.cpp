@@ -42,7 +42,7 @@ int upload(T *&dst, const T *src, size_t count, int64_t &bytes)
 void release_device(pconv_handle *h)
 {
     void *ptrs[] = {h->d_perm, h->d_row_ptr, h->d_kern, h->d_val_ptr, h->d_vals,
-                    h->d_slot_filter, h->d_chan_ptr, h->d_lone_visits, h->d_lone_bounds, h->d_meta, h->d_w4, h->d_flags, h->d_wdense, h->d_wnz};
+                    h->d_slot_filter, h->d_chan_ptr, h->d_lone_bounds, h->d_meta, h->d_w4, h->d_flags, h->d_wdense, h->d_wnz};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (h->h_err) (void)hipHostFree(h->h_err);
@@ -149,8 +149,12 @@ static int pack_impl(const float *w_dense, const uint8_t *pattern_id, const uint
             rc = upload(h->d_vals, reinterpret_cast<const float *>(h->canon.vals_bits.data()),
                         h->canon.vals_bits.size(), h->device_bytes);
         if (rc == PCONV_OK) rc = upload(h->d_slot_filter, h->tiled.slot_filter.data(), h->tiled.slot_filter.size(), h->device_bytes);
-        if (rc == PCONV_OK) rc = upload(h->d_lone_visits, h->tiled.lone_visits.data(), h->tiled.lone_visits.size(), h->device_bytes);
-        if (rc == PCONV_OK) rc = upload(h->d_lone_bounds, h->tiled.lone_bounds.data(), h->tiled.lone_bounds.size(), h->device_bytes);
+        if (rc == PCONV_OK) {
+            std::vector<uint32_t> lone = h->tiled.lone_bounds;                 // (one allocation for both)
+            lone.insert(lone.end(), h->tiled.lone_visits.begin(), h->tiled.lone_visits.end());
+            rc = upload(h->d_lone_bounds, lone.data(), lone.size(), h->device_bytes);
+            if (rc == PCONV_OK) h->d_lone_visits = h->d_lone_bounds + h->tiled.lone_bounds.size();
+        }
         if (rc == PCONV_OK) rc = upload(h->d_chan_ptr, h->tiled.chan_ptr.data(), h->tiled.chan_ptr.size(), h->device_bytes);
         if (rc == PCONV_OK && h->tiled.meta.size() < kTiledMaxRecords)
             rc = upload(h->d_meta, h->tiled.meta.data(), h->tiled.meta.size(), h->device_bytes);

@@ -3,6 +3,7 @@
 
 #include <atomic>
 #include <cstdint>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -53,6 +54,9 @@ struct TiledStream {
     std::vector<float>    w4;           // [R+1][4]
 };
 
+// A call's launch shape of the flat matrix-core kernel, once chosen (see choose_flat).
+struct FlatCall { int n = 0, h = 0, w = 0, stride = 0, layout = 0, index = 0, r = 0; int64_t plane = 0, lds = 0; };
+
 }  // namespace pconv
 
 struct pconv_handle {
@@ -70,7 +74,7 @@ struct pconv_handle {
     // device copies (register-tiled kernel)
     int32_t  *d_slot_filter = nullptr;
     uint32_t *d_chan_ptr = nullptr;
-    uint32_t *d_lone_visits = nullptr, *d_lone_bounds = nullptr;
+    uint32_t *d_lone_bounds = nullptr, *d_lone_visits = nullptr;              // (one allocation, bounds first)
     uint32_t *d_meta = nullptr;
     float    *d_w4 = nullptr;
     // device copies (matrix-core kernels, bf16 handles only): the masked weights as dense
@@ -91,6 +95,10 @@ struct pconv_handle {
     // writes (non-zero = a bounded wait inside a kernel ran out) and that the next call on the
     // handle reads without touching the device.
     uint32_t *h_err = nullptr;
+    // launch shapes of the last few kinds of calls: the choice takes 1.3 us, a third of a call's launch
+    mutable std::mutex flat_mutex;
+    mutable pconv::FlatCall flat_calls[4];
+    mutable unsigned flat_next = 0;
     int cus = 0;                     // compute units of `device`, read once at pack time
 };
 

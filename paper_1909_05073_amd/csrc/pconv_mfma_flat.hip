@@ -586,11 +586,31 @@ int flat_shape_of(const pconv_handle *h, int n, int hin, int win, int stride, in
     return choose_flat(h, n, hin, win, stride, layout, s) ? s.index : -1;
 }
 
+// choose_flat, or what it chose for the same call before
+static bool flat_shape(const pconv_handle *h, int n, int hin, int win, int stride, int layout, FlatShape &s)
+{
+    if (g_force_shape.load() >= 0) return choose_flat(h, n, hin, win, stride, layout, s);
+    {
+        const std::lock_guard<std::mutex> lock(h->flat_mutex);
+        for (const FlatCall &c : h->flat_calls)
+            if (c.n == n && c.h == hin && c.w == win && c.stride == stride && c.layout == layout) {
+                const auto &k = kShapes[c.index];
+                s = FlatShape{c.index, k[0], k[1], k[2], k[3], k[4], k[5], c.r, c.plane, c.lds};
+                return true;
+            }
+    }
+    if (!choose_flat(h, n, hin, win, stride, layout, s)) return false;
+    if (g_force_shape.load() >= 0) return true;                                // (pinned meanwhile: not the call's own shape)
+    const std::lock_guard<std::mutex> lock(h->flat_mutex);
+    h->flat_calls[h->flat_next++ % 4] = FlatCall{n, hin, win, stride, layout, s.index, s.r, s.plane, s.lds};
+    return true;
+}
+
 bool launch_conv_flat(const pconv_handle *h, const void *x, void *y, const float *bias, int n, int hin, int win,
                       int stride, int layout, int relu, void *stream, int &rc)
 {
     FlatShape best;
-    if (!choose_flat(h, n, hin, win, stride, layout, best)) return false;
+    if (!flat_shape(h, n, hin, win, stride, layout, best)) return false;
     FlatArgs a;
     a.x = static_cast<const uint16_t *>(x); a.y = static_cast<uint16_t *>(y); a.bias = bias;
     a.wd = h->d_wdense; a.nz = h->d_wnz;
