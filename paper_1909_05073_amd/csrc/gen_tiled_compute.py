@@ -64,7 +64,7 @@ QUAD_BYTES = 64 * 16             # one 16-byte quad of every lane
 CHAN_BYTES = 9 * QUAD_BYTES      # one staged channel: 64 patches x 36 floats
 
 
-def fetch(lines, uid):
+def fetch(lines, uid, sub2=False):
     """Fetch record s84 and go to its body: weights from LDS, record word from lane s84, the patch
     reload in line when the record starts a new channel, then one computed jump."""
     lines += [
@@ -87,7 +87,8 @@ def fetch(lines, uid):
         "s_mul_i32 s90, s90, %d" % CHAN_BYTES,
         "v_add_u32 v22, s90, %[va]",
     ]
-    for k in range(9):
+    # (outputs at even rows and columns read rows 0..4 and the left halo column: not quads 5 and 8)
+    for k in (0, 1, 2, 3, 4, 6, 7) if sub2 else range(9):
         b = INP + 4 * k
         lines.append("ds_read_b128 v[%d:%d], v22 offset:%d" % (b, b + 3, k * QUAD_BYTES))
     lines += [
@@ -109,7 +110,9 @@ def in_reg(row, col):
     return INP + 4 * row + col - 1
 
 
-def generate(words_in_scalars=False):
+def generate(words_in_scalars=False, sub2=False):
+    """The record loop.  sub2: of a patch only the outputs at even rows and columns (stride 2), a quarter of
+    the FMAs."""
     L = []
     L += [
         "s_getpc_b64 s[92:93]",
@@ -128,7 +131,7 @@ def generate(words_in_scalars=False):
         # chunk, the counters that other waves wait for) at the highest: see the end.
         "s_setprio 0",
     ]
-    fetch(L, "first")
+    fetch(L, "first", sub2)
     L.append(".p2align %d" % STRIDE_LOG2)
     L.append("TABLE_%=:")
     for slot in range(SLOTS):
@@ -139,13 +142,13 @@ def generate(words_in_scalars=False):
                 if not (mask >> t) & 1:
                     continue
                 r, c = divmod(t, 3)
-                for i in range(4):
-                    for k in range(4):
+                for i in range(0, 4, 2 if sub2 else 1):
+                    for k in range(0, 4, 2 if sub2 else 1):
                         L.append("v_fmac_f32 v%d, v%d, v%d" % (ACC + 16 * slot + 4 * i + k, WREG + j,
                                                                in_reg(i + r, k + c)))
                 j += 1
             L.append("s_add_u32 s84, s84, 1")
-            fetch(L, "%d_%d" % (slot, ci))
+            fetch(L, "%d_%d" % (slot, ci), sub2)
             L.append(".p2align %d" % STRIDE_LOG2)
     # the body of the end-of-list record: the loop is over (the weights fetched for it are not used)
     L.append("s_waitcnt lgkmcnt(0)")
@@ -222,6 +225,7 @@ def main():
     out = sys.argv[1]
     write_inc(out, generate())
     write_inc(os.path.join(os.path.dirname(out), "pconv_tiled_compute_scalar.inc"), generate(True))
+    write_inc(os.path.join(os.path.dirname(out), "pconv_tiled_compute_sub2.inc"), generate(sub2=True))
     write_inc(os.path.join(os.path.dirname(out), "pconv_tiled_patch_shifted.inc"), generate_patch_shifted())
     write_inc(os.path.join(os.path.dirname(out), "pconv_tiled_takeover.inc"), generate_takeover())
     write_code_header(os.path.join(os.path.dirname(out), "pconv_tiled_code_masks.inc"))

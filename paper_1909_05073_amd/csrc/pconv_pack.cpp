@@ -259,33 +259,38 @@ void build_tiled_stream(const Canonical &cn, const uint16_t *table, int np, int 
     // Waves on their own: the visits of a workgroup's filters (channels with a record) in order, and where each
     // wave's begin: consecutive visits whose costs (a visit loads the neighbourhood, a record is 64 FMAs and
     // its dispatch: about 100 and 60 cycles of a compute unit) add up to about the same.
-    out.lone_visits.clear();
+    out.lone_visits.resize(size_t(nb) * c_in * 3 * 2);
     out.lone_bounds.assign(size_t(nb) * 3 * (kLoneWaves + 1), 0);
+    uint32_t *next = out.lone_visits.data();
     for (int b = 0; b < nb; ++b)
         for (int form = 0; form < 3; ++form) {       // all slots, slots 0 and 1, slots 2 and 3
             const uint32_t *row = &out.chan_ptr[size_t(b) * out.row_len], *mid = &out.chan_mid[size_t(b) * out.row_len];
-            const size_t begin = out.lone_visits.size() / 2;
+            const uint32_t *from = form == 2 ? mid : row, *to = form == 1 ? mid : row + 1;
+            const uint32_t *begin = next;
             int64_t total = 0;
             for (int c = 0; c < c_in; ++c) {
-                const uint32_t from = form == 2 ? mid[c] : row[c], to = form == 1 ? mid[c] : row[c + 1];
-                if (to == from) continue;
-                out.lone_visits.push_back(from);
-                out.lone_visits.push_back(uint32_t(c) | (to - from) << 16);
-                total += 5 + 3 * int64_t(to - from);
+                const uint32_t records = to[c] - from[c];
+                next[0] = from[c];
+                next[1] = uint32_t(c) | records << 16;
+                next += records ? 2 : 0;
+                total += records ? 5 + 3 * records : 0;
             }
-            const size_t end = out.lone_visits.size() / 2;
             uint32_t *bounds = &out.lone_bounds[(size_t(b) * 3 + form) * (kLoneWaves + 1)];
-            size_t v = begin;
+            const int parts = int(std::min<ptrdiff_t>(kLoneWaves, (next - begin) / 2));
+            const uint32_t *v = begin;
             int64_t before = 0;
-            auto cost = [&]() { return 5 + 3 * int64_t(out.lone_visits[2 * v + 1] >> 16); };
-            const int parts = int(std::min<size_t>(kLoneWaves, end - begin));
-            for (int w = 0; w < kLoneWaves; ++w) {
+            for (int w = 0; w <= kLoneWaves; ++w) {
                 // up to the visit that ends nearest to w parts of the total
-                while (v < end && (w >= parts || (2 * before + cost()) * parts <= 2 * total * w)) { before += cost(); ++v; }
-                bounds[w] = uint32_t(v);
+                const int64_t limit = w < parts ? 2 * total * w / parts : 2 * total;
+                for (; v < next; v += 2) {
+                    const int64_t cost = 5 + 3 * int64_t(v[1] >> 16);
+                    if (2 * before + cost > limit) break;
+                    before += cost;
+                }
+                bounds[w] = uint32_t((v - out.lone_visits.data()) / 2);
             }
-            bounds[kLoneWaves] = uint32_t(end);
         }
+    out.lone_visits.resize(size_t(next - out.lone_visits.data()));
     for (int j = 0; j < 4; ++j) out.lone_visits.push_back(0u);                // (read by waves without a visit)
     // padding: the kernel asks for the words of records k+1 and k+2 while it executes record k
     for (int j = 0; j < 3; ++j) out.meta.push_back(0u);

@@ -149,7 +149,13 @@ __device__ __forceinline__ size_t act_at(int n, int c, int y, int x, int C, int 
 //
 // VEC: fp32 NCHW tensors at least 4 wide move the four centre columns of a patch row (and the four
 // outputs of a row) with one 128-bit access; the inputs go from global memory straight to LDS.
-template <typename T, int LAYOUT, bool VEC, int NW, int CH, bool SPLIT, bool PRIV = false>
+//
+// SUB2: stride 2 with all patches starting at even columns (an even width): the record loop forms only the
+// outputs that are stored, 16 FMAs a record instead of 64, and reads seven quads of a neighbourhood instead of
+// nine.  What is left is the staging of every chunk, which a quarter of the FMAs no longer covers (128 channels
+// @56, 16 images: 62.3 -> 55 us; the next record's weights asked for ahead of the FMAs change nothing, nor do
+// two smaller workgroups per compute unit, 77).
+template <typename T, int LAYOUT, bool VEC, int NW, int CH, bool SPLIT, bool PRIV = false, bool SUB2 = false>
 __global__ void __launch_bounds__(NW * 64, 4)   // 4 waves per SIMD: at most 128 VGPRs
 conv_tiled_kernel(const TiledArgs a)
 {
@@ -517,16 +523,24 @@ conv_tiled_kernel(const TiledArgs a)
                 // lane j = record j of the batch; the lanes behind the last record end the list
                 const uint32_t rm = uint32_t(fresh_lane()) < nb ? rec_m : kMetaEndOfList;
                 const uint32_t koff = __builtin_amdgcn_readfirstlane((k0 + base) * 4u);
-                asm volatile(
+#define PCONV_RECORD_LOOP_OPERANDS \
+                    : "+{v[64:79]}"(acc[0]), "+{v[80:95]}"(acc[1]), "+{v[96:111]}"(acc[2]), "+{v[112:127]}"(acc[3]) \
+                    : [recm] "v"(rm), [va] "v"(lds_base + buf_bytes + uint32_t(fresh_lane()) * 16u), \
+                      [wa] "s"(wa), [mp] "s"(a.meta), [koff] "s"(koff), [nb] "s"(nb), [chmask] "n"(CH - 1) \
+                    : "v22", "v23", "v24", "v25", "v26", "v27", "v28", "v29", "v30", "v31", "v32", "v33", \
+                      "v34", "v35", "v36", "v37", "v38", "v39", "v40", "v41", "v42", "v43", "v44", "v45", \
+                      "v46", "v47", "v48", "v49", "v50", "v51", "v52", "v53", "v54", "v55", "v56", "v57", \
+                      "v58", "v59", "v60", "v61", "v62", "v63", \
+                      "s84", "s85", "s86", "s90", "s91", "s92", "s93", "s94", "s95", "scc"
+                if constexpr (SUB2)
+                    asm volatile(
+#include "pconv_tiled_compute_sub2.inc"
+                        PCONV_RECORD_LOOP_OPERANDS);
+                else
+                    asm volatile(
 #include "pconv_tiled_compute.inc"
-                    : "+{v[64:79]}"(acc[0]), "+{v[80:95]}"(acc[1]), "+{v[96:111]}"(acc[2]), "+{v[112:127]}"(acc[3])
-                    : [recm] "v"(rm), [va] "v"(lds_base + buf_bytes + uint32_t(fresh_lane()) * 16u),
-                      [wa] "s"(wa), [mp] "s"(a.meta), [koff] "s"(koff), [nb] "s"(nb), [chmask] "n"(CH - 1)
-                    : "v22", "v23", "v24", "v25", "v26", "v27", "v28", "v29", "v30", "v31", "v32", "v33",
-                      "v34", "v35", "v36", "v37", "v38", "v39", "v40", "v41", "v42", "v43", "v44", "v45",
-                      "v46", "v47", "v48", "v49", "v50", "v51", "v52", "v53", "v54", "v55", "v56", "v57",
-                      "v58", "v59", "v60", "v61", "v62", "v63",
-                      "s84", "s85", "s86", "s90", "s91", "s92", "s93", "s94", "s95", "scc");
+                        PCONV_RECORD_LOOP_OPERANDS);
+#undef PCONV_RECORD_LOOP_OPERANDS
                 // No "memory" clobber on purpose: it would make the compiler wait for the
                 // global->LDS loads of the next chunk, which may be in flight here and go to the
                 // other buffer.  What the loop reads was published before (barrier / counters), or
@@ -1000,7 +1014,7 @@ conv_tiled_kernel(const TiledArgs a)
     }
 }
 
-template <typename T, int LAYOUT, bool VEC, int NW, int CH, bool SPLIT, bool PRIV = false>
+template <typename T, int LAYOUT, bool VEC, int NW, int CH, bool SPLIT, bool PRIV = false, bool SUB2 = false>
 hipError_t launch_shape(const TiledArgs &a, int64_t wgs, hipStream_t st, int dev)
 {
     // The kernel needs more dynamic LDS than the default limit: raised once per device (the flag is
@@ -1008,12 +1022,12 @@ hipError_t launch_shape(const TiledArgs &a, int64_t wgs, hipStream_t st, int dev
     static std::atomic<bool> attr_done[64];
     constexpr size_t lds_bytes = Shape<NW, CH>::LDS_BYTES;
     if (dev < 0 || dev >= 64 || !attr_done[dev].load(std::memory_order_acquire)) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_tiled_kernel<T, LAYOUT, VEC, NW, CH, SPLIT, PRIV>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_tiled_kernel<T, LAYOUT, VEC, NW, CH, SPLIT, PRIV, SUB2>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, int(lds_bytes));
         if (e != hipSuccess) return e;
         if (dev >= 0 && dev < 64) attr_done[dev].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((conv_tiled_kernel<T, LAYOUT, VEC, NW, CH, SPLIT, PRIV>), dim3(unsigned(wgs)), dim3(NW * 64), lds_bytes, st, a);
+    hipLaunchKernelGGL((conv_tiled_kernel<T, LAYOUT, VEC, NW, CH, SPLIT, PRIV, SUB2>), dim3(unsigned(wgs)), dim3(NW * 64), lds_bytes, st, a);
     return hipGetLastError();
 }
 
@@ -1025,6 +1039,8 @@ hipError_t launch_any(const TiledArgs &a, int64_t wgs, hipStream_t st, bool vec,
             return dtype == PCONV_F32 ? launch_shape<float, PCONV_NHWC, false, NW, CH, false, true>(a, wgs, st, dev)
                                       : launch_shape<bf16_t, PCONV_NHWC, false, NW, CH, false, true>(a, wgs, st, dev);
         }
+    if constexpr (NW == 16)
+        if (vec && a.sub2 && a.w % 2 == 0) return launch_shape<float, PCONV_NCHW, true, NW, CH, false, false, true>(a, wgs, st, dev);
     if (vec)
         return a.split_units ? launch_shape<float, PCONV_NCHW, true, NW, CH, true>(a, wgs, st, dev)
                              : launch_shape<float, PCONV_NCHW, true, NW, CH, false>(a, wgs, st, dev);

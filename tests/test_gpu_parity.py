@@ -599,6 +599,20 @@ def test_waves_on_their_own_tiles(shape, ks):
         hd.free()
 
 
+@pytest.mark.parametrize("ks", [0, 1, 2])
+@pytest.mark.parametrize("shape", [(1, 9, 6, 12, 12), (2, 20, 70, 13, 18), (3, 8, 40, 14, 14), (1, 33, 5, 5, 262), (2, 12, 17, 12, 15)])
+def test_stride2_record_loop(shape, ks):
+    """Stride 2 in whole units: the record loop that forms only the stored outputs (even widths, both ends of a
+    row, rows below the image), and an odd width, which keeps the full one."""
+    n, ci, co, h, w = shape
+    for dense in (False, True):
+        spec = LayerSpec("s2", n, ci, co, h, w, stride=2, keep_div=1.0 if dense else 2.0, num_patterns=1 if dense else 12,
+                         pattern_dist="dense" if dense else "uniform", count_dist="all" if dense else "pm30")
+        L = make_layer(spec, 7800 + ci); x = make_input(spec, 7800 + ci)
+        P.pconv_debug_set_tiling(16, ks, 0)
+        check_full(spec, L, x, "f32", "nchw", 2, relu=bool(n & 1), policy=2, what=f"s2{shape}_{ks}")
+
+
 FLAT_PINNED_WIDE = [  # enough blocks of channels and filters for the launch shapes that split both
     (2, 272, 97, 9, 11, 1), (3, 264, 260, 14, 14, 2), (1, 40, 264, 13, 30, 1), (40, 16, 30, 5, 7, 1),
 ]
