@@ -93,8 +93,9 @@ int pconv_project(const float *w_dense, const uint16_t *table, int num_patterns,
  * pconv_conv2d - the sparse convolution itself (Eq. (1) over the packed weights; the
  * "load redundancy elimination" stage of the paper: only inputs under kept taps of kept
  * kernels are touched).  Asynchronous on hip_stream; allocates nothing.  The packed weights in
- * the handle are only read.  A call does write two small things that belong to the handle: it
- * takes a ticket from a call counter, and, when the layer has so few tiles that workgroups share
+ * the handle are only read.  A call does write small things that belong to the handle: the launch
+ * shapes of its last kinds of calls are kept (under a lock); it takes a ticket from a call counter;
+ * and, when the layer has so few tiles that workgroups share
  * them, its workgroups signal each other through one of 64 rows of hand-over words in device
  * memory (row = ticket mod 64).  Calls on one handle may therefore run concurrently on different
  * streams, as long as no more than 64 such calls are in flight at once.  Under HIP graph capture
