@@ -344,6 +344,8 @@ def conv2d_pool2x2(handle: Handle, x, bias=None, relu: bool = False, out=None):
 
 def maxpool2x2(x, layout="nchw"):
     import torch
+    if not x.is_cuda:                                # (its address would be a host address to the kernel)
+        raise ValueError("x must be a CUDA tensor")
     lay = _LAYOUT[layout]
     if lay == NCHW:
         n, c, h, w = x.shape

@@ -199,3 +199,19 @@ def test_plan_reports_the_pinned_form_and_rejects_bad_calls():
             P.pconv_debug_plan(h, 1, 28, 28, **kw)
         assert e.value.status == status
     h.free()
+
+
+@pytest.mark.parametrize("call", ["conv2d", "conv2d_pool2x2", "maxpool2x2"])
+def test_torch_calls_refuse_host_tensors(call, monkeypatch):
+    """A tensor in host memory is refused with ValueError before the library or a stream is asked for."""
+    import torch
+
+    def reached(*args):
+        raise AssertionError("a host address went to the library")
+    for name in ("pconv_conv2d", "pconv_conv2d_pool2x2", "pconv_maxpool2x2", "_stream"):
+        monkeypatch.setattr(P, name, reached)
+    monkeypatch.setattr(P, "_lib", type("NoCalls", (), {"pconv_conv2d": staticmethod(reached)})())
+    x = torch.zeros(1, 4, 8, 8)
+    handle = P.Handle(0, 4, 4, P.F32)
+    with pytest.raises(ValueError):
+        P.maxpool2x2(x) if call == "maxpool2x2" else getattr(P, call)(handle, x)
