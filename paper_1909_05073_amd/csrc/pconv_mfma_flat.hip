@@ -48,6 +48,7 @@
 #include <type_traits>
 
 #include "pconv_fast_div.h"
+#include "pconv_flat_loads.h"
 #include "pconv_internal.h"
 
 namespace pconv {
@@ -163,27 +164,23 @@ conv_flat_kernel(const FlatArgs a)
         dst_step[i] = 8 - (wpos & 7);
     }
     // Pixels on their way to LDS.  ODD: where the planes of channels have an odd number of pixels, half of the
-    // items are not aligned to dwords, and such a load costs four times an aligned one: the five dwords
-    // around an item are loaded instead, the fifth into `fifth` (512@7: 11.4 -> 10.1 us with one image,
-    // 18.6 -> 17.6 with 32).
+    // items are not aligned to dwords, and such a load costs four times an aligned one: the dwords around an
+    // item are loaded instead, the fifth, if there is one, into `fifth` (512@7: 11.4 -> 10.1 us with one
+    // image, 18.6 -> 17.6 with 32).
     u32x4 raw[R][8];
     uint32_t fifth[R][8];
-    // A channel beyond c_in has an offset beyond the tensor (bit 31 set: tensors are smaller): zeros.
+    // (a channel beyond c_in is read as zeros: see flat_load)
     auto load_rows = [&](int g, u32x4 (&raw)[R][8], uint32_t (&fifth)[R][8], int j0, int j1) {          // channels (NHWC: pixels) j0 ... j1 - 1 of the items
-        const int c0 = g * (16 * KB), left = a.c_in - 1 - (c0 + g_item * 8);    // (its sign: the item's first channel is beyond)
+        const int c0 = g * (16 * KB);
 #pragma unroll
         for (int j = j0; j < j1; ++j) {
-            const uint32_t beyond = uint32_t(LAYOUT == PCONV_NCHW ? left - j : left) & 0x80000000u;   // (NHWC: c_in is a multiple of 8)
-            const uint32_t uniform = LAYOUT == PCONV_NCHW ? uint32_t(c0 + j) * plane_step : uint32_t(c0 + j * a.c_in) * 2u;
 #pragma unroll
             for (int i = 0; i < R; ++i) {
+                const FlatLoad at = flat_load<LAYOUT == PCONV_NCHW, ODD>(src[i], g_item, j, c0, a.c_in, plane_step);
+                raw[i][j] = load16(xbuf, at.lane, at.uniform);
                 if (ODD) {
-                    // (uniform + 2 * (j & 1) is a multiple of four: the blocks of channels begin at even ones)
-                    const uint32_t lane_at = ((src[i] + 2u * (j & 1)) & ~3u) | beyond, at = uniform - 2u * (j & 1);
-                    raw[i][j] = load16(xbuf, lane_at, at);
-                    fifth[i][j] = __builtin_amdgcn_raw_buffer_load_b32(xbuf, int(lane_at), int(at + 16u), 0);
-                } else {
-                    raw[i][j] = load16(xbuf, src[i] | beyond, uniform);
+                    const FlatLoad behind = flat_load_fifth(at, src[i], j);
+                    fifth[i][j] = __builtin_amdgcn_raw_buffer_load_b32(xbuf, int(behind.lane), int(behind.uniform), 0);
                 }
             }
         }
