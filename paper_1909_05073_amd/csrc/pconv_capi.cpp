@@ -149,15 +149,14 @@ static int pack_impl(const float *w_dense, const uint8_t *pattern_id, const uint
             rc = upload(h->d_vals, reinterpret_cast<const float *>(h->canon.vals_bits.data()),
                         h->canon.vals_bits.size(), h->device_bytes);
         if (rc == PCONV_OK) rc = upload(h->d_slot_filter, h->tiled.slot_filter.data(), h->tiled.slot_filter.size(), h->device_bytes);
-        if (rc == PCONV_OK) {
-            std::vector<uint32_t> lone = h->tiled.lone_bounds;                 // (one allocation for both)
-            lone.insert(lone.end(), h->tiled.lone_visits.begin(), h->tiled.lone_visits.end());
-            rc = upload(h->d_lone_bounds, lone.data(), lone.size(), h->device_bytes);
-            if (rc == PCONV_OK) h->d_lone_visits = h->d_lone_bounds + h->tiled.lone_bounds.size();
-        }
         if (rc == PCONV_OK) rc = upload(h->d_chan_ptr, h->tiled.chan_ptr.data(), h->tiled.chan_ptr.size(), h->device_bytes);
         if (rc == PCONV_OK && h->tiled.meta.size() < kTiledMaxRecords)
             rc = upload(h->d_meta, h->tiled.meta.data(), h->tiled.meta.size(), h->device_bytes);
+        if (rc == PCONV_OK && weight_dtype == PCONV_F32 && h->d_meta) {        // (what pconv_lone.hip serves)
+            const std::vector<uint32_t> lone = build_lone_lists(h->tiled, c_in);
+            rc = upload(h->d_lone_bounds, lone.data(), lone.size(), h->device_bytes);
+            if (rc == PCONV_OK) h->d_lone_visits = h->d_lone_bounds + lone_bounds_words(h->tiled);
+        }
         if (rc == PCONV_OK) rc = upload(h->d_w4, h->tiled.w4.data(), h->tiled.w4.size(), h->device_bytes);
         if (rc == PCONV_OK && weight_dtype == PCONV_BF16) {
             std::vector<uint16_t> wd; std::vector<uint32_t> nz;

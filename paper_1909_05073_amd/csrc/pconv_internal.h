@@ -14,9 +14,9 @@
 namespace pconv {
 
 constexpr int kFlagSlots = 64, kFlagWords = 1024;
+constexpr int kLoneWaves = 16;         // waves of a workgroup of pconv_lone.hip
 // The register-tiled kernel keeps a record index in 24 bits: a longer stream stays off the device,
 // and the layer runs on the other kernels.
-constexpr int kLoneWaves = 16;         // waves of a workgroup of pconv_lone.hip
 constexpr size_t kTiledMaxRecords = size_t(1) << 24;
 
 // Thread-local message for pconv_last_error().
@@ -44,10 +44,6 @@ struct TiledStream {
     int row_len = 0;                    // entries per chan_ptr row: round_up(C, kTileCH) + 1
     std::vector<int32_t>  slot_filter;  // [num_blocks * kTileFB] original filter index or -1
     std::vector<uint32_t> chan_ptr;     // [num_blocks][row_len]
-    std::vector<uint32_t> chan_mid;     // [num_blocks][row_len] first record of slots 2 and 3 of the channel
-    // pconv_lone.hip: {first record, channel | records << 16} of every visited channel, and the first visit of
-    // each wave, [num_blocks][all slots, slots 0 and 1, slots 2 and 3][kLoneWaves + 1]
-    std::vector<uint32_t> lone_visits, lone_bounds;
     int64_t visits = 0;                 // (block, channel) pairs with a record
     int64_t half_visits = 0;            // (block, half of its slots, channel) triples with a record
     std::vector<uint32_t> meta;         // [R+1] record words (see pconv_tiled_codes.h), one pad
@@ -74,7 +70,7 @@ struct pconv_handle {
     // device copies (register-tiled kernel)
     int32_t  *d_slot_filter = nullptr;
     uint32_t *d_chan_ptr = nullptr;
-    uint32_t *d_lone_bounds = nullptr, *d_lone_visits = nullptr;              // (one allocation, bounds first)
+    uint32_t *d_lone_bounds = nullptr, *d_lone_visits = nullptr;              // (one allocation; fp32 handles only)
     uint32_t *d_meta = nullptr;
     float    *d_w4 = nullptr;
     // device copies (matrix-core kernels, bf16 handles only): the masked weights as dense
@@ -113,6 +109,11 @@ int project_weights(const float *w, const uint16_t *table, int np, int c_out, in
 
 void build_tiled_stream(const Canonical &cn, const uint16_t *table, int np, int c_out, int c_in,
                         TiledStream &out);
+
+// The lists that pconv_lone.hip walks: the first visit of each wave, [num_blocks][all slots, slots 0 and 1, slots 2
+// and 3][kLoneWaves + 1], and behind them {first record, channel | records << 16} of every visited channel.
+inline size_t lone_bounds_words(const TiledStream &ts) { return size_t(ts.num_blocks) * 3 * (kLoneWaves + 1); }
+std::vector<uint32_t> build_lone_lists(const TiledStream &ts, int c_in);
 
 // Kernel launchers (pconv_kernels.hip, pconv_tiled.hip).  All return a pconv_status.
 int launch_conv_generic(const pconv_handle *h, const void *x, void *y, const float *bias, int n,

@@ -218,7 +218,6 @@ void build_tiled_stream(const Canonical &cn, const uint16_t *table, int np, int 
     }
 
     out.chan_ptr.assign(size_t(nb) * out.row_len, 0);
-    out.chan_mid.assign(size_t(nb) * out.row_len, 0);
     out.meta.clear();
     out.w4.clear();
     std::vector<std::vector<int32_t>> by_slot(FB, std::vector<int32_t>(size_t(c_in), -1));
@@ -233,8 +232,9 @@ void build_tiled_stream(const Canonical &cn, const uint16_t *table, int np, int 
         for (int c = 0; c < c_in; ++c) {
             row[c] = uint32_t(out.meta.size());
             bool first = true;
+            size_t mid = 0;                                              // first record of slots 2 and 3
             for (int s = 0; s < FB; ++s) {
-                if (s == FB / 2) out.chan_mid[size_t(b) * out.row_len + c] = uint32_t(out.meta.size());
+                if (s == FB / 2) mid = out.meta.size();
                 const int32_t k = by_slot[s][c];
                 if (k < 0) continue;
                 for (const Piece &pc : pieces[cn.pat[k]]) {
@@ -249,33 +249,44 @@ void build_tiled_stream(const Canonical &cn, const uint16_t *table, int np, int 
                     }
                 }
             }
+            out.half_visits += (mid > row[c]) + (out.meta.size() > mid);
         }
-        for (int c = c_in; c <= cpad; ++c) row[c] = out.chan_mid[size_t(b) * out.row_len + c] = uint32_t(out.meta.size());
-        for (int c = 0; c < c_in; ++c) {
-            const uint32_t mid = out.chan_mid[size_t(b) * out.row_len + c];
-            out.half_visits += (mid > row[c]) + (row[c + 1] > mid);
-        }
+        for (int c = c_in; c <= cpad; ++c) row[c] = uint32_t(out.meta.size());
     }
-    // Waves on their own: the visits of a workgroup's filters (channels with a record) in order, and where each
-    // wave's begin: consecutive visits whose costs (a visit loads the neighbourhood, a record is 64 FMAs and
-    // its dispatch: about 100 and 60 cycles of a compute unit) add up to about the same.
-    out.lone_visits.resize(size_t(nb) * c_in * 3 * 2);
-    out.lone_bounds.assign(size_t(nb) * 3 * (kLoneWaves + 1), 0);
-    uint32_t *next = out.lone_visits.data();
-    for (int b = 0; b < nb; ++b)
+    // padding: the kernel asks for the words of records k+1 and k+2 while it executes record k
+    for (int j = 0; j < 3; ++j) out.meta.push_back(0u);
+    for (int j = 0; j < 4; ++j) out.w4.push_back(0.0f);
+}
+
+// ---- lists of pconv_lone.hip ------------------------------------------------------------
+//
+// The visits of a workgroup's filters (channels with a record) in order, and where each wave's begin:
+// consecutive visits whose costs (a visit loads the neighbourhood, a record is 64 FMAs and its dispatch:
+// about 100 and 60 cycles of a compute unit) add up to about the same.
+std::vector<uint32_t> build_lone_lists(const TiledStream &ts, int c_in)
+{
+    std::vector<uint32_t> out(lone_bounds_words(ts) + size_t(ts.visits + ts.half_visits) * 2 + 4, 0u);   // (the last two: read by waves without a visit)
+    uint32_t *const visits = out.data() + lone_bounds_words(ts), *next = visits;
+    constexpr uint32_t kSlotsUpper = uint32_t(kTileFB / 2 * kNumCodes) << kMetaCaseShift;                // words of slots 2 and 3 are not below
+    for (int b = 0; b < ts.num_blocks; ++b) {
+        const uint32_t *row = &ts.chan_ptr[size_t(b) * ts.row_len];
         for (int form = 0; form < 3; ++form) {       // all slots, slots 0 and 1, slots 2 and 3
-            const uint32_t *row = &out.chan_ptr[size_t(b) * out.row_len], *mid = &out.chan_mid[size_t(b) * out.row_len];
-            const uint32_t *from = form == 2 ? mid : row, *to = form == 1 ? mid : row + 1;
             const uint32_t *begin = next;
             int64_t total = 0;
             for (int c = 0; c < c_in; ++c) {
-                const uint32_t records = to[c] - from[c];
-                next[0] = from[c];
-                next[1] = uint32_t(c) | records << 16;
-                next += records ? 2 : 0;
-                total += records ? 5 + 3 * records : 0;
+                uint32_t from = row[c], to = row[c + 1];
+                if (form > 0) {
+                    uint32_t mid = from;
+                    while (mid < to && ts.meta[mid] < kSlotsUpper) ++mid;
+                    (form == 1 ? to : from) = mid;
+                }
+                if (from == to) continue;
+                next[0] = from;
+                next[1] = uint32_t(c) | (to - from) << 16;
+                next += 2;
+                total += 5 + 3 * int64_t(to - from);
             }
-            uint32_t *bounds = &out.lone_bounds[(size_t(b) * 3 + form) * (kLoneWaves + 1)];
+            uint32_t *bounds = &out[(size_t(b) * 3 + form) * (kLoneWaves + 1)];
             const int parts = int(std::min<ptrdiff_t>(kLoneWaves, (next - begin) / 2));
             const uint32_t *v = begin;
             int64_t before = 0;
@@ -287,14 +298,11 @@ void build_tiled_stream(const Canonical &cn, const uint16_t *table, int np, int 
                     if (2 * before + cost > limit) break;
                     before += cost;
                 }
-                bounds[w] = uint32_t((v - out.lone_visits.data()) / 2);
+                bounds[w] = uint32_t((v - visits) / 2);
             }
         }
-    out.lone_visits.resize(size_t(next - out.lone_visits.data()));
-    for (int j = 0; j < 4; ++j) out.lone_visits.push_back(0u);                // (read by waves without a visit)
-    // padding: the kernel asks for the words of records k+1 and k+2 while it executes record k
-    for (int j = 0; j < 3; ++j) out.meta.push_back(0u);
-    for (int j = 0; j < 4; ++j) out.w4.push_back(0.0f);
+    }
+    return out;
 }
 
 // ---- dense per-tap matrices of the matrix-core kernel -----------------------------------

@@ -726,6 +726,31 @@ def test_device_pack_bit_exact_and_unpack_roundtrip():
         h.free()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_handle_holds_only_what_its_kernels_read(dtype):
+    """Device memory of a handle, array by array: the lists of the fp32 kernel for waves on their own are on fp32
+    handles only, the dense matrices of the matrix-core kernels on bf16 handles only."""
+    for f, c in [(70, 45), (3, 200), (64, 64)]:
+        spec = LayerSpec("bytes", 1, c, f, 8, 8, keep_div=3.0, num_patterns=8, count_dist="bernoulli")
+        L = make_layer(spec, 9100 + f)
+        h = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], dtype)
+        slots, records = P.pconv_debug_export_blocks(h)
+        info = h.info()
+        h.free()
+        nb, r = len(slots), int(records.sum())
+        conn = np.concatenate([L["conn"].astype(bool), np.zeros((1, c), bool)])[slots]        # [block][slot][channel]; -1: nothing
+        visits = int(conn.any(1).sum()) + int(conn[:, :2].any(1).sum()) + int(conn[:, 2:].any(1).sum())
+        want = 4 * f + 4 * (f + 1) + 8 * info.kept_kernels + 4 * info.nnz                      # canonical arrays
+        want += 16 * nb + 4 * nb * (8 * records.shape[1] + 1) + 4 * (r + 3) + 16 * (r + 1)      # record stream
+        want += 64 * 1024 * 4                                                                  # hand-over words
+        if dtype == "f32":
+            want += 4 * (nb * 3 * 17 + 2 * visits + 4)
+        else:
+            c32, f32 = -(-c // 32), -(-f // 32)
+            want += 2 * 9 * (2 * c32 + 1) * 32 * f32 * 16 + 4 * c32 * f32
+        assert info.device_bytes == want
+
+
 def test_run_to_run_bit_identical_and_stream():
     import torch
     spec = config_layers(2)[0]
