@@ -1182,12 +1182,12 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
         if (can_split && p.nw == 16) {
             // Many units, but not a multiple of the number of compute units: whole units leave part of
             // the chip idle in the last round.  Dealing the chunks of all units evenly (every workgroup
-            // one contiguous share, over all workgroups as one set) costs each workgroup the time of about
-            // seven chunks (further start-ups, the partial sums through memory with a device-wide release
-            // and acquire); a last round with few units runs faster than a full one (measured: 0.87 of it
-            // at 53 % busy).  So it pays for few, long units (256 channels @56, 32 images, 392 units of 32
-            // chunks 262 -> 250 us, 512 @28, 200 units of 64 chunks, 260 -> 248; 128 -> 256 @56, 16 chunks, 142 -> 156).
-            constexpr double kShareOverhead = 7.0;
+            // one contiguous share, over all workgroups as one set) was measured to cost each workgroup
+            // the time of about ten chunks (further start-ups, the partial sums through memory with a
+            // device-wide release and acquire); a last round with few units runs faster than a full
+            // one (measured: 0.87 of it at 53 % busy).  So it pays for few, long units only (VGG
+            // conv9: 200 units of 64 chunks, -4 %).
+            constexpr double kShareOverhead = 10.0;
             const double full = double(whole_units / slots), rest = double(whole_units % slots) / slots;
             const double t_whole = n_chunks * (full + (rest > 0.0 ? 0.72 + 0.28 * rest : 0.0));
             const double t_share = double(whole_units) * n_chunks / slots + kShareOverhead;
