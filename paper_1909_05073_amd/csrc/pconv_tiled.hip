@@ -1182,11 +1182,14 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
         if (can_split && p.nw == 16) {
             // Many units, but not a multiple of the number of compute units: whole units leave part of
             // the chip idle in the last round.  Dealing the chunks of all units evenly (every workgroup
-            // one contiguous share, over all workgroups as one set) was measured to cost each workgroup
-            // the time of about ten chunks (further start-ups, the partial sums through memory with a
-            // device-wide release and acquire); a last round with few units runs faster than a full
-            // one (measured: 0.87 of it at 53 % busy).  So it pays for few, long units only (VGG
-            // conv9: 200 units of 64 chunks, -4 %).
+            // one contiguous share, over all workgroups as one set) costs each workgroup further start-ups
+            // and the partial sums through memory with a device-wide release and acquire, taken as ten
+            // chunks; a last round with few units runs faster than a full one (measured: 0.87 of it at
+            // 53 % busy).  So it pays for few, long units only (512 channels @28, 64 images, 392 units of 64
+            // chunks).  With seven chunks 40 layers whose form that changes took 1.13 times as long on
+            // average: 256 channels @56, 32 images 290 -> 269 us and 138 -> 394 @28, 55 images 234 -> 181, but
+            // 128 @112, 32 images 286 -> 331, and 256 -> 8 @82x112, 17 images 32 -> 80, whose second launch
+            // and waves on their own (below) sharing rules out.
             constexpr double kShareOverhead = 10.0;
             const double full = double(whole_units / slots), rest = double(whole_units % slots) / slots;
             const double t_whole = n_chunks * (full + (rest > 0.0 ? 0.72 + 0.28 * rest : 0.0));

@@ -181,6 +181,20 @@ def test_spin_limit_leaves_the_plan_alone(call):
     h.free()
 
 
+@pytest.mark.parametrize("call,keep,want", [((17, 256, 8, 82, 112), 8.0, (4, 0, 0)), ((28, 128, 8, 123, 80), 5.0, (4, 0, 0)),
+                                            ((32, 128, 128, 112, 112), 3.6, (0, 0, 8)), ((16, 96, 96, 92, 92), 3.6, (0, 0, 5)),
+                                            ((64, 512, 512, 28, 28), 3.6, (0, 2, 0))])
+def test_sharing_gives_way_to_faster_forms(call, keep, want):
+    """(ks_log2, split_units, tail_tiles): layers for which waves on their own or a second launch take a fraction
+    of the time that shared units take are not shared; a long layer with a half empty last round is."""
+    n, ci, co, hh, ww = call
+    L = make_layer(LayerSpec("plan", n, ci, co, hh, ww, keep_div=keep), 4300)
+    h = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "f32", host_only=True)
+    p = P.pconv_debug_plan(h, n, hh, ww)
+    h.free()
+    assert (p.ks_log2, p.split_units, p.tail_tiles) == want
+
+
 def test_plan_reports_the_pinned_form_and_rejects_bad_calls():
     L = make_layer(LayerSpec("plan", 1, 256, 64, 28, 28), 4200)
     h = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "f32", host_only=True)
