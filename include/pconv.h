@@ -257,8 +257,8 @@ int pconv_set_kernel_policy(int policy);
 int pconv_debug_set_tiling(int waves, int ks_log2, int split_units);
 
 /* pconv_debug_set_flat_shape - for tests: pins the launch shape of the matrix-core kernel over flat runs of
- * pixels, 0 to 12 (filter blocks and pixel blocks of a wave, pixel parts and channel parts of a
- * workgroup; a call that the shape cannot serve takes the kernel over tiles of images).  Values out of
+ * pixels, 0 to 24 (filter blocks and pixel blocks of a wave, blocks of channels of a step, pixel, channel and
+ * filter parts of a workgroup; a call that the shape cannot serve takes the kernel over tiles of images).  Values out of
  * range mean automatic.  Process-wide. */
 int pconv_debug_set_flat_shape(int index);
 
@@ -276,7 +276,9 @@ typedef struct {
     int32_t tail_tiles;    /* register-tiled kernel: tiles of the last round that a second launch computes */
     int32_t flat_shape;    /* matrix cores: launch shape of the kernel over flat runs of pixels, as in
                             * pconv_debug_set_flat_shape; -1: tiles of images (or another kernel)     */
-    int32_t reserved[2];
+    int32_t lone_patches;  /* register-tiled kernel, fp32 NCHW, waves on their own (for the second launch too):
+                            * patches of a tile; 0: not used                                          */
+    int32_t lone_cut;      /* 1: those tiles begin and end inside rows of patches, 0: whole rows      */
 } pconv_plan;
 
 int pconv_debug_plan(const pconv_handle *h, int n, int h_in, int w_in, int stride, pconv_layout layout,

@@ -37,7 +37,7 @@ class pconv_info(C.Structure):
 
 class pconv_plan(C.Structure):
     _fields_ = [("kernel", C.c_int32), ("waves", C.c_int32), ("ks_log2", C.c_int32), ("split_units", C.c_int32),
-                ("tail_tiles", C.c_int32), ("flat_shape", C.c_int32), ("reserved", C.c_int32 * 2)]
+                ("tail_tiles", C.c_int32), ("flat_shape", C.c_int32), ("lone_patches", C.c_int32), ("lone_cut", C.c_int32)]
 
 
 _lib = None

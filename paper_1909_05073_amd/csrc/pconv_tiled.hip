@@ -1272,6 +1272,13 @@ void describe_tiled_plan(const pconv_handle *h, int n, int hin, int win, int str
     out.waves = p.nw; out.ks_log2 = p.priv && p.halves ? 5 : p.ks_log2;
     out.split_units = p.split ? (p.one_set ? 2 : 1) : 0;
     out.tail_tiles = p.tail_tiles;
+    if (p.vec && (p.priv || p.tail_tiles > 0)) {
+        const int px = (win + 3) / 4;
+        const int64_t patches = int64_t(n) * ((hin + 3) / 4) * px, first = (patches + 63) / 64 * 64 - int64_t(p.tail_tiles) * 64;
+        const LoneTiles t = lone_tiles(patches, px, p.priv ? 0 : lone_base(first, px), int64_t(h->tiled.num_blocks) << (p.priv && p.halves ? 1 : 0),
+                                       h->cus > 0 ? h->cus : 256);
+        out.lone_patches = t.lanes; out.lone_cut = t.cut;
+    }
 }
 
 bool tiled_shares_units(const pconv_handle *h, int n, int hin, int win)

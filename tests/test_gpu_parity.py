@@ -231,8 +231,8 @@ def test_ragged_shapes_layouts_strides(policy, dtype, layout, stride):
 @pytest.mark.parametrize("waves,ks_log2", [(0, -1), (8, 0), (16, 1), (16, 2)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_stride2_through_the_tiled_kernel(waves, ks_log2, dtype):
-    """Stride 2 on the register-tiled kernel (full-resolution sums, every other output stored) in
-    every workgroup shape, odd and even sizes, several chunks and filter groups."""
+    """Stride 2 on the register-tiled kernel in every workgroup shape, odd and even sizes (even widths with sixteen
+    waves form the stored outputs only, the others all of them), several chunks and filter groups."""
     for j, (n, ci, co, h, w) in enumerate([(2, 37, 150, 14, 14), (1, 64, 64, 29, 31), (3, 19, 70, 9, 22), (1, 130, 33, 7, 7)]):
         spec = LayerSpec(f"s2_{j}", n, ci, co, h, w, stride=2, dtype=dtype)
         L = make_layer(spec, 3000 + j); x = make_input(spec, 3000 + j)
@@ -312,18 +312,25 @@ def test_waves_on_their_own(shape, ks_log2):
         check_full(spec, L, x, "f32", "nchw", stride, relu=bool(n & 1), use_bias=bool(co & 1), policy=2, what=f"lone{shape}")
 
 
-@pytest.mark.parametrize("ks_log2", [-1, 4, 5])
-@pytest.mark.parametrize("shape,form", [((8, 96, 92, 35, 35), "plain"), ((8, 256, 256, 27, 27), "plain"),
-                                        ((6, 80, 22, 50, 50), "pool"), ((6, 80, 22, 50, 50), "stride2")])
-def test_waves_on_their_own_add_in_one_order(shape, form, ks_log2):
-    """Widths no multiple of 4, tiles that end between the last two patches of a row (64 * k % px == px - 1):
-    the columns the two patches share are stored by two workgroups, so every tile has to add the
-    channels in the same order.  Equal images in one batch lie differently in their tiles: their
-    outputs, and those of repeated calls, agree bit for bit."""
+ORDER_CASES = [  # (shape, form, ks_log2, tiles cut rows)
+    *[(sh, form, ks, False) for ks in (-1, 4, 5)
+      for sh, form in [((8, 96, 92, 35, 35), "plain"), ((8, 256, 256, 27, 27), "plain"), ((6, 80, 22, 50, 50), "pool"), ((6, 80, 22, 50, 50), "stride2")]],
+    ((4, 24, 24, 42, 129), "plain", -1, True), ((2, 40, 16, 66, 129), "plain", -1, True), ((2, 24, 24, 95, 139), "plain", 4, True),
+    ((5, 24, 24, 33, 146), "pool", -1, True), ((2, 40, 32, 36, 138), "pool", -1, True), ((4, 24, 24, 42, 129), "stride2", -1, True),
+    ((8, 40, 16, 18, 139), "stride2", -1, True), ((5, 24, 16, 21, 274), "plain", -1, True), ((5, 24, 32, 11, 275), "plain", 5, True),
+]
+
+
+@pytest.mark.parametrize("shape,form,ks_log2,cut", ORDER_CASES)
+def test_waves_on_their_own_add_in_one_order(shape, form, ks_log2, cut):
+    """Widths no multiple of 4.  Where tiles cut rows of patches and one ends between the last two patches of a row, the
+    columns that the two share are stored by two workgroups, so every tile has to add the channels in the
+    same order.  Equal images in one batch lie differently in their tiles: their outputs, and those of
+    repeated calls, agree bit for bit."""
     import torch
     n, ci, co, h, w = shape
-    px, patches = (w + 3) // 4, n * ((h + 3) // 4) * ((w + 3) // 4)
-    assert any(64 * k % px == px - 1 for k in range(1, (patches + 63) // 64))
+    px = (w + 3) // 4
+    per_image = (h + 3) // 4 * px
     spec = LayerSpec("order", 1, ci, co, h, w)
     L = make_layer(spec, 5400 + w); x = make_input(spec, 5400 + w)
     hd = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "f32")
@@ -331,7 +338,11 @@ def test_waves_on_their_own_add_in_one_order(shape, form, ks_log2):
     P.pconv_debug_set_tiling(0 if ks_log2 < 0 else 16, ks_log2, -1)
     plan = P.pconv_debug_plan(hd, n, h, w, 2 if form == "stride2" else 1, fuse_pool=form == "pool")
     assert plan.ks_log2 >= 4 if ks_log2 < 0 else plan.ks_log2 == ks_log2
-    say(f"[case] order {shape} {form} ks={plan.ks_log2}")
+    assert plan.lone_cut == cut and w % 4 != 0
+    if cut:
+        assert plan.lone_patches == 64 and per_image % 64 != 0
+        assert any(64 * k % px == px - 1 for k in range(1, (n * per_image + 63) // 64))
+    say(f"[case] order {shape} {form} ks={plan.ks_log2} cut={cut}")
     call = {"plain": lambda: P.conv2d(hd, xd, b), "pool": lambda: P.conv2d_pool2x2(hd, xd, b),
             "stride2": lambda: P.conv2d(hd, xd, b, stride=2)}[form]
     ys = [call() for _ in range(6)]
@@ -341,13 +352,20 @@ def test_waves_on_their_own_add_in_one_order(shape, form, ks_log2):
     hd.free()
 
 
-@pytest.mark.parametrize("shape,parted", [((17, 64, 16, 126, 126, 1), False), ((17, 64, 16, 128, 124, 1), False),
-                                          ((17, 64, 16, 127, 126, 2), False), ((21, 64, 16, 112, 114, 1), True),
-                                          ((21, 64, 16, 112, 113, 2), True), ((21, 40, 16, 111, 115, 1), True)])
-def test_last_round_in_a_second_launch(shape, parted):
-    """Some units more than whole rounds over the compute units: the tiles of the last ones are computed
-    by a second launch, also where it begins with the last patch of a row, which overlaps one of the
-    first launch (parted)."""
+TAIL_CASES = [  # (shape with stride, where the second launch begins, its tiles cut rows)
+    ((17, 64, 16, 126, 126, 1), "row", 0), ((17, 64, 16, 128, 124, 1), "twice", 0), ((17, 64, 16, 127, 126, 2), "row", 0),
+    ((21, 64, 16, 112, 114, 1), "twice", 0), ((21, 64, 16, 112, 113, 2), "twice", 0), ((21, 40, 16, 111, 115, 1), "twice", 0),
+    ((17, 24, 16, 131, 133, 1), "twice", 1), ((17, 24, 16, 131, 133, 2), "twice", 1), ((17, 24, 16, 57, 276, 1), "inside", 1),
+    ((21, 24, 16, 42, 282, 1), "inside", 1), ((30, 24, 16, 20, 450, 1), "parted", 1), ((30, 24, 16, 19, 449, 2), "parted", 1),
+]
+
+
+@pytest.mark.parametrize("shape,begins,cut", TAIL_CASES)
+def test_last_round_in_a_second_launch(shape, begins, cut):
+    """Some units more than whole rounds over the compute units: the tiles of the last ones are computed by a second
+    launch.  It begins with a whole row of patches: where the first launch ends with one ("row"), or inside the
+    one that it ends in, whose first patches are then computed by both ("twice").  Rows of more than 64 patches
+    it begins inside ("inside"), also with the last patch, which overlaps one of the first launch ("parted")."""
     n, ci, co, h, w, stride = shape
     spec = LayerSpec("tail", n, ci, co, h, w, stride=stride)
     L = make_layer(spec, 5300 + w); x = make_input(spec, 5300 + w)
@@ -356,7 +374,8 @@ def test_last_round_in_a_second_launch(shape, parted):
     hd.free()
     px = (w + 3) // 4
     first = 64 * ((n * ((h + 3) // 4) * px + 63) // 64 - plan.tail_tiles)
-    assert plan.tail_tiles > 0 and parted == (w % 4 != 0 and first % px == px - 1)
+    want = ("row" if first % px == 0 else "twice") if px <= 64 else "parted" if w % 4 != 0 and first % px == px - 1 else "inside"
+    assert plan.tail_tiles > 0 and begins == want and plan.lone_cut == cut
     check_full(spec, L, x, "f32", "nchw", stride, relu=True, policy=0, what=f"tail{shape}")
 
 
@@ -568,20 +587,25 @@ def test_matrix_core_flat_every_launch_shape(index, layout):
     assert served >= 1
 
 
-LONE_SHAPES = [  # (n, c_in, c_out, h, w): the last patch of a row shifted by 0, 1, 2, 3 columns; part tiles; several images a tile
+LONE_WHOLE = [  # (n, c_in, c_out, h, w): the last patch of a row shifted by 0, 1, 2, 3 columns; part tiles; several images a tile
     (1, 1, 4, 4, 4), (3, 17, 9, 5, 7), (2, 40, 6, 9, 60), (1, 33, 5, 14, 14), (5, 20, 8, 7, 9), (2, 15, 7, 6, 59),
-    (1, 70, 4, 13, 256), (1, 12, 6, 10, 130), (1, 9, 5, 6, 262), (2, 24, 4, 11, 101),      # (the last three: tiles that cut rows)
+    (1, 70, 4, 13, 256), (1, 12, 6, 10, 130), (2, 24, 4, 11, 101),
+]
+LONE_CUT = [  # the same shifts in tiles that cut rows: rows of more than 64 patches, and rows of 33 (tiles over several images)
+    (1, 9, 5, 6, 260), (1, 9, 5, 6, 259), (1, 9, 5, 6, 262), (2, 9, 5, 6, 261),
+    (4, 20, 32, 40, 132), (4, 20, 32, 38, 131), (4, 20, 32, 40, 130), (4, 20, 32, 39, 129),
 ]
 
 
 @pytest.mark.parametrize("ks", [4, 5])
-@pytest.mark.parametrize("shape", LONE_SHAPES)
-def test_waves_on_their_own_tiles(shape, ks):
+@pytest.mark.parametrize("shape,cut", [(sh, 0) for sh in LONE_WHOLE] + [(sh, 1) for sh in LONE_CUT])
+def test_waves_on_their_own_tiles(shape, cut, ks):
     """fp32 NCHW, every wave its own channels, all four or two slots per workgroup: whole rows of patches in
     a tile and not, every shift of the last patch, waves without a channel, dense kernels (three records
     each), stride 2 and the fused max-pool."""
     import torch
     n, ci, co, h, w = shape
+    P.pconv_set_kernel_policy(2)                         # (small images with stride 2 go to the gather kernel otherwise)
     for dense in (False, True):
         spec = LayerSpec("lone", n, ci, co, h, w, keep_div=1.0 if dense else 2.0, num_patterns=1 if dense else 8,
                          pattern_dist="dense" if dense else "zipf", count_dist="all" if dense else "pm30")
@@ -589,7 +613,8 @@ def test_waves_on_their_own_tiles(shape, ks):
         P.pconv_debug_set_tiling(16, ks, 0)
         for stride in (1, 2):
             y, hd = gpu_conv(L, x, "f32", stride=stride, relu=bool(n & 1))
-            assert P.pconv_debug_plan(hd, n, h, w, 1).ks_log2 == ks
+            plan = P.pconv_debug_plan(hd, n, h, w, stride)
+            assert plan.ks_log2 == ks and plan.lone_cut == cut
             yr, sr = oracle_full(L, x, "f32", "nchw", stride, bool(n & 1))
             assert_close(y, yr, sr, "f32", f"lone{shape}_{ks}_{stride}")
         if w % 2 == 0:
