@@ -665,6 +665,82 @@ def test_matrix_core_flat_wide_launch_shapes(index, layout):
     assert served >= 1
 
 
+FLAT_FULL = [  # (n, c_in, c_out, h, w, stride), three steps at least in every launch shape (48 blocks of 16 channels)
+    (3, 768, 160, 7, 7, 1), (2, 768, 160, 14, 14, 2), (2, 776, 150, 9, 11, 2), (2, 784, 120, 9, 13, 1),
+]
+
+
+def _no_empty_block(L, c_in, c_out):
+    """Whether every (tap, 16 channels, 32 filters) block of the masked weights holds a kept one."""
+    kept = (L["table"][L["pattern_id"]][..., None] >> np.arange(9) & 1).astype(bool) & L["conn"].astype(bool)[..., None]
+    return all(kept[f:f + 32, c:c + 16].any((0, 1)).all() for f in range(0, c_out, 32) for c in range(0, c_in, 16))
+
+
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+@pytest.mark.parametrize("index", range(25))
+def test_matrix_core_flat_loop_without_branches(index, layout):
+    """Layers without an empty block of weights run a loop without branches: every launch shape, pinned, with several
+    steps, both strides, planes with odd and even numbers of pixels, ragged last blocks."""
+    P.pconv_debug_set_flat_shape(index)
+    served = 0
+    for j, (n, ci, co, h, w, stride) in enumerate(FLAT_FULL):
+        spec = LayerSpec("flatfull", n, ci, co, h, w, stride=stride, dtype="bf16", keep_div=2.0)
+        L = make_layer(spec, 7500 + j)
+        assert _no_empty_block(L, ci, co)
+        hd = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "bf16")
+        got = P.pconv_debug_plan(hd, n, h, w, stride, layout).flat_shape
+        hd.free()
+        assert got in (index, -1)
+        if got < 0:
+            continue
+        served += 1
+        check_full(spec, L, make_input(spec, 7500 + j, layout), "bf16", layout, stride, relu=bool(j & 1), use_bias=not j & 2,
+                   policy=3, what=f"flatfull{index}_{j}_{layout}")
+    assert served >= 1
+
+
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+@pytest.mark.parametrize("shape", [(2, 33, 40, 7, 9, 1), (1, 64, 64, 7, 7, 1), (3, 40, 33, 13, 11, 2), (2, 48, 32, 8, 9, 1), (2, 32, 64, 14, 14, 2)])
+def test_matrix_core_flat_tensors_off_a_dword(shape, layout):
+    """Input and output begin two bytes off a dword (views into larger buffers), and the elements beside them are NaN:
+    planes with odd numbers of pixels, which are loaded by dwords, and with even ones; layers with empty blocks of
+    weights and without; several launch shapes."""
+    import torch
+    n, ci, co, h, w, stride = shape
+    if layout == "nhwc":
+        ci = (ci + 7) // 8 * 8
+    spec = LayerSpec("offdword", n, ci, co, h, w, stride=stride, dtype="bf16", keep_div=2.0)
+    nan = torch.tensor([float("nan")], device="cuda", dtype=torch.bfloat16)
+    for j, full in enumerate((False, True)):
+        L = make_layer(spec, 7600 + ci)
+        if full:                                     # a kept kernel with all taps in every block of channels and filters
+            L["table"] = np.append(L["table"][:-1], np.uint16(0x1FF))
+            L["pattern_id"][::16, ::8] = len(L["table"]) - 1
+            L["conn"][::16, ::8] = 1
+            assert _no_empty_block(L, ci, co)
+        else:
+            L["conn"][:, :16] = 0                    # a whole block of channels unused
+        x = make_input(spec, 7600 + ci, layout)
+        xd = torch.cat([nan, to_device(x, "bf16").flatten(), nan])[1:-1].view(x.shape)
+        assert xd.data_ptr() % 4 == 2 and xd.is_contiguous()
+        hd = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "bf16")
+        b = torch.from_numpy(L["bias"]).cuda()
+        shape_out = (n, co, spec.h_out, spec.w_out) if layout == "nchw" else (n, spec.h_out, spec.w_out, co)
+        yr, sr = oracle_full(L, x, "bf16", layout, stride, False, True)
+        P.pconv_set_kernel_policy(3)
+        for index in (-1, 2, 7, 11, 12, 24):
+            P.pconv_debug_set_flat_shape(index)
+            if P.pconv_debug_plan(hd, n, h, w, stride, layout).flat_shape < 0:
+                continue
+            say(f"[case] off a dword {shape} {layout} full={full} shape {index}")
+            buf = torch.full((int(np.prod(shape_out)) + 2,), 7.0, device="cuda", dtype=torch.bfloat16)
+            y = P.conv2d(hd, xd, b, stride=stride, layout=layout, out=buf[1:-1].view(shape_out))
+            torch.cuda.synchronize()
+            assert_close(y.float().cpu().numpy().astype(np.float64), yr, sr, "bf16", f"offdword{shape}_{layout}_{full}_{index}")
+            assert float(buf[0]) == 7.0 and float(buf[-1]) == 7.0
+        hd.free()
+
+
 def test_matrix_core_kernel_skips_empty_weight_blocks():
     """Connectivity so sparse that whole (tap, 16 channels, 32 filters) blocks hold no weight: the
     kernel skips them; and a layer with nothing kept at all."""
