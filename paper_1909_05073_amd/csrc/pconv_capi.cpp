@@ -132,7 +132,8 @@ static int pack_impl(const float *w_dense, const uint8_t *pattern_id, const uint
         h->K = int64_t(h->canon.cin.size());
         h->nnz = int64_t(h->canon.vals_bits.size());
 
-        build_tiled_stream(h->canon, table, num_patterns, c_out, c_in, h->tiled);
+        std::vector<uint32_t> chan_mid;
+        build_tiled_stream(h->canon, table, num_patterns, c_out, c_in, h->tiled, chan_mid);
         if (!to_device) { *out = h; return PCONV_OK; }
         hipError_t e = hipGetDevice(&h->device);
         if (e != hipSuccess) { delete h; return hip_fail("pconv_pack: hipGetDevice", e); }
@@ -153,7 +154,7 @@ static int pack_impl(const float *w_dense, const uint8_t *pattern_id, const uint
         if (rc == PCONV_OK && h->tiled.meta.size() < kTiledMaxRecords)
             rc = upload(h->d_meta, h->tiled.meta.data(), h->tiled.meta.size(), h->device_bytes);
         if (rc == PCONV_OK && weight_dtype == PCONV_F32 && h->d_meta) {        // (what pconv_lone.hip serves)
-            const std::vector<uint32_t> lone = build_lone_lists(h->tiled, c_in);
+            const std::vector<uint32_t> lone = build_lone_lists(h->tiled, chan_mid, c_in);
             rc = upload(h->d_lone_bounds, lone.data(), lone.size(), h->device_bytes);
             if (rc == PCONV_OK) h->d_lone_visits = h->d_lone_bounds + lone_bounds_words(h->tiled);
         }

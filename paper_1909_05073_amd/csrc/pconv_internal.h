@@ -107,13 +107,14 @@ int build_canonical(const float *w, const uint8_t *pid, const uint8_t *conn, con
 int project_weights(const float *w, const uint16_t *table, int np, int c_out, int c_in, int64_t keep,
                     uint8_t *pattern_id, uint8_t *conn);
 
+// chan_mid: [num_blocks][c_in] first record of slots 2 and 3 of a channel (what build_lone_lists needs)
 void build_tiled_stream(const Canonical &cn, const uint16_t *table, int np, int c_out, int c_in,
-                        TiledStream &out);
+                        TiledStream &out, std::vector<uint32_t> &chan_mid);
 
 // The lists that pconv_lone.hip walks: the first visit of each wave, [num_blocks][all slots, slots 0 and 1, slots 2
 // and 3][kLoneWaves + 1], and behind them {first record, channel | records << 16} of every visited channel.
 inline size_t lone_bounds_words(const TiledStream &ts) { return size_t(ts.num_blocks) * 3 * (kLoneWaves + 1); }
-std::vector<uint32_t> build_lone_lists(const TiledStream &ts, int c_in);
+std::vector<uint32_t> build_lone_lists(const TiledStream &ts, const std::vector<uint32_t> &chan_mid, int c_in);
 
 // Kernel launchers (pconv_kernels.hip, pconv_tiled.hip).  All return a pconv_status.
 int launch_conv_generic(const pconv_handle *h, const void *x, void *y, const float *bias, int n,

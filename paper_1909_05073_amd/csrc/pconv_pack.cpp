@@ -125,7 +125,7 @@ int build_canonical(const float *w, const uint8_t *pid, const uint8_t *conn, con
 // one filter from each slice of the sorted list; a local search then evens the counts out
 // chunk by chunk (see below).
 void build_tiled_stream(const Canonical &cn, const uint16_t *table, int np, int c_out, int c_in,
-                        TiledStream &out)
+                        TiledStream &out, std::vector<uint32_t> &chan_mid)
 {
     const int FB = kTileFB;
     const int nb = (c_out + FB - 1) / FB;
@@ -218,6 +218,7 @@ void build_tiled_stream(const Canonical &cn, const uint16_t *table, int np, int 
     }
 
     out.chan_ptr.assign(size_t(nb) * out.row_len, 0);
+    chan_mid.resize(size_t(nb) * c_in);
     out.meta.clear();
     out.w4.clear();
     std::vector<std::vector<int32_t>> by_slot(FB, std::vector<int32_t>(size_t(c_in), -1));
@@ -232,9 +233,9 @@ void build_tiled_stream(const Canonical &cn, const uint16_t *table, int np, int 
         for (int c = 0; c < c_in; ++c) {
             row[c] = uint32_t(out.meta.size());
             bool first = true;
-            size_t mid = 0;                                              // first record of slots 2 and 3
+            uint32_t &mid = chan_mid[size_t(b) * c_in + c];
             for (int s = 0; s < FB; ++s) {
-                if (s == FB / 2) mid = out.meta.size();
+                if (s == FB / 2) mid = uint32_t(out.meta.size());
                 const int32_t k = by_slot[s][c];
                 if (k < 0) continue;
                 for (const Piece &pc : pieces[cn.pat[k]]) {
@@ -263,28 +264,21 @@ void build_tiled_stream(const Canonical &cn, const uint16_t *table, int np, int 
 // The visits of a workgroup's filters (channels with a record) in order, and where each wave's begin:
 // consecutive visits whose costs (a visit loads the neighbourhood, a record is 64 FMAs and its dispatch:
 // about 100 and 60 cycles of a compute unit) add up to about the same.
-std::vector<uint32_t> build_lone_lists(const TiledStream &ts, int c_in)
+std::vector<uint32_t> build_lone_lists(const TiledStream &ts, const std::vector<uint32_t> &chan_mid, int c_in)
 {
-    std::vector<uint32_t> out(lone_bounds_words(ts) + size_t(ts.visits + ts.half_visits) * 2 + 4, 0u);   // (the last two: read by waves without a visit)
+    std::vector<uint32_t> out(lone_bounds_words(ts) + size_t(ts.visits + ts.half_visits) * 2 + 4);
     uint32_t *const visits = out.data() + lone_bounds_words(ts), *next = visits;
-    constexpr uint32_t kSlotsUpper = uint32_t(kTileFB / 2 * kNumCodes) << kMetaCaseShift;                // words of slots 2 and 3 are not below
     for (int b = 0; b < ts.num_blocks; ++b) {
-        const uint32_t *row = &ts.chan_ptr[size_t(b) * ts.row_len];
+        const uint32_t *row = &ts.chan_ptr[size_t(b) * ts.row_len], *mid = &chan_mid[size_t(b) * c_in];
         for (int form = 0; form < 3; ++form) {       // all slots, slots 0 and 1, slots 2 and 3
-            const uint32_t *begin = next;
+            const uint32_t *from = form == 2 ? mid : row, *to = form == 1 ? mid : row + 1, *begin = next;
             int64_t total = 0;
-            for (int c = 0; c < c_in; ++c) {
-                uint32_t from = row[c], to = row[c + 1];
-                if (form > 0) {
-                    uint32_t mid = from;
-                    while (mid < to && ts.meta[mid] < kSlotsUpper) ++mid;
-                    (form == 1 ? to : from) = mid;
-                }
-                if (from == to) continue;
-                next[0] = from;
-                next[1] = uint32_t(c) | (to - from) << 16;
-                next += 2;
-                total += 5 + 3 * int64_t(to - from);
+            for (int c = 0; c < c_in; ++c) {         // (a channel without a record is written over by the next one)
+                const uint32_t records = to[c] - from[c];
+                next[0] = from[c];
+                next[1] = uint32_t(c) | records << 16;
+                next += records ? 2 : 0;
+                total += records ? 5 + 3 * int64_t(records) : 0;
             }
             uint32_t *bounds = &out[(size_t(b) * 3 + form) * (kLoneWaves + 1)];
             const int parts = int(std::min<ptrdiff_t>(kLoneWaves, (next - begin) / 2));
@@ -302,6 +296,7 @@ std::vector<uint32_t> build_lone_lists(const TiledStream &ts, int c_in)
             }
         }
     }
+    std::fill(next, next + 4, 0u);                   // read by waves without a visit
     return out;
 }
 
