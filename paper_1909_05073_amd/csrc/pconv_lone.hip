@@ -81,7 +81,8 @@ conv_lone_kernel(const LoneArgs a)
     auto constant = [](const void *p) { return reinterpret_cast<ConstWords>(reinterpret_cast<uintptr_t>(p)); };
     const ConstWords bounds = constant(a.bounds) + (fblk * 3 + half + 1) * (NW + 1);
     const int v_lo = int(bounds[wave]), v_hi = int(bounds[wave + 1]), n_visits = v_hi - v_lo;
-    const int parts = max(1, min(NW, int(bounds[NW] - bounds[0])));            // the first waves, one visit each at least
+    // (waves from `parts` on have no visits; an earlier one may have none either, beside a very costly visit: it adds zeros)
+    const int parts = max(1, min(NW, int(bounds[NW] - bounds[0])));
     struct Visit { uint32_t record, channel_count; };
     const ConstWords visits = constant(a.visits), meta = constant(a.meta);
     auto visit_at = [&](int v) { return Visit{visits[2 * v], visits[2 * v + 1]}; };

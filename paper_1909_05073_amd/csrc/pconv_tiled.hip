@@ -1,4 +1,5 @@
-// Register-tiled PCONV kernel for gfx950 (stride 1; stride 2 as stride 1 with every other output stored).
+// Register-tiled PCONV kernel for gfx950 (stride 1; stride 2 at the same patches, of which the outputs at even rows
+// and columns are stored: see SUB2).
 //
 // Work decomposition.  A workgroup of NW waves owns 64 "patches" (a patch = a 4x4 block of output
 // pixels of one image; one patch per lane) and 4 * NW filters (4 per wave, its "slots").  Two shapes
@@ -1035,7 +1036,7 @@ template <int NW, int CH>
 hipError_t launch_any(const TiledArgs &a, int64_t wgs, hipStream_t st, bool vec, int layout, int dtype, int dev)
 {
     if constexpr (NW == 16)
-        if (a.priv) {
+        if (a.priv) {                                    // (channels last: pconv_lone.hip has every call of the kind with vec)
             return dtype == PCONV_F32 ? launch_shape<float, PCONV_NHWC, false, NW, CH, false, true>(a, wgs, st, dev)
                                       : launch_shape<bf16_t, PCONV_NHWC, false, NW, CH, false, true>(a, wgs, st, dev);
         }
@@ -1071,7 +1072,6 @@ void set_tiled_spin_limit(int limit) { g_spin_limit.store(limit > 0 ? limit : kD
 bool tiled_supported(const pconv_handle *h, int n, int hin, int win, int stride, int layout, int dtype)
 {
     (void)layout; (void)dtype;
-    // (stride 2 runs at full resolution and stores every other output)
     if (h->tiled.meta.size() >= kTiledMaxRecords || (stride != 1 && stride != 2)) return false;
     const int64_t patches = int64_t(n) * ((hin + 3) / 4) * ((win + 3) / 4);
     return patches < (int64_t(1) << 30);
@@ -1079,9 +1079,9 @@ bool tiled_supported(const pconv_handle *h, int n, int hin, int win, int stride,
 
 bool tiled_preferred(int hin, int win, int stride)
 {
-    // Stride 2 through this kernel computes four times the outputs it stores; measured 1.6 to 3.4
-    // times faster than the gather kernel all the same (ResNet-50 shapes, batch 32, inputs of 56x56,
-    // 28x28 and 14x14).  Smaller images are left to the gather kernel.
+    // Stride 2 stages four times the pixels it needs and, but for SUB2, forms four times the outputs it stores; without
+    // SUB2 it was measured 1.6 to 3.4 times as fast as the gather kernel all the same (ResNet-50 shapes, batch 32,
+    // inputs of 56x56, 28x28 and 14x14).  Smaller images are left to the gather kernel.
     return stride == 1 || int64_t(hin) * win >= 12 * 12;
 }
 
@@ -1171,6 +1171,9 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
     auto units_of = [&](int ks) { return (blocks + (p.nw >> ks) - 1) / (p.nw >> ks); };   // filter groups per tile
     const double records = double(h->tiled.meta.size()) * p.nw / blocks / n_chunks;       // of a whole unit's chunk
     const double visits = double(h->tiled.visits) / blocks, recs = double(h->tiled.meta.size()) / blocks;
+    // Stride 2 is priced as stride 1, although whole units with even widths do a quarter of the FMAs: staging is what
+    // such a unit takes its time for, and of 16 layers with stride 2 (32 to 512 channels, 14 to 224 pixels
+    // square, 1 to 64 images) the form chosen is the fastest of all that can be pinned.
     // a round of waves on their own: fp32 NCHW (pconv_lone.hip) per visited channel 0.035 us and per record 0.023,
     // fitted to 15 layers with 1 to 8 images (8 % off on average; 256 channels @56, one image: 17.3 us, 512
     // @28 and two slots 22; a sixth more where tiles cut rows of patches);
