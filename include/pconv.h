@@ -140,6 +140,17 @@ int pconv_conv2d_static(const pconv_handle *h, const void *x_dev, void *y_dev, c
                         int n, int h_in, int w_in, int stride, int pad,
                         pconv_layout layout, pconv_dtype act_dtype, int fuse_relu, void *hip_stream);
 
+/* pconv_conv2d_ws - pconv_conv2d for callers that can lend it `work_bytes` of device memory (aligned to 16 bytes, used
+ * in stream order until the call's work is done, its contents are lost).  pconv_conv2d_workspace says how much a call makes
+ * use of, 0 for most.  With less, or none, the call is pconv_conv2d.  With it, fp32 tensors with channels last are
+ * laid out channels first before and back after the convolution, whose kernels for that layout take
+ * half of the time or less; outputs are the same up to the order of the additions. */
+int64_t pconv_conv2d_workspace(const pconv_handle *h, int n, int h_in, int w_in, int stride, pconv_layout layout,
+                               pconv_dtype act_dtype);
+int pconv_conv2d_ws(const pconv_handle *h, const void *x_dev, void *y_dev, const float *bias_dev, int n, int h_in, int w_in,
+                    int stride, int pad, pconv_layout layout, pconv_dtype act_dtype, int fuse_relu, void *hip_stream,
+                    void *work, int64_t work_bytes);
+
 /*
  * pconv_get_async_error - PCONV_HIP_ERROR (once, with a message) if a kernel launched on this
  * handle gave up one of its bounded waits since the last report, else PCONV_OK.  Touches no

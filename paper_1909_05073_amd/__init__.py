@@ -67,6 +67,10 @@ def lib():
     L.pconv_conv2d.argtypes = [vp, vp, vp, vp, ip, ip, ip, ip, ip, ip, ip, ip, vp]
     L.pconv_conv2d_static.restype = ip
     L.pconv_conv2d_static.argtypes = [vp, vp, vp, vp, ip, ip, ip, ip, ip, ip, ip, ip, vp]
+    L.pconv_conv2d_workspace.restype = C.c_int64
+    L.pconv_conv2d_workspace.argtypes = [vp, ip, ip, ip, ip, ip, ip]
+    L.pconv_conv2d_ws.restype = ip
+    L.pconv_conv2d_ws.argtypes = [vp, vp, vp, vp, ip, ip, ip, ip, ip, ip, ip, ip, vp, vp, C.c_int64]
     L.pconv_conv2d_pool2x2.restype = ip
     L.pconv_conv2d_pool2x2.argtypes = [vp, vp, vp, vp, ip, ip, ip, ip, ip, ip, vp]
     L.pconv_free.restype = None
@@ -103,7 +107,7 @@ def lib():
     return L
 
 
-EXPORTED_SYMBOLS = ["pconv_project", "pconv_pack", "pconv_conv2d", "pconv_conv2d_static", "pconv_conv2d_pool2x2", "pconv_free", "pconv_maxpool2x2",
+EXPORTED_SYMBOLS = ["pconv_project", "pconv_pack", "pconv_conv2d", "pconv_conv2d_static", "pconv_conv2d_workspace", "pconv_conv2d_ws", "pconv_conv2d_pool2x2", "pconv_free", "pconv_maxpool2x2",
                     "pconv_get_info", "pconv_debug_export", "pconv_debug_export_blocks", "pconv_debug_pack_host",
                     "pconv_debug_unpack",
                     "pconv_set_kernel_policy", "pconv_debug_set_tiling", "pconv_debug_set_flat_shape", "pconv_debug_plan", "pconv_debug_set_spin_limit",
@@ -317,8 +321,29 @@ def conv2d(handle: Handle, x, bias=None, stride: int = 1, relu: bool = False, la
         out = torch.empty(shape, dtype=x.dtype, device=x.device)
     if bias is not None and (bias.dtype != torch.float32 or not bias.is_cuda):
         raise ValueError("bias must be a float32 CUDA tensor")
+    if lay == NHWC and dtype == F32:
+        return _conv2d_ws(handle, x, bias, stride, relu, out, n, h, w)
     rc = (_lib or lib()).pconv_conv2d(handle.ptr, x.data_ptr(), out.data_ptr(), (bias.data_ptr() or None) if bias is not None else None,
                                       n, h, w, stride, 1, lay, dtype, 1 if relu else 0, _stream(x.get_device()))
+    if rc != OK:
+        _check(rc)
+    return out
+
+
+def _conv2d_ws(handle: Handle, x, bias, stride, relu, out, n, h, w):
+    """conv2d of fp32 tensors with channels last: lends the call work space out of torch's pool, if there is any."""
+    import torch
+    L = _lib or lib()
+    size = L.pconv_conv2d_workspace(handle.ptr, n, h, w, stride, NHWC, F32)
+    work = None
+    if size > 0:
+        try:
+            work = torch.empty(size, dtype=torch.uint8, device=x.device)
+        except torch.cuda.OutOfMemoryError:
+            size = 0
+    rc = L.pconv_conv2d_ws(handle.ptr, x.data_ptr(), out.data_ptr(), (bias.data_ptr() or None) if bias is not None else None,
+                           n, h, w, stride, 1, NHWC, F32, 1 if relu else 0, _stream(x.get_device()),
+                           work.data_ptr() if work is not None else None, size)
     if rc != OK:
         _check(rc)
     return out

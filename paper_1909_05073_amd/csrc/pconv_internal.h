@@ -119,10 +119,11 @@ std::vector<uint32_t> build_lone_lists(const TiledStream &ts, const std::vector<
 // Kernel launchers (pconv_kernels.hip, pconv_tiled.hip).  All return a pconv_status.
 int launch_conv_generic(const pconv_handle *h, const void *x, void *y, const float *bias, int n,
                         int hin, int win, int stride, int layout, int dtype, int relu, void *stream);
-// static_scratch: take the hand-over words from the code object's static array instead of the handle.
+// static_scratch: take the hand-over words from the code object's static array instead of the handle.  y_last: fp32
+// NCHW calls only, not with pool: where the outputs go with channels last; y is work space.
 int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float *bias, int n,
                       int hin, int win, int stride, int layout, int dtype, int relu, int pool, void *stream,
-                      bool static_scratch = false);
+                      bool static_scratch = false, float *y_last = nullptr);
 // fp32 NCHW with few units of work: every wave on its own (pconv_lone.hip), from patch `patch_base` on.
 struct LoneTiles { int lanes; bool cut; int64_t tiles; };        // patches of a tile, tiles that cut rows, their number
 LoneTiles lone_tiles(int64_t patches, int px, int64_t patch_base, int64_t groups, int slots);
@@ -130,7 +131,9 @@ LoneTiles lone_tiles(int64_t patches, int px, int64_t patch_base, int64_t groups
 // patches are computed twice).
 inline int64_t lone_base(int64_t first, int px) { return px <= 64 ? first - first % px : first; }
 hipError_t launch_conv_lone(const pconv_handle *h, const float *x, float *y, const float *bias, int n, int hin, int win,
-                            int stride, int relu, int pool, bool halves, int64_t patch_base, void *stream);
+                            int stride, int relu, int pool, bool halves, int64_t patch_base, bool last, void *stream);
+// whether an fp32 call with channels last is better off with its tensors' layout changed before and after
+bool tiled_nchw_preferred(const pconv_handle *h, int n, int hin, int win, int stride);
 // whether the tiled kernel can write the 2x2 max-pooled output directly (pool = 1)
 bool tiled_pool_supported(const pconv_handle *h, int n, int hin, int win, int layout, int dtype);
 bool tiled_supported(const pconv_handle *h, int n, int hin, int win, int stride, int layout, int dtype);
@@ -164,6 +167,8 @@ void set_flat_shape(int index);
 // masked weights of a bf16 handle in the matrix-core kernel's layout (see pconv_handle::d_wdense)
 void build_dense_taps(const Canonical &cn, const uint16_t *table, int c_out, int c_in,
                       std::vector<uint16_t> &wd, std::vector<uint32_t> &nz);
+// dst[n][c][r] = src[n][r][c], floats
+int launch_transpose(const float *src, float *dst, int n, int rows, int cols, void *stream);
 int launch_maxpool2x2(const void *x, void *y, int n, int c, int h, int w, int layout, int dtype,
                       void *stream);
 

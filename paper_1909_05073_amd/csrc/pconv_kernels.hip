@@ -3,6 +3,7 @@
 // pconv_tiled.hip.
 #include <hip/hip_runtime.h>
 
+#include "pconv_fast_div.h"
 #include "pconv_internal.h"
 
 namespace pconv {
@@ -95,6 +96,50 @@ maxpool2x2_kernel(const T *__restrict__ x, T *__restrict__ y, int n_img, int c, 
     store_act(y, act_at<LAYOUT>(n, ch, oy, ox, c, ho, wo), m);
 }
 
+// dst[n][s][r] = src[n][r][s]: a workgroup moves a tile of 64 x 64 words through LDS, a thread 16 bytes at a time on
+// both sides.  Bound by memory.
+__global__ void __launch_bounds__(256)
+transpose_kernel(const float *__restrict__ src, float *__restrict__ dst, int rows, int cols, int tiles_c, int tiles, FastDiv div_c, FastDiv div_img)
+{
+    constexpr int TILE = 64, PITCH = TILE + 1;
+    __shared__ float lds[TILE * PITCH];
+    const int img = fast_div(int(blockIdx.x), div_img), in_img = int(blockIdx.x) - img * tiles;
+    const int tr = fast_div(in_img, div_c), tc = in_img - tr * tiles_c;
+    const int line = int(threadIdx.x) >> 4, quad = (int(threadIdx.x) & 15) * 4;
+    const size_t base = size_t(img) * rows * cols;
+    float v[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = tr * TILE + line + 16 * i, c = tc * TILE + quad;
+        const float *from = src + base + size_t(r) * cols + c;
+        if (r < rows && c + 4 <= cols) {
+            __builtin_memcpy(v[i], from, 16);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[i][k] = r < rows && c + k < cols ? from[k] : 0.0f;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) lds[(line + 16 * i) * PITCH + quad + k] = v[i][k];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int c = tc * TILE + line + 16 * i, r = tr * TILE + quad;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[i][k] = lds[(quad + k) * PITCH + line + 16 * i];
+        float *to = dst + base + size_t(c) * rows + r;
+        if (c < cols && r + 4 <= rows) {
+            __builtin_memcpy(to, v[i], 16);
+        } else if (c < cols) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (r + k < rows) to[k] = v[i][k];
+        }
+    }
+}
+
 int check_launch(const char *what)
 {
     hipError_t e = hipGetLastError();
@@ -126,6 +171,16 @@ int launch_conv_generic(const pconv_handle *h, const void *x, void *y, const flo
     }
 #undef PCONV_LAUNCH
     return check_launch("pconv_conv2d (generic kernel)");
+}
+
+int launch_transpose(const float *src, float *dst, int n, int rows, int cols, void *stream)
+{
+    const int tiles_c = (cols + 63) / 64;
+    const int64_t tiles = int64_t((rows + 63) / 64) * tiles_c, total = tiles * n;
+    if (total > 0x3FFFFFFF) { set_error("pconv_conv2d: too many workgroups"); return PCONV_UNSUPPORTED; }
+    hipLaunchKernelGGL(transpose_kernel, dim3(unsigned(total)), dim3(256), 0, static_cast<hipStream_t>(stream), src, dst, rows, cols,
+                       tiles_c, int(tiles), make_fast_div(uint32_t(tiles_c)), make_fast_div(uint32_t(tiles)));
+    return check_launch("pconv_conv2d (change of layout)");
 }
 
 int launch_maxpool2x2(const void *x, void *y, int n, int c, int h, int w, int layout, int dtype,

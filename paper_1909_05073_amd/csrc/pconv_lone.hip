@@ -25,6 +25,7 @@
 #include <algorithm>
 #include <atomic>
 #include <string>
+#include <type_traits>
 
 #include "pconv_fast_div.h"
 #include "pconv_internal.h"
@@ -53,8 +54,9 @@ struct LoneArgs {
     FastDiv div_img, div_px, div_groups;
 };
 
-// OVER: columns by which the last patch of a row is shifted left.  CUT: tiles may begin and end inside a row.
-template <int OVER, bool CUT>
+// OVER: columns by which the last patch of a row is shifted left.  CUT: tiles may begin and end inside a row.  LAST:
+// outputs with channels last.
+template <int OVER, bool CUT, bool LAST>
 __global__ void __launch_bounds__(NW * 64, 4)      // 4 waves per SIMD: at most 128 VGPRs
 conv_lone_kernel(const LoneArgs a)
 {
@@ -275,9 +277,21 @@ conv_lone_kernel(const LoneArgs a)
         if (a.sub2) {
             // of the row the even columns (the patch starts at a multiple of 4, or at w - 4)
             const int h2 = (a.h + 1) >> 1, w2 = (a.w + 1) >> 1, k0 = x0 & 1;
+            if (LAST) {
+                float *dst = a.y + ((size_t(n) * h2 + ((y0 + i) >> 1)) * w2 + ((x0 + k0) >> 1)) * a.c_out + f;
+                dst[0] = finish(k0 ? s[1] : s[0]);
+                if (((x0 + k0) >> 1) + 1 < w2) dst[a.c_out] = finish(k0 ? s[3] : s[2]);
+                return;
+            }
             float *dst = a.y + ((size_t(n) * a.c_out + f) * h2 + ((y0 + i) >> 1)) * w2 + ((x0 + k0) >> 1);
             dst[0] = finish(k0 ? s[1] : s[0]);
             if (((x0 + k0) >> 1) + 1 < w2) dst[1] = finish(k0 ? s[3] : s[2]);
+            return;
+        }
+        if (LAST) {
+            float *dst = a.y + ((size_t(n) * a.h + y0 + i) * a.w + x0) * a.c_out + f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) dst[size_t(k) * a.c_out] = finish(s[k]);
             return;
         }
         float *dst = a.y + ((size_t(n) * a.c_out + f) * a.h + y0 + i) * a.w + x0;
@@ -303,19 +317,19 @@ conv_lone_kernel(const LoneArgs a)
 
 constexpr size_t kLdsBytes = size_t(NW) * (kBatch + 2 * 4 * 64) * 16;   // weights and sums of two slots of every wave: 144 KB
 
-template <int OVER, bool CUT>
+template <int OVER, bool CUT, bool LAST>
 hipError_t launch_lone(const LoneArgs &a, unsigned wgs, hipStream_t st, int dev)
 {
     // More dynamic LDS than the default limit: raised once per device (the flag is set to the same
     // value by every thread that gets here first).
     static std::atomic<bool> attr_done[64];
     if (dev < 0 || dev >= 64 || !attr_done[dev].load(std::memory_order_acquire)) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_lone_kernel<OVER, CUT>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_lone_kernel<OVER, CUT, LAST>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, int(kLdsBytes));
         if (e != hipSuccess) return e;
         if (dev >= 0 && dev < 64) attr_done[dev].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((conv_lone_kernel<OVER, CUT>), dim3(wgs), dim3(NW * 64), kLdsBytes, st, a);
+    hipLaunchKernelGGL((conv_lone_kernel<OVER, CUT, LAST>), dim3(wgs), dim3(NW * 64), kLdsBytes, st, a);
     return hipGetLastError();
 }
 
@@ -337,7 +351,7 @@ LoneTiles lone_tiles(int64_t patches, int px, int64_t patch_base, int64_t groups
 }
 
 hipError_t launch_conv_lone(const pconv_handle *h, const float *x, float *y, const float *bias, int n, int hin, int win,
-                            int stride, int relu, int pool, bool halves, int64_t patch_base, void *stream)
+                            int stride, int relu, int pool, bool halves, int64_t patch_base, bool last, void *stream)
 {
     LoneArgs a;
     a.x = x; a.y = y; a.bias = bias;
@@ -360,11 +374,15 @@ hipError_t launch_conv_lone(const pconv_handle *h, const float *x, float *y, con
     a.div_img = make_fast_div(uint32_t(a.per_img)); a.div_px = make_fast_div(uint32_t(a.px)); a.div_groups = make_fast_div(uint32_t(a.n_groups));
     const unsigned wgs = unsigned((units + 7) / 8 * 8);
     hipStream_t st = static_cast<hipStream_t>(stream);
+    auto launch = [&](auto over, auto cut) {
+        return last ? launch_lone<over.value, cut.value, true>(a, wgs, st, h->device) : launch_lone<over.value, cut.value, false>(a, wgs, st, h->device);
+    };
+    auto launch_over = [&](auto over) { return t.cut ? launch(over, std::true_type{}) : launch(over, std::false_type{}); };
     switch (a.px * 4 - win) {
-    case 0: return t.cut ? launch_lone<0, true>(a, wgs, st, h->device) : launch_lone<0, false>(a, wgs, st, h->device);
-    case 1: return t.cut ? launch_lone<1, true>(a, wgs, st, h->device) : launch_lone<1, false>(a, wgs, st, h->device);
-    case 2: return t.cut ? launch_lone<2, true>(a, wgs, st, h->device) : launch_lone<2, false>(a, wgs, st, h->device);
-    default: return t.cut ? launch_lone<3, true>(a, wgs, st, h->device) : launch_lone<3, false>(a, wgs, st, h->device);
+    case 0: return launch_over(std::integral_constant<int, 0>{});
+    case 1: return launch_over(std::integral_constant<int, 1>{});
+    case 2: return launch_over(std::integral_constant<int, 2>{});
+    default: return launch_over(std::integral_constant<int, 3>{});
     }
 }
 

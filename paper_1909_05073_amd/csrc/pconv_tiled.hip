@@ -1085,6 +1085,27 @@ bool tiled_preferred(int hin, int win, int stride)
     return stride == 1 || int64_t(hin) * win >= 12 * 12;
 }
 
+// fp32 with channels last: the tensors laid out channels first before the convolution and back after it, or staged
+// through registers in the layout they have.  Of 175 layers (1 to 512 channels, 7 to 257 pixels square, 1 to 64 images) the
+// changes of layout take 4 us + 0.35 a MB of input, and 3 us + 0.36 a MB of output unless waves on their own store it
+// (0.86 a MB); what they save grows with the chunks of channels, more so where pixels are no whole quads of
+// channels, and with the output, which the other kernels store four bytes at a time.  us, with change and without: 128 channels @28,
+// eight images 21.7, 34.9; 200 to 50 @112, 16 images 210, 802; 99 to 40 @56, one image 13, 119; but 8 to 16 @20, 20, 13, and 40 to 32
+// filters of 8, 16 images of 75x80 36, 28.
+bool tiled_nchw_preferred(const pconv_handle *h, int n, int hin, int win, int stride)
+{
+    const bool pinned = g_force_waves.load() || g_force_ks.load() >= 0 || g_force_split.load() >= 0;
+    const double x_mb = double(n) * h->c_in * hin * win * 4e-6;
+    const double y_mb = double(n) * h->c_out * ((hin - 1) / stride + 1) * ((win - 1) / stride + 1) * 4e-6;
+    if (pinned || win < 4 || int64_t(n) * h->c_in * hin * win * 4 >= (int64_t(1) << 31) ||
+        !tiled_supported(h, n, hin, win, stride, PCONV_NCHW, PCONV_F32) || !tiled_preferred(hin, win, stride))
+        return false;
+    const bool quads = h->c_in % 4 == 0;
+    const bool many = h->c_in > 32 || (h->c_in > 16 && h->c_out > 8) || (!quads && h->c_in > 4) || (y_mb > 12.0 && y_mb > x_mb);
+    const int chunks = (h->c_in + kTileCH - 1) / kTileCH;
+    return many && (x_mb < 8.0 || 4.0 + 0.35 * x_mb < (quads ? 1.13 : 4.88) * chunks + 1.4 * y_mb);
+}
+
 bool tiled_pool_supported(const pconv_handle *h, int n, int hin, int win, int layout, int dtype)
 {
     return tiled_supported(h, n, hin, win, 1, layout, dtype) && dtype == PCONV_F32 && layout == PCONV_NCHW &&
@@ -1293,7 +1314,7 @@ bool tiled_shares_units(const pconv_handle *h, int n, int hin, int win)
 
 int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float *bias, int n,
                       int hin, int win, int stride, int layout, int dtype, int relu, int pool, void *stream,
-                      bool static_scratch)
+                      bool static_scratch, float *y_last)
 {
     TiledArgs a;
     a.sub2 = stride == 2;
@@ -1354,9 +1375,13 @@ int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float
         wgs = a.priv ? (units + 7) / 8 * 8 : int64_t((a.n_tiles + 7) / 8) * 8 * a.n_groups;   // one per unit of the largest set, in every set
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
+    // Channels last: waves on their own store that way themselves, four bytes at a time, up to 6 MB (0.86 us a MB for
+    // 3 us and 0.36 a MB); what the others have stored changes its layout.
+    const int64_t out_bytes = int64_t(n) * h->c_out * ((hin - 1) / stride + 1) * ((win - 1) / stride + 1) * 4;
+    const bool stores_last = y_last && vec && plan.priv && out_bytes < 6000000;
     auto lone = [&](bool halves, int64_t patch_base) {
-        return launch_conv_lone(h, static_cast<const float *>(x), static_cast<float *>(y), bias, n, hin, win, stride, relu,
-                                pool, halves, patch_base, stream);
+        return launch_conv_lone(h, static_cast<const float *>(x), stores_last ? y_last : static_cast<float *>(y), bias, n, hin, win, stride, relu,
+                                pool, halves, patch_base, stores_last, stream);
     };
     hipError_t e = vec && plan.priv ? lone(plan.halves, 0)
                    : nw == 16       ? launch_any<16, 8>(a, wgs, st, vec, layout, dtype, h->device)
@@ -1366,6 +1391,8 @@ int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float
         set_error(std::string("pconv_conv2d (tiled kernel): ") + hipGetErrorName(e));
         return PCONV_HIP_ERROR;
     }
+    if (y_last && !stores_last)
+        return launch_transpose(static_cast<const float *>(y), y_last, n, h->c_out, ((hin - 1) / stride + 1) * ((win - 1) / stride + 1), stream);
     return PCONV_OK;
 }
 
