@@ -263,7 +263,11 @@ void build_tiled_stream(const Canonical &cn, const uint16_t *table, int np, int 
 //
 // The visits of a workgroup's filters (channels with a record) in order, and where each wave's begin:
 // consecutive visits whose costs (a visit loads the neighbourhood, a record is 64 FMAs and its dispatch:
-// about 100 and 60 cycles of a compute unit) add up to about the same.
+// about 100 and 60 cycles of a compute unit) add up to the wave's share.  A SIMD has four of the 16 waves and serves
+// them oldest first: a visit takes 1360 cycles in the first four waves, 1560, 1690 and 1910 in the others (256 channels
+// @56), so the younger ones get less.  With equal shares the first four are done after 70 % of the loop: one image, us, equal and as
+// they are: 256 channels @56 18.8, 18.1; 512 @14 20.0, 18.8; 99 to 150 @37x45, three images 13.9, 13.4.
+constexpr int kLoneShare[kLoneWaves / 4] = {120, 105, 94, 81};
 std::vector<uint32_t> build_lone_lists(const TiledStream &ts, const std::vector<uint32_t> &chan_mid, int c_in)
 {
     std::vector<uint32_t> out(lone_bounds_words(ts) + size_t(ts.visits + ts.half_visits) * 2 + 4);
@@ -283,10 +287,12 @@ std::vector<uint32_t> build_lone_lists(const TiledStream &ts, const std::vector<
             uint32_t *bounds = &out[(size_t(b) * 3 + form) * (kLoneWaves + 1)];
             const int parts = int(std::min<ptrdiff_t>(kLoneWaves, (next - begin) / 2));
             const uint32_t *v = begin;
-            int64_t before = 0;
+            int64_t before = 0, shares = 0, share = 0;
+            for (int w = 0; w < parts; ++w) shares += kLoneShare[w / 4];
             for (int w = 0; w <= kLoneWaves; ++w) {
-                // up to the visit that ends nearest to w parts of the total
-                const int64_t limit = w < parts ? 2 * total * w / parts : 2 * total;
+                // up to the visit that ends nearest to the shares of the waves before
+                const int64_t limit = w < parts ? 2 * total * share / shares : 2 * total;
+                if (w < parts) share += kLoneShare[w / 4];
                 for (; v < next; v += 2) {
                     const int64_t cost = 5 + 3 * int64_t(v[1] >> 16);
                     if (2 * before + cost > limit) break;
