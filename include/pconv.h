@@ -258,7 +258,8 @@ int pconv_set_kernel_policy(int policy);
 /* pconv_debug_set_tiling - for tests: pins launch choices the register-tiled kernel otherwise
  * makes per call.  waves = 8 or 16 (workgroup size in waves; 0 = automatic); ks_log2 = 0, 1 or 2
  * (the waves of a workgroup split the input channels 1, 2 or 4 ways; 4 = sixteen ways, every wave
- * working on its own, where the call allows it, 5 = the same with two of four filters per workgroup;
+ * working on its own, where the call allows it, 5 = the same with two of four filters per workgroup,
+ * 6 and 7 = as 4 with workgroups of eight and four waves, fp32 NCHW only;
  * -1 = automatic);
  * split_units = 0, 1 or 2 (whether several workgroups may share one tile of outputs, each taking a
  * range of the input channels: 0 = never, 1 = yes, with the work dealt out per group of workgroups
@@ -281,7 +282,7 @@ int pconv_debug_set_flat_shape(int index);
  * PCONV_UNSUPPORTED where the call itself would give it. */
 typedef struct {
     int32_t kernel;        /* numbered as in pconv_set_kernel_policy: 1, 2 or 3                       */
-    int32_t waves;         /* register-tiled kernel, as in pconv_debug_set_tiling                     */
+    int32_t waves;         /* register-tiled kernel, waves of a workgroup                             */
     int32_t ks_log2;
     int32_t split_units;
     int32_t tail_tiles;    /* register-tiled kernel: tiles of the last round that a second launch computes */

@@ -131,7 +131,7 @@ LoneTiles lone_tiles(int64_t patches, int px, int64_t patch_base, int64_t groups
 // patches are computed twice).
 inline int64_t lone_base(int64_t first, int px) { return px <= 64 ? first - first % px : first; }
 hipError_t launch_conv_lone(const pconv_handle *h, const float *x, float *y, const float *bias, int n, int hin, int win,
-                            int stride, int relu, int pool, bool halves, int64_t patch_base, bool last, void *stream);
+                            int stride, int relu, int pool, bool halves, int waves, int64_t patch_base, bool last, void *stream);
 // whether an fp32 call with channels last is better off with its tensors' layout changed before and after
 bool tiled_nchw_preferred(const pconv_handle *h, int n, int hin, int win, int stride);
 // whether the tiled kernel can write the 2x2 max-pooled output directly (pool = 1)

@@ -1,21 +1,25 @@
-// fp32 PCONV for layers with few units of work: every wave on its own (NCHW, stride 1 and, storing every
+// fp32 PCONV for layers with few to middling numbers of units of work: every wave on its own (NCHW, stride 1 and, storing every
 // other output, stride 2).
 //
 // A workgroup is one tile of up to 64 patches (4x4 output pixels, one per lane) and one block of four
-// filters, or two of its four slots (halves, where there are too few blocks for the chip).  Its 16 waves
-// share out the visits of those filters: the channels that have a record, in an order and in portions fixed
+// filters, or two of its four slots (halves, where there are too few blocks for the chip).  Its waves, 16, 8 or 4
+// (one, two or four workgroups to a compute unit), share out the visits of those filters: the channels that have a record, in an order and in portions fixed
 // at pack time.  A wave loads the six input rows of a channel straight into the registers of the record
 // loop, takes the columns beside the patch out of the neighbouring lanes, runs the records and goes on:
 // nothing is staged and there is nothing to wait for but its own loads.  The visit after next is read from
 // the list and the first record words are on their way while the rows are.  At the end the 16 partial
 // sums are added through LDS.
 //
-// What bounds it: the vector-memory pipe.  A visit is six 1 KB loads of 16 cycles each for 1.5 records (97
-// FMAs), some 100 cycles of a compute unit; measured 110 to 120, with 16 waves in flight and no registers
-// left to load ahead.  Start 3600 cycles, sums and stores 5000.  Measured against the same split with the
-// channels staged through LDS and found by scanning the record bounds, one image, us: 256 channels @56 26.3 ->
-// 17.3 (20.2 with direct loads alone), 512 @14 31 -> 20, 512 @28 32 -> 22, 16 @16 8.1 -> 5.5.  Eight waves of
-// twice the registers that load a channel ahead: 24.1 for 256 @56.
+// What bounds it: the issue of vector instructions.  A visit has 97 FMAs (1.5 records) of 2.4 cycles and 12 moves between
+// lanes, and takes 1360 cycles of a wave in the oldest four of 16 waves and 1910 in the youngest (hence portions by
+// age, see the packer); its six 1 KB loads take 100 cycles of the vector-memory pipe per wave.  (Staging the rows
+// through LDS, which needs one to five loads for six, is no faster.)  Start 3600 cycles, sums and stores 5000 with 16
+// waves.  One image, us: 256 channels @56 16.4, 512 @14 19, 512 @28 22.5, 16 @16 5.2 for the kernel.
+//
+// Waves of a workgroup.  With 16 the end of every workgroup, its start and a last round of few workgroups leave the
+// compute unit to itself; with 8 or 4 other workgroups run meanwhile and a round is half or a quarter as long, but too few
+// workgroups leave it with few waves.  us with 16, 8 and 4 (see the estimates in pconv_tiled.hip): 64 channels @224, one
+// image 33, 23, 19; 128 @112 23, 19, 22; 256 @56 18, 22, 33; 512 @14, 32 images 113, 105, 100; 256 @28, 32 images 118, 99, 93.
 //
 // Tiles.  Where it costs little, a tile is a whole number of patch rows, so that every column beside a
 // patch is in the next lane or outside the image.  Otherwise (CUT: rows of more than 64 patches, or tiles that
@@ -35,7 +39,7 @@ namespace pconv {
 
 namespace {
 
-constexpr int FB = kTileFB, NW = kLoneWaves;
+constexpr int FB = kTileFB;
 constexpr uint32_t kOutOfRange = 0x80000000u;      // byte offset beyond any tensor served here
 constexpr int kBatch = 64;                         // records at hand per wave: one per lane
 
@@ -55,8 +59,8 @@ struct LoneArgs {
 };
 
 // OVER: columns by which the last patch of a row is shifted left.  CUT: tiles may begin and end inside a row.  LAST:
-// outputs with channels last.
-template <int OVER, bool CUT, bool LAST>
+// outputs with channels last.  NW: waves.
+template <int OVER, bool CUT, bool LAST, int NW>
 __global__ void __launch_bounds__(NW * 64, 4)      // 4 waves per SIMD: at most 128 VGPRs
 conv_lone_kernel(const LoneArgs a)
 {
@@ -81,10 +85,13 @@ conv_lone_kernel(const LoneArgs a)
     // (constant address space: scalar loads)
     typedef const uint32_t __attribute__((address_space(4))) *ConstWords;
     auto constant = [](const void *p) { return reinterpret_cast<ConstWords>(reinterpret_cast<uintptr_t>(p)); };
-    const ConstWords bounds = constant(a.bounds) + (fblk * 3 + half + 1) * (NW + 1);
-    const int v_lo = int(bounds[wave]), v_hi = int(bounds[wave + 1]), n_visits = v_hi - v_lo;
+    // (the portions are for 16 waves; with fewer, each gets the same number of visits)
+    const ConstWords bounds = constant(a.bounds) + (fblk * 3 + half + 1) * (kLoneWaves + 1);
+    const int v_first = int(bounds[0]), v_all = int(bounds[kLoneWaves]) - v_first;
+    const int v_lo = NW == kLoneWaves ? int(bounds[wave]) : v_first + v_all * wave / NW;
+    const int v_hi = NW == kLoneWaves ? int(bounds[wave + 1]) : v_first + v_all * (wave + 1) / NW, n_visits = v_hi - v_lo;
     // (waves from `parts` on have no visits; an earlier one may have none either, beside a very costly visit: it adds zeros)
-    const int parts = max(1, min(NW, int(bounds[NW] - bounds[0])));
+    const int parts = NW == kLoneWaves ? max(1, min(NW, v_all)) : NW;
     struct Visit { uint32_t record, channel_count; };
     const ConstWords visits = constant(a.visits), meta = constant(a.meta);
     auto visit_at = [&](int v) { return Visit{visits[2 * v], visits[2 * v + 1]}; };
@@ -93,14 +100,15 @@ conv_lone_kernel(const LoneArgs a)
     // (a wave without visits reads the padding at the end of the list)
     Visit now = visit_at(v), next = visit_at(after(v));
     const uint32_t k_lo = visits[2 * v_lo];
-    // what the end needs: filter and bias of the slot that this wave adds up in each pass
-    const int u = (wave >> 2) & 1, i = wave & 3;
-    int filter[FB / 2];
-    float slot_bias[FB / 2];
+    // what the end needs: filter and bias of the slots that this wave adds up: one in each pass, both with four waves
+    constexpr int SLOTS = NW < 8 ? FB : FB / 2, PER_PASS = 2 * SLOTS / FB;
+    const int u = NW < 8 ? 0 : (wave >> 2) & 1, i = wave & 3;
+    int filter[SLOTS];
+    float slot_bias[SLOTS];
 #pragma unroll
-    for (int pass = 0; pass < FB / 2; ++pass) {
-        filter[pass] = int(constant(a.slot_filter)[fblk * FB + 2 * pass + u]);
-        slot_bias[pass] = a.bias && filter[pass] >= 0 ? __uint_as_float(constant(a.bias)[filter[pass]]) : 0.0f;
+    for (int k = 0; k < SLOTS; ++k) {
+        filter[k] = int(constant(a.slot_filter)[fblk * FB + (NW < 8 ? k : 2 * k + u)]);
+        slot_bias[k] = a.bias && filter[k] >= 0 ? __uint_as_float(constant(a.bias)[filter[k]]) : 0.0f;
     }
 
     // ---- this lane's patch ----
@@ -251,11 +259,11 @@ conv_lone_kernel(const LoneArgs a)
     asm volatile("" : "+v"(lane_e));
     const Patch patch = patch_of(lane_e);
     const int n = patch.n, y0 = patch.y0, x0 = patch.x0;
-    auto store_rows = [&](int pass) {
+    auto store_rows = [&](int k, int u) {
         if (wave >= 8 || (a.pool && i >= 2) || (a.sub2 && (i & 1)) || !patch.valid) return;
-        const int f = filter[pass];
+        const int f = filter[k];
         if (f < 0) return;
-        const float b = slot_bias[pass];
+        const float b = slot_bias[k];
         auto sum_row = [&](int row) {
             v4f sum = red[(u * 4 + row) * 64 + lane];
 #pragma unroll 8
@@ -311,25 +319,25 @@ conv_lone_kernel(const LoneArgs a)
                 }
         }
         __syncthreads();
-        store_rows(pass);
+#pragma unroll
+        for (int k = 0; k < PER_PASS; ++k) store_rows(pass * PER_PASS + k, NW < 8 ? k : u);
     }
 }
 
-constexpr size_t kLdsBytes = size_t(NW) * (kBatch + 2 * 4 * 64) * 16;   // weights and sums of two slots of every wave: 144 KB
-
-template <int OVER, bool CUT, bool LAST>
+template <int OVER, bool CUT, bool LAST, int NW>
 hipError_t launch_lone(const LoneArgs &a, unsigned wgs, hipStream_t st, int dev)
 {
+    constexpr size_t kLdsBytes = size_t(NW) * (kBatch + 2 * 4 * 64) * 16;   // weights and sums of two slots of every wave: 144 KB for 16
     // More dynamic LDS than the default limit: raised once per device (the flag is set to the same
     // value by every thread that gets here first).
     static std::atomic<bool> attr_done[64];
     if (dev < 0 || dev >= 64 || !attr_done[dev].load(std::memory_order_acquire)) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_lone_kernel<OVER, CUT, LAST>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_lone_kernel<OVER, CUT, LAST, NW>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, int(kLdsBytes));
         if (e != hipSuccess) return e;
         if (dev >= 0 && dev < 64) attr_done[dev].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((conv_lone_kernel<OVER, CUT, LAST>), dim3(wgs), dim3(NW * 64), kLdsBytes, st, a);
+    hipLaunchKernelGGL((conv_lone_kernel<OVER, CUT, LAST, NW>), dim3(wgs), dim3(NW * 64), kLdsBytes, st, a);
     return hipGetLastError();
 }
 
@@ -351,7 +359,7 @@ LoneTiles lone_tiles(int64_t patches, int px, int64_t patch_base, int64_t groups
 }
 
 hipError_t launch_conv_lone(const pconv_handle *h, const float *x, float *y, const float *bias, int n, int hin, int win,
-                            int stride, int relu, int pool, bool halves, int64_t patch_base, bool last, void *stream)
+                            int stride, int relu, int pool, bool halves, int waves, int64_t patch_base, bool last, void *stream)
 {
     LoneArgs a;
     a.x = x; a.y = y; a.bias = bias;
@@ -375,7 +383,12 @@ hipError_t launch_conv_lone(const pconv_handle *h, const float *x, float *y, con
     const unsigned wgs = unsigned((units + 7) / 8 * 8);
     hipStream_t st = static_cast<hipStream_t>(stream);
     auto launch = [&](auto over, auto cut) {
-        return last ? launch_lone<over.value, cut.value, true>(a, wgs, st, h->device) : launch_lone<over.value, cut.value, false>(a, wgs, st, h->device);
+        constexpr int O = over.value;
+        constexpr bool C = cut.value;
+        if (last)                                        // (16 waves only: see launch_conv_tiled)
+            return launch_lone<O, C, true, 16>(a, wgs, st, h->device);
+        return waves == 16 ? launch_lone<O, C, false, 16>(a, wgs, st, h->device)
+               : waves == 8 ? launch_lone<O, C, false, 8>(a, wgs, st, h->device) : launch_lone<O, C, false, 4>(a, wgs, st, h->device);
     };
     auto launch_over = [&](auto over) { return t.cut ? launch(over, std::true_type{}) : launch(over, std::false_type{}); };
     switch (a.px * 4 - win) {

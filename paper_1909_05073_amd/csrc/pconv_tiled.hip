@@ -1063,7 +1063,7 @@ std::atomic<int> g_spin_limit{kDefaultSpinLimit};
 void set_tiled_tuning(int waves, int ks_log2, int split_units)
 {
     g_force_waves.store((waves == 8 || waves == 16) ? waves : 0);
-    g_force_ks.store((ks_log2 >= 0 && ks_log2 <= 2) || ks_log2 == 4 || ks_log2 == 5 ? ks_log2 : -1);
+    g_force_ks.store((ks_log2 >= 0 && ks_log2 <= 2) || (ks_log2 >= 4 && ks_log2 <= 7) ? ks_log2 : -1);
     g_force_split.store((split_units >= 0 && split_units <= 2) ? split_units : -1);
 }
 
@@ -1156,6 +1156,7 @@ namespace {
 struct TiledPlan {
     int nw;               // waves per workgroup
     bool vec, split, one_set, priv, halves;
+    int lone_waves;       // priv with vec: waves of a workgroup, 16, 8 or 4
     int ks_log2;
     int tail_tiles;       // tiles at the end that a second launch computes, by waves on their own
 };
@@ -1164,6 +1165,7 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
                      bool may_share = true)
 {
     TiledPlan p{};
+    p.lone_waves = 16;
     const int64_t x_bytes = int64_t(n) * h->c_in * hin * win * 4, y_bytes = int64_t(n) * h->c_out * hin * win * 4;
     const int force_waves = g_force_waves.load(), force_ks = g_force_ks.load(), force_split = g_force_split.load();
     p.vec = dtype == PCONV_F32 && layout == PCONV_NCHW && win >= 4 && x_bytes < (int64_t(1) << 31);
@@ -1195,13 +1197,32 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
     // Stride 2 is priced as stride 1, although whole units with even widths do a quarter of the FMAs: staging is what
     // such a unit takes its time for, and of 16 layers with stride 2 (32 to 512 channels, 14 to 224 pixels
     // square, 1 to 64 images) the form chosen is the fastest of all that can be pinned.
-    // a round of waves on their own: fp32 NCHW (pconv_lone.hip) per visited channel 0.035 us and per record 0.023,
-    // fitted to 15 layers with 1 to 8 images (8 % off on average; 256 channels @56, one image: 17.3 us, 512
-    // @28 and two slots 22; a sixth more where tiles cut rows of patches);
-    // channels last 3.3 for 16 channels (128 @28, eight images: 38 us, whole units 120, 81, 62)
-    auto lone = [&](double v, double r, bool cut) {
-        return p.vec ? (3.6 + 0.035 * v + 0.023 * r) * (cut ? 1.17 : 1.0) : 10.0 + 3.3 * ((h->c_in + 15) / 16);
+    // Waves on their own.  fp32 NCHW (pconv_lone.hip), 16, 8 or 4 waves per workgroup, so that a compute unit holds one, two
+    // or four: `units` workgroups of v visited channels and r records.  A round is a start and an end and the work of
+    // the workgroups of a compute unit, which takes longer per workgroup where fewer than four waves share a SIMD.
+    // Fitted to 62 layers with 1 to 64 images (5 % off on average; 256 channels @56, one image 18 us with 16, 22, 32;
+    // 64 @224, one image 33, 23, 19; 512 @14, 32 images 113, 105, 100); a sixth more where tiles cut rows of patches.
+    // Channels last 3.3 for 16 channels (128 @28, eight images: 38 us, whole units 120, 81, 62).
+    struct LoneCost { double base, round, visit, record, work[4]; };
+    static constexpr LoneCost kLoneCost[3] = {{1.84, 4.70, 0.0437, 0.0113, {1.0}}, {2.65, 3.40, 0.0395, 0.0151, {1.24, 2.0}},
+                                              {1.93, 3.46, 0.0382, 0.0153, {2.27, 2.81, 3.52, 4.0}}};
+    auto lone_time = [&](int waves, double units, double v, double r, bool cut) {
+        const LoneCost &c = kLoneCost[waves == 16 ? 0 : waves == 8 ? 1 : 2];
+        const int most = 16 / waves;
+        const double n = std::ceil(units / cus), full = std::floor(n / most), work = (c.visit * v + c.record * r) * (cut ? 1.17 : 1.0);
+        const int left = int(n - full * most);
+        return c.base + full * (c.round + most * work) + (left > 0 ? c.round + c.work[left - 1] * work : 0.0);
     };
+    // the number of waves with the smallest estimate
+    auto lone_best = [&](double units, double v, double r, bool cut, int &waves) {
+        double best = 0.0;
+        for (int w = 16; w >= 4; w /= 2) {
+            const double t = lone_time(w, units, v, r, cut);
+            if (w == 16 || t < best) { best = t; waves = w; }
+        }
+        return best;
+    };
+    const double lone_last = 10.0 + 3.3 * ((h->c_in + 15) / 16);     // (channels last: a round)
     if (whole_units > slots / 2) {
         if (can_split && p.nw == 16) {
             // Many units, but not a multiple of the number of compute units: whole units leave part of
@@ -1230,24 +1251,39 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
             const int main_tiles = int(int64_t(full) * (slots / 8) / units_of(0)) * 8, tail = n_tiles - main_tiles;
             if (full > 0.0 && rest > 0.0 && main_tiles > 0) {
                 const LoneTiles t = lone_tiles(patches, px, lone_base(int64_t(main_tiles) * 64, px), blocks, slots);
-                const double t_tail = 3.0 + std::ceil(double(t.tiles) * blocks / slots) * lone(visits, recs, t.cut);
-                if (t_tail < 0.8 * last) { p.tail_tiles = tail; t_best = full * round + t_tail; }
+                int waves = 16;
+                const double t_tail = 0.5 + lone_best(double(t.tiles) * blocks, visits, recs, t.cut, waves);
+                if (t_tail < 0.8 * last) { p.tail_tiles = tail; p.lone_waves = waves; t_best = full * round + t_tail; }
             }
             // Up to three blocks of filters leave most of a whole unit's waves idle: waves on their own may still be
             // faster (160 to 8 channels @95x102, 44 images: 81 us for 117).
             if (blocks < p.nw / 4) {
                 const LoneTiles t = lone_tiles(patches, px, 0, blocks, slots);
-                if (2.5 + std::ceil(double(t.tiles) * blocks / slots) * lone(visits, recs, t.cut) < 0.9 * t_best) {
-                    p.priv = true; p.ks_log2 = 4; p.tail_tiles = 0;
+                int waves = 16;
+                if (lone_best(double(t.tiles) * blocks, visits, recs, t.cut, waves) < 0.9 * t_best) {
+                    p.priv = true; p.ks_log2 = 4; p.tail_tiles = 0; p.lone_waves = waves;
                 }
+            }
+        }
+        // Waves on their own, two or four workgroups to a compute unit, have no last round to speak of (512 channels
+        // @28, 64 images, 12 uneven patterns 433 -> 398 us).  The estimates above are what a unit takes by
+        // itself; with the chip full it is 1.2 times that (0.17 to 0.31 more on nine layers), shared units 1.35.
+        if (p.vec && can_priv && blocks >= p.nw / 2 && force_split < 0 && force_ks < 0) {
+            const double chunk = 2.0 + 1.9 * records / 142.0, full = double(whole_units / slots), rest = double(whole_units % slots) / slots;
+            const double t_units = p.split ? 1.35 * chunk * (double(whole_units) * n_chunks / slots + 10.0)
+                                           : 1.2 * (6.0 + n_chunks * chunk) * (full + (rest > 0.0 ? 0.72 + 0.28 * rest : 0.0));
+            const LoneTiles t = lone_tiles(patches, px, 0, blocks, slots);
+            int waves = 16;
+            if (lone_best(double(t.tiles) * blocks, visits, recs, t.cut, waves) < 0.97 * t_units && p.tail_tiles == 0) {
+                p.priv = true; p.ks_log2 = 4; p.split = p.one_set = false; p.lone_waves = waves;
             }
         }
     } else {
         // Few units: the form with the smallest estimate, in microseconds, fitted to the VGG-16 layers
         // with one and four images.
         double best = 0.0;
-        auto consider = [&](double t, bool split, int ks, bool priv, bool halves = false) {
-            if (best == 0.0 || t < best) { best = t; p.split = split; p.ks_log2 = ks; p.priv = priv; p.halves = halves; }
+        auto consider = [&](double t, bool split, int ks, bool priv, bool halves = false, int waves = 16) {
+            if (best == 0.0 || t < best) { best = t; p.split = split; p.ks_log2 = ks; p.priv = priv; p.halves = halves; p.lone_waves = waves; }
         };
         // whole units, the waves of a workgroup splitting the channels of a chunk 1, 2 or 4 ways: a chunk
         // costs about 2 for its staging and 1.9 for 142 records on the whole workgroup (256 channels
@@ -1263,24 +1299,29 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
             consider(rounds * (6.0 + chunk_scale * n_chunks * (t_stage + t_records * records / 142.0 / (1 << ks))), false, ks, false);
         }
         // units shared by P workgroups, which pass the sums on one after the other (256 channels @56, one
-        // image: 99 us, four: 83)
+        // image: 99 us, four: 83; 256 @28, 24 images 111, 512 to 200 @40, eight images 159)
         if (can_split)
-            consider(6.0 + 4.6 * chunk_scale * whole_units * n_chunks / slots + std::min(90.0, 10.0 * slots / double(whole_units)), true, 0, false);
+            consider(1.2 * (6.0 + 4.6 * chunk_scale * whole_units * n_chunks / slots + std::min(90.0, 10.0 * slots / double(whole_units))), true, 0, false);
         // one filter block per workgroup, every wave its own channels
         if (can_priv) {
             const LoneTiles t = lone_tiles(patches, px, 0, blocks, slots);
-            const double tiles = p.vec ? double(t.tiles) : double(n_tiles), start = p.vec ? 2.5 : 0.0;
             const LoneTiles t2 = lone_tiles(patches, px, 0, 2 * blocks, slots);
-            consider(start + std::ceil(tiles * blocks / slots) * lone(visits, recs, t.cut), false, 4, true);
-            // two of the block's four filters per workgroup, where there are not enough blocks for the chip
-            if (p.vec)
-                consider(start + std::ceil(2.0 * t2.tiles * blocks / slots) * lone(double(h->tiled.half_visits) / (2 * blocks), recs / 2, t2.cut), false, 4, true, true);
+            if (p.vec) {
+                int waves = 16;
+                const double t_all = lone_best(double(t.tiles) * blocks, visits, recs, t.cut, waves);
+                consider(t_all, false, 4, true, false, waves);
+                // two of the block's four filters per workgroup, where there are not enough blocks for the chip
+                consider(lone_time(16, 2.0 * t2.tiles * blocks, double(h->tiled.half_visits) / (2 * blocks), recs / 2, t2.cut), false, 4, true, true);
+            } else {
+                consider(std::ceil(double(n_tiles) * blocks / slots) * lone_last, false, 4, true);
+            }
         }
     }
     if (force_split >= 0) { p.split = can_split && force_split != 0; p.one_set = p.split && force_split == 2; if (p.split) { p.ks_log2 = 0; p.priv = false; } }
     if (force_ks >= 0) {
         p.priv = force_ks >= 4 && can_priv;
         p.halves = force_ks == 5 && p.priv;
+        p.lone_waves = force_ks == 6 ? 8 : force_ks == 7 ? 4 : 16;
         p.ks_log2 = p.priv ? 4 : force_ks < 4 ? force_ks : 0;
         if (p.priv) p.split = p.one_set = false;
     }
@@ -1293,7 +1334,9 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
 void describe_tiled_plan(const pconv_handle *h, int n, int hin, int win, int stride, int layout, bool pool, pconv_plan &out)
 {
     const TiledPlan p = plan_tiled(h, n, hin, win, layout, h->wdtype, pool, stride == 2);
-    out.waves = p.nw; out.ks_log2 = p.priv && p.halves ? 5 : p.ks_log2;
+    const int lone_waves = p.vec && p.priv ? p.lone_waves : 16;
+    out.waves = lone_waves == 16 ? p.nw : lone_waves;
+    out.ks_log2 = p.priv && p.halves ? 5 : p.ks_log2;
     out.split_units = p.split ? (p.one_set ? 2 : 1) : 0;
     out.tail_tiles = p.tail_tiles;
     if (p.vec && (p.priv || p.tail_tiles > 0)) {
@@ -1378,15 +1421,15 @@ int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float
     // Channels last: waves on their own store that way themselves, four bytes at a time, up to 6 MB (0.86 us a MB for
     // 3 us and 0.36 a MB); what the others have stored changes its layout.
     const int64_t out_bytes = int64_t(n) * h->c_out * ((hin - 1) / stride + 1) * ((win - 1) / stride + 1) * 4;
-    const bool stores_last = y_last && vec && plan.priv && out_bytes < 6000000;
-    auto lone = [&](bool halves, int64_t patch_base) {
+    const bool stores_last = y_last && vec && plan.priv && plan.lone_waves == 16 && out_bytes < 6000000;
+    auto lone = [&](bool halves, int waves, int64_t patch_base) {
         return launch_conv_lone(h, static_cast<const float *>(x), stores_last ? y_last : static_cast<float *>(y), bias, n, hin, win, stride, relu,
-                                pool, halves, patch_base, stores_last, stream);
+                                pool, halves, waves, patch_base, stores_last, stream);
     };
-    hipError_t e = vec && plan.priv ? lone(plan.halves, 0)
+    hipError_t e = vec && plan.priv ? lone(plan.halves, plan.lone_waves, 0)
                    : nw == 16       ? launch_any<16, 8>(a, wgs, st, vec, layout, dtype, h->device)
                                     : launch_any<8, 4>(a, wgs, st, vec, layout, dtype, h->device);
-    if (e == hipSuccess && plan.tail_tiles > 0) e = lone(false, lone_base(int64_t(a.n_tiles) * 64, a.px));
+    if (e == hipSuccess && plan.tail_tiles > 0) e = lone(false, plan.lone_waves, lone_base(int64_t(a.n_tiles) * 64, a.px));
     if (e != hipSuccess) {
         set_error(std::string("pconv_conv2d (tiled kernel): ") + hipGetErrorName(e));
         return PCONV_HIP_ERROR;
