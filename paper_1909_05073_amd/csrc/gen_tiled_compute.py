@@ -226,6 +226,7 @@ def main():
     write_inc(out, generate())
     write_inc(os.path.join(os.path.dirname(out), "pconv_tiled_compute_scalar.inc"), generate(True))
     write_inc(os.path.join(os.path.dirname(out), "pconv_tiled_compute_sub2.inc"), generate(sub2=True))
+    write_inc(os.path.join(os.path.dirname(out), "pconv_tiled_compute_scalar_sub2.inc"), generate(True, True))
     write_inc(os.path.join(os.path.dirname(out), "pconv_tiled_patch_shifted.inc"), generate_patch_shifted())
     write_inc(os.path.join(os.path.dirname(out), "pconv_tiled_takeover.inc"), generate_takeover())
     write_code_header(os.path.join(os.path.dirname(out), "pconv_tiled_code_masks.inc"))

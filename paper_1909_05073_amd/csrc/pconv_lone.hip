@@ -59,8 +59,9 @@ struct LoneArgs {
 };
 
 // OVER: columns by which the last patch of a row is shifted left.  CUT: tiles may begin and end inside a row.  LAST:
-// outputs with channels last.  NW: waves.
-template <int OVER, bool CUT, bool LAST, int NW>
+// outputs with channels last.  NW: waves.  SUB2: stride 2 with all patches starting at even columns (an even width): only
+// the outputs that are stored are formed, a quarter of the FMAs, out of the first five rows and the column to the left.
+template <int OVER, bool CUT, bool LAST, int NW, bool SUB2>
 __global__ void __launch_bounds__(NW * 64, 4)      // 4 waves per SIMD: at most 128 VGPRs
 conv_lone_kernel(const LoneArgs a)
 {
@@ -101,13 +102,14 @@ conv_lone_kernel(const LoneArgs a)
     Visit now = visit_at(v), next = visit_at(after(v));
     const uint32_t k_lo = visits[2 * v_lo];
     // what the end needs: filter and bias of the slots that this wave adds up: one in each pass, both with four waves
-    constexpr int SLOTS = NW < 8 ? FB : FB / 2, PER_PASS = 2 * SLOTS / FB;
+    // (SUB2: one, all in one pass)
+    constexpr int SLOTS = SUB2 ? 1 : NW < 8 ? FB : FB / 2, PER_PASS = 2 * SLOTS / FB;
     const int u = NW < 8 ? 0 : (wave >> 2) & 1, i = wave & 3;
     int filter[SLOTS];
     float slot_bias[SLOTS];
 #pragma unroll
     for (int k = 0; k < SLOTS; ++k) {
-        filter[k] = int(constant(a.slot_filter)[fblk * FB + (NW < 8 ? k : 2 * k + u)]);
+        filter[k] = int(constant(a.slot_filter)[fblk * FB + (SUB2 ? wave & (FB - 1) : NW < 8 ? k : 2 * k + u)]);
         slot_bias[k] = a.bias && filter[k] >= 0 ? __uint_as_float(constant(a.bias)[filter[k]]) : 0.0f;
     }
 
@@ -157,7 +159,7 @@ conv_lone_kernel(const LoneArgs a)
     auto load_rows = [&](int c) {
         const int at = __builtin_amdgcn_readfirstlane(int(uint32_t(c) * plane));
 #pragma unroll
-        for (int r = 0; r < 6; ++r) rows[r] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(xbuf, int(row_at[r]), at, 0));
+        for (int r = 0; r < (SUB2 ? 5 : 6); ++r) rows[r] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(xbuf, int(row_at[r]), at, 0));
         if (CUT) outer = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, int(outer_at), at, 0));
     };
     if (n_visits > 0) load_rows(int(now.channel_count & 0xFFFFu));
@@ -182,11 +184,18 @@ conv_lone_kernel(const LoneArgs a)
     };
     fetch_batch(k_lo);
     uint32_t word0 = meta[now.record], word1 = meta[now.record + 1];           // (the stream is padded)
+    // the registers of the record loop
+    v16f in0, in1;
+    v4f in2;
+    if (SUB2) {                                    // (what is never read has to have a value)
+        rows[5] = v4f{zero, zero, zero, zero};
+#pragma unroll
+        for (int e = 0; e < 16; ++e) in1[e] = zero;
+        in2 = rows[5];
+    }
     for (int left = n_visits; left > 0; --left) {
         const uint32_t k = now.record, k_end = k + (now.channel_count >> 16);
         // the lane's 6x6 neighbourhood, in the order of the record loop's registers
-        v16f in0, in1;
-        v4f in2;
         float l[6], r6[6];
         {
             const uint32_t maskl = mask(0), maskr = mask(1);
@@ -202,46 +211,63 @@ conv_lone_kernel(const LoneArgs a)
             }
             // (lane 0 and lane 63 have nothing to read: zero, or see below; a lane shift may read a
             // register that a vector instruction wrote only after two more instructions)
-            asm("s_nop 1\n"
 #define PCONV_SHIFT(to, from, mask, way) "v_and_b32_dpp %" #to ", %" #from ", %" #mask " " way ":1 row_mask:0xf bank_mask:0xf bound_ctrl:0\n"
+            if constexpr (SUB2)
+                asm("s_nop 1\n"
+                    PCONV_SHIFT(0, 5, 10, "wave_shr") PCONV_SHIFT(1, 6, 10, "wave_shr") PCONV_SHIFT(2, 7, 10, "wave_shr")
+                    PCONV_SHIFT(3, 8, 10, "wave_shr") PCONV_SHIFT(4, 9, 10, "wave_shr")
+                    : "=&v"(l[0]), "=&v"(l[1]), "=&v"(l[2]), "=&v"(l[3]), "=&v"(l[4])
+                    : "v"(from_l[0]), "v"(from_l[1]), "v"(from_l[2]), "v"(from_l[3]), "v"(from_l[4]), "v"(maskl));
+            else
+            asm("s_nop 1\n"
                 PCONV_SHIFT(0, 12, 24, "wave_shr") PCONV_SHIFT(1, 13, 24, "wave_shr") PCONV_SHIFT(2, 14, 24, "wave_shr")
                 PCONV_SHIFT(3, 15, 24, "wave_shr") PCONV_SHIFT(4, 16, 24, "wave_shr") PCONV_SHIFT(5, 17, 24, "wave_shr")
                 PCONV_SHIFT(6, 18, 25, "wave_shl") PCONV_SHIFT(7, 19, 25, "wave_shl") PCONV_SHIFT(8, 20, 25, "wave_shl")
                 PCONV_SHIFT(9, 21, 25, "wave_shl") PCONV_SHIFT(10, 22, 25, "wave_shl") PCONV_SHIFT(11, 23, 25, "wave_shl")
-#undef PCONV_SHIFT
                 : "=&v"(l[0]), "=&v"(l[1]), "=&v"(l[2]), "=&v"(l[3]), "=&v"(l[4]), "=&v"(l[5]),
                   "=&v"(r6[0]), "=&v"(r6[1]), "=&v"(r6[2]), "=&v"(r6[3]), "=&v"(r6[4]), "=&v"(r6[5])
                 : "v"(from_l[0]), "v"(from_l[1]), "v"(from_l[2]), "v"(from_l[3]), "v"(from_l[4]), "v"(from_l[5]),
                   "v"(from_r[0]), "v"(from_r[1]), "v"(from_r[2]), "v"(from_r[3]), "v"(from_r[4]), "v"(from_r[5]),
                   "v"(maskl), "v"(maskr));
+#undef PCONV_SHIFT
             if (CUT) {
                 const uint32_t mask0 = mask(4), mask63 = mask(5);
 #pragma unroll
-                for (int r = 0; r < 6; ++r) {
+                for (int r = 0; r < (SUB2 ? 5 : 6); ++r) {
                     l[r] = __uint_as_float(__float_as_uint(l[r]) | (uint32_t(__builtin_amdgcn_readlane(__float_as_int(outer), 2 * r)) & mask0));
-                    r6[r] = __uint_as_float(__float_as_uint(r6[r]) | (uint32_t(__builtin_amdgcn_readlane(__float_as_int(outer), 2 * r + 1)) & mask63));
+                    if (!SUB2) r6[r] = __uint_as_float(__float_as_uint(r6[r]) | (uint32_t(__builtin_amdgcn_readlane(__float_as_int(outer), 2 * r + 1)) & mask63));
                 }
             }
         }
 #pragma unroll
         for (int e = 0; e < 16; ++e) in0[e] = rows[e >> 2][e & 3];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) in1[e] = rows[4 + (e >> 2)][e & 3];
+        for (int e = 0; e < (SUB2 ? 4 : 8); ++e) in1[e] = rows[4 + (e >> 2)][e & 3];
 #pragma unroll
-        for (int e = 0; e < 6; ++e) in1[8 + e] = l[e];
-        in1[14] = r6[0]; in1[15] = r6[1];
+        for (int e = 0; e < (SUB2 ? 5 : 6); ++e) in1[8 + e] = l[e];
+        if (!SUB2) {
+            in1[14] = r6[0]; in1[15] = r6[1];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) in2[e] = r6[2 + e];
+            for (int e = 0; e < 4; ++e) in2[e] = r6[2 + e];
+        }
         // (a visit has at most 36 records: four kernels of nine taps)
         if (k < kb || k_end > kb + kBatch) fetch_batch(k);
-        asm volatile(
+#define PCONV_RECORD_LOOP_OPERANDS \
+                : "+{v[64:79]}"(acc[0]), "+{v[80:95]}"(acc[1]), "+{v[96:111]}"(acc[2]), "+{v[112:127]}"(acc[3]), \
+                  "+{v[28:43]}"(in0), "+{v[44:59]}"(in1), "+{v[60:63]}"(in2) \
+                : [w0] "s"(word0 & ~kMetaFirstOfChannel), [w1] "s"(word1), [va] "v"(beside), \
+                  [wa] "s"(wa + (k - kb) * 16u), [mp] "s"(a.meta), [koff] "s"(k * 4u), [nb] "s"(k_end - k), [chmask] "n"(0) \
+                : "v22", "v23", "v24", "v25", "v26", "v27", \
+                  "s84", "s85", "s86", "s90", "s91", "s92", "s93", "s94", "s95", "scc", "memory"
+        if constexpr (SUB2)
+            asm volatile(
+#include "pconv_tiled_compute_scalar_sub2.inc"
+                PCONV_RECORD_LOOP_OPERANDS);
+        else
+            asm volatile(
 #include "pconv_tiled_compute_scalar.inc"
-                : "+{v[64:79]}"(acc[0]), "+{v[80:95]}"(acc[1]), "+{v[96:111]}"(acc[2]), "+{v[112:127]}"(acc[3]),
-                  "+{v[28:43]}"(in0), "+{v[44:59]}"(in1), "+{v[60:63]}"(in2)
-                : [w0] "s"(word0 & ~kMetaFirstOfChannel), [w1] "s"(word1), [va] "v"(beside),
-                  [wa] "s"(wa + (k - kb) * 16u), [mp] "s"(a.meta), [koff] "s"(k * 4u), [nb] "s"(k_end - k), [chmask] "n"(0)
-                : "v22", "v23", "v24", "v25", "v26", "v27",
-                  "s84", "s85", "s86", "s90", "s91", "s92", "s93", "s94", "s95", "scc", "memory");
+                PCONV_RECORD_LOOP_OPERANDS);
+#undef PCONV_RECORD_LOOP_OPERANDS
         if (left == 1) break;
         // the input registers are free: the next channel, and what is needed to know the one after it
         load_rows(int(next.channel_count & 0xFFFFu));
@@ -259,6 +285,29 @@ conv_lone_kernel(const LoneArgs a)
     asm volatile("" : "+v"(lane_e));
     const Patch patch = patch_of(lane_e);
     const int n = patch.n, y0 = patch.y0, x0 = patch.x0;
+    if constexpr (SUB2) {
+        // four outputs of a patch, all slots at once: wave s adds up slot s
+        if (wave < parts) {
+#pragma unroll
+            for (int k = 0; k < FB; ++k)
+                if (half < 0 || (k >> 1) == half) red[(wave * FB + k) * 64 + lane] = v4f{acc[k][0], acc[k][2], acc[k][8], acc[k][10]};
+        }
+        __syncthreads();
+        if (wave >= FB || (half >= 0 && (wave >> 1) != half) || filter[0] < 0 || !patch.valid) return;
+        v4f sum = red[wave * 64 + lane];
+#pragma unroll 8
+        for (int p = 1; p < parts; ++p) sum += red[(p * FB + wave) * 64 + lane];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            sum[k] += slot_bias[0];
+            if (a.relu) sum[k] = fmaxf(sum[k], 0.0f);
+        }
+        const int h2 = (a.h + 1) >> 1, w2 = a.w >> 1;
+        float *dst = a.y + ((size_t(n) * a.c_out + filter[0]) * h2 + (y0 >> 1)) * w2 + (x0 >> 1);
+        dst[0] = sum[0]; dst[1] = sum[1];
+        if (y0 + 2 < a.h) { dst[w2] = sum[2]; dst[w2 + 1] = sum[3]; }
+        return;
+    }
     auto store_rows = [&](int k, int u) {
         if (wave >= 8 || (a.pool && i >= 2) || (a.sub2 && (i & 1)) || !patch.valid) return;
         const int f = filter[k];
@@ -324,7 +373,7 @@ conv_lone_kernel(const LoneArgs a)
     }
 }
 
-template <int OVER, bool CUT, bool LAST, int NW>
+template <int OVER, bool CUT, bool LAST, int NW, bool SUB2 = false>
 hipError_t launch_lone(const LoneArgs &a, unsigned wgs, hipStream_t st, int dev)
 {
     constexpr size_t kLdsBytes = size_t(NW) * (kBatch + 2 * 4 * 64) * 16;   // weights and sums of two slots of every wave: 144 KB for 16
@@ -332,12 +381,12 @@ hipError_t launch_lone(const LoneArgs &a, unsigned wgs, hipStream_t st, int dev)
     // value by every thread that gets here first).
     static std::atomic<bool> attr_done[64];
     if (dev < 0 || dev >= 64 || !attr_done[dev].load(std::memory_order_acquire)) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_lone_kernel<OVER, CUT, LAST, NW>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_lone_kernel<OVER, CUT, LAST, NW, SUB2>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, int(kLdsBytes));
         if (e != hipSuccess) return e;
         if (dev >= 0 && dev < 64) attr_done[dev].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((conv_lone_kernel<OVER, CUT, LAST, NW>), dim3(wgs), dim3(NW * 64), kLdsBytes, st, a);
+    hipLaunchKernelGGL((conv_lone_kernel<OVER, CUT, LAST, NW, SUB2>), dim3(wgs), dim3(NW * 64), kLdsBytes, st, a);
     return hipGetLastError();
 }
 
@@ -385,6 +434,10 @@ hipError_t launch_conv_lone(const pconv_handle *h, const float *x, float *y, con
     auto launch = [&](auto over, auto cut) {
         constexpr int O = over.value;
         constexpr bool C = cut.value;
+        if constexpr (O % 2 == 0)
+            if (a.sub2 && !last)
+                return waves == 16 ? launch_lone<O, C, false, 16, true>(a, wgs, st, h->device)
+                       : waves == 8 ? launch_lone<O, C, false, 8, true>(a, wgs, st, h->device) : launch_lone<O, C, false, 4, true>(a, wgs, st, h->device);
         if (last)                                        // (16 waves only: see launch_conv_tiled)
             return launch_lone<O, C, true, 16>(a, wgs, st, h->device);
         return waves == 16 ? launch_lone<O, C, false, 16>(a, wgs, st, h->device)

@@ -1194,9 +1194,8 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
     auto units_of = [&](int ks) { return (blocks + (p.nw >> ks) - 1) / (p.nw >> ks); };   // filter groups per tile
     const double records = double(h->tiled.meta.size()) * p.nw / blocks / n_chunks;       // of a whole unit's chunk
     const double visits = double(h->tiled.visits) / blocks, recs = double(h->tiled.meta.size()) / blocks;
-    // Stride 2 is priced as stride 1, although whole units with even widths do a quarter of the FMAs: staging is what
-    // such a unit takes its time for, and of 16 layers with stride 2 (32 to 512 channels, 14 to 224 pixels
-    // square, 1 to 64 images) the form chosen is the fastest of all that can be pinned.
+    // Whole units with stride 2 are priced as with stride 1, although with even widths they do a quarter of the FMAs: staging
+    // is what such a unit takes its time for.
     // Waves on their own.  fp32 NCHW (pconv_lone.hip), 16, 8 or 4 waves per workgroup, so that a compute unit holds one, two
     // or four: `units` workgroups of v visited channels and r records.  A round is a start and an end and the work of
     // the workgroups of a compute unit, which takes longer per workgroup where fewer than four waves share a SIMD.
@@ -1209,7 +1208,7 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
     auto lone_time = [&](int waves, double units, double v, double r, bool cut) {
         const LoneCost &c = kLoneCost[waves == 16 ? 0 : waves == 8 ? 1 : 2];
         const int most = 16 / waves;
-        const double n = std::ceil(units / cus), full = std::floor(n / most), work = (c.visit * v + c.record * r) * (cut ? 1.17 : 1.0);
+        const double n = std::ceil(units / cus), full = std::floor(n / most), work = (c.visit * v + c.record * r) * (cut ? 1.17 : 1.0) * (sub2 && win % 2 == 0 ? 0.7 : 1.0);
         const int left = int(n - full * most);
         return c.base + full * (c.round + most * work) + (left > 0 ? c.round + c.work[left - 1] * work : 0.0);
     };
@@ -1421,7 +1420,7 @@ int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float
     // Channels last: waves on their own store that way themselves, four bytes at a time, up to 6 MB (0.86 us a MB for
     // 3 us and 0.36 a MB); what the others have stored changes its layout.
     const int64_t out_bytes = int64_t(n) * h->c_out * ((hin - 1) / stride + 1) * ((win - 1) / stride + 1) * 4;
-    const bool stores_last = y_last && vec && plan.priv && plan.lone_waves == 16 && out_bytes < 6000000;
+    const bool stores_last = y_last && vec && plan.priv && plan.lone_waves == 16 && out_bytes < 6000000 && !(a.sub2 && win % 2 == 0);
     auto lone = [&](bool halves, int waves, int64_t patch_base) {
         return launch_conv_lone(h, static_cast<const float *>(x), stores_last ? y_last : static_cast<float *>(y), bias, n, hin, win, stride, relu,
                                 pool, halves, waves, patch_base, stores_last, stream);
