@@ -1289,18 +1289,23 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
         // @56: 133, 98, 84 us; register staging, which nothing overlaps, 2.4 and 4.8 in quads of
         // channels, 8 and 4 otherwise, all with few units: a full chip stages slower, see
         // stage_quads); an eighth of the tiles shares the compute units of one XCD
+        // (`full`: more than a quarter of the chip's workgroups of 16 waves: they start together, and the memory shows;
+        // priced as alone, 8 to 512 channels @80 with stride 2, two images took 13.7 us for the 9.1 of waves on their own,
+        // 16 to 128 @112, three images 17.0 for 14.6, 32 to 256 @56, eight images 23.8 for 20.1; with 8 waves, 3 channels
+        // @224, one image, the channels split two ways in 196 workgroups are still faster than 98 whole units, 12.1 for 13.6)
         const bool quads = layout == PCONV_NHWC && h->c_in % 4 == 0;
         const double t_stage = p.vec ? 2.0 : quads ? 2.4 : 8.0, t_records = p.vec ? 1.9 : quads ? 4.8 : 4.0;
         const double chunk_scale = p.nw == 16 ? 1.0 : 0.5;
         for (int ks = 0; ks <= 2; ++ks) {
             if (ks > 0 && int64_t(n_tiles) * units_of(ks - 1) > slots / 2) break;
             const double rounds = std::ceil(double((n_tiles + 7) / 8) * units_of(ks) / (slots / 8.0));
-            consider(rounds * (6.0 + chunk_scale * n_chunks * (t_stage + t_records * records / 142.0 / (1 << ks))), false, ks, false);
+            const bool full = p.vec && p.nw == 16 && int64_t(n_tiles) * units_of(ks) > slots / 4;
+            consider(rounds * ((full ? 10.0 : 6.0) + (full ? 1.08 : 1.0) * chunk_scale * n_chunks * (t_stage + t_records * records / 142.0 / (1 << ks))), false, ks, false);
         }
         // units shared by P workgroups, which pass the sums on one after the other (256 channels @56, one
-        // image: 99 us, four: 83; 256 @28, 24 images 111, 512 to 200 @40, eight images 159)
+        // image: 99 us, four: 83; 192 to 128 @56, 12 images 106, waves on their own 85)
         if (can_split)
-            consider(1.2 * (6.0 + 4.6 * chunk_scale * whole_units * n_chunks / slots + std::min(90.0, 10.0 * slots / double(whole_units))), true, 0, false);
+            consider(1.45 * (6.0 + 4.6 * chunk_scale * whole_units * n_chunks / slots + std::min(90.0, 10.0 * slots / double(whole_units))), true, 0, false);
         // one filter block per workgroup, every wave its own channels
         if (can_priv) {
             const LoneTiles t = lone_tiles(patches, px, 0, blocks, slots);
