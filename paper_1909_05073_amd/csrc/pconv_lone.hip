@@ -1,20 +1,20 @@
-// fp32 PCONV for layers with few to middling numbers of units of work: every wave on its own (NCHW, stride 1 and, storing every
-// other output, stride 2).
+// fp32 PCONV for layers with few to middling numbers of units of work: every wave on its own (NCHW, stride 1 and 2).
 //
 // A workgroup is one tile of up to 64 patches (4x4 output pixels, one per lane) and one block of four
 // filters, or two of its four slots (halves, where there are too few blocks for the chip).  Its waves, 16, 8 or 4
-// (one, two or four workgroups to a compute unit), share out the visits of those filters: the channels that have a record, in an order and in portions fixed
-// at pack time.  A wave loads the six input rows of a channel straight into the registers of the record
+// (one, two or four workgroups to a compute unit), share out the visits of those filters: the channels that have a
+// record, in an order fixed at pack time.  A wave loads the six input rows of a channel straight into the registers of the record
 // loop, takes the columns beside the patch out of the neighbouring lanes, runs the records and goes on:
 // nothing is staged and there is nothing to wait for but its own loads.  The visit after next is read from
-// the list and the first record words are on their way while the rows are.  At the end the 16 partial
+// the list and the first record words are on their way while the rows are.  At the end the partial
 // sums are added through LDS.
 //
 // What bounds it: the issue of vector instructions.  A visit has 97 FMAs (1.5 records) of 2.4 cycles and 12 moves between
 // lanes, and takes 1360 cycles of a wave in the oldest four of 16 waves and 1910 in the youngest (hence portions by
-// age, see the packer); its six 1 KB loads take 100 cycles of the vector-memory pipe per wave.  (Staging the rows
-// through LDS, which needs one to five loads for six, is no faster.)  Start 3600 cycles, sums and stores 5000 with 16
-// waves.  One image, us: 256 channels @56 16.4, 512 @14 19, 512 @28 22.5, 16 @16 5.2 for the kernel.
+// age, see the packer); its six 1 KB loads take 100 cycles of the vector-memory pipe per wave.  (The rows staged in LDS
+// as one run of memory, one to five loads for six, the next channel's under the records: 19.8 us for 18.1 on that layer,
+// 512 @14, 32 images, 4 waves 104 for 92.)  Start 3600 cycles, sums and stores 5000 with 16
+// waves.  One image, us: 256 channels @56 16.5, 512 @14 18.6, 512 @28 22, 16 @16 5.2 for the kernel.
 //
 // Waves of a workgroup.  With 16 the end of every workgroup, its start and a last round of few workgroups leave the
 // compute unit to itself; with 8 or 4 other workgroups run meanwhile and a round is half or a quarter as long, but too few
