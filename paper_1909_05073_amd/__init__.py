@@ -330,12 +330,27 @@ def conv2d(handle: Handle, x, bias=None, stride: int = 1, relu: bool = False, la
     return out
 
 
+def _graph_pool_serves(device) -> bool:
+    """While the current stream is being captured: whether torch's allocator knows and serves it out of the graph's own pool.
+
+    A graph that is captured otherwise keeps the address of a tensor that is gone when the call returns."""
+    import torch
+    try:
+        at = torch.empty(1, dtype=torch.uint8, device=device).data_ptr()
+        return any(s["address"] <= at < s["address"] + s["total_size"] and tuple(s["segment_pool_id"]) != (0, 0)
+                   for s in torch.cuda.memory_snapshot())
+    except (RuntimeError, KeyError):
+        return False
+
+
 def _conv2d_ws(handle: Handle, x, bias, stride, relu, out, n, h, w):
     """conv2d of fp32 tensors with channels last: lends the call work space out of torch's pool, if there is any."""
     import torch
     L = _lib or lib()
     size = L.pconv_conv2d_workspace(handle.ptr, n, h, w, stride, NHWC, F32)
     work = None
+    if size > 0 and torch.cuda.is_current_stream_capturing() and not _graph_pool_serves(x.device):
+        size = 0
     if size > 0:
         try:
             work = torch.empty(size, dtype=torch.uint8, device=x.device)
