@@ -167,7 +167,9 @@ void set_flat_shape(int index);
 // masked weights of a bf16 handle in the matrix-core kernel's layout (see pconv_handle::d_wdense)
 void build_dense_taps(const Canonical &cn, const uint16_t *table, int c_out, int c_in,
                       std::vector<uint16_t> &wd, std::vector<uint32_t> &nz);
-// dst[n][c][r] = src[n][r][c], floats
+// dst[n][c][r] = src[n][r][c], floats, by tiles of 64 x 64.  A launch has fewer than 2^32 threads, 256 to a tile.
+constexpr int64_t kTransposeMaxTiles = (1 << 24) - 1;
+inline int64_t transpose_tiles(int64_t n, int64_t rows, int64_t cols) { return n * ((rows + 63) / 64) * ((cols + 63) / 64); }
 int launch_transpose(const float *src, float *dst, int n, int rows, int cols, void *stream);
 int launch_maxpool2x2(const void *x, void *y, int n, int c, int h, int w, int layout, int dtype,
                       void *stream);

@@ -176,8 +176,8 @@ int launch_conv_generic(const pconv_handle *h, const void *x, void *y, const flo
 int launch_transpose(const float *src, float *dst, int n, int rows, int cols, void *stream)
 {
     const int tiles_c = (cols + 63) / 64;
-    const int64_t tiles = int64_t((rows + 63) / 64) * tiles_c, total = tiles * n;
-    if (total > 0x3FFFFFFF) { set_error("pconv_conv2d: too many workgroups"); return PCONV_UNSUPPORTED; }
+    const int64_t tiles = transpose_tiles(1, rows, cols), total = tiles * n;
+    if (total > kTransposeMaxTiles) { set_error("pconv_conv2d: too many workgroups"); return PCONV_UNSUPPORTED; }
     hipLaunchKernelGGL(transpose_kernel, dim3(unsigned(total)), dim3(256), 0, static_cast<hipStream_t>(stream), src, dst, rows, cols,
                        tiles_c, int(tiles), make_fast_div(uint32_t(tiles_c)), make_fast_div(uint32_t(tiles)));
     return check_launch("pconv_conv2d (change of layout)");

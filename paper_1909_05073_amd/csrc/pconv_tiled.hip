@@ -1095,9 +1095,11 @@ bool tiled_preferred(int hin, int win, int stride)
 bool tiled_nchw_preferred(const pconv_handle *h, int n, int hin, int win, int stride)
 {
     const bool pinned = g_force_waves.load() || g_force_ks.load() >= 0 || g_force_split.load() >= 0;
+    const int64_t pixels_out = int64_t((hin - 1) / stride + 1) * ((win - 1) / stride + 1);
     const double x_mb = double(n) * h->c_in * hin * win * 4e-6;
-    const double y_mb = double(n) * h->c_out * ((hin - 1) / stride + 1) * ((win - 1) / stride + 1) * 4e-6;
+    const double y_mb = double(n) * h->c_out * pixels_out * 4e-6;
     if (pinned || win < 4 || int64_t(n) * h->c_in * hin * win * 4 >= (int64_t(1) << 31) ||
+        transpose_tiles(n, int64_t(hin) * win, h->c_in) > kTransposeMaxTiles || transpose_tiles(n, h->c_out, pixels_out) > kTransposeMaxTiles ||
         !tiled_supported(h, n, hin, win, stride, PCONV_NCHW, PCONV_F32) || !tiled_preferred(hin, win, stride))
         return false;
     const bool quads = h->c_in % 4 == 0;

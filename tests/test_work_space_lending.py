@@ -132,3 +132,33 @@ def test_a_capture_that_torch_does_not_know_of():
     hip("hipGraphExecDestroy", ready)
     hip("hipGraphDestroy", graph)
     h.free()
+
+
+@pytest.mark.gpu
+def test_more_images_than_a_transpose_has_workgroups():
+    """A launch has fewer than 2^32 threads, and every image takes a workgroup of 256: 2^24 images are left to the
+    kernel that takes them as they are, one fewer is the largest call that is lent work space."""
+    import torch
+    most, ci, co, hh, ww = (1 << 24) - 1, 5, 2, 1, 4
+    spec = LayerSpec("many", 64, ci, co, hh, ww, keep_div=1.5, count_dist="bernoulli")
+    W = make_layer(spec, 7960)
+    h = P.pconv_pack(W["w"], W["pattern_id"], W["conn"], W["table"], "f32")
+    ask = lambda n: P.lib().pconv_conv2d_workspace(h.ptr, n, hh, ww, 1, P.NHWC, P.F32)
+    assert ask(most + 1) == 0 and ask(1 << 25) == 0 and ask(most) > 0
+    b = torch.from_numpy(W["bias"]).cuda()
+    wt = oracle.masked_weights(W["w"], W["pattern_id"], W["conn"], W["table"])
+    few = [make_input(spec, 7961 + k) for k in range(2)]
+    x = torch.randn((most + 1, hh, ww, ci), device="cuda", generator=torch.Generator("cuda").manual_seed(3))
+    for xk, part in zip(few, (x[:64], x[most - 64:most])):
+        part.copy_(torch.from_numpy(xk.transpose(0, 2, 3, 1).copy()))
+    ys = []
+    for n in (most, most + 1):
+        say(f"[case] {n} images of {ci} channels, {hh}x{ww}")
+        ys.append(P.conv2d(h, x[:n], b, layout="nhwc"))
+        torch.cuda.synchronize()
+        for xk, part in zip(few, (ys[-1][:64], ys[-1][most - 64:most])):
+            yr, sr = oracle.conv2d(xk, wt, W["bias"], pad=1)
+            assert_close(part.permute(0, 3, 1, 2).cpu().numpy().astype(np.float64), yr, sr, "f32", f"{n} images")
+    # at most 45 products in either order: 2 * 45 * 2^-24 of the sum of their sizes, which is below 100
+    assert float((ys[0] - ys[1][:most]).abs().max()) < 1e-3
+    h.free()
