@@ -144,7 +144,11 @@ int pconv_conv2d_static(const pconv_handle *h, const void *x_dev, void *y_dev, c
  * in stream order until the call's work is done, its contents are lost).  pconv_conv2d_workspace says how much a call makes
  * use of, 0 for most.  With less, or none, the call is pconv_conv2d.  With it, fp32 tensors with channels last are
  * laid out channels first before and back after the convolution, whose kernels for that layout take
- * half of the time or less; outputs are the same up to the order of the additions. */
+ * half of the time or less; outputs are the same up to the order of the additions.
+ * The space holds the inputs (rounded up to 256 bytes) and, unless the convolution stores them channels last itself, the
+ * outputs once more, so it may be as large as the call's own tensors together: the inputs are below 2 GiB, the outputs
+ * below 8.  A caller that is short of memory asks for nothing and passes none.  pconv_debug_plan of such a call with
+ * PCONV_NCHW is how the convolution runs, with PCONV_NHWC how the call runs without the space. */
 int64_t pconv_conv2d_workspace(const pconv_handle *h, int n, int h_in, int w_in, int stride, pconv_layout layout,
                                pconv_dtype act_dtype);
 int pconv_conv2d_ws(const pconv_handle *h, const void *x_dev, void *y_dev, const float *bias_dev, int n, int h_in, int w_in,

@@ -344,7 +344,10 @@ def _graph_pool_serves(device) -> bool:
 
 
 def _conv2d_ws(handle: Handle, x, bias, stride, relu, out, n, h, w):
-    """conv2d of fp32 tensors with channels last: lends the call work space out of torch's pool, if there is any."""
+    """conv2d of fp32 tensors with channels last: lends the call work space out of torch's pool, if there is any.
+
+    Up to the size of x and out together.  On a card with less to spare torch first gives its cached blocks back, which
+    waits for the device, and the call then runs without; pconv_conv2d takes none in the first place."""
     import torch
     L = _lib or lib()
     size = L.pconv_conv2d_workspace(handle.ptr, n, h, w, stride, NHWC, F32)

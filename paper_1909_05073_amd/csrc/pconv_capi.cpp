@@ -253,12 +253,13 @@ static int choose_kernel(const pconv_handle *h, int n, int h_in, int w_in, int s
     return can_tile && (policy == 2 || (policy == 0 && tiled_preferred(h_in, w_in, stride))) ? 2 : 1;
 }
 
-// where the outputs lie in the work space of a call whose layout is changed, in bytes
+// Work space of a call whose layout is changed: the inputs channels first, and where the outputs lie behind them unless
+// the convolution stores them channels last itself (bytes).
 static int64_t workspace_y(const pconv_handle *h, int n, int h_in, int w_in) { return (int64_t(n) * h->c_in * h_in * w_in * 4 + 255) / 256 * 256; }
 
 static int conv2d_impl(const pconv_handle *h, const void *x_dev, void *y_dev, const float *bias_dev,
                        int n, int h_in, int w_in, int stride, int pad, pconv_layout layout,
-                       pconv_dtype act_dtype, int fuse_relu, void *hip_stream, bool static_scratch, float *work = nullptr)
+                       pconv_dtype act_dtype, int fuse_relu, void *hip_stream, bool static_scratch, float *work = nullptr, int64_t work_bytes = 0)
 {
     if (!h || !x_dev || !y_dev) { set_error("pconv_conv2d: null pointer argument"); return PCONV_INVALID_ARG; }
     if (x_dev == y_dev) { set_error("pconv_conv2d: y_dev must not alias x_dev"); return PCONV_INVALID_ARG; }
@@ -278,7 +279,8 @@ static int conv2d_impl(const pconv_handle *h, const void *x_dev, void *y_dev, co
     if (const int rc = take_async_error(h, "pconv_conv2d")) return rc;
     if (work) {                                          // channels last: laid out channels first for the convolution
         if (const int rc = launch_transpose(static_cast<const float *>(x_dev), work, n, h_in * w_in, h->c_in, hip_stream)) return rc;
-        return launch_conv_tiled(h, work, work + workspace_y(h, n, h_in, w_in) / 4, bias_dev, n, h_in, w_in, stride, PCONV_NCHW, PCONV_F32,
+        float *const y_first = work_bytes > workspace_y(h, n, h_in, w_in) ? work + workspace_y(h, n, h_in, w_in) / 4 : nullptr;
+        return launch_conv_tiled(h, work, y_first, bias_dev, n, h_in, w_in, stride, PCONV_NCHW, PCONV_F32,
                                  fuse_relu ? 1 : 0, 0, hip_stream, false, static_cast<float *>(y_dev));
     }
     const int kernel = choose_kernel(h, n, h_in, w_in, stride, int(layout), int(act_dtype));
@@ -313,6 +315,7 @@ int64_t pconv_conv2d_workspace(const pconv_handle *h, int n, int h_in, int w_in,
     if (!h || n <= 0 || h_in <= 0 || w_in <= 0 || (stride != 1 && stride != 2) || h->device < 0) return 0;
     if (layout != PCONV_NHWC || act_dtype != PCONV_F32 || h->wdtype != PCONV_F32 || g_policy.load() != 0) return 0;
     if (!tiled_nchw_preferred(h, n, h_in, w_in, stride)) return 0;
+    if (tiled_stores_last(h, n, h_in, w_in, stride)) return workspace_y(h, n, h_in, w_in);
     const int ho = (h_in - 1) / stride + 1, wo = (w_in - 1) / stride + 1;
     return workspace_y(h, n, h_in, w_in) + int64_t(n) * h->c_out * ho * wo * 4;
 }
@@ -326,7 +329,7 @@ int pconv_conv2d_ws(const pconv_handle *h, const void *x_dev, void *y_dev, const
         return conv2d_impl(h, x_dev, y_dev, bias_dev, n, h_in, w_in, stride, pad, layout, act_dtype, fuse_relu, hip_stream, false);
     if (reinterpret_cast<uintptr_t>(work) % 16 != 0) { set_error("pconv_conv2d_ws: the work space must be aligned to 16 bytes"); return PCONV_INVALID_ARG; }
     return conv2d_impl(h, x_dev, y_dev, bias_dev, n, h_in, w_in, stride, pad, layout, act_dtype, fuse_relu, hip_stream, false,
-                       static_cast<float *>(work));
+                       static_cast<float *>(work), need);
 }
 
 int pconv_conv2d_pool2x2(const pconv_handle *h, const void *x_dev, void *y_dev, const float *bias_dev,

@@ -120,7 +120,7 @@ std::vector<uint32_t> build_lone_lists(const TiledStream &ts, const std::vector<
 int launch_conv_generic(const pconv_handle *h, const void *x, void *y, const float *bias, int n,
                         int hin, int win, int stride, int layout, int dtype, int relu, void *stream);
 // static_scratch: take the hand-over words from the code object's static array instead of the handle.  y_last: fp32
-// NCHW calls only, not with pool: where the outputs go with channels last; y is work space.
+// NCHW calls only, not with pool: where the outputs go with channels last; y is work space, and null where tiled_stores_last.
 int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float *bias, int n,
                       int hin, int win, int stride, int layout, int dtype, int relu, int pool, void *stream,
                       bool static_scratch = false, float *y_last = nullptr);
@@ -134,6 +134,8 @@ hipError_t launch_conv_lone(const pconv_handle *h, const float *x, float *y, con
                             int stride, int relu, int pool, bool halves, int waves, int64_t patch_base, bool last, void *stream);
 // whether an fp32 call with channels last is better off with its tensors' layout changed before and after
 bool tiled_nchw_preferred(const pconv_handle *h, int n, int hin, int win, int stride);
+// whether the convolution of such a call stores its outputs with channels last itself, so that launch_conv_tiled needs no y
+bool tiled_stores_last(const pconv_handle *h, int n, int hin, int win, int stride);
 // whether the tiled kernel can write the 2x2 max-pooled output directly (pool = 1)
 bool tiled_pool_supported(const pconv_handle *h, int n, int hin, int win, int layout, int dtype);
 bool tiled_supported(const pconv_handle *h, int n, int hin, int win, int stride, int layout, int dtype);

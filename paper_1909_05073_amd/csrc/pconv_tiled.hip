@@ -1335,7 +1335,21 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
     return p;
 }
 
+// Channels last: waves on their own store that way themselves, four bytes at a time, up to 6 MB (0.86 us a MB for
+// 3 us and 0.36 a MB); what the others have stored changes its layout.
+bool may_store_last(const pconv_handle *h, int n, int hin, int win, int stride)
+{
+    const int64_t out_bytes = int64_t(n) * h->c_out * ((hin - 1) / stride + 1) * ((win - 1) / stride + 1) * 4;
+    return out_bytes < 6000000 && !(stride == 2 && win % 2 == 0);
+}
+bool stores_last(const TiledPlan &p) { return p.vec && p.priv && p.lone_waves == 16; }
+
 }  // namespace
+
+bool tiled_stores_last(const pconv_handle *h, int n, int hin, int win, int stride)
+{
+    return may_store_last(h, n, hin, win, stride) && stores_last(plan_tiled(h, n, hin, win, PCONV_NCHW, PCONV_F32, false, stride == 2));
+}
 
 void describe_tiled_plan(const pconv_handle *h, int n, int hin, int win, int stride, int layout, bool pool, pconv_plan &out)
 {
@@ -1385,6 +1399,8 @@ int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float
     // in every replay.)
     if (plan.split && !static_scratch && is_capturing(static_cast<hipStream_t>(stream)))
         plan = plan_tiled(h, n, hin, win, layout, dtype, pool != 0, stride == 2, false);
+    const bool last = y_last && stores_last(plan) && may_store_last(h, n, hin, win, stride);
+    if (!y && !last) { set_error("pconv_conv2d_ws: launch choices were pinned while the call began"); return PCONV_UNSUPPORTED; }
     const int nw = plan.nw, ch = nw == 16 ? 8 : 4;
     const bool vec = plan.vec;
     const int slots = (h->cus > 0 ? h->cus : 256) * (16 / nw);
@@ -1424,13 +1440,9 @@ int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float
         wgs = a.priv ? (units + 7) / 8 * 8 : int64_t((a.n_tiles + 7) / 8) * 8 * a.n_groups;   // one per unit of the largest set, in every set
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // Channels last: waves on their own store that way themselves, four bytes at a time, up to 6 MB (0.86 us a MB for
-    // 3 us and 0.36 a MB); what the others have stored changes its layout.
-    const int64_t out_bytes = int64_t(n) * h->c_out * ((hin - 1) / stride + 1) * ((win - 1) / stride + 1) * 4;
-    const bool stores_last = y_last && vec && plan.priv && plan.lone_waves == 16 && out_bytes < 6000000 && !(a.sub2 && win % 2 == 0);
     auto lone = [&](bool halves, int waves, int64_t patch_base) {
-        return launch_conv_lone(h, static_cast<const float *>(x), stores_last ? y_last : static_cast<float *>(y), bias, n, hin, win, stride, relu,
-                                pool, halves, waves, patch_base, stores_last, stream);
+        return launch_conv_lone(h, static_cast<const float *>(x), last ? y_last : static_cast<float *>(y), bias, n, hin, win, stride, relu,
+                                pool, halves, waves, patch_base, last, stream);
     };
     hipError_t e = vec && plan.priv ? lone(plan.halves, plan.lone_waves, 0)
                    : nw == 16       ? launch_any<16, 8>(a, wgs, st, vec, layout, dtype, h->device)
@@ -1440,7 +1452,7 @@ int launch_conv_tiled(const pconv_handle *h, const void *x, void *y, const float
         set_error(std::string("pconv_conv2d (tiled kernel): ") + hipGetErrorName(e));
         return PCONV_HIP_ERROR;
     }
-    if (y_last && !stores_last)
+    if (y_last && !last)
         return launch_transpose(static_cast<const float *>(y), y_last, n, h->c_out, ((hin - 1) / stride + 1) * ((win - 1) / stride + 1), stream);
     return PCONV_OK;
 }

@@ -73,6 +73,45 @@ def test_work_space_changes_the_layout_and_nothing_else(shape):
     h.free()
 
 
+# (shape, waves, ks_log2, tiles cut rows, the convolution stores channels last itself): four slots and two (ks_log2 5),
+# whole rows and cut ones, every shift of the last patch of a row, stride 2; and what changes its layout afterwards: few
+# waves, an even width with stride 2, large outputs
+FORMS = [((4, 33, 64, 32, 70, 1), 16, 4, 0, True), ((8, 128, 128, 28, 27, 2), 16, 4, 0, True), ((8, 128, 128, 28, 28, 1), 16, 4, 0, True),
+         ((1, 40, 64, 83, 136, 1), 16, 4, 1, True), ((1, 99, 128, 67, 97, 1), 16, 4, 1, True), ((1, 99, 128, 67, 98, 1), 16, 4, 1, True),
+         ((1, 99, 128, 67, 99, 1), 16, 4, 1, True), ((8, 128, 33, 37, 87, 2), 16, 4, 1, True), ((1, 99, 128, 52, 76, 1), 16, 5, 1, True),
+         ((1, 64, 16, 10, 300, 1), 16, 5, 1, True), ((1, 64, 16, 10, 298, 1), 16, 5, 1, True), ((1, 64, 16, 10, 299, 2), 16, 5, 1, True),
+         ((2, 64, 64, 8, 8, 1), 16, 5, 0, True), ((2, 130, 20, 14, 14, 2), 16, 5, 0, False), ((8, 128, 128, 28, 28, 2), 16, 4, 0, False),
+         ((8, 128, 33, 37, 89, 2), 8, 4, 0, False), ((4, 17, 130, 61, 59, 1), 8, 4, 1, False), ((8, 40, 200, 40, 36, 1), 4, 4, 0, False)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,waves,ks_log2,cut,itself", FORMS)
+def test_work_space_is_what_the_form_of_a_call_uses(shape, waves, ks_log2, cut, itself):
+    import torch
+    n, ci, co, hh, ww, stride = shape
+    spec, L, x = make(shape, 7800 + ci)
+    h = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "f32")
+    plan = P.pconv_debug_plan(h, n, hh, ww, stride)
+    assert (plan.waves, plan.ks_log2, plan.lone_cut) == (waves, ks_log2, cut)
+    b = torch.from_numpy(L["bias"]).cuda()
+    xd = to_device(x, "f32")
+    xl = xd.permute(0, 2, 3, 1).contiguous()
+    size = P.lib().pconv_conv2d_workspace(h.ptr, n, hh, ww, stride, P.NHWC, P.F32)
+    first = P.conv2d(h, xd, b, stride=stride)
+    assert size == -(-xd.numel() * 4 // 256) * 256 + (0 if itself else first.numel() * 4)
+    say(f"[case] form {shape}: waves={waves} ks={ks_log2} cut={cut} stores channels last={itself}")
+    work = torch.full((size + 1024,), 0xA5, dtype=torch.uint8, device="cuda")
+    y = torch.full_like(first.permute(0, 2, 3, 1).contiguous(), float("nan"))
+    assert P.lib().pconv_conv2d_ws(h.ptr, xl.data_ptr(), y.data_ptr(), b.data_ptr(), n, hh, ww, stride, 1, P.NHWC, P.F32, 0,
+                                   torch.cuda.current_stream().cuda_stream or None, work.data_ptr(), size) == P.OK
+    torch.cuda.synchronize()
+    assert torch.equal(y.permute(0, 3, 1, 2), first) and bool((work[size:] == 0xA5).all())
+    wt = oracle.masked_weights(L["w"], L["pattern_id"], L["conn"], L["table"])
+    yr, sr = oracle.conv2d(x, wt, L["bias"], stride=stride, pad=1)
+    assert_close(first.cpu().numpy().astype(np.float64), yr, sr, "f32", f"form{shape}")
+    h.free()
+
+
 @pytest.mark.gpu
 def test_work_space_calls_under_capture():
     """The work space comes out of the graph's own pool; every replay sees its own input."""
