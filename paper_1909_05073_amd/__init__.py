@@ -71,6 +71,8 @@ def lib():
     L.pconv_conv2d_workspace.argtypes = [vp, ip, ip, ip, ip, ip, ip]
     L.pconv_conv2d_ws.restype = ip
     L.pconv_conv2d_ws.argtypes = [vp, vp, vp, vp, ip, ip, ip, ip, ip, ip, ip, ip, vp, vp, C.c_int64]
+    L.hipThreadExchangeStreamCaptureMode.restype = ip            # (of the HIP runtime, which the library is linked to)
+    L.hipThreadExchangeStreamCaptureMode.argtypes = [C.POINTER(ip)]
     L.pconv_conv2d_pool2x2.restype = ip
     L.pconv_conv2d_pool2x2.argtypes = [vp, vp, vp, vp, ip, ip, ip, ip, ip, ip, vp]
     L.pconv_free.restype = None
@@ -330,17 +332,28 @@ def conv2d(handle: Handle, x, bias=None, stride: int = 1, relu: bool = False, la
     return out
 
 
+_CAPTURE_MODE_RELAXED = 2                            # hipStreamCaptureModeRelaxed
+
+
 def _graph_pool_serves(device) -> bool:
     """While the current stream is being captured: whether torch's allocator knows and serves it out of the graph's own pool.
 
-    A graph that is captured otherwise keeps the address of a tensor that is gone when the call returns."""
+    A graph that is captured otherwise keeps the address of a tensor that is gone when the call returns.  Such a
+    capture in HIP's global or thread-local mode is made invalid by the queries of events that the allocator may have
+    outstanding, so it is asked in the relaxed mode."""
     import torch
+    mode = C.c_int(_CAPTURE_MODE_RELAXED)
+    exchange = (_lib or lib()).hipThreadExchangeStreamCaptureMode
+    if exchange(C.byref(mode)) != 0:
+        return False
     try:
         at = torch.empty(1, dtype=torch.uint8, device=device).data_ptr()
         return any(s["address"] <= at < s["address"] + s["total_size"] and tuple(s["segment_pool_id"]) != (0, 0)
                    for s in torch.cuda.memory_snapshot())
     except (RuntimeError, KeyError):
         return False
+    finally:
+        exchange(C.byref(mode))
 
 
 def _conv2d_ws(handle: Handle, x, bias, stride, relu, out, n, h, w):

@@ -16,7 +16,7 @@ class FakeLibrary:
     """Asks for work space and notes what it is lent."""
 
     def __init__(self):
-        self.lent = []
+        self.lent, self.mode, self.knows_modes = [], 0, True
 
     def pconv_conv2d_workspace(self, *call):
         return 4096
@@ -24,6 +24,12 @@ class FakeLibrary:
     def pconv_conv2d_ws(self, *call):
         self.lent.append(call[-2:])
         return P.OK
+
+    def hipThreadExchangeStreamCaptureMode(self, mode):
+        if not self.knows_modes:
+            return 1
+        self.mode, mode._obj.value = mode._obj.value, self.mode
+        return 0
 
 
 @pytest.fixture
@@ -40,6 +46,7 @@ def binding(monkeypatch):
         out = torch.zeros((1, 8, 8, 64))
         assert P._conv2d_ws(SimpleNamespace(ptr=1), x, None, 1, False, out, 1, 8, 8) is out
         return fake.lent.pop()
+    call.library = fake
     return call, monkeypatch, torch
 
 
@@ -73,6 +80,30 @@ def test_captured_calls_are_lent_memory_of_the_graph_or_none(binding, pool, lend
     assert (bool(ptr), size) == ((True, 4096) if lends else (False, 0))
 
 
+def test_the_allocator_is_asked_in_the_relaxed_mode_of_captures(binding):
+    """It queries the events that it has outstanding, which makes a capture in another mode invalid."""
+    call, monkeypatch, torch = binding
+    empty, asked, pool = torch.empty, [], [(0, 0)]
+
+    def note(size, **kw):
+        asked.append((size, call.library.mode))
+        return empty(size, **kw)
+    monkeypatch.setattr(torch, "empty", note)
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: True)
+    monkeypatch.setattr(torch.cuda, "memory_snapshot", lambda: [{"address": 0, "total_size": 1 << 62, "segment_pool_id": pool[0]}])
+    assert call() == (None, 0) and asked == [(1, 2)] and call.library.mode == 0
+    pool[0] = (3, 0)
+    assert call()[1] == 4096 and asked == [(1, 2), (1, 2), (4096, 0)] and call.library.mode == 0
+
+    def refuse(size, **kw):
+        raise RuntimeError("refused")
+    monkeypatch.setattr(torch, "empty", refuse)
+    assert call() == (None, 0) and call.library.mode == 0
+    call.library.knows_modes = False
+    monkeypatch.setattr(torch, "empty", note)
+    assert call() == (None, 0) and len(asked) == 3
+
+
 @pytest.mark.gpu
 def test_captures_of_torch_have_a_pool():
     import torch
@@ -86,8 +117,10 @@ def test_captures_of_torch_have_a_pool():
 
 
 @pytest.mark.gpu
-def test_a_capture_that_torch_does_not_know_of():
-    """Captured with the HIP runtime alone, the output given: nothing of torch's ordinary pool may get into the graph."""
+@pytest.mark.parametrize("outstanding", [False, True])
+def test_a_capture_that_torch_does_not_know_of(outstanding):
+    """Captured with the HIP runtime alone, the output given: nothing of torch's ordinary pool may get into the graph,
+    and the capture stays valid, also where torch's allocator has an event to query (outstanding)."""
     import torch
     L = P.lib()                                      # (the HIP runtime is a dependency of the library)
 
@@ -109,11 +142,21 @@ def test_a_capture_that_torch_does_not_know_of():
     with torch.cuda.stream(side):
         P.conv2d(h, xs, b, layout="nhwc", out=ys)
     torch.cuda.synchronize()
-    say("[case] capture by the HIP runtime")
-    st, graph, ready = C.c_void_p(side.cuda_stream), C.c_void_p(), C.c_void_p()
+    say(f"[case] capture by the HIP runtime outstanding={outstanding}")
+    st, graph, ready, state = C.c_void_p(side.cuda_stream), C.c_void_p(), C.c_void_p(), C.c_int()
+    if outstanding:
+        t = torch.zeros(1 << 20, device="cuda")
+        other = torch.cuda.Stream()
+        other.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(other):
+            t.add_(1.0)
+        t.record_stream(other)
+        del t
     with torch.cuda.stream(side):
         hip("hipStreamBeginCapture", st, C.c_int(0))
         P.conv2d(h, xs, b, layout="nhwc", out=ys)
+        hip("hipStreamIsCapturing", st, C.byref(state))
+        assert state.value == 1                      # (active; 2: invalid)
         hip("hipStreamEndCapture", st, C.byref(graph))
     hip("hipGraphInstantiate", C.byref(ready), graph, None, None, C.c_size_t(0))
     # what the ordinary pool hands out next, on either stream: of the size that the call would have been lent
