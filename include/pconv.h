@@ -155,6 +155,13 @@ int pconv_conv2d_ws(const pconv_handle *h, const void *x_dev, void *y_dev, const
                     int stride, int pad, pconv_layout layout, pconv_dtype act_dtype, int fuse_relu, void *hip_stream,
                     void *work, int64_t work_bytes);
 
+/* pconv_conv2d_or_workspace - question and call in one, for callers whose calls mostly use none: where
+ * pconv_conv2d_workspace is 0 this is pconv_conv2d and returns its status, which is not positive; elsewhere it does
+ * nothing and returns the size, for pconv_conv2d_ws. */
+int64_t pconv_conv2d_or_workspace(const pconv_handle *h, const void *x_dev, void *y_dev, const float *bias_dev, int n, int h_in,
+                                  int w_in, int stride, int pad, pconv_layout layout, pconv_dtype act_dtype, int fuse_relu,
+                                  void *hip_stream);
+
 /*
  * pconv_get_async_error - PCONV_HIP_ERROR (once, with a message) if a kernel launched on this
  * handle gave up one of its bounded waits since the last report, else PCONV_OK.  Touches no

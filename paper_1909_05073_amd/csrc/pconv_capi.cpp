@@ -332,6 +332,14 @@ int pconv_conv2d_ws(const pconv_handle *h, const void *x_dev, void *y_dev, const
                        static_cast<float *>(work), need);
 }
 
+int64_t pconv_conv2d_or_workspace(const pconv_handle *h, const void *x_dev, void *y_dev, const float *bias_dev, int n, int h_in,
+                                  int w_in, int stride, int pad, pconv_layout layout, pconv_dtype act_dtype, int fuse_relu,
+                                  void *hip_stream)
+{
+    const int64_t need = pconv_conv2d_workspace(h, n, h_in, w_in, stride, layout, act_dtype);
+    return need > 0 ? need : pconv_conv2d(h, x_dev, y_dev, bias_dev, n, h_in, w_in, stride, pad, layout, act_dtype, fuse_relu, hip_stream);
+}
+
 int pconv_conv2d_pool2x2(const pconv_handle *h, const void *x_dev, void *y_dev, const float *bias_dev,
                          int n, int h_in, int w_in, pconv_layout layout, pconv_dtype act_dtype,
                          int fuse_relu, void *hip_stream)

@@ -17,11 +17,18 @@ class FakeLibrary:
 
     def __init__(self):
         self.lent, self.mode, self.knows_modes = [], 0, True
+        self.asks, self.calls = 4096, []
 
     def pconv_conv2d_workspace(self, *call):
-        return 4096
+        self.calls.append("workspace")
+        return self.asks
+
+    def pconv_conv2d_or_workspace(self, *call):
+        self.calls.append("or_workspace")
+        return self.asks
 
     def pconv_conv2d_ws(self, *call):
+        self.calls.append("ws")
         self.lent.append(call[-2:])
         return P.OK
 
@@ -44,7 +51,7 @@ def binding(monkeypatch):
 
     def call():
         out = torch.zeros((1, 8, 8, 64))
-        assert P._conv2d_ws(SimpleNamespace(ptr=1), x, None, 1, False, out, 1, 8, 8) is out
+        assert P._conv2d_ws(SimpleNamespace(ptr=1, c_in=64), x, None, 1, False, out, 1, 8, 8) is out
         return fake.lent.pop()
     call.library = fake
     return call, monkeypatch, torch
@@ -54,6 +61,22 @@ def test_ordinary_calls_are_lent_what_they_ask_for(binding):
     call, _, _ = binding
     ptr, size = call()
     assert ptr and size == 4096
+
+
+def test_small_layers_are_one_call_of_the_library(binding):
+    """Asking first and calling then cost layers that use no work space a sixth of their time on the host."""
+    import torch
+    call, _, _ = binding
+    fake = call.library
+    x = out = torch.zeros((1, 8, 8, 8))
+    small = lambda: P._conv2d_ws(SimpleNamespace(ptr=1, c_in=8), x, None, 1, False, out, 1, 8, 8)
+    fake.asks = P.OK
+    assert small() is out and len(fake.calls) == 1
+    fake.asks = 4096                                 # (such a layer that does use it)
+    assert small() is out and fake.lent.pop()[1] == 4096
+    fake.asks, fake.pconv_last_error = P.INVALID_ARG, lambda: b"refused"
+    with pytest.raises(P.PconvError):
+        small()
 
 
 def test_without_memory_for_it_the_call_goes_on_without(binding):
