@@ -54,18 +54,36 @@ def test_small_workgroups(shape, cut, waves, ks):
         hd.free()
 
 
-@pytest.mark.parametrize("ks", [6, 7])
-def test_equal_images_get_equal_outputs(ks):
-    """Tiles that end between the two patches that share columns of a row: both workgroups store them."""
+# (n, c_in, c_out, h, w): widths 1, 2 and 3 beyond a multiple of 4, rows of fewer and of more than 64 patches
+PARTED = [(4, 24, 24, 42, 129), (4, 24, 24, 42, 130), (5, 24, 24, 33, 146), (3, 24, 24, 95, 139), (5, 24, 16, 21, 274)]
+
+
+@pytest.mark.parametrize("form", ["plain", "stride2", "pool"])
+@pytest.mark.parametrize("waves,ks", [(16, 4), (16, 5), (8, 6), (4, 7)])
+@pytest.mark.parametrize("shape", PARTED)
+def test_equal_images_get_equal_outputs(shape, waves, ks, form):
+    """Tiles that cut rows, one of which ends between the last two patches of a row: both workgroups store the columns
+    that these share.  With stride 2 and an even width the stored outputs have a loop and a sum of their own."""
     import torch
-    for n, ci, co, h, w in [(8, 96, 92, 35, 35), (4, 24, 24, 42, 129)]:
-        spec = LayerSpec("wg", 1, ci, co, h, w)
-        L = make_layer(spec, 6300 + w); x = make_input(spec, 6300 + w)
-        hd = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "f32")
-        P.pconv_debug_set_tiling(16, ks, -1)
-        say(f"[case] equal images ks={ks} {(n, ci, co, h, w)}")
-        xd = to_device(x, "f32").repeat(n, 1, 1, 1)
-        ys = [P.conv2d(hd, xd) for _ in range(4)]
-        torch.cuda.synchronize()
-        assert all(torch.equal(y, ys[0]) for y in ys) and torch.equal(ys[0], ys[0][:1].expand_as(ys[0]))
-        hd.free()
+    n, ci, co, h, w = shape
+    if form == "pool" and w % 2:
+        pytest.skip("the fused pool takes even widths")
+    px, stride = (w + 3) // 4, 2 if form == "stride2" else 1
+    per_image = (h + 3) // 4 * px
+    spec = LayerSpec("wg", 1, ci, co, h, w)
+    L = make_layer(spec, 6300 + w); x = make_input(spec, 6300 + w)
+    hd = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "f32")
+    P.pconv_debug_set_tiling(16, ks, -1)
+    plan = P.pconv_debug_plan(hd, n, h, w, stride, fuse_pool=form == "pool")
+    assert (plan.waves, plan.ks_log2, plan.lone_cut, plan.lone_patches) == (waves, 5 if ks == 5 else 4, 1, 64)
+    assert w % 4 and per_image % 64 and any(64 * k % px == px - 1 for k in range(1, (n * per_image + 63) // 64))
+    say(f"[case] equal images {shape} waves={waves} ks={ks} {form}")
+    xd = to_device(x, "f32").repeat(n, 1, 1, 1)
+    ys = [P.conv2d_pool2x2(hd, xd) if form == "pool" else P.conv2d(hd, xd, stride=stride) for _ in range(4)]
+    torch.cuda.synchronize()
+    assert all(torch.equal(y, ys[0]) for y in ys) and torch.equal(ys[0], ys[0][:1].expand_as(ys[0]))
+    if form != "pool":
+        wt = oracle.masked_weights(L["w"], L["pattern_id"], L["conn"], L["table"])
+        yr, sr = oracle.conv2d(x, wt, None, stride=stride, pad=1)
+        assert_close(ys[0][:1].cpu().numpy().astype(np.float64), yr, sr, "f32", f"equal{shape} {form}")
+    hd.free()
