@@ -1203,12 +1203,15 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
     // the workgroups of a compute unit, which takes longer per workgroup where fewer than four waves share a SIMD.
     // Fitted to 62 layers with 1 to 64 images (5 % off on average; 256 channels @56, one image 18 us with 16, 22, 32;
     // 64 @224, one image 33, 23, 19; 512 @14, 32 images 113, 105, 100); a sixth more where tiles cut rows of patches.
+    // Two slots a workgroup (the fourth row, 16 waves): one pass of sums for two, a round costs 3.1 for 4.7.  Fitted to 6 600
+    // drawn layers (9 % off).  Priced with the first row, 1 130 of 7 400 layers with few units took 4 or 8 waves and 1.1 to 1.4
+    // times as long: 11 to 44 channels @12x14, 27 images 6.7 us for 4.9, 24 to 329 @19, two images 6.1 for 4.8.
     // Channels last 3.3 for 16 channels (128 @28, eight images: 38 us, whole units 120, 81, 62).
     struct LoneCost { double base, round, visit, record, work[4]; };
-    static constexpr LoneCost kLoneCost[3] = {{1.84, 4.70, 0.0437, 0.0113, {1.0}}, {2.65, 3.40, 0.0395, 0.0151, {1.24, 2.0}},
-                                              {1.93, 3.46, 0.0382, 0.0153, {2.27, 2.81, 3.52, 4.0}}};
-    auto lone_time = [&](int waves, double units, double v, double r, bool cut) {
-        const LoneCost &c = kLoneCost[waves == 16 ? 0 : waves == 8 ? 1 : 2];
+    static constexpr LoneCost kLoneCost[4] = {{1.84, 4.70, 0.0437, 0.0113, {1.0}}, {2.65, 3.40, 0.0395, 0.0151, {1.24, 2.0}},
+                                              {1.93, 3.46, 0.0382, 0.0153, {2.27, 2.81, 3.52, 4.0}}, {1.1, 3.1, 0.053, 0.017, {1.0}}};
+    auto lone_time = [&](int waves, bool halves, double units, double v, double r, bool cut) {
+        const LoneCost &c = kLoneCost[halves ? 3 : waves == 16 ? 0 : waves == 8 ? 1 : 2];
         const int most = 16 / waves;
         const double n = std::ceil(units / cus), full = std::floor(n / most), work = (c.visit * v + c.record * r) * (cut ? 1.17 : 1.0) * (sub2 && win % 2 == 0 ? 0.7 : 1.0);
         const int left = int(n - full * most);
@@ -1218,7 +1221,7 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
     auto lone_best = [&](double units, double v, double r, bool cut, int &waves) {
         double best = 0.0;
         for (int w = 16; w >= 4; w /= 2) {
-            const double t = lone_time(w, units, v, r, cut);
+            const double t = lone_time(w, false, units, v, r, cut);
             if (w == 16 || t < best) { best = t; waves = w; }
         }
         return best;
@@ -1317,7 +1320,7 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
                 const double t_all = lone_best(double(t.tiles) * blocks, visits, recs, t.cut, waves);
                 consider(t_all, false, 4, true, false, waves);
                 // two of the block's four filters per workgroup, where there are not enough blocks for the chip
-                consider(lone_time(16, 2.0 * t2.tiles * blocks, double(h->tiled.half_visits) / (2 * blocks), recs / 2, t2.cut), false, 4, true, true);
+                consider(lone_time(16, true, 2.0 * t2.tiles * blocks, double(h->tiled.half_visits) / (2 * blocks), recs / 2, t2.cut), false, 4, true, true);
             } else {
                 consider(std::ceil(double(n_tiles) * blocks / slots) * lone_last, false, 4, true);
             }

@@ -1,0 +1,36 @@
+"""The form that a call of the register-tiled kernel (fp32 NCHW) takes, for layers where another one was measured slower."""
+import pytest
+
+import paper_1909_05073_amd as P
+from pconv_inputs import LayerSpec, make_layer
+
+
+def plan_of(shape, keep):
+    """(waves of a workgroup, ks_log2, split_units) on 256 compute units."""
+    n, ci, co, h, w, stride = shape
+    L = make_layer(LayerSpec("plan", 1, ci, co, 8, 8, stride=stride, keep_div=keep), 8100 + ci)
+    hd = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "f32", host_only=True)
+    p = P.pconv_debug_plan(hd, n, h, w, stride)
+    hd.free()
+    assert p.kernel == 2
+    return p.waves, p.ks_log2, p.split_units
+
+
+# ((n, c_in, c_out, h, w, stride), keep, us with two slots, us with four slots and the best number of waves)
+TWO_SLOTS = [((27, 11, 44, 12, 14, 1), 2.5, 4.9, 5.9), ((2, 24, 329, 19, 19, 1), 8.0, 4.8, 6.0), ((1, 11, 69, 39, 46, 1), 2.5, 4.8, 5.8),
+             ((6, 8, 8, 23, 25, 1), 1.5, 4.6, 5.4), ((3, 6, 18, 29, 29, 2), 1.5, 4.3, 5.2), ((2, 29, 10, 16, 16, 1), 8.0, 4.2, 5.3)]
+
+
+@pytest.mark.parametrize("shape,keep,two,four", TWO_SLOTS)
+def test_small_layers_take_two_slots_a_workgroup(shape, keep, two, four):
+    assert two < 0.9 * four and plan_of(shape, keep)[:2] == (16, 5)
+
+
+# (..., waves, us, us with two slots)
+FOUR_SLOTS = [((30, 325, 46, 29, 31, 1), 8.0, 8, 22.5, 25.2), ((1, 160, 44, 200, 160, 1), 2.5, 8, 28.9, 31.9),
+              ((45, 244, 25, 56, 46, 1), 3.6, 4, 62.0, 70.1)]
+
+
+@pytest.mark.parametrize("shape,keep,waves,four,two", FOUR_SLOTS)
+def test_larger_ones_keep_four(shape, keep, waves, four, two):
+    assert four < 0.95 * two and plan_of(shape, keep)[:2] == (waves, 4)
