@@ -1199,30 +1199,38 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
     // Whole units with stride 2 are priced as with stride 1, although with even widths they do a quarter of the FMAs: staging
     // is what such a unit takes its time for.
     // Waves on their own.  fp32 NCHW (pconv_lone.hip), 16, 8 or 4 waves per workgroup, so that a compute unit holds one, two
-    // or four: `units` workgroups of v visited channels and r records.  A round is a start and an end and the work of
+    // or four: tiles x groups workgroups of v visited channels and r records.  A round is a start and an end and the work of
     // the workgroups of a compute unit, which takes longer per workgroup where fewer than four waves share a SIMD.
     // Fitted to 62 layers with 1 to 64 images (5 % off on average; 256 channels @56, one image 18 us with 16, 22, 32;
     // 64 @224, one image 33, 23, 19; 512 @14, 32 images 113, 105, 100); a sixth more where tiles cut rows of patches.
     // Two slots a workgroup (the fourth row, 16 waves): one pass of sums for two, a round costs 3.1 for 4.7.  Fitted to 6 600
     // drawn layers (9 % off).  Priced with the first row, 1 130 of 7 400 layers with few units took 4 or 8 waves and 1.1 to 1.4
     // times as long: 11 to 44 channels @12x14, 27 images 6.7 us for 4.9, 24 to 329 @19, two images 6.1 for 4.8.
+    // Every workgroup of a tile reads the same channels.  They come from the L2 while the tiles that the 32 compute units of an
+    // XCD work on at a time (4 KB a channel) fit its 4 MB: up to 25 TB/s were seen then, 16 with 6 to 9 MB, 13 with more; so what does
+    // not fit is charged at 33 TB/s on top.  Priced without, 491 to 63 filters @79x82, stride 2, 36 images took 603 us for the
+    // 254 of whole units, 412 to 57 @120x144, seven images 301 for 153.
     // Channels last 3.3 for 16 channels (128 @28, eight images: 38 us, whole units 120, 81, 62).
     struct LoneCost { double base, round, visit, record, work[4]; };
     static constexpr LoneCost kLoneCost[4] = {{1.84, 4.70, 0.0437, 0.0113, {1.0}}, {2.65, 3.40, 0.0395, 0.0151, {1.24, 2.0}},
                                               {1.93, 3.46, 0.0382, 0.0153, {2.27, 2.81, 3.52, 4.0}}, {1.1, 3.1, 0.053, 0.017, {1.0}}};
-    auto lone_time = [&](int waves, bool halves, double units, double v, double r, bool cut) {
+    auto lone_time = [&](int waves, bool halves, const LoneTiles &t, double v, double r) {
         const LoneCost &c = kLoneCost[halves ? 3 : waves == 16 ? 0 : waves == 8 ? 1 : 2];
-        const int most = 16 / waves;
-        const double n = std::ceil(units / cus), full = std::floor(n / most), work = (c.visit * v + c.record * r) * (cut ? 1.17 : 1.0) * (sub2 && win % 2 == 0 ? 0.7 : 1.0);
+        const int most = 16 / waves, groups = halves ? 2 * blocks : blocks;
+        const bool quarter = sub2 && win % 2 == 0;
+        const double units = double(t.tiles) * groups, n = std::ceil(units / cus), full = std::floor(n / most);
+        const double work = (c.visit * v + c.record * r) * (t.cut ? 1.17 : 1.0) * (quarter ? 0.7 : 1.0);
         const int left = int(n - full * most);
-        return c.base + full * (c.round + most * work) + (left > 0 ? c.round + c.work[left - 1] * work : 0.0);
+        const double in_flight = std::min(double(t.tiles) / 8, std::max(1.0, cus / 8.0 * most / groups)), mb = in_flight * h->c_in * 4e-3;
+        const double mb_read = units * v * (quarter ? 5 : 6) * 1024e-6 * t.lanes / 64;
+        return c.base + full * (c.round + most * work) + (left > 0 ? c.round + c.work[left - 1] * work : 0.0) + (mb > 4.0 ? mb_read * (1.0 - 4.0 / mb) / 33.0 : 0.0);
     };
     // the number of waves with the smallest estimate
-    auto lone_best = [&](double units, double v, double r, bool cut, int &waves) {
+    auto lone_best = [&](const LoneTiles &t, int &waves) {
         double best = 0.0;
         for (int w = 16; w >= 4; w /= 2) {
-            const double t = lone_time(w, false, units, v, r, cut);
-            if (w == 16 || t < best) { best = t; waves = w; }
+            const double time = lone_time(w, false, t, visits, recs);
+            if (w == 16 || time < best) { best = time; waves = w; }
         }
         return best;
     };
@@ -1256,7 +1264,7 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
             if (full > 0.0 && rest > 0.0 && main_tiles > 0) {
                 const LoneTiles t = lone_tiles(patches, px, lone_base(int64_t(main_tiles) * 64, px), blocks, slots);
                 int waves = 16;
-                const double t_tail = 0.5 + lone_best(double(t.tiles) * blocks, visits, recs, t.cut, waves);
+                const double t_tail = 0.5 + lone_best(t, waves);
                 if (t_tail < 0.8 * last) { p.tail_tiles = tail; p.lone_waves = waves; t_best = full * round + t_tail; }
             }
             // Up to three blocks of filters leave most of a whole unit's waves idle: waves on their own may still be
@@ -1264,7 +1272,7 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
             if (blocks < p.nw / 4) {
                 const LoneTiles t = lone_tiles(patches, px, 0, blocks, slots);
                 int waves = 16;
-                if (lone_best(double(t.tiles) * blocks, visits, recs, t.cut, waves) < 0.9 * t_best) {
+                if (lone_best(t, waves) < 0.9 * t_best) {
                     p.priv = true; p.ks_log2 = 4; p.tail_tiles = 0; p.lone_waves = waves;
                 }
             }
@@ -1278,7 +1286,7 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
                                            : 1.2 * (6.0 + n_chunks * chunk) * (full + (rest > 0.0 ? 0.72 + 0.28 * rest : 0.0));
             const LoneTiles t = lone_tiles(patches, px, 0, blocks, slots);
             int waves = 16;
-            if (lone_best(double(t.tiles) * blocks, visits, recs, t.cut, waves) < 0.97 * t_units && p.tail_tiles == 0) {
+            if (lone_best(t, waves) < 0.97 * t_units && p.tail_tiles == 0) {
                 p.priv = true; p.ks_log2 = 4; p.split = p.one_set = false; p.lone_waves = waves;
             }
         }
@@ -1317,10 +1325,10 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
             const LoneTiles t2 = lone_tiles(patches, px, 0, 2 * blocks, slots);
             if (p.vec) {
                 int waves = 16;
-                const double t_all = lone_best(double(t.tiles) * blocks, visits, recs, t.cut, waves);
+                const double t_all = lone_best(t, waves);
                 consider(t_all, false, 4, true, false, waves);
                 // two of the block's four filters per workgroup, where there are not enough blocks for the chip
-                consider(lone_time(16, true, 2.0 * t2.tiles * blocks, double(h->tiled.half_visits) / (2 * blocks), recs / 2, t2.cut), false, 4, true, true);
+                consider(lone_time(16, true, t2, double(h->tiled.half_visits) / (2 * blocks), recs / 2), false, 4, true, true);
             } else {
                 consider(std::ceil(double(n_tiles) * blocks / slots) * lone_last, false, 4, true);
             }

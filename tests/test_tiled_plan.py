@@ -28,9 +28,28 @@ def test_small_layers_take_two_slots_a_workgroup(shape, keep, two, four):
 
 # (..., waves, us, us with two slots)
 FOUR_SLOTS = [((30, 325, 46, 29, 31, 1), 8.0, 8, 22.5, 25.2), ((1, 160, 44, 200, 160, 1), 2.5, 8, 28.9, 31.9),
-              ((45, 244, 25, 56, 46, 1), 3.6, 4, 62.0, 70.1)]
+              ((24, 31, 330, 26, 20, 1), 3.6, 4, 18.3, 42.0), ((9, 38, 47, 104, 124, 2), 1.5, 4, 19.8, 46.8)]
 
 
 @pytest.mark.parametrize("shape,keep,waves,four,two", FOUR_SLOTS)
 def test_larger_ones_keep_four(shape, keep, waves, four, two):
     assert four < 0.95 * two and plan_of(shape, keep)[:2] == (waves, 4)
+
+
+# (..., us of the whole or shared units taken, us of workgroups of 4 waves on their own)
+BEYOND_L2 = [((36, 491, 63, 79, 82, 2), 3.6, 254, 603), ((5, 385, 44, 165, 200, 1), 3.6, 165, 318), ((7, 368, 50, 181, 182, 1), 8.0, 152, 244),
+             ((62, 149, 50, 82, 98, 2), 2.5, 152, 245), ((16, 256, 47, 152, 152, 1), 2.5, 272, 425)]
+
+
+@pytest.mark.parametrize("shape,keep,units,lone", BEYOND_L2)
+def test_tiles_beyond_the_l2_are_not_read_by_every_block_of_filters(shape, keep, units, lone):
+    assert units < 0.95 * lone and plan_of(shape, keep)[1] < 4
+
+
+# (..., us with 4 waves on their own, us of whole units)
+WITHIN_L2 = [((4, 113, 110, 117, 141, 1), 8.0, 35.1, 51.0), ((12, 61, 402, 42, 34, 1), 3.6, 31.8, 42.7), ((23, 173, 385, 26, 29, 1), 3.6, 70.8, 102.4)]
+
+
+@pytest.mark.parametrize("shape,keep,lone,units", WITHIN_L2)
+def test_others_are(shape, keep, lone, units):
+    assert lone < 0.95 * units and plan_of(shape, keep)[:2] == (4, 4)
