@@ -1278,12 +1278,18 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
             }
         }
         // Waves on their own, two or four workgroups to a compute unit, have no last round to speak of (512 channels
-        // @28, 64 images, 12 uneven patterns 433 -> 398 us).  The estimates above are what a unit takes by
-        // itself; with the chip full it is 1.2 times that (0.17 to 0.31 more on nine layers), shared units 1.35.
+        // @28, 64 images, 12 uneven patterns: 436 us as whole units, 380 as shared ones, 365 with 4 waves).  The estimates above
+        // are what a unit takes by itself; with the chip full and its waves busy it is 1.37 times that, taken as 1.25 so that fewer
+        // layers lose by the change (of 1 500 drawn ones five take more than 1.1 times what the units take), shared units 1.28;
+        // even widths with stride 2, which form a quarter of the FMAs, 1.05.  Waves without a block of filters leave the others
+        // their share of the record loop: priced as busy, 8 to 12 blocks took up to 1.4 times the time of whole units (10 to 75 filters
+        // @134x160, 41 images 118 us for 101, 32 to 35 @204x207, 37 images 178 for 143), and so did stride 2 (200 to 460 @64, eight images
+        // 127 for 103).
         if (p.vec && can_priv && blocks >= p.nw / 2 && force_split < 0 && force_ks < 0) {
-            const double chunk = 2.0 + 1.9 * records / 142.0, full = double(whole_units / slots), rest = double(whole_units % slots) / slots;
-            const double t_units = p.split ? 1.35 * chunk * (double(whole_units) * n_chunks / slots + 10.0)
-                                           : 1.2 * (6.0 + n_chunks * chunk) * (full + (rest > 0.0 ? 0.72 + 0.28 * rest : 0.0));
+            const double busy = double(blocks) / (units_of(0) * p.nw);
+            const double chunk = 2.0 + 1.9 * records * busy / 142.0, full = double(whole_units / slots), rest = double(whole_units % slots) / slots;
+            const double t_units = p.split ? 1.28 * chunk * (double(whole_units) * n_chunks / slots + 10.0)
+                                           : (sub2 && win % 2 == 0 ? 1.05 : 1.25) * (6.0 + n_chunks * chunk) * (full + (rest > 0.0 ? 0.72 + 0.28 * rest : 0.0));
             const LoneTiles t = lone_tiles(patches, px, 0, blocks, slots);
             int waves = 16;
             if (lone_best(t, waves) < 0.97 * t_units && p.tail_tiles == 0) {

@@ -53,3 +53,13 @@ WITHIN_L2 = [((4, 113, 110, 117, 141, 1), 8.0, 35.1, 51.0), ((12, 61, 402, 42, 3
 @pytest.mark.parametrize("shape,keep,lone,units", WITHIN_L2)
 def test_others_are(shape, keep, lone, units):
     assert lone < 0.95 * units and plan_of(shape, keep)[:2] == (4, 4)
+
+
+# (..., us of whole units, us of workgroups of 4 waves on their own): waves of a unit without filters; stride 2 with an even width
+IDLE_OR_QUARTER = [((37, 32, 35, 204, 207, 1), 3.6, 143, 178), ((41, 10, 75, 134, 160, 1), 3.6, 101, 118), ((52, 82, 30, 185, 148, 1), 2.5, 270, 327),
+                   ((8, 200, 460, 64, 64, 2), 2.5, 103, 127), ((44, 170, 153, 87, 88, 2), 2.5, 328, 395), ((28, 332, 502, 49, 58, 2), 3.6, 420, 485)]
+
+
+@pytest.mark.parametrize("shape,keep,units,lone", IDLE_OR_QUARTER)
+def test_units_with_idle_waves_or_a_quarter_of_the_outputs(shape, keep, units, lone):
+    assert units < 0.95 * lone and plan_of(shape, keep)[1] < 4
