@@ -1086,12 +1086,16 @@ bool tiled_preferred(int hin, int win, int stride)
 }
 
 // fp32 with channels last: the tensors laid out channels first before the convolution and back after it, or staged
-// through registers in the layout they have.  Of 175 layers (1 to 512 channels, 7 to 257 pixels square, 1 to 64 images) the
-// changes of layout take 4 us + 0.35 a MB of input, and 3 us + 0.36 a MB of output unless waves on their own store it
-// (0.86 a MB); what they save grows with the chunks of channels, more so where pixels are no whole quads of
-// channels, and with the output, which the other kernels store four bytes at a time.  us, with change and without: 128 channels @28,
-// eight images 21.7, 34.9; 200 to 50 @112, 16 images 210, 802; 99 to 40 @56, one image 13, 119; but 8 to 16 @20, 20, 13, and 40 to 32
-// filters of 8, 16 images of 75x80 36, 28.
+// through registers in the layout they have.  The changes of layout take 4 us + 0.35 a MB of input, and 3 us + 0.36 a MB of
+// output unless waves on their own store it (0.86 a MB); what they save grows with the chunks of channels, more so where
+// pixels are no whole quads of channels, and with the output, which the other kernels store four bytes at a time.  us, with change
+// and without: 128 channels @28, eight images 20, 34; 200 to 50 @112, 16 images 210, 802; 99 to 40 @56, one image 13, 119; but 8 to
+// 16 @20, 20, 13.  With one line for all, 130 of 13 600 drawn layers that changed their layout took more than 1.1 times as long for it:
+// - Quads of channels, 8 MB of input and more: 4 us + 0.35 a MB was too little for the smaller gains (76 to 13 @70, 39 images 69, 58,
+//   72 to 8 @117, seven images 31, 26); 8 + 0.38 leaves 6 of 1 000 layers more than a tenth slower, for 26.
+// - One chunk of channels stages in no more than the changes take unless the output is most of the call: with more than 1.5 MB of input, 18 MB
+//   of output and three times the input leave 5 of 1 700, for 95 (4 to 5 @158x126, 44 images 59, 31; 5 to 13 @223x178, stride 2, four
+//   images 19, 12; but 5 to 25 @209x212, 19 images 84, 151).
 bool tiled_nchw_preferred(const pconv_handle *h, int n, int hin, int win, int stride)
 {
     const bool pinned = g_force_waves.load() || g_force_ks.load() >= 0 || g_force_split.load() >= 0;
@@ -1105,7 +1109,8 @@ bool tiled_nchw_preferred(const pconv_handle *h, int n, int hin, int win, int st
     const bool quads = h->c_in % 4 == 0;
     const bool many = h->c_in > 32 || (h->c_in > 16 && h->c_out > 8) || (!quads && h->c_in > 4) || (y_mb > 12.0 && y_mb > x_mb);
     const int chunks = (h->c_in + kTileCH - 1) / kTileCH;
-    return many && (x_mb < 8.0 || 4.0 + 0.35 * x_mb < (quads ? 1.13 : 4.88) * chunks + 1.4 * y_mb);
+    if (chunks == 1) return many && (x_mb < 1.5 || (y_mb > 18.0 && y_mb > 3.0 * x_mb));
+    return many && (x_mb < 8.0 || (quads ? 8.0 + 0.38 * x_mb < 1.13 * chunks + 1.4 * y_mb : 4.0 + 0.35 * x_mb < 4.88 * chunks + 1.4 * y_mb));
 }
 
 bool tiled_pool_supported(const pconv_handle *h, int n, int hin, int win, int layout, int dtype)

@@ -112,6 +112,25 @@ def test_work_space_is_what_the_form_of_a_call_uses(shape, waves, ks_log2, cut, 
     h.free()
 
 
+# ((n, c_in, c_out, h, w, stride), keep, us as it is, us channels first): the layout stays
+AS_IT_IS = [((44, 4, 5, 158, 126, 1), 3.6, 31, 59), ((4, 5, 13, 223, 178, 2), 8.0, 12, 19), ((42, 7, 35, 66, 79, 2), 3.6, 21, 30),
+            ((13, 4, 35, 220, 176, 2), 3.6, 35, 48), ((25, 8, 18, 97, 99, 1), 2.5, 30, 35), ((39, 76, 13, 70, 70, 1), 2.5, 58, 69),
+            ((7, 72, 8, 117, 117, 1), 2.5, 26, 31), ((33, 36, 7, 50, 50, 1), 2.5, 18, 21)]
+# it changes
+CHANNELS_FIRST = [((8, 128, 128, 28, 28, 1), 3.6, 34, 20), ((19, 5, 25, 209, 212, 1), 3.6, 151, 84), ((4, 4, 471, 223, 223, 1), 3.6, 680, 359),
+                  ((16, 200, 50, 112, 112, 1), 3.6, 802, 210), ((5, 6, 12, 38, 38, 1), 3.6, 20, 11)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,keep,as_it_is,first", AS_IT_IS + CHANNELS_FIRST)
+def test_the_layout_changes_where_that_is_faster(shape, keep, as_it_is, first):
+    n, ci, co, hh, ww, stride = shape
+    L = make_layer(LayerSpec("ws", 1, ci, co, 8, 8, stride=stride, keep_div=keep), 7700 + ci)
+    h = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "f32")
+    assert (P.lib().pconv_conv2d_workspace(h.ptr, n, hh, ww, stride, P.NHWC, P.F32) > 0) == (first < as_it_is)
+    h.free()
+
+
 @pytest.mark.gpu
 def test_work_space_calls_under_capture():
     """The work space comes out of the graph's own pool; every replay sees its own input."""
