@@ -365,10 +365,11 @@ def _conv2d_ws(handle: Handle, x, bias, stride, relu, out, n, h, w):
     Up to the size of x and out together.  On a card with less to spare torch first gives its cached blocks back, which
     waits for the device, and the call then runs without; pconv_conv2d takes none in the first place."""
     L = _lib or lib()
-    call = (handle.ptr, x.data_ptr(), out.data_ptr(), (bias.data_ptr() or None) if bias is not None else None,
+    ptr, c = handle.ptr, handle.c_in
+    call = (ptr, x.data_ptr(), out.data_ptr(), (bias.data_ptr() or None) if bias is not None else None,
             n, h, w, stride, 1, NHWC, F32, 1 if relu else 0, _stream(x.get_device()))
-    if handle.c_in > 32:
-        size = L.pconv_conv2d_workspace(handle.ptr, n, h, w, stride, NHWC, F32)
+    if c > 16 or (c > 4 and c % 4):                  # (mostly some)
+        size = L.pconv_conv2d_workspace(ptr, n, h, w, stride, NHWC, F32)
     else:                                            # (mostly none: question and call are one; 4.8 us on the host for 5.6)
         size = L.pconv_conv2d_or_workspace(*call)
         if size <= 0:
