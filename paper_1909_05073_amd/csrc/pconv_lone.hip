@@ -9,12 +9,15 @@
 // the list and the first record words are on their way while the rows are.  At the end the partial
 // sums are added through LDS.
 //
-// What bounds it: the issue of vector instructions.  A visit has 97 FMAs (1.5 records) of 2.4 cycles and 12 moves between
-// lanes, and takes 1360 cycles of a wave in the oldest four of 16 waves and 1910 in the youngest (hence portions by
-// age, see the packer); its six 1 KB loads take 100 cycles of the vector-memory pipe per wave.  (The rows staged in LDS
-// as one run of memory, one to five loads for six, the next channel's under the records: 19.8 us for 18.1 on that layer,
-// 512 @14, 32 images, 4 waves 104 for 92.)  Start 3600 cycles, sums and stores 5000 with 16
-// waves.  One image, us: 256 channels @56 16.5, 512 @14 18.6, 512 @28 22, 16 @16 5.2 for the kernel.
+// What bounds it: the vector-memory pipe, and the issue of vector instructions behind it.  A visit takes 1360 cycles of a wave
+// in the oldest four of 16 waves and 1910 in the youngest (hence portions by age, see the packer), so a compute unit ends
+// one in 100 cycles, and its six 1 KB loads take the pipe 16.5 cycles each; its 97 FMAs (1.5 records) of 2.4 cycles and 12 moves
+// between lanes are 260 of the 400 cycles that a SIMD has for it.  Over the whole kernel (256 channels @56, counters) the pipe has
+// 18 700 of the 35 000 cycles that a wave lives and vector issue 16 500; with 4 waves and few records a visit (512 @28, 64 images,
+// uneven) 62 and 38 %, stride 2 62 and 23.  Fewer loads by themselves do not help: the rows staged in LDS as one run of memory,
+// one to five loads for six, the next channel's under the records: 19.8 us for 18.1 on the first layer, 512 @14, 32 images, 4 waves
+// 104 for 92.  Start 3600 cycles, sums and stores 5000 with 16 waves.  One image, us: 256 channels @56 16.4, 512 @14 18.6, 512 @28 22,
+// 16 @16 5.7 for the kernel.
 //
 // Waves of a workgroup.  With 16 the end of every workgroup, its start and a last round of few workgroups leave the
 // compute unit to itself; with 8 or 4 other workgroups run meanwhile and a round is half or a quarter as long, but too few

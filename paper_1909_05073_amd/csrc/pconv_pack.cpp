@@ -266,7 +266,10 @@ void build_tiled_stream(const Canonical &cn, const uint16_t *table, int np, int 
 // about 100 and 60 cycles of a compute unit) add up to the wave's share.  A SIMD has four of the 16 waves and serves
 // them oldest first: a visit takes 1360 cycles in the first four waves, 1560, 1690 and 1910 in the others (256 channels
 // @56), so the younger ones get less.  With equal shares the first four are done after 70 % of the loop: one image, us, equal and as
-// they are: 256 channels @56 18.8, 18.1; 512 @14 20.0, 18.8; 99 to 150 @37x45, three images 13.9, 13.4.
+// they are: 256 channels @56 18.8, 18.1; 512 @14 20.0, 18.8; 99 to 150 @37x45, three images 13.9, 13.4.  The shares come from the first of
+// these and serve every form with 16 waves, also two slots, stride 2 and cut tiles, whose visits were not timed one by one: of
+// 8 900 drawn layers that kept such a form by the change two took more than 1.1 times as long, the two-slot ones 3 % less
+// and the others 6 % less on average.  Workgroups of 8 and 4 waves deal out visits by number.
 constexpr int kLoneShare[kLoneWaves / 4] = {120, 105, 94, 81};
 std::vector<uint32_t> build_lone_lists(const TiledStream &ts, const std::vector<uint32_t> &chan_mid, int c_in)
 {

@@ -1273,7 +1273,9 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
                 if (t_tail < 0.8 * last) { p.tail_tiles = tail; p.lone_waves = waves; t_best = full * round + t_tail; }
             }
             // Up to three blocks of filters leave most of a whole unit's waves idle: waves on their own may still be
-            // faster (160 to 8 channels @95x102, 44 images: 81 us for 117).
+            // faster (160 to 8 channels @95x102, 44 images: 81 us for 117).  Four to seven blocks are asked neither here nor
+            // below and stay whole units, also where waves on their own are faster: 64 to 16 @112x138, stride 2, 32 images 46 us,
+            // 32 with 4 waves; 128 to 16 @112, 16 images 51, 31; but 128 to 28 54, 51.  Nor are they asked where units are shared.
             if (blocks < p.nw / 4) {
                 const LoneTiles t = lone_tiles(patches, px, 0, blocks, slots);
                 int waves = 16;
