@@ -1291,12 +1291,12 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
         // even widths with stride 2, which form a quarter of the FMAs, 1.05.  Waves without a block of filters leave the others
         // their share of the record loop: priced as busy, 8 to 12 blocks took up to 1.4 times the time of whole units (10 to 75 filters
         // @134x160, 41 images 118 us for 101, 32 to 35 @204x207, 37 images 178 for 143), and so did stride 2 (200 to 460 @64, eight images
-        // 127 for 103).
+        // 127 for 103).  With the pool 1.1, as the outputs stored are a quarter (10 to 144 @172x206, five images 32.6 for 25.9).
         if (p.vec && can_priv && blocks >= p.nw / 2 && force_split < 0 && force_ks < 0) {
             const double busy = double(blocks) / (units_of(0) * p.nw);
             const double chunk = 2.0 + 1.9 * records * busy / 142.0, full = double(whole_units / slots), rest = double(whole_units % slots) / slots;
             const double t_units = p.split ? 1.28 * chunk * (double(whole_units) * n_chunks / slots + 10.0)
-                                           : (sub2 && win % 2 == 0 ? 1.05 : 1.25) * (6.0 + n_chunks * chunk) * (full + (rest > 0.0 ? 0.72 + 0.28 * rest : 0.0));
+                                           : (sub2 && win % 2 == 0 ? 1.05 : pool ? 1.1 : 1.25) * (6.0 + n_chunks * chunk) * (full + (rest > 0.0 ? 0.72 + 0.28 * rest : 0.0));
             const LoneTiles t = lone_tiles(patches, px, 0, blocks, slots);
             int waves = 16;
             if (lone_best(t, waves) < 0.97 * t_units && p.tail_tiles == 0) {
@@ -1318,7 +1318,8 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
         // (`full`: more than a quarter of the chip's workgroups of 16 waves: they start together, and the memory shows;
         // priced as alone, 8 to 512 channels @80 with stride 2, two images took 13.7 us for the 9.1 of waves on their own,
         // 16 to 128 @112, three images 17.0 for 14.6, 32 to 256 @56, eight images 23.8 for 20.1; with 8 waves, 3 channels
-        // @224, one image, the channels split two ways in 196 workgroups are still faster than 98 whole units, 12.1 for 13.6)
+        // @224, one image, the channels split two ways in 196 workgroups are still faster than 98 whole units, 12.1 for 13.6; with the
+        // pool, which stores a quarter, 7: priced as without, 5 to 429 @118x140, one image 13.2 for 10.7, 16 to 118 @175 17.8 for 14.5)
         const bool quads = layout == PCONV_NHWC && h->c_in % 4 == 0;
         const double t_stage = p.vec ? 2.0 : quads ? 2.4 : 8.0, t_records = p.vec ? 1.9 : quads ? 4.8 : 4.0;
         const double chunk_scale = p.nw == 16 ? 1.0 : 0.5;
@@ -1326,7 +1327,7 @@ TiledPlan plan_tiled(const pconv_handle *h, int n, int hin, int win, int layout,
             if (ks > 0 && int64_t(n_tiles) * units_of(ks - 1) > slots / 2) break;
             const double rounds = std::ceil(double((n_tiles + 7) / 8) * units_of(ks) / (slots / 8.0));
             const bool full = p.vec && p.nw == 16 && int64_t(n_tiles) * units_of(ks) > slots / 4;
-            consider(rounds * ((full ? 10.0 : 6.0) + (full ? 1.08 : 1.0) * chunk_scale * n_chunks * (t_stage + t_records * records / 142.0 / (1 << ks))), false, ks, false);
+            consider(rounds * ((full ? pool ? 7.0 : 10.0 : 6.0) + (full ? 1.08 : 1.0) * chunk_scale * n_chunks * (t_stage + t_records * records / 142.0 / (1 << ks))), false, ks, false);
         }
         // units shared by P workgroups, which pass the sums on one after the other (256 channels @56, one
         // image: 99 us, four: 83; 192 to 128 @56, 12 images 106, waves on their own 85)

@@ -5,12 +5,12 @@ import paper_1909_05073_amd as P
 from pconv_inputs import LayerSpec, make_layer
 
 
-def plan_of(shape, keep):
+def plan_of(shape, keep, pool=False):
     """(waves of a workgroup, ks_log2, split_units) on 256 compute units."""
     n, ci, co, h, w, stride = shape
     L = make_layer(LayerSpec("plan", 1, ci, co, 8, 8, stride=stride, keep_div=keep), 8100 + ci)
     hd = P.pconv_pack(L["w"], L["pattern_id"], L["conn"], L["table"], "f32", host_only=True)
-    p = P.pconv_debug_plan(hd, n, h, w, stride)
+    p = P.pconv_debug_plan(hd, n, h, w, stride, fuse_pool=pool)
     hd.free()
     assert p.kernel == 2
     return p.waves, p.ks_log2, p.split_units
@@ -63,3 +63,17 @@ IDLE_OR_QUARTER = [((37, 32, 35, 204, 207, 1), 3.6, 143, 178), ((41, 10, 75, 134
 @pytest.mark.parametrize("shape,keep,units,lone", IDLE_OR_QUARTER)
 def test_units_with_idle_waves_or_a_quarter_of_the_outputs(shape, keep, units, lone):
     assert units < 0.95 * lone and plan_of(shape, keep)[1] < 4
+
+
+# (..., us of whole units, us of workgroups of 4 waves on their own), the max-pool fused
+POOLED = [((5, 10, 144, 172, 206, 1), 8.0, 25.9, 32.6), ((1, 5, 429, 118, 140, 1), 3.6, 10.7, 13.2), ((2, 16, 118, 175, 176, 1), 3.6, 14.5, 17.8),
+          ((32, 18, 46, 214, 170, 1), 8.0, 59.4, 72.4), ((16, 7, 123, 54, 64, 1), 3.6, 10.1, 12.1)]
+
+
+@pytest.mark.parametrize("shape,keep,units,lone", POOLED)
+def test_units_that_store_pooled_outputs(shape, keep, units, lone):
+    assert units < 0.95 * lone and plan_of(shape, keep, pool=True)[1] < 4
+
+
+def test_pooled_layers_of_many_channels_stay_on_their_own():
+    assert plan_of((32, 512, 512, 14, 14, 1), 3.6, pool=True)[:2] == (4, 4)
